@@ -146,7 +146,7 @@ ForwardWs forward_ws_grouped(int64_t M, int64_t N, int64_t K, int groups_k, int 
     return w;
 }
 struct LnBackwardWs {
-    size_t rowstats, partials, total;
+    size_t rowstats, partials, min_total, total;  // min_total is required, total is what helps
 };
 LnBackwardWs ln_backward_ws(int64_t M, int64_t K, int groups_k) {
     LnBackwardWs w{};
@@ -154,8 +154,8 @@ LnBackwardWs ln_backward_ws(int64_t M, int64_t K, int groups_k) {
     w.rowstats = off;
     off += align256((size_t)M * groups_k * 16);
     w.partials = off;
-    off += align256((size_t)ln_backward_chunks(M) * 2 * (size_t)K * 8);
-    w.total = off;
+    w.min_total = off + align256((size_t)ln_backward_min_chunks(M) * 2 * (size_t)K * 8);
+    w.total = off + align256((size_t)ln_backward_chunks(M, K) * 2 * (size_t)K * 8);
     return w;
 }
 // Eq. 6: codes, then gamma and (xhat field) eta, row sums, the quantiser's own scratch
@@ -719,13 +719,14 @@ int bitlinear_layernorm_backward(const float* dXhat, const float* X, int64_t M, 
     if (!dXhat || !X) return BL_ERR_NULL;
     const LnBackwardWs ws = ln_backward_ws(M, K, groups_k);
     const bool affine = dgain || dbias;
-    if (affine && (!workspace || workspace_bytes < ws.total)) return BL_ERR_WORKSPACE;
+    if (affine && (!workspace || workspace_bytes < ws.min_total)) return BL_ERR_WORKSPACE;
     LnBackwardArgs a{};
     a.g = dXhat; a.X = X; a.M = M * groups_k; a.K = Kg; a.gain = ln_gain; a.eps = ln_eps;
     a.groups = groups_k; a.dX = dX;
     a.rowstats = affine ? (double*)((char*)workspace + ws.rowstats) : nullptr;
     double* partials = affine ? (double*)((char*)workspace + ws.partials) : nullptr;
-    return check_hip(launch_ln_backward(a, dgain, dbias, partials, (hipStream_t)stream));
+    return check_hip(launch_ln_backward(a, dgain, dbias, partials,
+                                        affine ? workspace_bytes - ws.partials : 0, (hipStream_t)stream));
 }
 
 int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int threads, uint32_t* sink,

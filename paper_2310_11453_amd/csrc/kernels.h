@@ -161,8 +161,9 @@ struct LnBackwardArgs {
     double* rowstats;  // [M][2] = (mean, rstd), or nullptr
 };
 bool ln_backward_supported(int64_t K);
-int ln_backward_chunks(int64_t tokens);
+int ln_backward_min_chunks(int64_t tokens);
+int ln_backward_chunks(int64_t tokens, int64_t width);
 hipError_t launch_ln_backward(const LnBackwardArgs& a, float* dgain, float* dbias, double* partials,
-                              hipStream_t s);
+                              size_t partials_bytes, hipStream_t s);
 
 }  // namespace bl

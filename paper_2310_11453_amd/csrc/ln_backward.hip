@@ -244,20 +244,29 @@ __global__ __launch_bounds__(512) void ln_backward_long(LnBackwardArgs a) {
     }
 }
 
-// Column sums for the gain and bias gradients: thread = one float4 of columns of the full
-// token width (groups * K), workgroup row = a chunk of tokens; fp64 partials per chunk.
+// Column sums for the gain and bias gradients.  A workgroup takes 64 float4 columns of the full
+// token width (groups * K) and a chunk of tokens; its four waves take every fourth token of the
+// chunk (whole 1 KiB lines each) and meet in LDS: fp64 partials per chunk.  Bound by the latency of
+// its loads (8 M K bytes, in cache after the statistics pass): the chunks are short enough that
+// some 1024 workgroups are in flight, and two tokens of a wave are loaded at once.  M = 1000, K = 2048: 5.1 us;
+// in 8 chunks, a thread walking 125 tokens (16 workgroups in all), it took 44.7 us.
+constexpr int kAffineWaves = 4;
 __global__ __launch_bounds__(256) void ln_backward_affine_partial(LnBackwardArgs a, int64_t tokens,
                                                                   int64_t width, int rows_per_chunk,
                                                                   double* __restrict__ partials) {
-    const int64_t c4 = (int64_t)blockIdx.x * 256 + threadIdx.x;  // float4 column
-    if (c4 * 4 >= width) return;
-    const int grp = (int)(c4 * 4 / a.K);
+    __shared__ double sums[kAffineWaves - 1][kWave][8];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t c4 = (int64_t)blockIdx.x * kWave + lane;  // float4 column
+    const bool in = c4 * 4 < width;
+    const int64_t cc = in ? c4 : 0;
+    const int grp = (int)(cc * 4 / a.K);
     const int64_t m0 = (int64_t)blockIdx.y * rows_per_chunk;
     const int64_t m1 = m0 + rows_per_chunk < tokens ? m0 + rows_per_chunk : tokens;
     double dg[4] = {0, 0, 0, 0}, db[4] = {0, 0, 0, 0};
-    for (int64_t m = m0; m < m1; ++m) {
-        const float4 x = reinterpret_cast<const float4*>(a.X + m * width)[c4];
-        const float4 g = reinterpret_cast<const float4*>(a.g + m * width)[c4];
+#pragma unroll 2
+    for (int64_t m = m0 + wave; m < m1; m += kAffineWaves) {
+        const float4 x = reinterpret_cast<const float4*>(a.X + m * width)[cc];
+        const float4 g = reinterpret_cast<const float4*>(a.g + m * width)[cc];
         const double mu = a.rowstats[2 * (m * a.groups + grp)];
         const double rstd = a.rowstats[2 * (m * a.groups + grp) + 1];
         dg[0] = fma((double)g.x, ((double)x.x - mu) * rstd, dg[0]);
@@ -266,6 +275,22 @@ __global__ __launch_bounds__(256) void ln_backward_affine_partial(LnBackwardArgs
         dg[3] = fma((double)g.w, ((double)x.w - mu) * rstd, dg[3]);
         db[0] += (double)g.x; db[1] += (double)g.y; db[2] += (double)g.z; db[3] += (double)g.w;
     }
+    if (wave > 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sums[wave - 1][lane][i] = dg[i];
+            sums[wave - 1][lane][4 + i] = db[i];
+        }
+    }
+    __syncthreads();
+    if (wave > 0 || !in) return;
+#pragma unroll
+    for (int w = 0; w < kAffineWaves - 1; ++w)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            dg[i] += sums[w][lane][i];
+            db[i] += sums[w][lane][4 + i];
+        }
     double* p = partials + ((int64_t)blockIdx.y * 2) * width + c4 * 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -274,27 +299,47 @@ __global__ __launch_bounds__(256) void ln_backward_affine_partial(LnBackwardArgs
     }
 }
 
+// A workgroup folds 32 columns: eight threads share a column's chunks and meet in LDS.
 __global__ __launch_bounds__(256) void ln_backward_affine_final(const double* __restrict__ partials,
                                                                 int chunks, int64_t width,
                                                                 float* __restrict__ dgain,
                                                                 float* __restrict__ dbias) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= width) return;
+    __shared__ double sums[2][8][32];
+    const int col = threadIdx.x & 31, part = threadIdx.x >> 5;
+    const int64_t k = (int64_t)blockIdx.x * 32 + col;  // width is a multiple of 32
     double dg = 0.0, db = 0.0;
-    for (int cidx = 0; cidx < chunks; ++cidx) {
+#pragma unroll 4
+    for (int cidx = part; cidx < chunks; cidx += 8) {
         dg += partials[((int64_t)cidx * 2) * width + k];
         db += partials[((int64_t)cidx * 2 + 1) * width + k];
     }
-    if (dgain) dgain[k] = (float)dg;
-    if (dbias) dbias[k] = (float)db;
+    sums[0][part][col] = dg;
+    sums[1][part][col] = db;
+    __syncthreads();
+    if (part > 1) return;  // thread rows 0 and 1: gain and bias
+    double r = sums[part][0][col];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) r += sums[part][i][col];
+    float* const o = part ? dbias : dgain;
+    if (o) o[k] = (float)r;
 }
 
 bool ln_backward_supported(int64_t K) { return K % 4 == 0; }
 static bool ln_backward_in_registers(int64_t K) { return K / 4 <= 8 * kWave * 8; }
 
-int ln_backward_chunks(int64_t tokens) {
+// Chunks of tokens of the column sums.  What the workspace must hold at least: 128 tokens a chunk,
+// 64 chunks at most.
+int ln_backward_min_chunks(int64_t tokens) {
     int64_t c = (tokens + 127) / 128;
     return (int)(c < 1 ? 1 : c > 64 ? 64 : c);
+}
+// What it is asked for: enough chunks for about 1024 workgroups (`width` / 256 share a chunk), at
+// least 16 tokens (four per wave) in each.
+int ln_backward_chunks(int64_t tokens, int64_t width) {
+    int64_t c = 1024 / ((width + 255) / 256);
+    if (c > (tokens + 15) / 16) c = (tokens + 15) / 16;
+    const int64_t lo = ln_backward_min_chunks(tokens);
+    return (int)(c > 128 ? 128 : c < lo ? lo : c);
 }
 
 template <int WPR, int NV>
@@ -304,9 +349,9 @@ static void launch_rows(const LnBackwardArgs& a, hipStream_t s) {
 }
 
 // a.M counts rows of a.K elements (tokens * groups); a.rowstats must be given when dgain or
-// dbias is wanted; `partials` holds chunks * 2 * width doubles.
+// dbias is wanted; `partials` holds at least ln_backward_min_chunks * 2 * width doubles.
 hipError_t launch_ln_backward(const LnBackwardArgs& a, float* dgain, float* dbias, double* partials,
-                              hipStream_t s) {
+                              size_t partials_bytes, hipStream_t s) {
     const int64_t K4 = a.K / 4;
     int wpr = 1;
     while (wpr < 8 && K4 > (int64_t)wpr * kWave * 8) wpr *= 2;
@@ -332,12 +377,15 @@ hipError_t launch_ln_backward(const LnBackwardArgs& a, float* dgain, float* dbia
         st.dX = nullptr;
         if (!rows(st)) return hipErrorInvalidValue;
         const int64_t tokens = a.M / a.groups, width = a.K * a.groups;
-        const int chunks = ln_backward_chunks(tokens);
+        const int64_t room = (int64_t)(partials_bytes / ((size_t)width * 16));
+        int chunks = ln_backward_chunks(tokens, width);
+        if (chunks > room) chunks = ln_backward_min_chunks(tokens);
         const int rows_per_chunk = (int)((tokens + chunks - 1) / chunks);
-        dim3 grid((unsigned)((width / 4 + 255) / 256), (unsigned)chunks);
+        chunks = (int)((tokens + rows_per_chunk - 1) / rows_per_chunk);  // the ones that hold tokens
+        dim3 grid((unsigned)((width / 4 + kWave - 1) / kWave), (unsigned)chunks);
         ln_backward_affine_partial<<<grid, 256, 0, s>>>(a, tokens, width, rows_per_chunk, partials);
-        ln_backward_affine_final<<<(unsigned)((width + 255) / 256), 256, 0, s>>>(partials, chunks, width,
-                                                                                  dgain, dbias);
+        ln_backward_affine_final<<<(unsigned)(width / 32), 256, 0, s>>>(partials, chunks, width, dgain,
+                                                                         dbias);
     }
     if (a.dX && !rows(a)) return hipErrorInvalidValue;
     return hipGetLastError();

@@ -41,7 +41,10 @@ SHAPES = [(1, 32, 1), (5, 96, 1), (33, 256, 1), (100, 2048, 1), (17, 4096, 1), (
           (6, 16384, 1), (40, 1024, 4), (12, 2048, 8), (3, 384, 4),
           # rows longer than the registers hold (the 30B down-projection's K and beyond), walked
           # from memory; also as K-groups
-          (5, 28672, 1), (3, 36000, 1), (2, 65536, 1), (4, 57344, 2)]
+          (5, 28672, 1), (3, 36000, 1), (2, 65536, 1), (4, 57344, 2),
+          # column sums over several chunks of tokens, the last one short, and a width that is not
+          # a multiple of a workgroup's 256 columns
+          (1000, 288, 1), (531, 2048, 1), (65, 1184, 37)]
 
 
 @pytest.mark.parametrize("M,K,groups", SHAPES)
