@@ -321,6 +321,7 @@ int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int thre
  *   quant_wpr=w         quantiser: waves per row (1, 2, 4, 8)
  *   bwd_ring=1|2        backward GEMMs: the ring kernel / the small kernel
  *   bwd_grid=g, bwd_rowmajor=1   backward ring kernel: workgroups, plain tile order
+ *   bwd_splits=n        backward ring kernels: slices of the reduction
  * Returns BL_OK, or BL_ERR_UNSUPPORTED (unknown name or bad syntax; nothing changes). */
 int bitlinear_set_tuning(const char* spec);
 

@@ -27,6 +27,7 @@ const TuningField kTuningFields[] = {
     {"group_slices", &Tuning::group_slices},
     {"quant_wpr", &Tuning::quant_wpr},           {"bwd_ring", &Tuning::bwd_ring},
     {"bwd_grid", &Tuning::bwd_grid},             {"bwd_rowmajor", &Tuning::bwd_rowmajor},
+    {"bwd_splits", &Tuning::bwd_splits},
     {"mid_kernel", &Tuning::mid_kernel},
 };
 Tuning g_tuning{};
@@ -647,13 +648,14 @@ int bitlinear_backward_ste(const float* dY, int64_t M, int64_t N, int64_t K, con
     if (!dY || !gamma) return BL_ERR_NULL;
     if (dX && (!packed || !beta)) return BL_ERR_NULL;
     if (dW && !codes) return BL_ERR_NULL;
-    const size_t need = bitlinear_workspace_bytes(BL_OP_BACKWARD, M, N, K, granularity, 0);
-    if (!workspace || workspace_bytes < need) return BL_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < backward_workspace_min_bytes(M, N, K) + 256)
+        return BL_ERR_WORKSPACE;
     BackwardArgs a{};
     a.dY = dY; a.M = M; a.N = N; a.K = K; a.codes = codes; a.gamma = gamma;
     a.per_tensor = granularity == BL_GAMMA_PER_TENSOR;
     a.packed = (const uint32_t*)packed; a.beta = beta; a.dX = dX; a.dW = dW;
     a.workspace = (void*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
+    a.workspace_bytes = workspace_bytes - ((uintptr_t)a.workspace - (uintptr_t)workspace);
     return check_hip(launch_backward(a, (hipStream_t)stream));
 }
 

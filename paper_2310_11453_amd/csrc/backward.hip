@@ -373,7 +373,16 @@ __device__ inline void ring_tile_origin(int t, int G, int grid_i, int grid_j, in
     j0 = logical < 0 ? -1 : (int64_t)(logical % grid_j) * BN;
 }
 
-template <int NS>
+// Slices of the reduction (SPLIT).  A product whose tiles cannot fill the CUs (dX^ of 1000 tokens x
+// 2048 columns: 32 tiles) is cut along r as well: work item t is tile t / splits, slice t % splits
+// of `per` stages, and C is then the base of the slices' fp32 sums [splits][I][J], which
+// fold_slices adds in the order 0, 1, ... and scales.  Workgroups go round-robin to the XCDs, so
+// the items of one slice share an L2 when splits divides 8 and the XCD streams only its r range.
+struct RingSlices {
+    int splits, per;  // per: stages of 32 r in a slice
+};
+
+template <int NS, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __restrict__ A,
                                                             const uint16_t* __restrict__ B,
                                                             int64_t I, int64_t J, int64_t Rp,
@@ -381,7 +390,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
                                                             const float* __restrict__ scale_ptr,
                                                             float scale_mul, float* __restrict__ C,
                                                             int grid_i, int grid_j, int blk_i,
-                                                            int blk_j) {
+                                                            int blk_j, RingSlices sl) {
     constexpr int BM = 256, BN = 256, WN = 4, THREADS = 512, WTM = 128, WTN = 64, MI = 4, NI = 2;
     constexpr int PA = BM * 4 / THREADS, PB = BN * 4 / THREADS, P = PA + PB;
     constexpr int A_BYTES = BM * 64, STAGE_BYTES = (BM + BN) * 64;
@@ -391,13 +400,28 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
     const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
     const int wm = w / WN, wn = w % WN;
     const int j = l & 31, g2 = l >> 5;
-    const int nst = (int)(Rp / 32);
-    const int ntiles = grid_i * grid_j;
+    const int nst_all = (int)(Rp / 32);
+    const int nitems = grid_i * grid_j * (SPLIT ? sl.splits : 1);
+    int nst = nst_all;  // stages of the current work item, the first one st0 (SPLIT)
+    int st0 = 0;
     // groups of NS stages whose look-ahead stage st+NS-1 exists for every stage of the group
-    const int main_groups = nst >= 2 * NS - 1 ? (nst - (2 * NS - 1)) / NS + 1 : 0;
+    int main_groups = nst >= 2 * NS - 1 ? (nst - (2 * NS - 1)) / NS + 1 : 0;
 
     auto tile_origin = [&](int t, int64_t& i0, int64_t& j0) {
-        ring_tile_origin(t, (int)gridDim.x, grid_i, grid_j, blk_i, blk_j, BM, BN, i0, j0);
+        if constexpr (SPLIT) {
+            const int tile = t / sl.splits;
+            i0 = (int64_t)(tile / grid_j) * BM;
+            j0 = (int64_t)(tile % grid_j) * BN;
+        } else {
+            ring_tile_origin(t, (int)gridDim.x, grid_i, grid_j, blk_i, blk_j, BM, BN, i0, j0);
+        }
+    };
+    auto set_slice = [&](int t) {
+        if constexpr (SPLIT) {
+            st0 = (t % sl.splits) * sl.per;
+            nst = nst_all - st0 < sl.per ? nst_all - st0 : sl.per;
+            main_groups = nst >= 2 * NS - 1 ? (nst - (2 * NS - 1)) / NS + 1 : 0;
+        }
     };
 
     // DMA: thread -> PA + PB pieces of 16 bytes per stage; piece = (row, swizzled segment).
@@ -422,8 +446,8 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
             if (j0 + row > J - 1) row = (int)(J - 1 - j0);
             goffB[q] = (uint32_t)row * pitch + seg;
         }
-        baseA = reinterpret_cast<const uint8_t*>(A) + i0 * (int64_t)pitch;
-        baseB = reinterpret_cast<const uint8_t*>(B) + j0 * (int64_t)pitch;
+        baseA = reinterpret_cast<const uint8_t*>(A) + i0 * (int64_t)pitch + (int64_t)st0 * 64;
+        baseB = reinterpret_cast<const uint8_t*>(B) + j0 * (int64_t)pitch + (int64_t)st0 * 64;
     };
     const uint32_t lds_wave = (uint32_t)(w * kWave * 16);
     // stage `st` into ring slot st % NS; `src_st` is the stage whose bytes are read (== st, or
@@ -475,6 +499,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
     int64_t i0, j0;
     tile_origin(t, i0, j0);
     if (i0 < 0) return;  // uniform for the whole workgroup
+    set_slice(t);
     setup_dma(i0, j0);
     issue_tile_start();
 
@@ -502,8 +527,10 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
         block_barrier();
         const int t_next = t + (int)gridDim.x;
         int64_t i0n = -1, j0n = -1;
-        if (t_next < ntiles) tile_origin(t_next, i0n, j0n);
+        if (t_next < nitems) tile_origin(t_next, i0n, j0n);
+        float* const Cs = SPLIT ? C + (int64_t)(t % sl.splits) * I * J : C;
         if (i0n >= 0) {
+            set_slice(t_next);
             setup_dma(i0n, j0n);
             issue_tile_start();
         }
@@ -518,7 +545,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
 #pragma unroll
                 for (int s = 0; s < NI; ++s) {
                     const int64_t jj = j0 + wn * WTN + 32 * s + j;
-                    if (jj < J) __builtin_nontemporal_store(scale * acc[mi][s][r], &C[i * J + jj]);  // streaming
+                    if (jj < J) __builtin_nontemporal_store(scale * acc[mi][s][r], &Cs[i * J + jj]);  // streaming
                 }
             }
         if (i0n < 0) break;
@@ -563,7 +590,7 @@ __device__ inline void a_words_wait(v4i (&a)[4], uint32_t (&wd)[2]) {
                  : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(wd[0]), "+v"(wd[1]));
 }
 
-template <int NS>
+template <int NS, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __restrict__ A,
                                                              const uint32_t* __restrict__ Sw,
                                                              int64_t I, int64_t J, int64_t Rp,
@@ -571,7 +598,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
                                                              const float* __restrict__ scale_ptr,
                                                              float scale_mul, float* __restrict__ C,
                                                              int grid_i, int grid_j, int blk_i,
-                                                             int blk_j) {
+                                                             int blk_j, RingSlices sl) {
     constexpr int BM = 256, BN = 256, WN = 4, THREADS = 512, WTM = 128, WTN = 64, MI = 4, NI = 2;
     constexpr int PA = BM * 4 / THREADS, P = PA + 1;  // DMA operations per thread and stage
     constexpr int STAGE_BYTES = BM * 64;
@@ -582,12 +609,27 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
     const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
     const int wm = w / WN, wn = w % WN;
     const int j = l & 31, g2 = l >> 5;
-    const int nst = (int)(Rp / 32);
-    const int ntiles = grid_i * grid_j;
-    const int main_groups = nst >= 2 * NS - 1 ? (nst - (2 * NS - 1)) / NS + 1 : 0;
+    const int nst_all = (int)(Rp / 32);
+    const int nitems = grid_i * grid_j * (SPLIT ? sl.splits : 1);
+    int nst = nst_all;  // stages of the current work item, the first one st0 (SPLIT)
+    int st0 = 0;
+    int main_groups = nst >= 2 * NS - 1 ? (nst - (2 * NS - 1)) / NS + 1 : 0;
 
     auto tile_origin = [&](int t, int64_t& i0, int64_t& j0) {
-        ring_tile_origin(t, (int)gridDim.x, grid_i, grid_j, blk_i, blk_j, BM, BN, i0, j0);
+        if constexpr (SPLIT) {
+            const int tile = t / sl.splits;
+            i0 = (int64_t)(tile / grid_j) * BM;
+            j0 = (int64_t)(tile % grid_j) * BN;
+        } else {
+            ring_tile_origin(t, (int)gridDim.x, grid_i, grid_j, blk_i, blk_j, BM, BN, i0, j0);
+        }
+    };
+    auto set_slice = [&](int t) {
+        if constexpr (SPLIT) {
+            st0 = (t % sl.splits) * sl.per;
+            nst = nst_all - st0 < sl.per ? nst_all - st0 : sl.per;
+            main_groups = nst >= 2 * NS - 1 ? (nst - (2 * NS - 1)) / NS + 1 : 0;
+        }
     };
 
     uint32_t goffA[PA];
@@ -603,10 +645,10 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
             if (i0 + row > I - 1) row = (int)(I - 1 - i0);
             goffA[q] = (uint32_t)row * pitch + seg;
         }
-        baseA = reinterpret_cast<const uint8_t*>(A) + i0 * (int64_t)pitch;
+        baseA = reinterpret_cast<const uint8_t*>(A) + i0 * (int64_t)pitch + (int64_t)st0 * 64;
         int64_t col = j0 + wn * WTN + l;  // columns past J re-read the last one (never stored)
         if (col > J - 1) col = J - 1;
-        wsrc = Sw + col;
+        wsrc = Sw + (int64_t)st0 * J + col;
     };
     const uint32_t lds_wave = (uint32_t)(w * kWave * 16);
     // sign words of stage sb (the last stage's again when sb does not exist) into slot sb % NS
@@ -700,6 +742,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
     int64_t i0, j0;
     tile_origin(t, i0, j0);
     if (i0 < 0) return;  // uniform for the whole workgroup
+    set_slice(t);
     setup_dma(i0, j0);
     issue_tile_start();
 
@@ -731,8 +774,10 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
         block_barrier();
         const int t_next = t + (int)gridDim.x;
         int64_t i0n = -1, j0n = -1;
-        if (t_next < ntiles) tile_origin(t_next, i0n, j0n);
+        if (t_next < nitems) tile_origin(t_next, i0n, j0n);
+        float* const Cs = SPLIT ? C + (int64_t)(t % sl.splits) * I * J : C;
         if (i0n >= 0) {
+            set_slice(t_next);
             setup_dma(i0n, j0n);
             issue_tile_start();
         }
@@ -746,13 +791,36 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
 #pragma unroll
                 for (int s = 0; s < NI; ++s) {
                     const int64_t jj = j0 + wn * WTN + 32 * s + j;
-                    if (jj < J) __builtin_nontemporal_store(scale * acc[mi][s][r], &C[i * J + jj]);
+                    if (jj < J) __builtin_nontemporal_store(scale * acc[mi][s][r], &Cs[i * J + jj]);
                 }
             }
         if (i0n < 0) break;
         t = t_next;
         i0 = i0n;
         j0 = j0n;
+    }
+}
+
+// out = scale * (slice 0 + slice 1 + ...), the sums a split product left.  HBM- (mostly cache-) bound.
+// VEC: 16 bytes per lane; the slices always allow it (their rows are a multiple of 32 wide), `out`
+// when it is 16-byte aligned.
+template <bool VEC>
+__global__ __launch_bounds__(256) void fold_slices(const float* __restrict__ part, int splits,
+                                                   int64_t count, const float* __restrict__ scale_ptr,
+                                                   float scale_mul, float* __restrict__ out) {
+    constexpr int E = VEC ? 4 : 1;
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * E;
+    if (i >= count) return;
+    const float scale = (scale_ptr ? *scale_ptr : 1.0f) * scale_mul;
+    if constexpr (VEC) {
+        v4f v = *reinterpret_cast<const v4f*>(part + i);
+#pragma unroll 4
+        for (int s = 1; s < splits; ++s) v += *reinterpret_cast<const v4f*>(part + s * count + i);
+        *reinterpret_cast<v4f*>(out + i) = v * scale;
+    } else {
+        float v = part[i];
+        for (int s = 1; s < splits; ++s) v += part[s * count + i];
+        out[i] = v * scale;
     }
 }
 
@@ -768,29 +836,59 @@ static int bwd_num_cus() {
     return n;
 }
 
-// The persistent 256 x 256 kernels are used when their tiles fill at least half the CUs (and a
-// lane's byte offset into a block of 256 rows fits 32 bits); the plan is the grid and the block of
-// tiles an XCD runs together (ring_tile_origin): blk_i x blk_j = grid / 8 tiles out of its
-// grid_i / 8 rows, as square as the divisors allow; 0 = no such tiling.
+// The persistent 256 x 256 kernels take every product whose byte offsets into a block of 256 rows
+// fit 32 bits.  The plan is the grid, the block of tiles an XCD runs together (ring_tile_origin):
+// blk_i x blk_j = grid / 8 tiles out of its grid_i / 8 rows, as square as the divisors allow; 0 =
+// no such tiling; and the slices of the reduction.
 struct RingPlan {
     bool use;
     int grid, gi, gj, blk_i, blk_j;
+    RingSlices sl;
 };
-static RingPlan ring_plan(int64_t I, int64_t J, int64_t ld) {
+
+// Slices of a product of `tiles` tiles and nst stages on `cus` CUs: the count that costs least, in
+// units of 1 us, when a stage takes 0.6 us on a CU, an item 7 us besides, and the fp32 sums of a
+// slice (`bytes`) are written and read at 5 TB/s by a second launch of 4 us.  dX^ of M = 1000, N = 8192,
+// K = 2048 (32 tiles of 256 stages): 6 slices, 43 us and 11 us for the fold; on 64 workgroups of the
+// small kernel it took 185 us and the bf16 copy of the weights 8 us more than the sign words.
+static RingSlices ring_slices(int64_t tiles, int64_t nst, double bytes, int64_t cus) {
+    RingSlices best{1, (int)nst};
+    double best_cost = 1e30;
+    for (int64_t want = 1; want <= 16; ++want) {
+        const int64_t per = (nst + want - 1) / want, n = (nst + per - 1) / per;
+        if (want > 1 && per < 8) break;
+        const int64_t rounds = (tiles * n + cus - 1) / cus;
+        const double cost = (double)rounds * (0.6 * (double)per + 7.0) +
+                            (n > 1 ? 4.0 + (double)n * bytes * 2.0 / 5e6 : 0.0);
+        if (cost < best_cost * 0.97) {
+            best_cost = cost;
+            best = RingSlices{(int)n, (int)per};
+        }
+    }
+    return best;
+}
+
+static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp, int64_t ld) {
     RingPlan p{};
     const int64_t gi = (I + 255) / 256, gj = (J + 255) / 256;
     p.gi = (int)gi;
     p.gj = (int)gj;
-    p.use = gi * gj * 2 >= bwd_num_cus() && ld < ((int64_t)1 << 22);
-    if (tuning().bwd_ring) p.use = tuning().bwd_ring == 1 && ld < ((int64_t)1 << 22);
+    p.use = ld < ((int64_t)1 << 22) && gi * gj <= ((int64_t)1 << 26);
+    if (tuning().bwd_ring == 2) p.use = false;
     if (!p.use) return p;
-    int grid = bwd_num_cus();
-    if (tuning().bwd_grid > 0) grid = tuning().bwd_grid;
-    if (grid > gi * gj) grid = (int)(gi * gj);
+    int cus = bwd_num_cus();
+    if (tuning().bwd_grid > 0) cus = tuning().bwd_grid;
+    const int64_t ntiles = gi * gj, nst = Rp / 32;
+    p.sl = ring_slices(ntiles, nst, (double)I * (double)J * 4.0, cus);
+    if (const int n = tuning().bwd_splits) {
+        const int64_t per = (nst + n - 1) / n;
+        p.sl = RingSlices{(int)((nst + per - 1) / per), (int)per};
+    }
+    const int64_t items = ntiles * p.sl.splits;
+    const int grid = cus > items ? (int)items : cus;
     p.grid = grid;
-    const int64_t ntiles = gi * gj;
-    if (ntiles % 8 == 0 && grid % 8 == 0 && gi % 8 == 0 && (ntiles / 8) % (grid / 8) == 0 &&
-        !tuning().bwd_rowmajor) {
+    if (p.sl.splits == 1 && ntiles % 8 == 0 && grid % 8 == 0 && gi % 8 == 0 &&
+        (ntiles / 8) % (grid / 8) == 0 && !tuning().bwd_rowmajor) {
         const int cpx = grid / 8;
         const int64_t rx = gi / 8;
         for (int br = 1; br <= cpx; ++br) {
@@ -805,16 +903,41 @@ static RingPlan ring_plan(int64_t I, int64_t J, int64_t ld) {
     }
     return p;
 }
+// the plan when no room for slices is there
+static RingPlan unsliced(RingPlan p, int64_t Rp) {
+    const int64_t ntiles = (int64_t)p.gi * p.gj;
+    p.sl = RingSlices{1, (int)(Rp / 32)};
+    if (p.grid > ntiles) p.grid = (int)ntiles;
+    return p;
+}
+static size_t slices_bytes(const RingPlan& p, int64_t I, int64_t J) {
+    return p.use && p.sl.splits > 1 ? (size_t)p.sl.splits * I * J * 4 : 0;
+}
 
-// C[I][J] = scale * A[I][:] . B[J][:]: the ring kernel, else the 256 x 128 kernel with a workgroup
-// per tile.
+static void launch_fold(const float* part, const RingPlan& p, int64_t count, const float* scale_ptr,
+                        float scale_mul, float* C, hipStream_t s) {
+    if (((uintptr_t)C & 15) == 0 && (count & 3) == 0)
+        fold_slices<true><<<(unsigned)((count / 4 + 255) / 256), 256, 0, s>>>(
+            part, p.sl.splits, count, scale_ptr, scale_mul, C);
+    else
+        fold_slices<false><<<(unsigned)((count + 255) / 256), 256, 0, s>>>(
+            part, p.sl.splits, count, scale_ptr, scale_mul, C);
+}
+
+// C[I][J] = scale * A[I][:] . B[J][:]: the ring kernel (in slices of r where the plan has them and
+// `part` has room), else the 256 x 128 kernel with a workgroup per tile.
 static void launch_gemm_tn(const uint16_t* A, const uint16_t* B, int64_t I, int64_t J, int64_t Rp,
-                           int64_t ld, const float* scale_ptr, float scale_mul, float* C,
-                           hipStream_t s) {
-    const RingPlan p = ring_plan(I, J, ld);
-    if (p.use) {
-        gemm_tn_bf16_ring<4><<<(unsigned)p.grid, 512, 0, s>>>(A, B, I, J, Rp, ld, scale_ptr, scale_mul,
-                                                               C, p.gi, p.gj, p.blk_i, p.blk_j);
+                           int64_t ld, const float* scale_ptr, float scale_mul, float* C, float* part,
+                           size_t part_bytes, hipStream_t s) {
+    RingPlan p = ring_plan(I, J, Rp, ld);
+    if (slices_bytes(p, I, J) > part_bytes) p = unsliced(p, Rp);
+    if (p.use && p.sl.splits > 1) {
+        gemm_tn_bf16_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(
+            A, B, I, J, Rp, ld, nullptr, 1.0f, part, p.gi, p.gj, 0, 0, p.sl);
+        launch_fold(part, p, I * J, scale_ptr, scale_mul, C, s);
+    } else if (p.use) {
+        gemm_tn_bf16_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
+            A, B, I, J, Rp, ld, scale_ptr, scale_mul, C, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
     } else {
         const unsigned blocks = (unsigned)(((I + 255) / 256) * ((J + 127) / 128));
         gemm_tn_bf16<256, 128><<<blocks, 256, 0, s>>>(A, B, I, J, Rp, ld, scale_ptr, scale_mul, C);
@@ -832,15 +955,22 @@ static inline int64_t row_pitch(int64_t Rp) { return Rp % 2048 == 0 ? Rp + 64 : 
 // product, else the bf16 copy St[K][Nl]
 static size_t signs_bytes(int64_t M, int64_t N, int64_t K) {
     const int64_t Np = pad32(N), Nl = row_pitch(Np);
-    return ring_plan(M, K, Nl).use ? (size_t)(Np / 32) * K * 4 : (size_t)K * Nl * 2;
+    return ring_plan(M, K, Np, Nl).use ? (size_t)(Np / 32) * K * 4 : (size_t)K * Nl * 2;
 }
 
-size_t backward_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+// What the copies need: g[M][Nl], the signs, gwT[N][Ml], qT[K][Ml] (bf16), each region 256-byte aligned.
+size_t backward_workspace_min_bytes(int64_t M, int64_t N, int64_t K) {
     const int64_t Nl = row_pitch(pad32(N)), Ml = row_pitch(pad32(M));
-    // g[M][Nl], the signs, gwT[N][Ml], qT[K][Ml] (bf16), each region 256-byte aligned
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
     return al((size_t)M * Nl * 2) + al(signs_bytes(M, N, K)) + al((size_t)N * Ml * 2) +
            al((size_t)K * Ml * 2);
+}
+// The same and room for the slices of whichever product is cut (one after the other): optional.
+size_t backward_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    const int64_t Np = pad32(N), Mp = pad32(M);
+    const size_t dx = slices_bytes(ring_plan(M, K, Np, row_pitch(Np)), M, K);
+    const size_t dw = slices_bytes(ring_plan(N, K, Mp, row_pitch(Mp)), N, K);
+    return backward_workspace_min_bytes(M, N, K) + (dx > dw ? dx : dw);
 }
 
 hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
@@ -852,28 +982,38 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
     uint16_t* St = (uint16_t*)(ws + al((size_t)M * Nl * 2));
     uint16_t* gwT = (uint16_t*)((char*)St + al(signs_bytes(M, N, K)));
     uint16_t* qT = (uint16_t*)((char*)gwT + al((size_t)N * Ml * 2));
+    const size_t base = backward_workspace_min_bytes(M, N, K);
+    float* part = (float*)(ws + base);
+    const size_t part_bytes = a.workspace_bytes > base ? a.workspace_bytes - base : 0;
 
     // dY is read once: g for dX and gwT for dW come out of the same pass when both are wanted
     launch_cast_transpose<float>(a.dY, M, N, Np, Nl, Mp, Ml, a.per_tensor ? nullptr : a.gamma,
                                  a.dX ? g : nullptr, a.dW ? gwT : nullptr, s);
     if (a.dX) {
-        const RingPlan p = ring_plan(M, K, Nl);
+        RingPlan p = ring_plan(M, K, Np, Nl);
         if (p.use) {  // +-1 from sign words inside the kernel: no bf16 copy of the weights
+            if (slices_bytes(p, M, K) > part_bytes) p = unsliced(p, Np);
             uint32_t* Sw = (uint32_t*)St;
             dim3 gb((unsigned)(Np / 32), (unsigned)tiles_k(K));
             bits_transpose_words<<<gb, 256, 0, s>>>(a.packed, N, K, Sw);
-            gemm_tn_signs_ring<4><<<(unsigned)p.grid, 512, 0, s>>>(g, Sw, M, K, Np, Nl, a.beta, 1.0f,
-                                                                    a.dX, p.gi, p.gj, p.blk_i, p.blk_j);
+            if (p.sl.splits > 1) {
+                gemm_tn_signs_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(
+                    g, Sw, M, K, Np, Nl, nullptr, 1.0f, part, p.gi, p.gj, 0, 0, p.sl);
+                launch_fold(part, p, M * K, a.beta, 1.0f, a.dX, s);
+            } else {
+                gemm_tn_signs_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
+                    g, Sw, M, K, Np, Nl, a.beta, 1.0f, a.dX, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
+            }
         } else {
             dim3 gb((unsigned)((tiles_n(N) + 3) / 4), (unsigned)tiles_k(K));
             bits_transpose_bf16<<<gb, 256, 0, s>>>(a.packed, N, K, Np, Nl, St);
-            launch_gemm_tn(g, St, M, K, Np, Nl, a.beta, 1.0f, a.dX, s);
+            launch_gemm_tn(g, St, M, K, Np, Nl, a.beta, 1.0f, a.dX, nullptr, 0, s);
         }
     }
     if (a.dW) {
         launch_cast_transpose<int8_t>(a.codes, M, K, K, 0, Mp, Ml, nullptr, nullptr, qT, s);
         launch_gemm_tn(gwT, qT, N, K, Mp, Ml, a.per_tensor ? a.gamma : nullptr,
-                       a.per_tensor ? 1.0f / 128.0f : 1.0f, a.dW, s);
+                       a.per_tensor ? 1.0f / 128.0f : 1.0f, a.dW, part, part_bytes, s);
     }
     return hipGetLastError();
 }

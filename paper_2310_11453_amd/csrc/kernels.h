@@ -21,6 +21,7 @@ struct Tuning {
     int bwd_ring;          // backward GEMM: 1 = ring kernel, 2 = small kernel
     int bwd_grid;          // backward ring kernel: workgroups
     int bwd_rowmajor;      // backward ring kernel: plain row-major tile order
+    int bwd_splits;        // backward ring kernels: slices of the reduction
     int group_slices;      // grouped layer, M <= 64: every K-group a slice of the grid (work item) of its own
     int mid_kernel;        // 32 < M <= 64: 1 = LDS-tiled kernel with the in-workgroup K split
 };
@@ -145,7 +146,9 @@ struct BackwardArgs {
     float* dX;
     float* dW;
     void* workspace;
+    size_t workspace_bytes;  // at least backward_workspace_min_bytes
 };
+size_t backward_workspace_min_bytes(int64_t M, int64_t N, int64_t K);
 size_t backward_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t launch_backward(const BackwardArgs& a, hipStream_t s);
 

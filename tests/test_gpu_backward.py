@@ -134,3 +134,31 @@ def test_backward_training_shape_sampled(bl):
                                          float(b), True, rows_dx=rows_dx, rows_dw=rows_dw)
     close(dX.cpu().numpy()[rows_dx], dX_ref)
     close(dW.cpu().numpy()[rows_dw], dW_ref)
+
+
+@pytest.mark.parametrize("M,N,K", [(8, 512, 256), (290, 520, 288), (96, 1056, 1024), (513, 2080, 544)])
+@pytest.mark.parametrize("splits", [2, 3, 7])
+def test_backward_slices_of_the_reduction_exact(bl, tuning, M, N, K, splits):
+    """Both ring kernels with the reduction cut into slices (last slice shorter, slices of one stage,
+    slices shorter than the ring) and folded, on integers: exact.  With a workspace that only holds
+    the operand copies the product runs unsliced, with the same result."""
+    print(f"backward slices M={M} N={N} K={K} splits={splits}", flush=True)
+    tuning("bwd_ring=1,bwd_splits=1")
+    small = bl.workspace_bytes(bl.OP_BACKWARD, M, N, K, True)
+    tuning(f"bwd_ring=1,bwd_splits={splits}")
+    assert bl.workspace_bytes(bl.OP_BACKWARD, M, N, K, True) > small
+    rng = np.random.default_rng(M + splits)
+    W = wl.make_weight(N, K, 0.02, 5)
+    dY = rng.integers(-4, 5, (M, N)).astype(f32)
+    q = rng.integers(-128, 128, (M, K)).astype(np.int8)
+    packed, _, _ = bl.bitlinear_pack_weights(dev(W))
+    one = torch.ones(1, device="cuda")
+    g128 = torch.full((1,), 128.0, device="cuda")
+    sign = oracle.unpack_canonical(
+        bl.bitlinear_packed_to_canonical(packed, N, K).cpu().numpy().view(np.uint32), K)
+    dX_ref = (dY.astype(np.int64) @ sign.astype(np.int64)).astype(f32)
+    dW_ref = (dY.astype(np.int64).T @ q.astype(np.int64)).astype(f32)
+    for ws in (None, torch.empty(small, dtype=torch.uint8, device="cuda")):
+        dX, dW = bl.bitlinear_backward_ste(dev(dY), dev(q), g128, packed, one, True, workspace=ws)
+        assert np.array_equal(dX.cpu().numpy(), dX_ref)
+        assert np.array_equal(dW.cpu().numpy(), dW_ref)
