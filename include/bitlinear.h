@@ -74,7 +74,9 @@ size_t bitlinear_packed_bytes(int64_t N, int64_t K, unsigned flags);
 
 /* host: scratch bytes the given operation needs; 0 for an invalid argument.  BL_OP_MATMUL
  * is the one operation whose need may be 0 for a valid shape (its workspace is optional and
- * only some shapes have a use for it). */
+ * only some shapes have a use for it).  The sizes for the forward calls at M > 64, for
+ * BL_OP_BACKWARD and for BL_OP_LN_BACKWARD include an optional part (partial sums of shapes that are
+ * cut along the reduction to fill the chip): without it the same call runs uncut. */
 size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int granularity,
                                  unsigned flags);
 
@@ -140,8 +142,8 @@ int bitlinear_forward(const float* X, int64_t M, int64_t K, const void* packed, 
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the workspace is a
  * 16 MiB array the library itself holds in device memory (one copy per GPU, kept until the
  * process ends).  The call allocates nothing and runs the same kernels as bitlinear_forward:
- * same arguments, same result bit for bit.  Shapes whose workspace
- * (bitlinear_workspace_bytes(BL_OP_FORWARD, ...)) exceeds 16 MiB = 16777216 bytes return
+ * same arguments, same result bit for bit.  Shapes whose required workspace (without the
+ * optional part for M > 64, see bitlinear_workspace_bytes) exceeds 16 MiB = 16777216 bytes return
  * BL_ERR_UNSUPPORTED: roughly M * K <= 16 MiB less the K-split partial sums, i.e. every
  * decode batch (M <= 64 at K <= 65536), not the prefill batches.  All calls on one GPU share
  * the array: calls that overlap in time (different streams, or threads) race; calls ordered
@@ -313,7 +315,8 @@ int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int thre
  *   mid_split_tiles=c   16 < M <= 64: 512-element chunks of K per slice
  *   mid_only=1          16 < M <= 32: skip the register-streaming kernel
  *   mid_kernel=1        32 < M <= 64: the LDS-tiled kernel with the K split inside the workgroup
- *   prefill_tile=1|2    M > 64: 128 x 256 or 256 x 256 output tiles
+ *   prefill_tile=1|2|3|4   M > 64: 128 x 256, 256 x 256, 128 x 128 or 64 x 128 output tiles
+ *   prefill_split=n     M > 64, tiles 3 and 4: slices of K
  *   prefill_grid=g      M > 64: workgroups of the persistent kernel
  *   group_slices=1      grouped layers up to 64 tokens: every K-group a work item of its own instead of
  *                       several K-groups inside one workgroup

@@ -23,7 +23,7 @@ const TuningField kTuningFields[] = {
     {"decode_tiles", &Tuning::decode_tiles},     {"mid_nosplit", &Tuning::mid_nosplit},
     {"mid_split_tiles", &Tuning::mid_split_tiles}, {"mid_only", &Tuning::mid_only},
     {"prefill_tile", &Tuning::prefill_tile},     {"prefill_grid", &Tuning::prefill_grid},
-    {"prefill_xbm", &Tuning::prefill_xbm},
+    {"prefill_xbm", &Tuning::prefill_xbm},       {"prefill_split", &Tuning::prefill_split},
     {"group_slices", &Tuning::group_slices},
     {"quant_wpr", &Tuning::quant_wpr},           {"bwd_ring", &Tuning::bwd_ring},
     {"bwd_grid", &Tuning::bwd_grid},             {"bwd_rowmajor", &Tuning::bwd_rowmajor},
@@ -86,8 +86,10 @@ QuantWs quant_ws(int64_t M, int granularity) {
     w.total = off;
     return w;
 }
+// `total` is what a caller must bring.  Behind it, optional, room for the K-slices of a large batch
+// (M > 64, one K-group): `full` is what bitlinear_workspace_bytes asks for.
 struct ForwardWs {
-    size_t codes, gamma, rowsum, quant, split, split_bytes, xhat, total;
+    size_t codes, gamma, rowsum, quant, split, split_bytes, xhat, total, full;
 };
 ForwardWs forward_ws(int64_t M, int64_t N, int64_t K, int granularity) {
     ForwardWs w{};
@@ -106,6 +108,7 @@ ForwardWs forward_ws(int64_t M, int64_t N, int64_t K, int granularity) {
     w.xhat = off;  // one token: the normalised row, fp32 [K] (what the codes were rounded from)
     off += M == 1 ? align256((size_t)K * 4) : 0;
     w.total = off;
+    w.full = off + prefill_split_bytes(M, N, K);
     return w;
 }
 
@@ -144,6 +147,7 @@ ForwardWs forward_ws_grouped(int64_t M, int64_t N, int64_t K, int groups_k, int 
     w.split_bytes = group_slices_bytes(M, N, groups_k);
     off += align256(w.split_bytes);
     w.total = off;
+    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K) : 0);
     return w;
 }
 struct LnBackwardWs {
@@ -177,7 +181,13 @@ ForwardWs forward_ws_nonneg(int64_t M, int64_t N, int64_t K, int groups_k, int g
     w.split_bytes = group_slices_bytes(M, N, groups_k);
     off += align256(w.split_bytes);
     w.total = off;
+    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K) : 0);
     return w;
+}
+// what the caller brought past the required bytes, for the K-slices of a large batch
+void offer_slices(GemmArgs& a, char* base, size_t required, size_t workspace_bytes) {
+    a.split_ws = workspace_bytes > required ? (int32_t*)(base + required) : nullptr;
+    a.split_ws_bytes = workspace_bytes - required;
 }
 void plain_fields(GemmArgs& a) {
     a.ldq = a.K;
@@ -248,7 +258,7 @@ size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int gr
             return quant_ws(M, granularity).total;
         case BL_OP_FORWARD:
             if (M < 0 || M > kMaxDim || !shape_ok(N, K)) return 0;
-            return forward_ws(M, N, K, granularity).total;
+            return forward_ws(M, N, K, granularity).full;
         case BL_OP_BACKWARD:
             if (M < 0 || M > kMaxDim || !shape_ok(N, K)) return 0;
             return backward_workspace_bytes(M, N, K) + 256;
@@ -257,10 +267,11 @@ size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int gr
             return ln_backward_ws(M, K, 1).total;
         case BL_OP_FORWARD_NONNEG:
             if (M < 0 || M > kMaxDim || !shape_ok(N, K)) return 0;
-            return forward_ws_nonneg(M, N, K, 1, granularity).total;
+            return forward_ws_nonneg(M, N, K, 1, granularity).full;
         case BL_OP_MATMUL:
             if (M < 0 || M > kMaxDim || !shape_ok(N, K)) return 0;
-            return gemm_split_ws_bytes(M, N, K);  // 0 for most shapes: nothing is needed
+            // 0 for most shapes: nothing is needed
+            return M <= 64 ? gemm_split_ws_bytes(M, N, K) : prefill_split_bytes(M, N, K);
         default:
             return 0;
     }
@@ -373,6 +384,7 @@ int bitlinear_forward(const float* X, int64_t M, int64_t K, const void* packed, 
     plain_fields(a);
     a.split_ws = ws.split_bytes ? (int32_t*)(base + ws.split) : nullptr;
     a.split_ws_bytes = ws.split_bytes;
+    if (M > 64) offer_slices(a, base, ws.total, workspace_bytes);
     if (M <= 16) return check_hip(launch_gemm_decode(a, (hipStream_t)stream));
     return check_hip(launch_gemm_prefill(a, (hipStream_t)stream));
 }
@@ -427,11 +439,11 @@ size_t bitlinear_workspace_bytes_grouped(int op, int64_t M, int64_t N, int64_t K
         case BL_OP_QUANT:
             return quant_ws_grouped(M, groups_k, granularity).total;
         case BL_OP_FORWARD:
-            return forward_ws_grouped(M, N, K, groups_k, granularity).total;
+            return forward_ws_grouped(M, N, K, groups_k, granularity).full;
         case BL_OP_LN_BACKWARD:
             return ln_backward_ws(M, K, groups_k).total;
         case BL_OP_FORWARD_NONNEG:
-            return forward_ws_nonneg(M, N, K, groups_k, granularity).total;
+            return forward_ws_nonneg(M, N, K, groups_k, granularity).full;
         default:
             return 0;
     }
@@ -597,6 +609,7 @@ static int forward_grouped_impl(const float* X, int64_t M, int64_t K, const void
             a.eta = eta + gk;
             a.wsum = wsum + (int64_t)gk * N;
         }
+        if (M > 64) offer_slices(a, base, ws.total, workspace_bytes);
         const hipError_t e = M <= 16 ? launch_gemm_decode(a, (hipStream_t)stream)
                                      : launch_gemm_prefill(a, (hipStream_t)stream);
         if (e != hipSuccess) return BL_ERR_HIP;

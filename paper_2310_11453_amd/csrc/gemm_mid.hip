@@ -26,17 +26,14 @@
 namespace bl {
 
 namespace mid {
-constexpr int BM = 64, BN = 128, KG = 4, WN = 2;
-constexpr int THREADS = KG * WN * kWave;      // 512
-constexpr int GT = WN * kWave;                // threads of a K-group
+constexpr int BN = 128, WN = 2;
+constexpr int THREADS = 512;
 constexpr int STAGE_K = 128;                  // k per stage: a row of a stage is one 128-byte line
-constexpr int STAGE_BYTES = BM * STAGE_K;     // 8 KiB
-constexpr int P = BM * (STAGE_K / 16) / GT;   // 16-byte DMA pieces per thread and stage: 4
-constexpr int NBW = (BN / 16) / WN;           // packed tiles per wave and chunk: 4
 constexpr int SPC = kChunkK / STAGE_K;        // stages per 512-chunk: 4
-static_assert(P == 4 && NBW == 4 && SPC == 4, "tile shape");
+constexpr int P = 4;                          // 16-byte DMA pieces per thread and stage
+static_assert(SPC == 4, "tile shape");
 
-// operands of one half-step (rows j and 32 + j of the stage), complete on exit
+// operands of one half-step (rows j and 32 + j of the wave's 64), complete on exit
 __device__ inline void read_a(v4i (&a)[2], uint32_t ad) {
     asm volatile(
         "ds_read_b128 %0, %2\n\t"
@@ -71,7 +68,10 @@ __device__ inline void lds_wait(v4i (&a)[2]) {
 }
 }  // namespace mid
 
-// Work item = (column tile, K-slice): blockIdx.x = slice * grid_n + tile.  With a.split_k the
+// Tile BM x 128 (64 x 64 per wave): BM = 64 has four K-groups of two waves, BM = 128 two K-groups of
+// four.  Work item = (K-slice, column tile, row tile), row tiles fastest; with several row tiles
+// (M > 64) each XCD gets one contiguous range of the items, so that the row tiles of a column
+// tile, which read the same packed bits, share an L2.  With a.split_k the
 // slice's partial sums 2 * sum_k q b go to a.split_ws and splitk_reduce finishes; otherwise the
 // workgroup owns all of K and writes Y.
 // gmode 2 (a grouped layer, Eq. 13-15): a work item is (column tile, four K-groups of the layer), one
@@ -79,25 +79,42 @@ __device__ inline void lds_wait(v4i (&a)[2]) {
 // its own blob) and its sums go, without being added, to that group's slice of a.split_ws.
 // gmode 1: a work item is (column tile, one K-group of the layer), split over the workgroup's four.
 // NS = stages in each group's ring.
-template <int NS>
-__global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int grid_n, int gmode) {
+// ROWS = false: one row tile (M <= BM).
+template <int BM, int NS, bool ROWS>
+__global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int grid_m, int grid_n,
+                                                                int splits, int gmode) {
     using namespace mid;
-    // rings of the four K-groups; after the walk the same bytes hold two 64 x 128 int32 sums
+    constexpr int WM = BM / 64, GW = WM * WN;   // waves of a K-group
+    constexpr int KG = THREADS / kWave / GW;    // K-groups
+    constexpr int GT = GW * kWave;              // threads of a K-group
+    constexpr int STAGE_BYTES = BM * STAGE_K;   // 8 or 16 KiB
+    constexpr int NBW = (BN / 16) / GW;         // packed tiles per wave and chunk
+    constexpr int REG = KG / 2;                 // BM x BN int32 sums that meet in LDS
+    static_assert(P == BM * (STAGE_K / 16) / GT && NBW * GW * 16 == BN, "tile shape");
+    // rings of the K-groups; after the walk the same bytes hold REG sums
     __shared__ __attribute__((aligned(1024))) uint8_t smA[KG * NS * STAGE_BYTES];
     __shared__ __attribute__((aligned(1024))) uint8_t smB[KG * (BN / 16) * 1024];
-    static_assert(KG * NS * STAGE_BYTES >= 2 * BM * BN * 4, "room for the reduction");
+    static_assert(KG * NS * STAGE_BYTES >= REG * BM * BN * 4, "room for the reduction");
     static_assert(NS >= 4, "the wait bookkeeping below: a stage's codes are requested NS-1 >= 3 stages ahead");
 
     // wave-uniform values in scalar registers: the loop below branches on them
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
-    const int kg = w / WN, wn = w % WN;
+    const int kg = w / GW, wi = w % GW, wm = wi / WN, wn = wi % WN;
     const int tg = threadIdx.x % GT;  // thread inside the K-group
     const int j = l & 31, g2 = l >> 5;
     const int64_t M = a.M, N = a.N;
     const int64_t TN = tiles_n(N);
     const int64_t TKp = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
-    const int sp = (int)blockIdx.x / grid_n;
-    const int64_t n0 = (int64_t)((int)blockIdx.x % grid_n) * BN;
+    int item = (int)blockIdx.x, tm = 0;
+    if constexpr (ROWS) {  // the host rounds the grid up to a multiple of 8
+        item = (item & 7) * (int)(gridDim.x >> 3) + (item >> 3);
+        if (item >= grid_m * grid_n * splits) return;  // uniform for the workgroup
+        tm = item % grid_m;
+        item /= grid_m;
+    }
+    const int sp = item / grid_n;
+    const int64_t m0 = ROWS ? (int64_t)tm * BM : 0;
+    const int64_t n0 = (int64_t)(item % grid_n) * BN;
 
     // ---- this item's slice of K, then this group's chunks of it ----------------------------
     int64_t ki0 = 0, Ki = a.K;
@@ -134,7 +151,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
 
     // ---- epilogue operands of this thread's outputs, requested now ---------------------------
     // thread -> columns nq .. nq+3 of the tile, rows er + 16 h
-    constexpr int EH = BM * (BN / 4) / THREADS;  // 4
+    constexpr int EH = BM * (BN / 4) / THREADS;  // 4 or 8
     constexpr int ER = THREADS / (BN / 4);       // 16
     const int er = (int)threadIdx.x >> 5;
     const int64_t nq = n0 + (threadIdx.x & 31) * 4;
@@ -142,7 +159,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     int e_rs[EH];
 #pragma unroll
     for (int h = 0; h < EH; ++h) {
-        const int64_t m = er + ER * h < M ? er + ER * h : M - 1;
+        const int64_t m = m0 + er + ER * h < M ? m0 + er + ER * h : M - 1;
         e_gamma[h] = a.gamma[a.per_tensor ? 0 : m * a.gstride];
         e_rs[h] = a.rowsum[m * a.gstride];
         e_eta[h] = *(a.eta ? a.eta + (a.per_tensor ? 0 : m * a.gstride) : a.gamma);
@@ -156,7 +173,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         e_ws[c] = *(a.eta ? a.wsum + n : a.rowsum);
     }
 
-    // ---- DMA of this group.  A stage is 64 rows of 128 bytes; thread -> four 16-byte pieces of
+    // ---- DMA of this group.  A stage is BM rows of 128 bytes; thread -> four 16-byte pieces of
     // it, piece = (row, physical segment).  The eight lanes of a row sit in one instruction, so
     // the row's line is requested once.  Segments are XOR-swizzled with (row / 2) % 8: the
     // 16-byte operand reads of 16 consecutive rows then touch every LDS bank exactly once.
@@ -169,17 +186,17 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         const int slot = q * GT + tg;
         int row = slot >> 3;
         gseg[q] = ((slot & 7) ^ ((row >> 1) & 7)) * 16;
-        if (row > M - 1) row = (int)(M - 1);
-        gsrc[q] = a.codes + (int64_t)row * a.ldq + k0 + gseg[q];
+        if (m0 + row > M - 1) row = (int)(M - 1 - m0);
+        gsrc[q] = a.codes + (m0 + row) * a.ldq + k0 + gseg[q];
     }
     const uint32_t* bsrc[NBW];
 #pragma unroll
     for (int q = 0; q < NBW; ++q) {
-        int64_t tn = (n0 >> 4) + wn + q * WN;
+        int64_t tn = (n0 >> 4) + wi + q * GW;
         if (tn > TN - 1) tn = TN - 1;
         bsrc[q] = a.packed + tile_dword_offset(tn, k0 / kChunkK, TKp) + l * 4;
     }
-    const uint32_t lds_wave = (uint32_t)(wn * kWave * 16);
+    const uint32_t lds_wave = (uint32_t)(wi * kWave * 16);
     // clamp: a stage that may reach past the group's K re-reads the last 16 valid bytes of the
     // row instead (the packed bits there are zero, or masked)
     auto issue = [&](int st, bool clamp) {
@@ -202,7 +219,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         for (int q = 0; q < NBW; ++q)
             __builtin_amdgcn_global_load_lds(
                 (const void*)(bsrc[q] + tk * 256),
-                (__attribute__((address_space(3))) void*)(ringB + (wn + q * WN) * 1024), 16, 0, 0);
+                (__attribute__((address_space(3))) void*)(ringB + (wi + q * GW) * 1024), 16, 0, 0);
     };
 
     const uint32_t b_lane = (uint32_t)(uintptr_t)ringB + ((wn * 64 + j) >> 4) * 1024 +
@@ -212,7 +229,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     uint32_t a_lane[4];
 #pragma unroll
     for (int hs = 0; hs < 4; ++hs)
-        a_lane[hs] = (uint32_t)(uintptr_t)ringA + j * STAGE_K + ((2 * hs + g2) ^ sw) * 16;
+        a_lane[hs] = (uint32_t)(uintptr_t)ringA + (wm * 64 + j) * STAGE_K + ((2 * hs + g2) ^ sw) * 16;
     auto a_addr = [&](int st, int hs) { return a_lane[hs] + (uint32_t)((st % NS) * STAGE_BYTES); };
 
     v16i acc[2][2];
@@ -309,16 +326,16 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     wait_vmcnt<0>();
     __syncthreads();  // every group is done with its ring
 
-    // ---- add the four groups: lane (j, g2) of wave wn holds columns 64*wn + 32*s + j, rows
-    // 32*mi + 8*(r/4) + 4*g2 + r%4; groups 2,3 write, groups 0,1 add theirs, then all threads
-    // read both sums ------------------------------------------------------------------------
+    // ---- add the groups: lane (j, g2) of wave (wm, wn) holds columns 64*wn + 32*s + j, rows
+    // 64*wm + 32*mi + 8*(r/4) + 4*g2 + r%4; the upper half of the groups writes, the lower half
+    // adds theirs, then all threads read the REG sums ------------------------------------------
     int* red = reinterpret_cast<int*>(smA);
     auto red_at = [&](int region, int mi, int s2, int r) {
-        return red + region * (BM * BN) + (32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3)) * BN + wn * 64 +
+        return red + region * (BM * BN) + (wm * 64 + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3)) * BN + wn * 64 +
                32 * s2 + j;
     };
-    if (gmode == 2) {  // four K-groups of the layer: each group's sums to its own slice
-        static_assert(KG * NS * STAGE_BYTES >= KG * BM * BN * 4, "room for the four groups' sums");
+    if constexpr (BM == 64) if (gmode == 2) {  // four K-groups of the layer: each group's sums to its own slice
+        static_assert(NS * STAGE_BYTES >= BM * BN * 4, "room for the four groups' sums");
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -343,16 +360,16 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         }
         return;
     }
-    if (kg >= 2) {
+    if (kg >= REG) {
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
             for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) *red_at(kg - 2, mi, s2, r) = acc[mi][s2][r];
+                for (int r = 0; r < 16; ++r) *red_at(kg - REG, mi, s2, r) = acc[mi][s2][r];
     }
     __syncthreads();
-    if (kg < 2) {
+    if (kg < REG) {
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -365,10 +382,11 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // ---- epilogue (Eq. 11): sum_k q s = 2 sum_k q b - sum_k q ; y = that * (beta gamma / 128) ----
 #pragma unroll
     for (int h = 0; h < EH; ++h) {
-        const int64_t m = er + ER * h;
+        const int64_t m = m0 + er + ER * h;
         if (m >= M || nq >= N) continue;
         const int* p0 = red + (er + ER * h) * BN + (threadIdx.x & 31) * 4;
-        const v4i s4 = *reinterpret_cast<const v4i*>(p0) + *reinterpret_cast<const v4i*>(p0 + BM * BN);
+        v4i s4 = *reinterpret_cast<const v4i*>(p0);
+        if constexpr (REG == 2) s4 += *reinterpret_cast<const v4i*>(p0 + BM * BN);
         const bool vec = (N & 3) == 0;  // then nq + 3 < N and the row starts 16-byte aligned
         if (to_slices) {
             int* o = a.split_ws + ((int64_t)sp * M + m) * N + nq;
@@ -432,7 +450,7 @@ int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
 hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
     GemmArgs a = a_in;
     a.split_k = 0;
-    if (a.M > mid::BM || a.K >= ((int64_t)1 << 22) || a.ldq >= ((int64_t)1 << 22))
+    if (a.M > 64 || a.K >= ((int64_t)1 << 22) || a.ldq >= ((int64_t)1 << 22))
         return hipErrorInvalidValue;
     const int grid_n = (int)((a.N + mid::BN - 1) / mid::BN);
     int splits = 1;
@@ -445,14 +463,38 @@ hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
         // four K-groups per work item, one per K-group of the workgroup, unless the layer's groups
         // are long enough to be worth splitting over the workgroup's four themselves
         gmode = tuning().group_slices || tiles_k(a.K) >= 8 ? 1 : 2;
-        splits = gmode == 2 ? (a.kgroups + mid::KG - 1) / mid::KG : a.kgroups;
+        splits = gmode == 2 ? (a.kgroups + 3) / 4 : a.kgroups;
     } else if (per && a.split_ws && a.split_ws_bytes >= need && !tuning().mid_nosplit) {
         splits = (int)((tiles_k(a.K) + per - 1) / per);
         a.tk_pitch = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
         a.split_k = per * kChunkK;
     }
-    gemm_mid_kernel<4><<<(unsigned)(grid_n * splits), mid::THREADS, 0, s>>>(a, grid_n, gmode);
+    gemm_mid_kernel<64, 4, false><<<(unsigned)(grid_n * splits), mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
     if (splits > 1 || gmode) launch_splitk_reduce(a, gmode ? a.kgroups : splits, s);
+    return hipGetLastError();
+}
+
+// M > 64, one K-group: bm x 128 tiles (bm = 64 or 128), K in slices of `per` 512-chunks (per >= the
+// chunks of K: no slices; else a.split_ws must hold slices * M * N * 4 bytes).
+hipError_t launch_gemm_mid_tiles(const GemmArgs& a_in, int bm, int64_t per, hipStream_t s) {
+    GemmArgs a = a_in;
+    const int64_t TK = tiles_k(a.K);
+    const int grid_m = (int)((a.M + bm - 1) / bm), grid_n = (int)((a.N + mid::BN - 1) / mid::BN);
+    const int splits = (int)((TK + per - 1) / per);
+    a.split_k = 0;
+    if (splits > 1) {
+        if (!a.split_ws || a.split_ws_bytes < (size_t)splits * a.M * a.N * 4) return hipErrorInvalidValue;
+        a.tk_pitch = a.tk_pitch ? a.tk_pitch : TK;
+        a.split_k = per * kChunkK;
+    }
+    int64_t items = (int64_t)grid_m * grid_n * splits;
+    if (items > ((int64_t)1 << 30)) return hipErrorInvalidValue;
+    items = (items + 7) / 8 * 8;
+    if (bm == 64)
+        gemm_mid_kernel<64, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, 0);
+    else
+        gemm_mid_kernel<128, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, 0);
+    if (splits > 1) launch_splitk_reduce(a, splits, s);
     return hipGetLastError();
 }
 

@@ -544,33 +544,78 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
             <<<(unsigned)grid, WM * WN * kWave, 0, s>>>(a, grid_m, grid_n, xbm);
 }
 
+// Kernel and K-slices for M > 64: the cheapest of all by these costs in us, fitted to medians of graph
+// replays (n stages of 64 k, c 512-chunks per K-group of the workgroup):
+//   a round of 128 x 256 tiles   8 + 0.37 n     (n = 32: 19.5, 64: 30, 128: 50, 256: 89 to 112)
+//   a round of 256 x 256 tiles  14 + 0.62 n     (n = 32: 33, 64: 51 to 58, 112: 82, 256: 158)
+//   a round of the 128 x 128 and 64 x 128 tiles  5 + 4.2 c   (c = 1: 9, 2: 14, 4: 22, 8: 32 to 36)
+//   slices of K                  4 + the int32 sums written and read at 5 TB/s
+// The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
+// ones win: 333 x 2048 x 2048 9.8 us (64 x 128) against 19.4 us (128 x 256), 200 x 4096 x 16384
+// 22.1 (128 x 128) against 30, 333 x 8192 x 2048 18.5 (64 x 128 in 2 slices) against 50; 1000 x 2048
+// x 8192 stays with 128 x 256: 21.3 against 28.4.
+struct PrefillPlan {
+    int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
+    int64_t per;  // 512-chunks of K per slice (3 and 4)
+};
+static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+    const int64_t cus = num_cus(), TK = tiles_k(K), nst = (K + kStageK - 1) / kStageK;
+    const int force = tuning().prefill_tile;
+    PrefillPlan best{2, TK};
+    double best_us = 1e30;
+    auto offer = [&](int tile, int64_t per, double us) {
+        if (us < best_us) {
+            best_us = us;
+            best = PrefillPlan{tile, per};
+        }
+    };
+    for (int tile = 1; tile <= 4; ++tile) {
+        if (force && tile != force) continue;
+        const int64_t bm = tile == 4 ? 64 : tile == 2 ? 256 : 128, bn = tile <= 2 ? 256 : 128;
+        const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+        if (tile <= 2) {
+            const int64_t rounds = (tiles + cus - 1) / cus;
+            offer(tile, TK, (double)rounds * (tile == 1 ? 8.0 + 0.37 * nst : 14.0 + 0.62 * nst));
+            continue;
+        }
+        const int kg = tile == 3 ? 2 : 4;
+        for (int64_t want = 1; want <= 8; ++want) {
+            if (tuning().prefill_split && want != tuning().prefill_split) continue;
+            const int64_t per = (TK + want - 1) / want, n = (TK + per - 1) / per;
+            const double bytes = (double)n * (double)M * (double)N * 4.0;
+            if (n > 1 && (n != want || bytes > (double)ws_bytes)) continue;
+            const int64_t rounds = (tiles * n + cus - 1) / cus;
+            offer(tile, per, (double)rounds * (5.0 + 4.2 * (double)((per + kg - 1) / kg)) +
+                                 (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0));
+        }
+    }
+    return best;
+}
+// Room for the K-slices of the plan (M > 64): optional, without it K is not split.
+size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K) {
+    if (M <= 64) return 0;
+    const PrefillPlan p = prefill_plan(M, N, K, (size_t)1 << 40);
+    const int64_t n = (tiles_k(K) + p.per - 1) / p.per;
+    return n > 1 ? (size_t)n * M * N * 4 : 0;
+}
+
 // K < 2^22 is required (the per-lane offset into a block of 256 rows is kept in 32 bits).
 hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
     GemmArgs a = a_in;
     a.split_k = 0;  // set here only
     if (a.K >= ((int64_t)1 << 22) || a.ldq >= ((int64_t)1 << 22)) return hipErrorInvalidValue;
-    int pick;
-    if (tuning().prefill_tile) pick = tuning().prefill_tile;
-    else if (a.M <= 64) pick = 0;
-    else {
-        // 256x256 unless the 128-row tile needs fewer block-rounds of work on the CUs.  A 128-row
-        // tile expands every weight bit for half as many MFMAs: per unit of work it measured
-        // 1.12-1.17 times the 256-row tile's time (4096 x 7168 x 21504: 530 us in 11 rounds of
-        // 128-row tiles, 514 us in 6 rounds of 256-row tiles), hence the 8/7.
-        const int64_t cus = num_cus();
-        auto cost = [&](int64_t bm, int64_t bn) {
-            const int64_t blocks = ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn);
-            return ((blocks + cus - 1) / cus) * bm * bn * (bm == 128 ? 8 : 7);
-        };
-        pick = cost(128, 256) < cost(256, 256) ? 1 : 2;
-    }
     if (a.M <= 64) {  // up to 32 tokens: gemm_stream.hip where it takes the shape; else gemm_mid.hip
         if (!tuning().mid_only && a_in.kgroups <= 1 && launch_gemm_stream(a_in, s)) return hipGetLastError();
         return launch_gemm_mid(a_in, s);
     }
     // K-groups in one launch: the 128-row tile, whose accumulators leave room for the fp32 copy
-    if (a.kgroups > 1) pick = 1;
-    if (pick == 1) launch_tile<128, 256, 2, 4, 8>(a, s);
+    if (a.kgroups > 1) {
+        launch_tile<128, 256, 2, 4, 8>(a, s);
+        return hipGetLastError();
+    }
+    const PrefillPlan p = prefill_plan(a.M, a.N, a.K, a.split_ws ? a.split_ws_bytes : 0);
+    if (p.tile >= 3) return launch_gemm_mid_tiles(a, p.tile == 3 ? 128 : 64, p.per, s);
+    if (p.tile == 1) launch_tile<128, 256, 2, 4, 8>(a, s);
     else launch_tile<256, 256, 2, 4, 8>(a, s);
     return hipGetLastError();
 }

@@ -14,7 +14,8 @@ struct Tuning {
     int mid_nosplit;       // 16 < M <= 64: never split K over workgroups
     int mid_split_tiles;   // 16 < M <= 64: 512-chunks of K per slice
     int mid_only;          // 16 < M <= 32: skip the register-streaming kernel
-    int prefill_tile;      // M > 64: 1 = 128 x 256 tiles, 2 = 256 x 256
+    int prefill_tile;      // M > 64: 1 = 128 x 256 tiles, 2 = 256 x 256, 3 = 128 x 128, 4 = 64 x 128
+    int prefill_split;     // M > 64, tiles 3 and 4: slices of K
     int prefill_grid;      // M > 64: workgroups of the persistent kernel
     int prefill_xbm;       // M > 64: tile rows in the block of tiles an XCD owns (0: one)
     int quant_wpr;         // quantiser: waves per row (1, 2, 4, 8)
@@ -124,6 +125,7 @@ struct GemmArgs {
 };
 bool gemm_decode_fuses_quant(int64_t M, int64_t K, int64_t N);
 size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t K);
+size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K);
 int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K);
 void launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_read_probe(const void* src, size_t bytes, int workgroups, int threads,
@@ -131,6 +133,7 @@ hipError_t launch_read_probe(const void* src, size_t bytes, int workgroups, int 
 hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_prefill(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_mid(const GemmArgs& a, hipStream_t s);  // 16 < M <= 64
+hipError_t launch_gemm_mid_tiles(const GemmArgs& a, int bm, int64_t per, hipStream_t s);  // M > 64
 bool launch_gemm_stream(const GemmArgs& a, hipStream_t s);      // 16 < M <= 32; false: not taken
 int64_t stream_split_tiles(int64_t M, int64_t K);
 

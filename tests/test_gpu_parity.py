@@ -201,6 +201,44 @@ def test_matmul_random_shapes(bl, M, K, N):
         assert np.array_equal(host(y), y_ref)
 
 
+# More than 64 tokens: every tile shape on every form of edge (rows, columns and K one past a tile, K
+# within one chunk, fewer chunks than K-groups or slices, N not a multiple of 4) and, for the tiles
+# that allow it, K in slices; the nonnegative quantiser's epilogue; a workspace without room for
+# the slices.
+TILE_SHAPES = [(65, 32, 33), (129, 544, 130), (192, 2080, 256), (257, 4128, 390), (100, 1024, 37)]
+
+
+@pytest.mark.parametrize("M,K,N", TILE_SHAPES)
+def test_matmul_large_batch_tiles(bl, tuning, M, K, N):
+    print(f"matmul tiles M={M} K={K} N={N}", flush=True)
+    sd = wl.seed_for(2, 13 * M + K + N)
+    W = wl.make_weight(N, K, 0.02, sd)
+    X = wl.make_activation(M, K, sd)
+    packed, alpha, beta = bl.bitlinear_pack_weights(dev(W))
+    codes, gamma, rowsum, _ = bl.bitlinear_quant_act(dev(X))
+    sign = oracle.unpack_canonical(host(bl.bitlinear_packed_to_canonical(packed, N, K)).view(np.uint32), K)
+    acc_ref = oracle.matmul_i32(host(codes), sign)
+    y_ref = oracle.dequant(acc_ref, host(gamma), host(beta))
+    wsum = bl.bitlinear_weight_rowsums(packed, N, K)
+    nonneg = None
+    for spec in ["prefill_tile=1", "prefill_tile=2", "prefill_tile=3,prefill_split=1",
+                 "prefill_tile=4,prefill_split=1", "prefill_tile=3,prefill_split=2",
+                 "prefill_tile=3,prefill_split=4", "prefill_tile=4,prefill_split=3"]:
+        print(f"  {spec}", flush=True)
+        tuning(spec)
+        need = bl.workspace_bytes(bl.OP_MATMUL, M, N, K)
+        for ws in (None, torch.empty(need, dtype=torch.uint8, device="cuda") if need else None):
+            acc = bl.bitlinear_matmul(codes, gamma, rowsum, packed, N, beta, flags=bl.FLAG_OUT_ACC_I32,
+                                      workspace=ws)
+            assert np.array_equal(host(acc), acc_ref)
+            y = bl.bitlinear_matmul(codes, gamma, rowsum, packed, N, beta, workspace=ws)
+            assert np.array_equal(host(y), y_ref)
+        yn = bl.bitlinear_forward_nonneg(dev(X), packed, N, beta, wsum)
+        assert nonneg is None or torch.equal(yn, nonneg)
+        nonneg = yn
+        assert torch.equal(bl.bitlinear_forward(dev(X), packed, N, beta), y)
+
+
 # 17 to 32 tokens (weights streamed through registers): N not a multiple of 4 (element-wise
 # stores), one to four pairs of tiles per workgroup, 1 / 5 / 7 / 8 waves, chunks spread unevenly
 # over the waves, a K long enough for two slices, and a shape the kernel hands to the mid-batch one
