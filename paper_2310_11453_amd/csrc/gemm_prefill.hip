@@ -123,11 +123,7 @@ __device__ inline void lds_write_b32(uint32_t ad, uint32_t v) {
 // GEN = false: the plain layer (one beta, Y = result): nothing of what follows costs anything.
 // GEN = true adds beta per column group (Eq. 13), accumulation over K-groups, the shift term of
 // Eq. 6.
-// KGRP = true (with GEN): all a.kgroups K-groups of a grouped layer (Eq. 13-15) in this launch.  A
-// work item is (tile, group), the groups of a tile following each other on the same workgroup:
-// each group's int32 sums are dequantised with that group's beta_g gamma_g / 128 (and shifted by
-// its eta_g) into an fp32 register copy of the tile, which is stored once, after the last group.
-template <int BM, int BN, int WM, int WN, int NS, bool GEN, bool KGRP = false>
+template <int BM, int BN, int WM, int WN, int NS, bool GEN>
 __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs a, int grid_m,
                                                                         int grid_n, int xbm) {
     constexpr int THREADS = WM * WN * kWave;
@@ -197,7 +193,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
     int gseg[P];
     const int8_t* gbase = a.codes;
     const uint32_t* bsrc[NBW];
-    auto setup_dma = [&](int64_t m0, int64_t n0, int grp) {
+    auto setup_dma = [&](int64_t m0, int64_t n0) {
 #pragma unroll
         for (int q = 0; q < P; ++q) {
             const int slot = q * THREADS + threadIdx.x;
@@ -206,15 +202,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
             if (m0 + row > M - 1) row = (int)(M - 1 - m0);
             goff[q] = (uint32_t)row * (uint32_t)a.ldq + gseg[q];
         }
-        gbase = a.codes + m0 * a.ldq + (KGRP ? (int64_t)grp * K : 0);
+        gbase = a.codes + m0 * a.ldq;
         // packed weights: tile t of the block goes to smB + t KiB, lane for lane as it lies in
         // memory; wave w moves tiles w, w + NWAVES, ...  Columns past N read a valid tile.
 #pragma unroll
         for (int q = 0; q < NBW; ++q) {
             int64_t tn = (n0 >> 4) + w + q * NWAVES;
             if (tn > TN - 1) tn = TN - 1;
-            bsrc[q] = a.packed + (KGRP ? (int64_t)grp * a.group_packed : 0) +
-                      tile_dword_offset(tn, 0, TKp) + l * 4;
+            bsrc[q] = a.packed + tile_dword_offset(tn, 0, TKp) + l * 4;
         }
     };
     const uint32_t lds_wave = (uint32_t)(w * kWave * 16);
@@ -324,14 +319,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
     };
 
     int t = (int)blockIdx.x, parity = 0;
-    int grp = 0;  // KGRP: the K-group of the current work item
-    const int ngroups = KGRP ? a.kgroups : 1;
     int64_t m0, n0;
     tile_origin(t, m0, n0);
     if (m0 < 0) return;  // uniform for the whole workgroup
-    setup_dma(m0, n0, 0);
+    setup_dma(m0, n0);
     issue_tile_start();
-    float side[KGRP ? MI : 1][KGRP ? NI : 1][16];  // KGRP: the tile's sum over the groups so far
 
     while (true) {
         if constexpr (GEN) {
@@ -348,14 +340,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                 // with one beta for the matrix the quotient is 0 by itself; the Eq. 6 operands are
                 // read from a valid stand-in address when they are not in use
                 const uint32_t bg = (uint32_t)n / (uint32_t)a.beta_rows;
-                // KGRP: group grp's entries lie grp further on (gamma, rowsum, eta: [M][groups] or
-                // [groups] per tensor; beta: [row groups][groups]); wsum: [groups][N]
-                const int64_t go = KGRP ? grp : 0;
-                const float gm = a.gamma[(a.per_tensor ? 0 : m * a.gstride) + go];
-                const int rs = a.rowsum[m * a.gstride + go];
-                const float b = a.beta[bg * a.beta_stride + go];
-                const float e = *(a.eta ? a.eta + (a.per_tensor ? 0 : m * a.gstride) + go : a.gamma);
-                const int ws = *(a.eta ? a.wsum + go * a.N + n : a.rowsum);
+                const float gm = a.gamma[a.per_tensor ? 0 : m * a.gstride];
+                const int rs = a.rowsum[m * a.gstride];
+                const float b = a.beta[bg * a.beta_stride];
+                const float e = *(a.eta ? a.eta + (a.per_tensor ? 0 : m * a.gstride) : a.gamma);
+                const int ws = *(a.eta ? a.wsum + n : a.rowsum);
                 if (i < BM) {
                     // gamma / 128 is exact, so beta * (gamma / 128) has the bits of (beta * gamma) / 128
                     lds_write_b32((uint32_t)(uintptr_t)&smScale[parity][i], __float_as_uint(gm * 0.0078125f));
@@ -409,15 +398,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
 
         // Every wave is done with the LDS ring: start the next tile's stream, then store.
         block_barrier();
-        // the next work item: the tile's next K-group, else the workgroup's next tile
-        const bool last_group = !KGRP || grp + 1 == ngroups;
-        const int grp_next = last_group ? 0 : grp + 1;
-        const int t_next = last_group ? t + (int)gridDim.x : t;
+        const int t_next = t + (int)gridDim.x;
         int64_t m0n = -1, n0n = -1;
-        if (!last_group) m0n = m0, n0n = n0;
-        else if (t_next < ntiles) tile_origin(t_next, m0n, n0n);
+        if (t_next < ntiles) tile_origin(t_next, m0n, n0n);
         if (m0n >= 0) {
-            setup_dma(m0n, n0n, grp_next);
+            setup_dma(m0n, n0n);
             issue_tile_start();
         }
 
@@ -461,19 +446,6 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                         // y = acc * ((beta * gamma) / 128)
                         // (GEN: sc4 holds gamma / 128, else the whole scale)
                         float y = GEN ? (float)pm * (bcol[s] * sc4[rr]) : (float)pm * sc4[rr];
-                        if constexpr (KGRP) {
-                            if (a.eta) {  // Eq. 6 / Eq. 14: + (beta_g * eta_g) * sum_{k in g} s[n,k]
-                                const float e = lds_read_f32(
-                                    (uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi + 8 * rq + 4 * g2 + rr]);
-                                y = y + (bcol[s] * e) * wcol[s];
-                            }
-                            // groups are added in the order 0, 1, ... (as launches per group would)
-                            if (grp) y = y + side[mi][s][r];
-                            side[mi][s][r] = y;
-                            if (!last_group) continue;
-                            __builtin_nontemporal_store(y, &a.Y[m * a.N + n]);
-                            continue;
-                        }
                         if (special) {  // uniform
                             if (a.out_acc) {
                                 reinterpret_cast<int*>(a.Y)[m * a.N + n] = pm;
@@ -494,11 +466,304 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
             }
         if (m0n < 0) break;
         t = t_next;
-        grp = grp_next;
         m0 = m0n;
         n0 = n0n;
         parity ^= 1;
     }
+}
+
+// ---- grouped layers (Eq. 13-15): all K-groups of a 128 x 256 tile in one workgroup --------------
+// Y[m,n] = sum_g (beta_g[n] * (gamma_g[m] / 128)) * (2 sum_{k in g} q b - sum_{k in g} q)  (+ Eq. 6's
+// (beta_g eta_g) wsum_g): a work item is (tile, K-group), the groups of a tile following each other;
+// each item's int32 sums are dequantised into an fp32 register copy of the tile in the order 0, 1,
+// ..., which is stored once, after the last group.
+//
+// Bound by the matrix pipe and, at short groups, by whatever happens between items: K = 7168 in 8
+// groups is 14 stages an item.  So the stream of operands does not stop there.  Codes, packed bits
+// and the items' scales have cursors of their own that run ahead of the multiplication (7 stages, two
+// 512-chunks, one item) straight across the ends of groups and tiles; every mid-stage point issues
+// the same operations, so the waits are the same constants everywhere.  The bits have two LDS buffers
+// (a chunk's bits are requested when the chunk before the last starts), the scales two as well.
+// A group's K may end inside a stage or a chunk: what follows meets zero bits (tiles are padded with
+// them), and the at most 32 bytes behind the codes of the last row lie in the workspace.  A cursor
+// at the end of the workgroup's work re-reads its last piece into a buffer nobody reads.
+//
+// The waits.  Mid-point of stage s (between its half-steps), per wave and in this order: wait,
+// barrier, [last stage of a chunk: read the next chunk's bits], [first stage of an item: request
+// the next item's scales], [first stage of a chunk: request the bits of the chunk after the next],
+// request codes of stage s + 7.  Needed there: codes of stage s + 1, with the codes of stages s + 2
+// .. s + 6 (five operations) younger; the bits read there, and at the fold the scales: younger than
+// these are the codes of at least 2 nst - 1 stages and the bits of a chunk, five or more when an item
+// has two stages or more (nst).  One wait for all but the last five covers all three; items of one
+// stage wait for everything.
+//
+// 1000 x 7168 x 28672 in 8 x 8 groups: the layer takes 250 us; with the ring drained and filled for every item
+// and the scales loaded behind it, 445 us.
+template <bool ETA>
+__global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid_m, int grid_n) {
+    constexpr int BM = 128, BN = 256, WN = 4, NS = 8, THREADS = 512, NWAVES = 8;
+    constexpr int WTM = 64, WTN = 64, MI = 2, NI = 2;
+    constexpr int STAGE_BYTES = BM * kStageK;  // 8 KiB: one 16-byte DMA piece per thread
+    constexpr int BITS_BYTES = (BN / 16) * 1024;
+    constexpr int NBW = BN / 16 / NWAVES;
+    __shared__ __attribute__((aligned(1024))) uint8_t smA[NS * STAGE_BYTES];
+    __shared__ __attribute__((aligned(1024))) uint8_t smB[2 * BITS_BYTES];
+    // per item: gamma [128], row sums [128], beta [256]; Eq. 6: eta [128], unused [128], wsum [256]
+    __shared__ __attribute__((aligned(1024))) uint32_t smS[2][THREADS];
+    __shared__ __attribute__((aligned(1024))) uint32_t smE[2][ETA ? THREADS : 4];
+
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
+    const int wm = w / WN, wn = w % WN;
+    const int j = l & 31, g2 = l >> 5;
+    const int M = (int)a.M, N = (int)a.N;
+    const int TN = (int)tiles_n(a.N);
+    const int64_t TK = tiles_k(a.K);
+    const int nst = (int)((a.K + kStageK - 1) / kStageK), nch = (int)TK;
+    const int ntiles = grid_m * grid_n, G = (int)gridDim.x, ngroups = a.kgroups;
+
+    // a workgroup's tiles t = blockIdx.x, + G, ...: one contiguous range of the row-major sequence of
+    // tiles per XCD (as in gemm_prefill_kernel); false: no such tile
+    auto tile_origin = [&](int t, int& m0, int& n0) {
+        if (t >= ntiles) return false;
+        int logical = t;
+        if ((ntiles & 7) == 0 && (G & 7) == 0) {
+            const int q = ((t % G) >> 3) + (t / G) * (G >> 3);
+            if (q >= (ntiles >> 3)) return false;
+            logical = (t & 7) * (ntiles >> 3) + q;
+        }
+        m0 = logical / grid_n * BM;
+        n0 = logical % grid_n * BN;
+        return true;
+    };
+    // a position in the workgroup's sequence of items
+    struct Item {
+        int t, grp, m0, n0;
+    };
+    // false (and unchanged) at the last item
+    auto next_item = [&](Item& it) {
+        if (it.grp + 1 < ngroups) {
+            ++it.grp;
+            return true;
+        }
+        int m0, n0;
+        if (!tile_origin(it.t + G, m0, n0)) return false;
+        it = Item{it.t + G, 0, m0, n0};
+        return true;
+    };
+    Item cur{(int)blockIdx.x, 0, 0, 0};
+    if (!tile_origin(cur.t, cur.m0, cur.n0)) return;  // uniform for the whole workgroup
+    Item ca = cur, cb = cur, cs = cur;                // codes, bits, scales
+
+    // ---- codes: thread -> one piece (row, swizzled segment) of a stage ------------------------
+    const int arow = (int)threadIdx.x >> 2;
+    const int aseg = (((int)threadIdx.x & 3) ^ ((arow >> 2) & 3)) * 16;
+    uint32_t goff = 0;
+    const int8_t* abase = nullptr;
+    int ast = 0, aslot = 0;
+    auto set_codes = [&]() {
+        const int last = M - 1 - ca.m0;
+        goff = (uint32_t)(arow < last ? arow : last) * (uint32_t)a.ldq + aseg;
+        abase = a.codes + (int64_t)ca.m0 * a.ldq + (int64_t)ca.grp * a.K;
+    };
+    auto issue_codes = [&]() {
+        __builtin_amdgcn_global_load_lds(
+            (const void*)(abase + (int64_t)ast * kStageK + goff),
+            (__attribute__((address_space(3))) void*)(smA + aslot * STAGE_BYTES + w * (kWave * 16)), 16, 0, 0);
+        aslot = (aslot + 1) & (NS - 1);
+        if (ast + 1 < nst) ++ast;
+        else if (next_item(ca)) {
+            ast = 0;
+            set_codes();
+        }
+    };
+    // ---- packed bits: wave w moves tiles w and w + 8 of the block; columns past N read a valid tile
+    int bch = 0, bbuf = 0;
+    auto issue_bits = [&]() {
+#pragma unroll
+        for (int q = 0; q < NBW; ++q) {
+            int tn = (cb.n0 >> 4) + w + q * NWAVES;
+            if (tn > TN - 1) tn = TN - 1;
+            __builtin_amdgcn_global_load_lds(
+                (const void*)(a.packed + (int64_t)cb.grp * a.group_packed +
+                              tile_dword_offset(tn, bch, TK) + l * 4),
+                (__attribute__((address_space(3))) void*)(smB + bbuf * BITS_BYTES + (w + q * NWAVES) * 1024),
+                16, 0, 0);
+        }
+        bbuf ^= 1;
+        if (bch + 1 < nch) ++bch;
+        else if (next_item(cb)) bch = 0;
+    };
+    // ---- scales of an item: a dword per thread (two with Eq. 6) -----------------------------------
+    int sbuf = 0;
+    auto issue_scales = [&]() {
+        const int i = (int)threadIdx.x;
+        const int r = cs.m0 + (i & (BM - 1)), c = cs.n0 + (i & (BN - 1));
+        const int64_t m = r < M ? r : M - 1;
+        const int n = c < N ? c : N - 1;
+        const int64_t gi = (a.per_tensor ? 0 : m * a.gstride) + cs.grp;
+        const void* src;
+        if (w < 2) src = a.gamma + gi;  // uniform branches
+        else if (w < 4) src = a.rowsum + m * a.gstride + cs.grp;
+        else src = a.beta + (int64_t)((uint32_t)n / (uint32_t)a.beta_rows) * a.beta_stride + cs.grp;
+        __builtin_amdgcn_global_load_lds(
+            src, (__attribute__((address_space(3))) void*)(&smS[sbuf][w * kWave]), 4, 0, 0);
+        if constexpr (ETA) {
+            if (w < 4) src = a.eta + gi;
+            else src = a.wsum + (int64_t)cs.grp * a.N + n;
+            __builtin_amdgcn_global_load_lds(
+                src, (__attribute__((address_space(3))) void*)(&smE[sbuf][w * kWave]), 4, 0, 0);
+        }
+        sbuf ^= 1;
+        next_item(cs);
+    };
+
+    // operand addresses, as in gemm_prefill_kernel
+    const uint32_t b_lane = (uint32_t)(uintptr_t)smB + ((wn * WTN + j) >> 4) * 1024 +
+                            (g2 * 16 + (j & 15)) * 16;
+    const int sw = (j >> 2) & 3;
+    const uint32_t a_lane[2] = {
+        (uint32_t)(uintptr_t)smA + (wm * WTM + j) * kStageK + ((g2) ^ sw) * 16,
+        (uint32_t)(uintptr_t)smA + (wm * WTM + j) * kStageK + ((2 + g2) ^ sw) * 16};
+
+    v16i acc[MI][NI];
+    v4i bw[NI][2];
+    v4i ax[MI], ay[MI], bx[NI], by[NI];
+    float side[MI][NI][16] = {};  // the tile's sum over the groups so far
+    // acc += ac x b; meanwhile an = operands at `ad`, bn = plane i of half h (see gemm_prefill_kernel)
+    auto half_step = [&](const v4i(&ac)[MI], const v4i(&b)[NI], v4i(&bn)[NI], int h, int i, v4i(&an)[MI],
+                         uint32_t ad) {
+        lds_issue(an, ad);
+        asm volatile("" : "+v"(bw[0][h]), "+v"(bw[1][h]));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int s = 0; s < NI; ++s) {
+                acc[mi][s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ac[mi], b[s], acc[mi][s], 0, 0, 0);
+                const int q = mi * NI + s;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int idx = q * 2 + e;
+                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] >> i) & 0x01010101u);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            }
+        asm volatile("" : "+v"(bn[0]), "+v"(bn[1]));
+        __builtin_amdgcn_sched_barrier(0);
+        lds_wait(an);
+    };
+
+    const bool one_stage = nst == 1;
+    int slot = 0, rbuf = 0;  // the stage's ring slot; the buffer the current chunk's bits came from
+    auto stage = [&](auto ic, bool last, bool first_chunk) {
+        constexpr int i = decltype(ic)::value;
+        half_step(ax, bx, by, 1, i, ay, a_lane[1] + (uint32_t)(slot * STAGE_BYTES));
+        if (one_stage) wait_vmcnt<0>();
+        else wait_vmcnt<5>();
+        block_barrier();
+        if (last) {
+            rbuf ^= 1;
+            lds_read_bits(bw, b_lane + (uint32_t)(rbuf * BITS_BYTES));
+        }
+        if constexpr (i == 0) {
+            if (first_chunk) issue_scales();
+            issue_bits();
+        }
+        issue_codes();
+        slot = (slot + 1) & (NS - 1);
+        half_step(ay, by, bx, 0, last ? 0 : i + 1, ax, a_lane[0] + (uint32_t)(slot * STAGE_BYTES));
+    };
+    auto clear = [&]() {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int s = 0; s < NI; ++s)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[mi][s][r] = 0;
+    };
+
+    set_codes();
+    issue_scales();
+    issue_bits();
+    issue_bits();
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) issue_codes();
+    wait_vmcnt<NS - 2>();  // younger than stage 0: stages 1 .. 6
+    block_barrier();
+    lds_read_bits(bw, b_lane);
+    lds_read_a(ax, a_lane[0]);
+#pragma unroll
+    for (int s = 0; s < NI; ++s)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) bx[s][d] = (int)((uint32_t)bw[s][0][d] & 0x01010101u);
+    clear();
+
+    int fbuf = 0;  // the scales of the item being folded
+    while (true) {
+        for (int c = 0; c < nch; ++c) {
+            const int len = nst - 8 * c;  // stages of this chunk: min(len, 8)
+            static_for<0, 8>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                if (i < len) stage(ic, i == 7 || i + 1 == len, c == 0);
+            });
+        }
+        // ---- fold: lane (j, g2) holds column n, rows 8 (r / 4) + 4 g2 + r % 4 of each sub-tile ----
+        float bcol[NI], wcol[NI];
+#pragma unroll
+        for (int s = 0; s < NI; ++s) {
+            const int col = wn * WTN + 32 * s + j;
+            bcol[s] = lds_read_f32((uint32_t)(uintptr_t)&smS[fbuf][2 * BM + col]);
+            wcol[s] = ETA ? (float)__float_as_int(lds_read_f32((uint32_t)(uintptr_t)&smE[fbuf][2 * BM + col]))
+                            : 0.f;
+        }
+        const uint32_t row_base = (uint32_t)(uintptr_t)&smS[fbuf][wm * WTM + 4 * g2];
+        const uint32_t eta_base = (uint32_t)(uintptr_t)&smE[fbuf][wm * WTM + 4 * g2];
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                v4f sc4;
+                v4i rs4;
+                lds_read_rows(sc4, rs4, row_base + (32 * mi + 8 * rq) * 4, row_base + (BM + 32 * mi + 8 * rq) * 4);
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const int r = rq * 4 + rr;
+                    const float sc = sc4[rr] * 0.0078125f;  // gamma / 128, exact
+                    const float e = ETA ? lds_read_f32(eta_base + (32 * mi + 8 * rq + rr) * 4) : 0.f;
+#pragma unroll
+                    for (int s = 0; s < NI; ++s) {
+                        float y = (float)(2 * acc[mi][s][r] - rs4[rr]) * (bcol[s] * sc);
+                        if constexpr (ETA) y = y + (bcol[s] * e) * wcol[s];
+                        side[mi][s][r] = y + side[mi][s][r];
+                    }
+                }
+            }
+        if (cur.grp + 1 == ngroups) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int m = cur.m0 + wm * WTM + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3);
+                    if (m >= M) continue;
+#pragma unroll
+                    for (int s = 0; s < NI; ++s) {
+                        const int n = cur.n0 + wn * WTN + 32 * s + j;
+                        if (n < N) __builtin_nontemporal_store(side[mi][s][r], &a.Y[(int64_t)m * N + n]);
+                    }
+                }
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int s = 0; s < NI; ++s)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) side[mi][s][r] = 0.f;
+        }
+        if (!next_item(cur)) break;
+        fbuf ^= 1;
+        clear();
+    }
+    wait_vmcnt<0>();
 }
 
 static int num_cus() {
@@ -529,13 +794,6 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
     int xbm = 1;
     if ((ntiles & 7) == 0 && (grid & 7) == 0 && tuning().prefill_xbm > 0)
         xbm = tuning().prefill_xbm < grid_m ? tuning().prefill_xbm : grid_m;
-    if constexpr (BM == 128) {
-        if (a.kgroups > 1) {  // all K-groups of a grouped layer in this launch
-            gemm_prefill_kernel<BM, BN, WM, WN, NS, true, true>
-                <<<(unsigned)grid, WM * WN * kWave, 0, s>>>(a, grid_m, grid_n, xbm);
-            return;
-        }
-    }
     if (plain)
         gemm_prefill_kernel<BM, BN, WM, WN, NS, false>
             <<<(unsigned)grid, WM * WN * kWave, 0, s>>>(a, grid_m, grid_n, xbm);
@@ -608,9 +866,13 @@ hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
         if (!tuning().mid_only && a_in.kgroups <= 1 && launch_gemm_stream(a_in, s)) return hipGetLastError();
         return launch_gemm_mid(a_in, s);
     }
-    // K-groups in one launch: the 128-row tile, whose accumulators leave room for the fp32 copy
     if (a.kgroups > 1) {
-        launch_tile<128, 256, 2, 4, 8>(a, s);
+        const int grid_m = (int)((a.M + 127) / 128), grid_n = (int)((a.N + 255) / 256);
+        int grid = num_cus();  // one workgroup per CU
+        if (tuning().prefill_grid > 0) grid = tuning().prefill_grid;
+        if (grid > grid_m * grid_n) grid = grid_m * grid_n;
+        if (a.eta) gemm_group_kernel<true><<<(unsigned)grid, 512, 0, s>>>(a, grid_m, grid_n);
+        else gemm_group_kernel<false><<<(unsigned)grid, 512, 0, s>>>(a, grid_m, grid_n);
         return hipGetLastError();
     }
     const PrefillPlan p = prefill_plan(a.M, a.N, a.K, a.split_ws ? a.split_ws_bytes : 0);

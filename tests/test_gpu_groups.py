@@ -149,6 +149,19 @@ def test_grouped_forward_group_placement(bl, tuning, M, K, N, gn, gk):
     assert np.array_equal(y0, y1)
 
 
+@pytest.mark.parametrize("M,Kg,N,gn,gk,grid", [(130, 32, 272, 1, 5, 2), (300, 64, 528, 3, 8, 2),
+                                               (257, 96, 512, 1, 3, 1), (300, 160, 272, 1, 4, 3),
+                                               (129, 512, 288, 2, 2, 2), (200, 544, 520, 1, 4, 2),
+                                               (512, 576, 1024, 8, 2, 8), (150, 1120, 256, 1, 3, 1)])
+def test_grouped_forward_large_batch_stream(bl, tuning, M, Kg, N, gn, gk, grid):
+    """More than 64 tokens: the operand stream runs on across the ends of groups and tiles.  Groups of
+    one stage, two stages, one chunk, one stage past a chunk, an odd number of chunks and a K that ends
+    inside a stage, on few enough workgroups that each walks several tiles."""
+    print(f"grouped stream M={M} Kg={Kg} N={N} gn={gn} gk={gk} grid={grid}", flush=True)
+    tuning(f"prefill_grid={grid}")
+    _check_forward(bl, M, Kg * gk, N, gn, gk, False, 700 + M)
+
+
 def test_grouped_forward_full_size_30b(bl):
     """A 30B-shaped layer (7168 -> 28672) with eight groups on each axis, decode and prefill batch:
     alpha_g, beta_g and all bits; codes and gamma_g given the normalised input the GPU dumped;
