@@ -7,18 +7,16 @@
 // Both are bf16 MFMA contractions with fp32 accumulation (+-1 and int8 codes are exact in
 // bf16; only dY is rounded).
 //
-// Structure.  Each operand is first written once in the layout the MFMA wants, i.e. with the
-// reduction index contiguous and padded with zeros to a multiple of 32:
-//   g   [M][Np]   rows of dY, cast                (A operand of dX, reduction over N)
-//   Sw  [Np/32][K] the signs of 32 weight rows of a column in one word (B operand of dX for
-//                 large operands: the kernel builds +-1 bf16 from it in registers), or
-//   St  [K][Np]   +-1 as bf16 from the packed bits (B operand of dX for small operands)
-//   gwT [N][Mp]   dY transposed, scaled, cast      (A operand of dW, reduction over M)
-//   qT  [K][Mp]   codes transposed, cast           (B operand of dW)
+// Structure.  Each operand is first written once in the layout the product kernels read (in blocks
+// of 32 reduction indices, padded with zeros; see block_offset):
+//   g   [M][Np]    rows of dY, cast                (A operand of dX, reduction over N)
+//   Sw  [Np/32][K] the signs of 32 weight rows of a column in one word (B operand of dX: the
+//                  kernel builds +-1 bf16 from it in registers)
+//   gwT [N][Mp]    dY transposed, scaled, cast     (A operand of dW, reduction over M)
+//   qT  [K][Mp]    codes transposed, cast          (B operand of dW)
 // (one pass over dY writes g and gwT) and one product, C[I][J] = scale * sum_r A[I][r] B[J][r],
-// serves both: persistent 256 x 256 kernels fed by DMA for large operands, a plain 256 x 128
-// kernel otherwise.  The preparation passes are HBM-bound and small next to the 2*M*N*K flops
-// of each product.
+// serves both: persistent 256 x 256 kernels fed by DMA, cut along r where the tiles are few.  The
+// preparation passes are HBM-bound and small next to the 2*M*N*K flops of each product.
 
 #include "common.h"
 #include "kernels.h"
@@ -35,11 +33,19 @@ __device__ inline uint32_t bf16_bits(float v) {
     return u >> 16;
 }
 
-// Rows of the bf16 copies are `ld` elements apart, ld >= the padded length: see row_pitch().
+// Layout of the bf16 copies: blocks of 32 reduction indices, inside a block row by row, i.e. element
+// (row, r) of a copy with R rows lies at ((r / 32) * R + row) * 32 + r % 32.  A stage of the product
+// kernels (32 r of 256 rows) is then 16 KiB in one piece: whole 128-byte lines, each requested once.
+// (Row-major copies gave it 64 bytes of each of 256 rows, half a line per request, and a pitch that
+// had to be kept off multiples of 4 KiB.)  M = 8192, 4096 -> 16384: dW 963 -> 946 us, the pass over dY 205 ->
+// 188 us, whose stores fall on contiguous 256-byte pieces now.
+__host__ __device__ inline int64_t block_offset(int64_t row, int64_t r, int64_t R) {
+    return ((r >> 5) * R + row) * 32 + (r & 31);
+}
 //
 // ---- in[R][C] (fp32 or int8) -> bf16 copies, one read of the input ----------------------------
-//   rows[R][Cp]  = bf16(in)                      (row pitch ld_rows; columns C..Cp-1 zero)
-//   tr  [C][Rp]  = bf16(scale_r * in)^T          (row pitch ld_tr; columns R..Rp-1 zero)
+//   rows[R][Cp]  = bf16(in)                      (reduction over C; columns C..Cp-1 zero)
+//   tr  [C][Rp]  = bf16(scale_r * in)^T          (reduction over R; columns R..Rp-1 zero)
 // scale_r = row_gamma[r] / 128 or 1.  Either output may be null.  A workgroup takes a 64 x 64
 // tile: each thread reads 4 x 4 consecutive elements, writes its 8-byte pieces of `rows`, and
 // the transpose goes through LDS (row pitch 66 halfwords: the 4-row steps of the 16 lanes that
@@ -47,8 +53,7 @@ __device__ inline uint32_t bf16_bits(float v) {
 // VEC: C % 4 == 0 and `in` 16-byte aligned, so that a thread's 4 elements are one load.
 template <typename IN, bool VEC>
 __global__ __launch_bounds__(256) void cast_transpose_bf16(const IN* __restrict__ in, int64_t R,
-                                                           int64_t C, int64_t Cp, int64_t ld_rows,
-                                                           int64_t Rp, int64_t ld_tr,
+                                                           int64_t C, int64_t Cp, int64_t Rp,
                                                            const float* __restrict__ row_gamma,
                                                            uint16_t* __restrict__ rows,
                                                            uint16_t* __restrict__ tr) {
@@ -76,7 +81,7 @@ __global__ __launch_bounds__(256) void cast_transpose_bf16(const IN* __restrict_
             }
         }
         if (rows && r < R && c < Cp)
-            *reinterpret_cast<uint2*>(rows + r * ld_rows + c) =
+            *reinterpret_cast<uint2*>(rows + block_offset(r, c, R)) =
                 make_uint2(bf16_bits(v[0]) | (bf16_bits(v[1]) << 16),
                            bf16_bits(v[2]) | (bf16_bits(v[3]) << 16));
         if (row_gamma && r < R) {
@@ -96,64 +101,23 @@ __global__ __launch_bounds__(256) void cast_transpose_bf16(const IN* __restrict_
         const int cl = idx >> 4, rl = (idx & 15) * 4;
         const int64_t c = c0 + cl, r = r0 + rl;
         if (c < C && r < Rp)
-            *reinterpret_cast<uint2*>(tr + c * ld_tr + r) =
+            *reinterpret_cast<uint2*>(tr + block_offset(c, r, C)) =
                 make_uint2((uint32_t)tile[rl][cl] | ((uint32_t)tile[rl + 1][cl] << 16),
                            (uint32_t)tile[rl + 2][cl] | ((uint32_t)tile[rl + 3][cl] << 16));
     }
 }
 
 template <typename IN>
-static void launch_cast_transpose(const IN* in, int64_t R, int64_t C, int64_t Cp, int64_t ld_rows,
-                                  int64_t Rp, int64_t ld_tr, const float* row_gamma, uint16_t* rows,
-                                  uint16_t* tr, hipStream_t s) {
+static void launch_cast_transpose(const IN* in, int64_t R, int64_t C, int64_t Cp, int64_t Rp,
+                                  const float* row_gamma, uint16_t* rows, uint16_t* tr, hipStream_t s) {
     // the grid covers the padded extents of whichever outputs are written
     const int64_t cols = rows ? Cp : C, rws = tr ? Rp : R;
     dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rws + 63) / 64));
     const bool vec = C % 4 == 0 && ((uintptr_t)in & 15) == 0;
     if (vec)
-        cast_transpose_bf16<IN, true><<<grid, 256, 0, s>>>(in, R, C, Cp, ld_rows, Rp, ld_tr,
-                                                           row_gamma, rows, tr);
+        cast_transpose_bf16<IN, true><<<grid, 256, 0, s>>>(in, R, C, Cp, Rp, row_gamma, rows, tr);
     else
-        cast_transpose_bf16<IN, false><<<grid, 256, 0, s>>>(in, R, C, Cp, ld_rows, Rp, ld_tr,
-                                                            row_gamma, rows, tr);
-}
-
-// ---- St[K][Np] = +-1 as bf16 from the packed tiles ------------------------------------------
-// One workgroup expands 64 weight rows (4 tiles) x 512 columns: thread -> (k, 8 rows), 16 bytes.
-__global__ __launch_bounds__(256) void bits_transpose_bf16(const uint32_t* __restrict__ packed,
-                                                           int64_t N, int64_t K, int64_t Np,
-                                                           int64_t ld, uint16_t* __restrict__ St) {
-    __shared__ uint32_t sm[4][256];
-    const int64_t TN = tiles_n(N), TK = tiles_k(K);
-    const int64_t tn0 = (int64_t)blockIdx.x * 4, tk = blockIdx.y;
-    for (int t = 0; t < 4; ++t) {
-        uint32_t v = 0;  // rows past N: zero bits; their columns of St are the zero padding
-        if (tn0 + t < TN) v = packed[tile_dword_offset(tn0 + t, tk, TK) + threadIdx.x];
-        sm[t][threadIdx.x] = v;
-    }
-    __syncthreads();
-    for (int it = 0; it < 16; ++it) {
-        const int o = it * 256 + threadIdx.x;  // 512 k x 8 row-groups
-        const int kl = o >> 3, seg = o & 7;    // seg: tile seg/2, rows 8*(seg%2)..+7
-        const int64_t k = tk * kChunkK + kl, n = tn0 * 16 + seg * 8;
-        if (k >= K || n >= Np) continue;
-        const int i = kl >> 6, g = (kl & 63) >> 4, d = (kl & 15) >> 2, j = kl & 3;
-        uint32_t w[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            uint32_t pair = 0;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int c = (seg & 1) * 8 + 2 * p + e;
-                const uint32_t dw = sm[seg >> 1][(g * 16 + c) * 4 + d];
-                const uint32_t bit = (dw >> (8 * j + i)) & 1u;
-                const uint32_t val = (n + 2 * p + e < N) ? (bit ? 0x3f80u : 0xbf80u) : 0u;
-                pair |= val << (16 * e);
-            }
-            w[p] = pair;
-        }
-        *reinterpret_cast<uint4*>(St + k * ld + n) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
+        cast_transpose_bf16<IN, false><<<grid, 256, 0, s>>>(in, R, C, Cp, Rp, row_gamma, rows, tr);
 }
 
 // ---- Sw[Np/32][K]: the signs of 32 consecutive weight rows of one column k in one word -------
@@ -191,113 +155,7 @@ __global__ __launch_bounds__(256) void bits_transpose_words(const uint32_t* __re
     }
 }
 
-// ---- C[I][J] = scale * sum_r A[I][r] B[J][r], bf16 operands, fp32 accumulate -------------------
-// Workgroup tile 256 x 128, four waves of 128 x 64 (4 x 2 MFMA tiles of 32 x 32), stage = 32
-// reduction elements (64-byte rows, padded to 80 in LDS: conflict-free 16-byte operand reads).
-// Global -> registers -> LDS double buffering.  scale = *scale_ptr * scale_mul (either may be
-// neutral).
-constexpr int kBwdPitch = 80;
-
-template <int BM, int BN>
-__global__ __launch_bounds__(256, 2) void gemm_tn_bf16(const uint16_t* __restrict__ A,
-                                                       const uint16_t* __restrict__ B, int64_t I,
-                                                       int64_t J, int64_t Rp, int64_t ld,
-                                                       const float* __restrict__ scale_ptr,
-                                                       float scale_mul, float* __restrict__ C) {
-    constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 32, NI = WTN / 32;
-    constexpr int PA = BM * 4 / 256, PB = BN * 4 / 256;
-    __shared__ __attribute__((aligned(16))) uint8_t smA[2][BM * kBwdPitch];
-    __shared__ __attribute__((aligned(16))) uint8_t smB[2][BN * kBwdPitch];
-
-    const int grid_j = (int)((J + BN - 1) / BN);
-    const int64_t i0 = (int64_t)(blockIdx.x / grid_j) * BM, j0 = (int64_t)(blockIdx.x % grid_j) * BN;
-    const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
-    const int wm = w >> 1, wn = w & 1, jl = l & 31, g2 = l >> 5;
-
-    v4i ra[PA], rb[PB];
-    auto load_stage = [&](int64_t r0) {
-#pragma unroll
-        for (int q = 0; q < PA; ++q) {
-            const int p = threadIdx.x + q * 256;
-            int64_t row = i0 + (p >> 2);
-            if (row > I - 1) row = I - 1;
-            ra[q] = *reinterpret_cast<const v4i*>(A + row * ld + r0 + (p & 3) * 8);
-        }
-#pragma unroll
-        for (int q = 0; q < PB; ++q) {
-            const int p = threadIdx.x + q * 256;
-            int64_t row = j0 + (p >> 2);
-            if (row > J - 1) row = J - 1;
-            rb[q] = *reinterpret_cast<const v4i*>(B + row * ld + r0 + (p & 3) * 8);
-        }
-    };
-    auto store_stage = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < PA; ++q) {
-            const int p = threadIdx.x + q * 256;
-            *reinterpret_cast<v4i*>(&smA[buf][(p >> 2) * kBwdPitch + (p & 3) * 16]) = ra[q];
-        }
-#pragma unroll
-        for (int q = 0; q < PB; ++q) {
-            const int p = threadIdx.x + q * 256;
-            *reinterpret_cast<v4i*>(&smB[buf][(p >> 2) * kBwdPitch + (p & 3) * 16]) = rb[q];
-        }
-    };
-
-    v16f acc[MI][NI];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int s = 0; s < NI; ++s)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mi][s][r] = 0.f;
-
-    const int64_t nst = Rp / 32;
-    load_stage(0);
-    store_stage(0);
-    __syncthreads();
-    for (int64_t st = 0; st < nst; ++st) {
-        const int buf = (int)(st & 1);
-        if (st + 1 < nst) load_stage((st + 1) * 32);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            v4i av[MI], bv[NI];
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-                av[mi] = *reinterpret_cast<const v4i*>(
-                    &smA[buf][(wm * WTM + 32 * mi + jl) * kBwdPitch + (2 * h + g2) * 16]);
-#pragma unroll
-            for (int s = 0; s < NI; ++s)
-                bv[s] = *reinterpret_cast<const v4i*>(
-                    &smB[buf][(wn * WTN + 32 * s + jl) * kBwdPitch + (2 * h + g2) * 16]);
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int s = 0; s < NI; ++s)
-                    acc[mi][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(v8bf, av[mi]), __builtin_bit_cast(v8bf, bv[s]),
-                        acc[mi][s], 0, 0, 0);
-        }
-        if (st + 1 < nst) store_stage(buf ^ 1);
-        __syncthreads();
-    }
-
-    const float scale = (scale_ptr ? *scale_ptr : 1.0f) * scale_mul;
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t i = i0 + wm * WTM + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3);
-            if (i >= I) continue;
-#pragma unroll
-            for (int s = 0; s < NI; ++s) {
-                const int64_t j = j0 + wn * WTN + 32 * s + jl;
-                if (j < J) C[i * J + j] = scale * acc[mi][s][r];
-            }
-        }
-}
-
-// ---- the same product for large operands: LDS ring fed by DMA --------------------------------
+// ---- C[I][J] = scale * sum_r A[I][r] B[J][r], bf16 operands, fp32 accumulation: LDS ring fed by DMA --
 // Workgroup tile 256 x 256, eight waves of 128 x 64 (4 x 2 MFMA tiles), one workgroup per CU,
 // persistent over the tiles.  A stage is 32 reduction elements: 64-byte rows of A and of B,
 // streamed global -> LDS by global_load_lds_dwordx4 into a ring of NS stages; the 16-byte
@@ -386,7 +244,6 @@ template <int NS, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __restrict__ A,
                                                             const uint16_t* __restrict__ B,
                                                             int64_t I, int64_t J, int64_t Rp,
-                                                            int64_t ld,
                                                             const float* __restrict__ scale_ptr,
                                                             float scale_mul, float* __restrict__ C,
                                                             int grid_i, int grid_j, int blk_i,
@@ -428,7 +285,6 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
     // Rows past the matrix re-read its last row (their results are never stored).
     uint32_t goffA[PA], goffB[PB];
     const uint8_t *baseA = nullptr, *baseB = nullptr;
-    const uint32_t pitch = (uint32_t)ld * 2;
     auto setup_dma = [&](int64_t i0, int64_t j0) {
 #pragma unroll
         for (int q = 0; q < PA; ++q) {
@@ -436,7 +292,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
             int row = slot >> 2;
             const int seg = ((slot & 3) ^ ((row >> 2) & 3)) * 16;
             if (i0 + row > I - 1) row = (int)(I - 1 - i0);
-            goffA[q] = (uint32_t)row * pitch + seg;
+            goffA[q] = (uint32_t)row * 64 + seg;
         }
 #pragma unroll
         for (int q = 0; q < PB; ++q) {
@@ -444,10 +300,10 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
             int row = slot >> 2;
             const int seg = ((slot & 3) ^ ((row >> 2) & 3)) * 16;
             if (j0 + row > J - 1) row = (int)(J - 1 - j0);
-            goffB[q] = (uint32_t)row * pitch + seg;
+            goffB[q] = (uint32_t)row * 64 + seg;
         }
-        baseA = reinterpret_cast<const uint8_t*>(A) + i0 * (int64_t)pitch + (int64_t)st0 * 64;
-        baseB = reinterpret_cast<const uint8_t*>(B) + j0 * (int64_t)pitch + (int64_t)st0 * 64;
+        baseA = reinterpret_cast<const uint8_t*>(A) + (st0 * I + i0) * 64;
+        baseB = reinterpret_cast<const uint8_t*>(B) + (st0 * J + j0) * 64;
     };
     const uint32_t lds_wave = (uint32_t)(w * kWave * 16);
     // stage `st` into ring slot st % NS; `src_st` is the stage whose bytes are read (== st, or
@@ -457,12 +313,12 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
 #pragma unroll
         for (int q = 0; q < PA; ++q)
             __builtin_amdgcn_global_load_lds(
-                (const void*)(baseA + (int64_t)src_st * 64 + goffA[q]),
+                (const void*)(baseA + src_st * I * 64 + goffA[q]),
                 (__attribute__((address_space(3))) void*)(dst + q * THREADS * 16), 16, 0, 0);
 #pragma unroll
         for (int q = 0; q < PB; ++q)
             __builtin_amdgcn_global_load_lds(
-                (const void*)(baseB + (int64_t)src_st * 64 + goffB[q]),
+                (const void*)(baseB + src_st * J * 64 + goffB[q]),
                 (__attribute__((address_space(3))) void*)(dst + A_BYTES + q * THREADS * 16), 16, 0,
                 0);
     };
@@ -594,7 +450,6 @@ template <int NS, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __restrict__ A,
                                                              const uint32_t* __restrict__ Sw,
                                                              int64_t I, int64_t J, int64_t Rp,
-                                                             int64_t ld,
                                                              const float* __restrict__ scale_ptr,
                                                              float scale_mul, float* __restrict__ C,
                                                              int grid_i, int grid_j, int blk_i,
@@ -635,7 +490,6 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
     uint32_t goffA[PA];
     const uint8_t* baseA = nullptr;
     const uint32_t* wsrc = Sw;  // this lane's column of the sign words, stage 0
-    const uint32_t pitch = (uint32_t)ld * 2;
     auto setup_dma = [&](int64_t i0, int64_t j0) {
 #pragma unroll
         for (int q = 0; q < PA; ++q) {
@@ -643,9 +497,9 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
             int row = slot >> 2;
             const int seg = ((slot & 3) ^ ((row >> 2) & 3)) * 16;
             if (i0 + row > I - 1) row = (int)(I - 1 - i0);
-            goffA[q] = (uint32_t)row * pitch + seg;
+            goffA[q] = (uint32_t)row * 64 + seg;
         }
-        baseA = reinterpret_cast<const uint8_t*>(A) + i0 * (int64_t)pitch + (int64_t)st0 * 64;
+        baseA = reinterpret_cast<const uint8_t*>(A) + (st0 * I + i0) * 64;
         int64_t col = j0 + wn * WTN + l;  // columns past J re-read the last one (never stored)
         if (col > J - 1) col = J - 1;
         wsrc = Sw + (int64_t)st0 * J + col;
@@ -665,7 +519,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
 #pragma unroll
         for (int q = 0; q < PA; ++q)
             __builtin_amdgcn_global_load_lds(
-                (const void*)(baseA + (int64_t)src_st * 64 + goffA[q]),
+                (const void*)(baseA + src_st * I * 64 + goffA[q]),
                 (__attribute__((address_space(3))) void*)(dst + q * THREADS * 16), 16, 0, 0);
     };
     auto issue_tile_start = [&]() {
@@ -836,12 +690,10 @@ static int bwd_num_cus() {
     return n;
 }
 
-// The persistent 256 x 256 kernels take every product whose byte offsets into a block of 256 rows
-// fit 32 bits.  The plan is the grid, the block of tiles an XCD runs together (ring_tile_origin):
+// The plan of a product: the grid, the block of tiles an XCD runs together (ring_tile_origin):
 // blk_i x blk_j = grid / 8 tiles out of its grid_i / 8 rows, as square as the divisors allow; 0 =
 // no such tiling; and the slices of the reduction.
 struct RingPlan {
-    bool use;
     int grid, gi, gj, blk_i, blk_j;
     RingSlices sl;
 };
@@ -849,8 +701,8 @@ struct RingPlan {
 // Slices of a product of `tiles` tiles and nst stages on `cus` CUs: the count that costs least, in
 // units of 1 us, when a stage takes 0.6 us on a CU, an item 7 us besides, and the fp32 sums of a
 // slice (`bytes`) are written and read at 5 TB/s by a second launch of 4 us.  dX^ of M = 1000, N = 8192,
-// K = 2048 (32 tiles of 256 stages): 6 slices, 43 us and 11 us for the fold; on 64 workgroups of the
-// small kernel it took 185 us and the bf16 copy of the weights 8 us more than the sign words.
+// K = 2048 (32 tiles of 256 stages): 6 slices, 43 us and 11 us for the fold; in 64 tiles of
+// 256 x 128, each walking all of N, it took 185 us.
 static RingSlices ring_slices(int64_t tiles, int64_t nst, double bytes, int64_t cus) {
     RingSlices best{1, (int)nst};
     double best_cost = 1e30;
@@ -868,14 +720,11 @@ static RingSlices ring_slices(int64_t tiles, int64_t nst, double bytes, int64_t 
     return best;
 }
 
-static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp, int64_t ld) {
+static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp) {
     RingPlan p{};
     const int64_t gi = (I + 255) / 256, gj = (J + 255) / 256;
     p.gi = (int)gi;
     p.gj = (int)gj;
-    p.use = ld < ((int64_t)1 << 22) && gi * gj <= ((int64_t)1 << 26);
-    if (tuning().bwd_ring == 2) p.use = false;
-    if (!p.use) return p;
     int cus = bwd_num_cus();
     if (tuning().bwd_grid > 0) cus = tuning().bwd_grid;
     const int64_t ntiles = gi * gj, nst = Rp / 32;
@@ -911,7 +760,7 @@ static RingPlan unsliced(RingPlan p, int64_t Rp) {
     return p;
 }
 static size_t slices_bytes(const RingPlan& p, int64_t I, int64_t J) {
-    return p.use && p.sl.splits > 1 ? (size_t)p.sl.splits * I * J * 4 : 0;
+    return p.sl.splits > 1 ? (size_t)p.sl.splits * I * J * 4 : 0;
 }
 
 static void launch_fold(const float* part, const RingPlan& p, int64_t count, const float* scale_ptr,
@@ -924,95 +773,83 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
             part, p.sl.splits, count, scale_ptr, scale_mul, C);
 }
 
-// C[I][J] = scale * A[I][:] . B[J][:]: the ring kernel (in slices of r where the plan has them and
-// `part` has room), else the 256 x 128 kernel with a workgroup per tile.
+// C[I][J] = scale * A[I][:] . B[J][:], in slices of r where the plan has them and `part` has room
 static void launch_gemm_tn(const uint16_t* A, const uint16_t* B, int64_t I, int64_t J, int64_t Rp,
-                           int64_t ld, const float* scale_ptr, float scale_mul, float* C, float* part,
+                           const float* scale_ptr, float scale_mul, float* C, float* part,
                            size_t part_bytes, hipStream_t s) {
-    RingPlan p = ring_plan(I, J, Rp, ld);
+    RingPlan p = ring_plan(I, J, Rp);
     if (slices_bytes(p, I, J) > part_bytes) p = unsliced(p, Rp);
-    if (p.use && p.sl.splits > 1) {
-        gemm_tn_bf16_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(
-            A, B, I, J, Rp, ld, nullptr, 1.0f, part, p.gi, p.gj, 0, 0, p.sl);
+    if (p.sl.splits > 1) {
+        gemm_tn_bf16_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(A, B, I, J, Rp, nullptr, 1.0f, part,
+                                                                     p.gi, p.gj, 0, 0, p.sl);
         launch_fold(part, p, I * J, scale_ptr, scale_mul, C, s);
-    } else if (p.use) {
-        gemm_tn_bf16_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
-            A, B, I, J, Rp, ld, scale_ptr, scale_mul, C, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
     } else {
-        const unsigned blocks = (unsigned)(((I + 255) / 256) * ((J + 127) / 128));
-        gemm_tn_bf16<256, 128><<<blocks, 256, 0, s>>>(A, B, I, J, Rp, ld, scale_ptr, scale_mul, C);
+        gemm_tn_bf16_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
+            A, B, I, J, Rp, scale_ptr, scale_mul, C, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 static inline int64_t pad32(int64_t v) { return (v + 31) / 32 * 32; }
-// Row pitch (elements) of a bf16 copy whose rows hold Rp elements.  A GEMM stage reads 64 bytes
-// from each of 512 rows; with rows a multiple of 4 KiB apart those reads would all fall on the
-// same memory channel, so such rows are set 128 bytes further apart.
-static inline int64_t row_pitch(int64_t Rp) { return Rp % 2048 == 0 ? Rp + 64 : Rp; }
 
-// bytes of the +-1 operand of dX^: sign words [Np / 32][K] when the persistent kernel takes the
-// product, else the bf16 copy St[K][Nl]
-static size_t signs_bytes(int64_t M, int64_t N, int64_t K) {
-    const int64_t Np = pad32(N), Nl = row_pitch(Np);
-    return ring_plan(M, K, Np, Nl).use ? (size_t)(Np / 32) * K * 4 : (size_t)K * Nl * 2;
-}
-
-// What the copies need: g[M][Nl], the signs, gwT[N][Ml], qT[K][Ml] (bf16), each region 256-byte aligned.
-size_t backward_workspace_min_bytes(int64_t M, int64_t N, int64_t K) {
-    const int64_t Nl = row_pitch(pad32(N)), Ml = row_pitch(pad32(M));
+// What the copies need: g[M][Np], the sign words [Np / 32][K], gwT[N][Mp], qT[K][Mp] (bf16), each
+// region 256-byte aligned.
+struct BackwardWs {
+    size_t words, gwT, qT, total;
+};
+static BackwardWs backward_ws(int64_t M, int64_t N, int64_t K) {
+    const int64_t Np = pad32(N), Mp = pad32(M);
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    return al((size_t)M * Nl * 2) + al(signs_bytes(M, N, K)) + al((size_t)N * Ml * 2) +
-           al((size_t)K * Ml * 2);
+    BackwardWs w{};
+    w.words = al((size_t)M * Np * 2);
+    w.gwT = w.words + al((size_t)(Np / 32) * K * 4);
+    w.qT = w.gwT + al((size_t)N * Mp * 2);
+    w.total = w.qT + al((size_t)K * Mp * 2);
+    return w;
 }
+size_t backward_workspace_min_bytes(int64_t M, int64_t N, int64_t K) { return backward_ws(M, N, K).total; }
 // The same and room for the slices of whichever product is cut (one after the other): optional.
 size_t backward_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    const int64_t Np = pad32(N), Mp = pad32(M);
-    const size_t dx = slices_bytes(ring_plan(M, K, Np, row_pitch(Np)), M, K);
-    const size_t dw = slices_bytes(ring_plan(N, K, Mp, row_pitch(Mp)), N, K);
-    return backward_workspace_min_bytes(M, N, K) + (dx > dw ? dx : dw);
+    const size_t dx = slices_bytes(ring_plan(M, K, pad32(N)), M, K);
+    const size_t dw = slices_bytes(ring_plan(N, K, pad32(M)), N, K);
+    const size_t need = backward_ws(M, N, K).total + (dx > dw ? dx : dw);
+    // never less than four bf16 copies of a small product's operands, which callers may have budgeted
+    const size_t copies = 2 * ((size_t)M * pad32(N) * 2 + (size_t)K * pad32(N) + (size_t)K * pad32(M));
+    const bool small = ((M + 255) / 256) * ((K + 255) / 256) < 128;
+    return small && need < copies ? copies : need;
 }
 
 hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
     const int64_t M = a.M, N = a.N, K = a.K, Np = pad32(N), Mp = pad32(M);
-    const int64_t Nl = row_pitch(Np), Ml = row_pitch(Mp);
-    auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    char* ws = (char*)a.workspace;
-    uint16_t* g = (uint16_t*)ws;
-    uint16_t* St = (uint16_t*)(ws + al((size_t)M * Nl * 2));
-    uint16_t* gwT = (uint16_t*)((char*)St + al(signs_bytes(M, N, K)));
-    uint16_t* qT = (uint16_t*)((char*)gwT + al((size_t)N * Ml * 2));
-    const size_t base = backward_workspace_min_bytes(M, N, K);
-    float* part = (float*)(ws + base);
-    const size_t part_bytes = a.workspace_bytes > base ? a.workspace_bytes - base : 0;
+    const BackwardWs ws = backward_ws(M, N, K);
+    char* base = (char*)a.workspace;
+    uint16_t* g = (uint16_t*)base;
+    uint32_t* Sw = (uint32_t*)(base + ws.words);
+    uint16_t* gwT = (uint16_t*)(base + ws.gwT);
+    uint16_t* qT = (uint16_t*)(base + ws.qT);
+    float* part = (float*)(base + ws.total);
+    const size_t part_bytes = a.workspace_bytes > ws.total ? a.workspace_bytes - ws.total : 0;
 
     // dY is read once: g for dX and gwT for dW come out of the same pass when both are wanted
-    launch_cast_transpose<float>(a.dY, M, N, Np, Nl, Mp, Ml, a.per_tensor ? nullptr : a.gamma,
+    launch_cast_transpose<float>(a.dY, M, N, Np, Mp, a.per_tensor ? nullptr : a.gamma,
                                  a.dX ? g : nullptr, a.dW ? gwT : nullptr, s);
-    if (a.dX) {
-        RingPlan p = ring_plan(M, K, Np, Nl);
-        if (p.use) {  // +-1 from sign words inside the kernel: no bf16 copy of the weights
-            if (slices_bytes(p, M, K) > part_bytes) p = unsliced(p, Np);
-            uint32_t* Sw = (uint32_t*)St;
-            dim3 gb((unsigned)(Np / 32), (unsigned)tiles_k(K));
-            bits_transpose_words<<<gb, 256, 0, s>>>(a.packed, N, K, Sw);
-            if (p.sl.splits > 1) {
-                gemm_tn_signs_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(
-                    g, Sw, M, K, Np, Nl, nullptr, 1.0f, part, p.gi, p.gj, 0, 0, p.sl);
-                launch_fold(part, p, M * K, a.beta, 1.0f, a.dX, s);
-            } else {
-                gemm_tn_signs_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
-                    g, Sw, M, K, Np, Nl, a.beta, 1.0f, a.dX, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
-            }
+    if (a.dX) {  // +-1 from sign words inside the kernel: no bf16 copy of the weights
+        RingPlan p = ring_plan(M, K, Np);
+        if (slices_bytes(p, M, K) > part_bytes) p = unsliced(p, Np);
+        dim3 gb((unsigned)(Np / 32), (unsigned)tiles_k(K));
+        bits_transpose_words<<<gb, 256, 0, s>>>(a.packed, N, K, Sw);
+        if (p.sl.splits > 1) {
+            gemm_tn_signs_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(g, Sw, M, K, Np, nullptr, 1.0f, part,
+                                                                          p.gi, p.gj, 0, 0, p.sl);
+            launch_fold(part, p, M * K, a.beta, 1.0f, a.dX, s);
         } else {
-            dim3 gb((unsigned)((tiles_n(N) + 3) / 4), (unsigned)tiles_k(K));
-            bits_transpose_bf16<<<gb, 256, 0, s>>>(a.packed, N, K, Np, Nl, St);
-            launch_gemm_tn(g, St, M, K, Np, Nl, a.beta, 1.0f, a.dX, nullptr, 0, s);
+            gemm_tn_signs_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
+                g, Sw, M, K, Np, a.beta, 1.0f, a.dX, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
         }
     }
     if (a.dW) {
-        launch_cast_transpose<int8_t>(a.codes, M, K, K, 0, Mp, Ml, nullptr, nullptr, qT, s);
-        launch_gemm_tn(gwT, qT, N, K, Mp, Ml, a.per_tensor ? a.gamma : nullptr,
+        launch_cast_transpose<int8_t>(a.codes, M, K, K, Mp, nullptr, nullptr, qT, s);
+        launch_gemm_tn(gwT, qT, N, K, Mp, a.per_tensor ? a.gamma : nullptr,
                        a.per_tensor ? 1.0f / 128.0f : 1.0f, a.dW, part, part_bytes, s);
     }
     return hipGetLastError();

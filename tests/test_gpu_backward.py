@@ -143,9 +143,9 @@ def test_backward_slices_of_the_reduction_exact(bl, tuning, M, N, K, splits):
     slices shorter than the ring) and folded, on integers: exact.  With a workspace that only holds
     the operand copies the product runs unsliced, with the same result."""
     print(f"backward slices M={M} N={N} K={K} splits={splits}", flush=True)
-    tuning("bwd_ring=1,bwd_splits=1")
-    small = bl.workspace_bytes(bl.OP_BACKWARD, M, N, K, True)
-    tuning(f"bwd_ring=1,bwd_splits={splits}")
+    tuning(f"bwd_splits={splits}")
+    Np, Mp = (N + 31) // 32 * 32, (M + 31) // 32 * 32
+    small = sum((b + 255) // 256 * 256 for b in (2 * M * Np, Np // 32 * K * 4, 2 * N * Mp, 2 * K * Mp)) + 256
     assert bl.workspace_bytes(bl.OP_BACKWARD, M, N, K, True) > small
     rng = np.random.default_rng(M + splits)
     W = wl.make_weight(N, K, 0.02, 5)
