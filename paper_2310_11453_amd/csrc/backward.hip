@@ -155,54 +155,6 @@ __global__ __launch_bounds__(256) void bits_transpose_words(const uint32_t* __re
     }
 }
 
-// ---- C[I][J] = scale * sum_r A[I][r] B[J][r], bf16 operands, fp32 accumulation: LDS ring fed by DMA --
-// Workgroup tile 256 x 256, eight waves of 128 x 64 (4 x 2 MFMA tiles), one workgroup per CU,
-// persistent over the tiles.  A stage is 32 reduction elements: 64-byte rows of A and of B,
-// streamed global -> LDS by global_load_lds_dwordx4 into a ring of NS stages; the 16-byte
-// segments of a row are XOR-swizzled with (row/4)%4, so the operand reads of 16 consecutive rows
-// touch every bank once.  The unit of work is a half-step (16 elements, 8 MFMAs): one asm block
-// issues the LDS reads of the next half-step's operands, then the MFMAs of the current one, then
-// waits for the reads.  Between the half-steps of stage st every wave waits for its own DMA of
-// stage st+1 (s_waitcnt vmcnt(n), n counted by hand), meets the others at a bare s_barrier, and
-// the DMA of stage st+NS-1 goes to the buffer stage st-1 has left.
-__device__ inline void bf16_read_ops(v4i (&a)[4], v4i (&b)[2], uint32_t ad_a, uint32_t ad_b) {
-    asm volatile(
-        "ds_read_b128 %0, %6\n\t"
-        "ds_read_b128 %1, %6 offset:2048\n\t"
-        "ds_read_b128 %2, %6 offset:4096\n\t"
-        "ds_read_b128 %3, %6 offset:6144\n\t"
-        "ds_read_b128 %4, %7\n\t"
-        "ds_read_b128 %5, %7 offset:2048\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(b[0]), "=&v"(b[1])
-        : "v"(ad_a), "v"(ad_b));
-}
-// acc[mi][s] += ac[mi] x bc[s]; an, bn = operands at ad_a, ad_b, complete on exit
-__device__ inline void bf16_half_step(v16f (&acc)[4][2], const v4i (&ac)[4], const v4i (&bc)[2],
-                                      v4i (&an)[4], v4i (&bn)[2], uint32_t ad_a, uint32_t ad_b) {
-    asm volatile(
-        "ds_read_b128 %8, %20\n\t"
-        "ds_read_b128 %9, %20 offset:2048\n\t"
-        "ds_read_b128 %12, %21\n\t"
-        "ds_read_b128 %13, %21 offset:2048\n\t"
-        "ds_read_b128 %10, %20 offset:4096\n\t"
-        "ds_read_b128 %11, %20 offset:6144\n\t"
-        "v_mfma_f32_32x32x16_bf16 %0, %14, %18, %0\n\t"
-        "v_mfma_f32_32x32x16_bf16 %1, %14, %19, %1\n\t"
-        "v_mfma_f32_32x32x16_bf16 %2, %15, %18, %2\n\t"
-        "v_mfma_f32_32x32x16_bf16 %3, %15, %19, %3\n\t"
-        "v_mfma_f32_32x32x16_bf16 %4, %16, %18, %4\n\t"
-        "v_mfma_f32_32x32x16_bf16 %5, %16, %19, %5\n\t"
-        "v_mfma_f32_32x32x16_bf16 %6, %17, %18, %6\n\t"
-        "v_mfma_f32_32x32x16_bf16 %7, %17, %19, %7\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[2][0]),
-          "+v"(acc[2][1]), "+v"(acc[3][0]), "+v"(acc[3][1]), "=&v"(an[0]), "=&v"(an[1]),
-          "=&v"(an[2]), "=&v"(an[3]), "=&v"(bn[0]), "=&v"(bn[1])
-        : "v"(ac[0]), "v"(ac[1]), "v"(ac[2]), "v"(ac[3]), "v"(bc[0]), "v"(bc[1]), "v"(ad_a),
-          "v"(ad_b));
-}
-
 // Tile order of the persistent bf16 kernels.  Workgroups are dealt round-robin to the 8 XCDs (one
 // L2 each).  An XCD gets grid_i / 8 whole rows of tiles, and the G / 8 tiles it runs together
 // form a blk_i x blk_j block of them: both operands are equally wide here, so what the XCD
@@ -240,21 +192,58 @@ struct RingSlices {
     int splits, per;  // per: stages of 32 r in a slice
 };
 
+// ---- C[I][J] = scale * sum_r A[I][r] B[J][r], bf16 operands, fp32 accumulation -----------------
+// Workgroup tile 256 x 256, four waves of 128 x 128 (4 x 4 MFMA tiles), one workgroup per CU,
+// persistent over the tiles.  A stage is 32 reduction elements: 64-byte rows of A and of B,
+// streamed global -> LDS by global_load_lds_dwordx4 into a ring of NS stages; the 16-byte
+// segments of a row are XOR-swizzled with (row/4)%4, so the operand reads of 16 consecutive rows
+// touch every bank once.  Between the half-steps of stage st every wave waits for its own DMA of
+// stage st+1 (s_waitcnt vmcnt(n), n counted by hand), meets the others at a bare s_barrier, and
+// the DMA of stage st+NS-1 goes to the buffer stage st-1 has left.
+//
+// Why four waves.  With eight waves of 128 x 64 LDS sets the pace: every operand row is read by the
+// waves that share it, 96 KiB of reads and 32 KiB of DMA writes a stage, at 128 bytes a cycle as
+// long as the MFMAs of the stage take (1024 cycles).  128 x 128 waves read 64 KiB.  There is one wave
+// per SIMD then: 256 accumulator registers (the compiler keeps them in the AGPR half of the file),
+// and only the wave's own instruction stream hides latency.  A half-step (16 r) is 16 MFMAs, 512
+// cycles; the reads of the next one's operands go out behind its first four, the DMA of a stage (its
+// addresses and issue would idle the pipe) behind each row of four.  M = 8192, 4096 -> 16384: dW
+// 900 us, 946 us with eight waves; without any DMA in the loop (timing only) it takes 740 us.
+__device__ inline void wide_issue(v4i (&a)[4], v4i (&b)[4], uint32_t ad_a, uint32_t ad_b) {
+    asm volatile(
+        "ds_read_b128 %0, %8\n\t"
+        "ds_read_b128 %1, %8 offset:2048\n\t"
+        "ds_read_b128 %2, %8 offset:4096\n\t"
+        "ds_read_b128 %3, %8 offset:6144\n\t"
+        "ds_read_b128 %4, %9\n\t"
+        "ds_read_b128 %5, %9 offset:2048\n\t"
+        "ds_read_b128 %6, %9 offset:4096\n\t"
+        "ds_read_b128 %7, %9 offset:6144"
+        : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]),
+          "=&v"(b[3])
+        : "v"(ad_a), "v"(ad_b));
+}
+__device__ inline void wide_wait(v4i (&a)[4], v4i (&b)[4]) {
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]),
+                   "+v"(b[3]));
+}
+
 template <int NS, bool SPLIT>
-__global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __restrict__ A,
+__global__ __launch_bounds__(256, 1) void gemm_tn_bf16_wide(const uint16_t* __restrict__ A,
                                                             const uint16_t* __restrict__ B,
                                                             int64_t I, int64_t J, int64_t Rp,
                                                             const float* __restrict__ scale_ptr,
                                                             float scale_mul, float* __restrict__ C,
                                                             int grid_i, int grid_j, int blk_i,
                                                             int blk_j, RingSlices sl) {
-    constexpr int BM = 256, BN = 256, WN = 4, THREADS = 512, WTM = 128, WTN = 64, MI = 4, NI = 2;
+    constexpr int BM = 256, BN = 256, WN = 2, THREADS = 256, WTM = 128, WTN = 128, MI = 4, NI = 4;
     constexpr int PA = BM * 4 / THREADS, PB = BN * 4 / THREADS, P = PA + PB;
     constexpr int A_BYTES = BM * 64, STAGE_BYTES = (BM + BN) * 64;
     static_assert((NS - 1) * P < 64, "vmcnt range");
     __shared__ __attribute__((aligned(1024))) uint8_t sm[NS * STAGE_BYTES];
 
-    const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
     const int wm = w / WN, wn = w % WN;
     const int j = l & 31, g2 = l >> 5;
     const int nst_all = (int)(Rp / 32);
@@ -308,19 +297,20 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
     const uint32_t lds_wave = (uint32_t)(w * kWave * 16);
     // stage `st` into ring slot st % NS; `src_st` is the stage whose bytes are read (== st, or
     // the last stage when st does not exist: the slot is filled with bytes nobody uses)
-    auto issue = [&](int st, int src_st) {
+    // (piece q of A and of B)
+    static_assert(PA == PB && PA == MI, "one piece of each per row of MFMAs");
+    auto issue_piece = [&](int st, int src_st, int q) {
         uint8_t* dst = sm + (st % NS) * STAGE_BYTES + lds_wave;
+        __builtin_amdgcn_global_load_lds(
+            (const void*)(baseA + src_st * I * 64 + goffA[q]),
+            (__attribute__((address_space(3))) void*)(dst + q * THREADS * 16), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(
+            (const void*)(baseB + src_st * J * 64 + goffB[q]),
+            (__attribute__((address_space(3))) void*)(dst + A_BYTES + q * THREADS * 16), 16, 0, 0);
+    };
+    auto issue = [&](int st, int src_st) {
 #pragma unroll
-        for (int q = 0; q < PA; ++q)
-            __builtin_amdgcn_global_load_lds(
-                (const void*)(baseA + src_st * I * 64 + goffA[q]),
-                (__attribute__((address_space(3))) void*)(dst + q * THREADS * 16), 16, 0, 0);
-#pragma unroll
-        for (int q = 0; q < PB; ++q)
-            __builtin_amdgcn_global_load_lds(
-                (const void*)(baseB + src_st * J * 64 + goffB[q]),
-                (__attribute__((address_space(3))) void*)(dst + A_BYTES + q * THREADS * 16), 16, 0,
-                0);
+        for (int q = 0; q < PA; ++q) issue_piece(st, src_st, q);
     };
     auto issue_tile_start = [&]() {
 #pragma unroll
@@ -338,16 +328,35 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
 
     v16f acc[MI][NI];
     v4i ax[MI], ay[MI], bx[NI], by[NI];
+    // acc += ac x bc; an, bn = operands at ad_a, ad_b, valid on return; between(mi) is placed behind the
+    // MFMAs of row mi: the DMA of a stage, whose addresses and issue would otherwise idle the pipe
+    auto half_step = [&](const v4i(&ac)[MI], const v4i(&bc)[NI], v4i(&an)[MI], v4i(&bn)[NI], uint32_t ad_a,
+                         uint32_t ad_b, auto between) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+            for (int s = 0; s < NI; ++s)
+                acc[mi][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, ac[mi]),
+                                                                     __builtin_bit_cast(v8bf, bc[s]),
+                                                                     acc[mi][s], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (mi == 0) wide_issue(an, bn, ad_a, ad_b);
+            between(mi);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wide_wait(an, bn);
+    };
     // In: ax/bx = operands of (st, half 0).  Out: operands of (st+1, half 0); for the last stage
     // these are stale ring bytes that nobody uses.
     auto stage = [&](int st, bool ahead) {
-        bf16_half_step(acc, ax, bx, ay, by, a_lane[1] + ring(st), b_lane[1] + ring(st));
+        half_step(ax, bx, ay, by, a_lane[1] + ring(st), b_lane[1] + ring(st), [](int) {});
         // younger than stage st+1: stages st+2 .. st+NS-2
         if (ahead) wait_vmcnt<(NS - 3) * P>();
         else wait_vmcnt<0>();
         block_barrier();
-        if (ahead) issue(st + NS - 1, st + NS - 1);
-        bf16_half_step(acc, ay, by, ax, bx, a_lane[0] + ring(st + 1), b_lane[0] + ring(st + 1));
+        half_step(ay, by, ax, bx, a_lane[0] + ring(st + 1), b_lane[0] + ring(st + 1), [&](int mi) {
+            if (ahead) issue_piece(st + NS - 1, st + NS - 1, mi);
+        });
     };
 
     const float scale = (scale_ptr ? *scale_ptr : 1.0f) * scale_mul;
@@ -369,15 +378,12 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_bf16_ring(const uint16_t* __re
 
         wait_vmcnt<(NS - 2) * P>();  // younger than stage 0: stages 1 .. NS-2
         block_barrier();
-        bf16_read_ops(ax, bx, a_lane[0], b_lane[0]);
+        wide_issue(ax, bx, a_lane[0], b_lane[0]);
+        wide_wait(ax, bx);
 
         for (int gidx = 0; gidx < main_groups; ++gidx)
             static_for<0, NS>([&](auto ic) { stage(gidx * NS + decltype(ic)::value, true); });
         for (int st = main_groups * NS; st < nst; ++st) stage(st, st + NS - 1 < nst);
-
-        // the accumulators were last written inside an asm block: let the matrix pipeline
-        // retire them before ordinary instructions read them
-        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 
         // every wave is done with the ring: start the next tile's stream, then store
         block_barrier();
@@ -780,11 +786,11 @@ static void launch_gemm_tn(const uint16_t* A, const uint16_t* B, int64_t I, int6
     RingPlan p = ring_plan(I, J, Rp);
     if (slices_bytes(p, I, J) > part_bytes) p = unsliced(p, Rp);
     if (p.sl.splits > 1) {
-        gemm_tn_bf16_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(A, B, I, J, Rp, nullptr, 1.0f, part,
+        gemm_tn_bf16_wide<4, true><<<(unsigned)p.grid, 256, 0, s>>>(A, B, I, J, Rp, nullptr, 1.0f, part,
                                                                      p.gi, p.gj, 0, 0, p.sl);
         launch_fold(part, p, I * J, scale_ptr, scale_mul, C, s);
     } else {
-        gemm_tn_bf16_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
+        gemm_tn_bf16_wide<4, false><<<(unsigned)p.grid, 256, 0, s>>>(
             A, B, I, J, Rp, scale_ptr, scale_mul, C, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
     }
 }
