@@ -87,7 +87,7 @@ QuantWs quant_ws(int64_t M, int granularity) {
     return w;
 }
 // `total` is what a caller must bring.  Behind it, optional, room for the K-slices of a large batch
-// (M > 64, one K-group): `full` is what bitlinear_workspace_bytes asks for.
+// (M > 64) or K-groups: `full` is what bitlinear_workspace_bytes asks for.
 struct ForwardWs {
     size_t codes, gamma, rowsum, quant, split, split_bytes, xhat, total, full;
 };
@@ -147,7 +147,8 @@ ForwardWs forward_ws_grouped(int64_t M, int64_t N, int64_t K, int groups_k, int 
     w.split_bytes = group_slices_bytes(M, N, groups_k);
     off += align256(w.split_bytes);
     w.total = off;
-    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K) : 0);
+    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K)
+                                  : group_split_bytes(M, N, K / groups_k, groups_k));
     return w;
 }
 struct LnBackwardWs {
@@ -181,7 +182,8 @@ ForwardWs forward_ws_nonneg(int64_t M, int64_t N, int64_t K, int groups_k, int g
     w.split_bytes = group_slices_bytes(M, N, groups_k);
     off += align256(w.split_bytes);
     w.total = off;
-    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K) : 0);
+    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K)
+                                  : group_split_bytes(M, N, K / groups_k, groups_k));
     return w;
 }
 // what the caller brought past the required bytes, for the K-slices of a large batch
@@ -592,6 +594,7 @@ static int forward_grouped_impl(const float* X, int64_t M, int64_t K, const void
         }
         a.kgroups = groups_k; a.group_packed = (int64_t)blob_dwords;
         a.split_ws = (int32_t*)(base + ws.split); a.split_ws_bytes = ws.split_bytes;
+        if (M > 64) offer_slices(a, base, ws.total, workspace_bytes);
         return check_hip(M <= 16 ? launch_gemm_decode(a, (hipStream_t)stream)
                                  : launch_gemm_prefill(a, (hipStream_t)stream));
     }

@@ -474,26 +474,27 @@ hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
     return hipGetLastError();
 }
 
-// M > 64, one K-group: bm x 128 tiles (bm = 64 or 128), K in slices of `per` 512-chunks (per >= the
-// chunks of K: no slices; else a.split_ws must hold slices * M * N * 4 bytes).
+// M > 64: bm x 128 tiles (bm = 64 or 128), K in slices of `per` 512-chunks (per >= the chunks of K: no
+// slices; else a.split_ws must hold slices * M * N * 4 bytes).  A grouped layer: a slice per K-group.
 hipError_t launch_gemm_mid_tiles(const GemmArgs& a_in, int bm, int64_t per, hipStream_t s) {
     GemmArgs a = a_in;
     const int64_t TK = tiles_k(a.K);
     const int grid_m = (int)((a.M + bm - 1) / bm), grid_n = (int)((a.N + mid::BN - 1) / mid::BN);
-    const int splits = (int)((TK + per - 1) / per);
+    const bool grouped = a.kgroups > 1;
+    const int splits = grouped ? a.kgroups : (int)((TK + per - 1) / per);
     a.split_k = 0;
     if (splits > 1) {
         if (!a.split_ws || a.split_ws_bytes < (size_t)splits * a.M * a.N * 4) return hipErrorInvalidValue;
         a.tk_pitch = a.tk_pitch ? a.tk_pitch : TK;
-        a.split_k = per * kChunkK;
+        if (!grouped) a.split_k = per * kChunkK;
     }
     int64_t items = (int64_t)grid_m * grid_n * splits;
     if (items > ((int64_t)1 << 30)) return hipErrorInvalidValue;
     items = (items + 7) / 8 * 8;
     if (bm == 64)
-        gemm_mid_kernel<64, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, 0);
+        gemm_mid_kernel<64, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, grouped);
     else
-        gemm_mid_kernel<128, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, 0);
+        gemm_mid_kernel<128, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, grouped);
     if (splits > 1) launch_splitk_reduce(a, splits, s);
     return hipGetLastError();
 }

@@ -857,6 +857,39 @@ size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K) {
     return n > 1 ? (size_t)n * M * N * 4 : 0;
 }
 
+// The same choice for a grouped layer (K = a group's): 0 = the stream kernel, 3 or 4 = the tiles of
+// gemm_mid.hip with every K-group an item of its own, its int32 sums in a slice that the fold
+// dequantises (same fp32 operations in the same order, same bits).  The stream kernel's round of
+// tiles costs 6 + groups (1 + 0.42 n) us (1000 x 7168 x 28672, 8 groups: 238 us in 4 rounds).
+// Whole layers, stream / 128 x 128 slices / 64 x 128 slices: 100 x 4096 x 4096 in 2 groups 37 / 20 / 18, 300 x
+// 4096 x 7168 in 4 groups 63 / 44 / 44, 500 x 2048 x 2048 in 4 groups 29 / 27 / 33; 1000 x 4096 x 4096 in
+// 8 groups 54 / 102 / 150.
+static int group_plan(int64_t M, int64_t N, int64_t K, int groups, size_t ws_bytes) {
+    const int64_t cus = num_cus(), TK = tiles_k(K), nst = (K + kStageK - 1) / kStageK;
+    const int force = tuning().prefill_tile;
+    const double bytes = (double)groups * (double)M * (double)N * 4.0;
+    const int64_t rounds = ((M + 127) / 128 * ((N + 255) / 256) + cus - 1) / cus;
+    double best_us = (double)rounds * (6.0 + groups * (1.0 + 0.42 * (double)nst));
+    int best = 0;
+    for (int tile = 3; tile <= 4; ++tile) {
+        if ((force && tile != force) || bytes > (double)ws_bytes) continue;
+        const int64_t bm = tile == 4 ? 64 : 128, kg = tile == 3 ? 2 : 4;
+        const int64_t items = ((M + bm - 1) / bm) * ((N + 127) / 128) * groups;
+        const double us = (double)((items + cus - 1) / cus) * (5.0 + 4.2 * (double)((TK + kg - 1) / kg)) +
+                          4.0 + bytes * 2.0 / 5e6;
+        if (us < best_us || force) {
+            best_us = us;
+            best = tile;
+        }
+    }
+    return best;
+}
+// Room for the slices of the plan (M > 64): optional.
+size_t group_split_bytes(int64_t M, int64_t N, int64_t K, int groups) {
+    if (M <= 64 || groups <= 1 || !group_plan(M, N, K, groups, (size_t)1 << 40)) return 0;
+    return (size_t)groups * M * N * 4;
+}
+
 // K < 2^22 is required (the per-lane offset into a block of 256 rows is kept in 32 bits).
 hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
     GemmArgs a = a_in;
@@ -867,6 +900,8 @@ hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
         return launch_gemm_mid(a_in, s);
     }
     if (a.kgroups > 1) {
+        const int tile = group_plan(a.M, a.N, a.K, a.kgroups, a.split_ws ? a.split_ws_bytes : 0);
+        if (tile) return launch_gemm_mid_tiles(a, tile == 3 ? 128 : 64, tiles_k(a.K), s);
         const int grid_m = (int)((a.M + 127) / 128), grid_n = (int)((a.N + 255) / 256);
         int grid = num_cus();  // one workgroup per CU
         if (tuning().prefill_grid > 0) grid = tuning().prefill_grid;

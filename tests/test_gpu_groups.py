@@ -162,6 +162,21 @@ def test_grouped_forward_large_batch_stream(bl, tuning, M, Kg, N, gn, gk, grid):
     _check_forward(bl, M, Kg * gk, N, gn, gk, False, 700 + M)
 
 
+@pytest.mark.parametrize("M,Kg,N,gn,gk", [(65, 96, 272, 1, 5), (200, 544, 528, 3, 4), (130, 2080, 37, 1, 2)])
+def test_grouped_forward_large_batch_slices(bl, tuning, M, Kg, N, gn, gk):
+    """More than 64 tokens: every K-group an item of its own with its sums in a slice, on both tile
+    heights, against the oracle and, bit for bit, against the kernel that walks a tile's groups."""
+    print(f"grouped large-batch slices M={M} Kg={Kg} N={N} gn={gn} gk={gk}", flush=True)
+    X, W = layer(M, Kg * gk, N, 800 + M)
+    packed, alpha, beta = bl.bitlinear_pack_weights_grouped(dev(W), gn, gk)
+    tuning("prefill_tile=1")
+    y0 = host(bl.bitlinear_forward_grouped(dev(X), packed, N, beta, gn, gk))
+    for tile in (3, 4):
+        tuning(f"prefill_tile={tile}")
+        assert np.array_equal(host(bl.bitlinear_forward_grouped(dev(X), packed, N, beta, gn, gk)), y0)
+        _check_forward(bl, M, Kg * gk, N, gn, gk, False, 800 + M)
+
+
 def test_grouped_forward_full_size_30b(bl):
     """A 30B-shaped layer (7168 -> 28672) with eight groups on each axis, decode and prefill batch:
     alpha_g, beta_g and all bits; codes and gamma_g given the normalised input the GPU dumped;
