@@ -136,7 +136,8 @@ def _ptr(t: torch.Tensor | None, dtype=None):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream of the current device; building a torch.cuda.Stream object for it costs 2.6 us
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _gran(per_tensor: bool) -> int:
