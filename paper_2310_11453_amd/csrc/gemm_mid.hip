@@ -132,11 +132,11 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // gmode 2: the whole group (nothing for a group past the layer's last)
     const int64_t c0 = gmode == 2 ? 0 : TKi * kg / KG;
     const int64_t c1 = gmode == 2 ? (lgrp < a.kgroups ? TKi : 0) : TKi * (kg + 1) / KG;
-    const int64_t k0 = ki0 + c0 * kChunkK;
-    int64_t K = Ki - c0 * kChunkK;  // this group's K
-    if (K > (c1 - c0) * kChunkK) K = (c1 - c0) * kChunkK;
-    if (c1 == c0) K = 0;
     const int64_t TK = c1 - c0;
+    // a group without chunks reads the first bytes of the rows and multiplies by zero
+    const int64_t k0 = TK > 0 ? ki0 + c0 * kChunkK : 0;
+    int64_t K = Ki - c0 * kChunkK;  // this group's K
+    if (K > TK * kChunkK) K = TK * kChunkK;
     // Every group walks the same number of stages, whole chunks of the longest group; what lies
     // past a group's own K meets zero bits (padding of its last chunk, or a zero mask past its
     // last chunk), so it adds nothing.
@@ -179,16 +179,18 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // 16-byte operand reads of 16 consecutive rows then touch every LDS bank exactly once.
     uint8_t* const ringA = smA + kg * (NS * STAGE_BYTES);
     uint8_t* const ringB = smB + kg * ((BN / 16) * 1024);
-    const int8_t* gsrc[P];
-    int gseg[P];
+    // (row offsets fit 32 bits: at most 128 rows of less than 2^22 bytes)
+    const int8_t* const gbase = a.codes + m0 * a.ldq + k0;
+    uint32_t grow[P], gseg[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) {
         const int slot = q * GT + tg;
         int row = slot >> 3;
-        gseg[q] = ((slot & 7) ^ ((row >> 1) & 7)) * 16;
+        gseg[q] = (uint32_t)(((slot & 7) ^ ((row >> 1) & 7)) * 16);
         if (m0 + row > M - 1) row = (int)(M - 1 - m0);
-        gsrc[q] = a.codes + (m0 + row) * a.ldq + k0 + gseg[q];
+        grow[q] = (uint32_t)row * (uint32_t)a.ldq;
     }
+    const uint32_t klast = K >= 16 ? (uint32_t)K - 16 : 0;
     const uint32_t* bsrc[NBW];
 #pragma unroll
     for (int q = 0; q < NBW; ++q) {
@@ -197,22 +199,19 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         bsrc[q] = a.packed + tile_dword_offset(tn, k0 / kChunkK, TKp) + l * 4;
     }
     const uint32_t lds_wave = (uint32_t)(wi * kWave * 16);
-    // clamp: a stage that may reach past the group's K re-reads the last 16 valid bytes of the
-    // row instead (the packed bits there are zero, or masked)
-    auto issue = [&](int st, bool clamp) {
+    // Past the group's K the last 16 valid bytes of the row are read again (the packed bits there are
+    // zero, or masked); a min per piece instead of a branch.
+    auto issue_piece = [&](int st, int q) {
+        const uint32_t k = (uint32_t)(st * STAGE_K) + gseg[q];
+        __builtin_amdgcn_global_load_lds(
+            (const void*)(gbase + (grow[q] + (k < klast ? k : klast))),
+            (__attribute__((address_space(3))) void*)(ringA + (st % NS) * STAGE_BYTES + q * GT * 16 +
+                                                      lds_wave),
+            16, 0, 0);
+    };
+    auto issue = [&](int st) {
 #pragma unroll
-        for (int q = 0; q < P; ++q) {
-            const int8_t* src = gsrc[q] + (int64_t)st * STAGE_K;
-            if (clamp) {
-                const int64_t k = (int64_t)st * STAGE_K + gseg[q];
-                if (k > K - 16) src -= k - (K - 16);
-            }
-            __builtin_amdgcn_global_load_lds(
-                (const void*)src,
-                (__attribute__((address_space(3))) void*)(ringA + (st % NS) * STAGE_BYTES +
-                                                          q * GT * 16 + lds_wave),
-                16, 0, 0);
-        }
+        for (int q = 0; q < P; ++q) issue_piece(st, q);
     };
     auto issue_bits = [&](int64_t tk) {
 #pragma unroll
@@ -244,13 +243,9 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // multiplies A[u % 2] by B[u % 4], starts the LDS reads of A[(u + 1) % 2] and builds B[(u + 2) % 4].
     v4i bw[2][2], bwn[2][2];
     v4i A[2][2], B[4][2];
-    const bool has_k = TK > 0;  // a group without chunks requests nothing and multiplies by zero
-
-    if (has_k) {
-        issue_bits(0);
+    issue_bits(0);
 #pragma unroll
-        for (int s = 0; s < NS - 1; ++s) issue(s, true);
-    }
+    for (int s = 0; s < NS - 1; ++s) issue(s);
     wait_vmcnt<(NS - 2) * P>();  // younger than stage 0: stages 1 .. NS-2
     block_barrier();
     read_bits(bw, b_lane);
@@ -272,7 +267,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // what the waits of stages 1 and 2 are for, and the wait of stage 3, which is for a group
     // requested after them, covers them: three stages for a trip to HBM, then they are read.
     for (int64_t c = 0; c < TKmax; ++c) {
-        const bool bits_next = has_k && c + 1 < TK;
+        const bool bits_next = c + 1 < TK;
         static_for<0, 16>([&](auto uc) {
             constexpr int u = decltype(uc)::value;
             constexpr int s = u >> 2, hs = u & 3;
@@ -284,9 +279,12 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
                 else wait_vmcnt<(NS - 3) * P>();
                 block_barrier();
                 if (s == 3) read_bits(bwn, b_lane);
-                if (ahead && has_k) issue(st + NS - 1, (int64_t)(st + NS) * STAGE_K > K);  // clamp only past K
-                if (s == 0 && bits_next) issue_bits(c + 1);
             }
+            // stage st + NS - 1 goes out behind the MFMAs of this half-step (two pieces) and of the next
+            // (two more, then in stage 0 the bits): in one piece behind the barrier, with a branch per
+            // piece for the end of K, it idled the matrix pipe of all waves at once (7168 -> 28672 at
+            // M = 64: 22.8 us, now 21.2)
+            const bool more = hs >= 2 && st + NS - 1 < nrun;
             constexpr int u2 = u + 2;  // the operand built in this half-step
             constexpr int i2 = (u2 >> 1) & 7, h2 = u2 & 1;
             v4i(&src)[2][2] = u2 >= 16 ? bwn : bw;
@@ -313,9 +311,19 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
                     }
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                    if constexpr (hs >= 2) {
+                        if (s2 == 1) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            if (more) issue_piece(st + NS - 1, (hs - 2) * 2 + mi);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
                 }
             asm volatile("" : "+v"(bn[0]), "+v"(bn[1]));
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (u == 3) {
+                if (bits_next) issue_bits(c + 1);
+            }
             lds_wait(an);
         });
 #pragma unroll
