@@ -74,7 +74,7 @@ size_t bitlinear_packed_bytes(int64_t N, int64_t K, unsigned flags);
 
 /* host: scratch bytes the given operation needs; 0 for an invalid argument.  BL_OP_MATMUL
  * is the one operation whose need may be 0 for a valid shape (its workspace is optional and
- * only some shapes have a use for it).  The sizes for the forward calls at M > 64, for
+ * only some shapes have a use for it).  The sizes for the forward calls at M > 32, for
  * BL_OP_BACKWARD and for BL_OP_LN_BACKWARD include an optional part (partial sums of shapes that are
  * cut along the reduction to fill the chip): without it the same call runs uncut. */
 size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int granularity,
@@ -143,7 +143,7 @@ int bitlinear_forward(const float* X, int64_t M, int64_t K, const void* packed, 
  * 16 MiB array the library itself holds in device memory (one copy per GPU, kept until the
  * process ends).  The call allocates nothing and runs the same kernels as bitlinear_forward:
  * same arguments, same result bit for bit.  Shapes whose required workspace (without the
- * optional part for M > 64, see bitlinear_workspace_bytes) exceeds 16 MiB = 16777216 bytes return
+ * optional part for M > 32, see bitlinear_workspace_bytes) exceeds 16 MiB = 16777216 bytes return
  * BL_ERR_UNSUPPORTED: roughly M * K <= 16 MiB less the K-split partial sums, i.e. every
  * decode batch (M <= 64 at K <= 65536), not the prefill batches.  All calls on one GPU share
  * the array: calls that overlap in time (different streams, or threads) race; calls ordered

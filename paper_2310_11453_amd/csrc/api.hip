@@ -3,6 +3,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/bitlinear.h"
@@ -86,8 +87,8 @@ QuantWs quant_ws(int64_t M, int granularity) {
     w.total = off;
     return w;
 }
-// `total` is what a caller must bring.  Behind it, optional, room for the K-slices of a large batch
-// (M > 64) or K-groups: `full` is what bitlinear_workspace_bytes asks for.
+// `total` is what a caller must bring.  Behind it, optional, room for (more) slices of K (M > 32) or
+// for K-groups (M > 64): `full` is what bitlinear_workspace_bytes asks for.
 struct ForwardWs {
     size_t codes, gamma, rowsum, quant, split, split_bytes, xhat, total, full;
 };
@@ -186,10 +187,12 @@ ForwardWs forward_ws_nonneg(int64_t M, int64_t N, int64_t K, int groups_k, int g
                                   : group_split_bytes(M, N, K / groups_k, groups_k));
     return w;
 }
-// what the caller brought past the required bytes, for the K-slices of a large batch
+// what the caller brought past the required bytes, for slices, where it is more than `a` already has
 void offer_slices(GemmArgs& a, char* base, size_t required, size_t workspace_bytes) {
-    a.split_ws = workspace_bytes > required ? (int32_t*)(base + required) : nullptr;
-    a.split_ws_bytes = workspace_bytes - required;
+    const size_t room = workspace_bytes - required;
+    if (room <= a.split_ws_bytes) return;
+    a.split_ws = (int32_t*)(base + required);
+    a.split_ws_bytes = room;
 }
 void plain_fields(GemmArgs& a) {
     a.ldq = a.K;
@@ -273,7 +276,7 @@ size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int gr
         case BL_OP_MATMUL:
             if (M < 0 || M > kMaxDim || !shape_ok(N, K)) return 0;
             // 0 for most shapes: nothing is needed
-            return M <= 64 ? gemm_split_ws_bytes(M, N, K) : prefill_split_bytes(M, N, K);
+            return std::max(M <= 64 ? gemm_split_ws_bytes(M, N, K) : 0, prefill_split_bytes(M, N, K));
         default:
             return 0;
     }
@@ -386,7 +389,7 @@ int bitlinear_forward(const float* X, int64_t M, int64_t K, const void* packed, 
     plain_fields(a);
     a.split_ws = ws.split_bytes ? (int32_t*)(base + ws.split) : nullptr;
     a.split_ws_bytes = ws.split_bytes;
-    if (M > 64) offer_slices(a, base, ws.total, workspace_bytes);
+    if (M > 32) offer_slices(a, base, ws.total, workspace_bytes);
     if (M <= 16) return check_hip(launch_gemm_decode(a, (hipStream_t)stream));
     return check_hip(launch_gemm_prefill(a, (hipStream_t)stream));
 }
@@ -612,7 +615,7 @@ static int forward_grouped_impl(const float* X, int64_t M, int64_t K, const void
             a.eta = eta + gk;
             a.wsum = wsum + (int64_t)gk * N;
         }
-        if (M > 64) offer_slices(a, base, ws.total, workspace_bytes);
+        if (M > 32) offer_slices(a, base, ws.total, workspace_bytes);
         const hipError_t e = M <= 16 ? launch_gemm_decode(a, (hipStream_t)stream)
                                      : launch_gemm_prefill(a, (hipStream_t)stream);
         if (e != hipSuccess) return BL_ERR_HIP;

@@ -133,8 +133,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     const int64_t c0 = gmode == 2 ? 0 : TKi * kg / KG;
     const int64_t c1 = gmode == 2 ? (lgrp < a.kgroups ? TKi : 0) : TKi * (kg + 1) / KG;
     const int64_t TK = c1 - c0;
-    // a group without chunks reads the first bytes of the rows and multiplies by zero
-    const int64_t k0 = TK > 0 ? ki0 + c0 * kChunkK : 0;
+    const int64_t k0 = ki0 + c0 * kChunkK;
     int64_t K = Ki - c0 * kChunkK;  // this group's K
     if (K > TK * kChunkK) K = TK * kChunkK;
     // Every group walks the same number of stages, whole chunks of the longest group; what lies
@@ -243,9 +242,12 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // multiplies A[u % 2] by B[u % 4], starts the LDS reads of A[(u + 1) % 2] and builds B[(u + 2) % 4].
     v4i bw[2][2], bwn[2][2];
     v4i A[2][2], B[4][2];
-    issue_bits(0);
+    const bool has_k = TK > 0;  // a group without chunks requests nothing and multiplies by zero
+    if (has_k) {
+        issue_bits(0);
 #pragma unroll
-    for (int s = 0; s < NS - 1; ++s) issue(s);
+        for (int s = 0; s < NS - 1; ++s) issue(s);
+    }
     wait_vmcnt<(NS - 2) * P>();  // younger than stage 0: stages 1 .. NS-2
     block_barrier();
     read_bits(bw, b_lane);
@@ -284,7 +286,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
             // (two more, then in stage 0 the bits): in one piece behind the barrier, with a branch per
             // piece for the end of K, it idled the matrix pipe of all waves at once (7168 -> 28672 at
             // M = 64: 22.8 us, now 21.2)
-            const bool more = hs >= 2 && st + NS - 1 < nrun;
+            const bool more = hs >= 2 && has_k && st + NS - 1 < nrun;
             constexpr int u2 = u + 2;  // the operand built in this half-step
             constexpr int i2 = (u2 >> 1) & 7, h2 = u2 & 1;
             v4i(&src)[2][2] = u2 >= 16 ? bwn : bw;
@@ -433,12 +435,11 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     }
 }
 
-// Small batches (16 < M <= 64) leave most of the chip idle when N supplies few 64 x 128 tiles
-// (fewer than half the CUs): K is then split over workgroups too, so that about one work item
-// runs per CU, as long as the partial sums (M*N*4 bytes a slice) stay below the packed weights.
-// Measured on the 28672 -> 7168 layer at M = 64: 70 us unsplit, 30 us in 4 slices, 38 us in 8;
-// with 168 tiles or more a split only adds traffic.  256 CUs are assumed (the workspace is sized
-// from this too).  Returns tiles of K per slice, 0 = no split.
+// Small batches (16 < M <= 64) leave most of the chip idle when N supplies few 64 x 128 tiles: K is
+// then split over workgroups too, and splitk_reduce folds the slices.
+
+// 512-chunks of K per slice in the workspace that a call must bring (0 = no slices): about one work
+// item per CU, sums no larger than the packed weights.  256 CUs are assumed.
 int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
     if (M <= 16 || M > 64) return 0;
     if (const int64_t per = tuning().mid_split_tiles) return per > 0 && per < tiles_k(K) ? per : 0;
@@ -453,8 +454,39 @@ int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
     return (TK + per - 1) / per >= 2 ? per : 0;
 }
 
+// What the launch takes of ws_bytes: the slices of least cost, in us: a round of items 5 + 4.1 c (c
+// 512-chunks per K-group of the workgroup), the slices 4 and their sums written and read at 5 TB/s.  64 x
+// 7168 x 7168: 16.3 us in 4 slices, 18.9 in 3 (what the rule above gives); 48 x 16384 x 4096: 14.0 us
+// without, 17.7 in 2.  Returns 512-chunks per slice, 0 = no slices.
+static int64_t mid_slice_tiles(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+    const int64_t TK = tiles_k(K), tiles = (N + mid::BN - 1) / mid::BN;
+    if (const int64_t per = tuning().mid_split_tiles)
+        return per > 0 && per < TK && (size_t)((TK + per - 1) / per) * M * N * 4 <= ws_bytes ? per : 0;
+    int64_t best = 0;
+    double best_us = 1e30;
+    for (int64_t want = 1; want <= 16; ++want) {
+        const int64_t per = (TK + want - 1) / want, n = (TK + per - 1) / per;
+        const double bytes = (double)n * (double)M * (double)N * 4.0;
+        if (n > 1 && bytes > (double)ws_bytes) continue;
+        const double us = (double)((tiles * n + 255) / 256) * (5.0 + 4.1 * (double)((per + 3) / 4)) +
+                          (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = n > 1 ? per : 0;
+        }
+    }
+    return best;
+}
+// Room for them (32 < M <= 64), where it is more than the required slices take: optional.
+size_t mid_split_bytes(int64_t M, int64_t N, int64_t K) {
+    if (M <= 32 || M > 64) return 0;
+    const int64_t per = mid_slice_tiles(M, N, K, (size_t)1 << 40);
+    const size_t bytes = per ? (size_t)((tiles_k(K) + per - 1) / per) * M * N * 4 : 0;
+    return bytes > gemm_split_ws_bytes(M, N, K) ? bytes : 0;
+}
+
 // 16 < M <= 64.  K is also split over workgroups (second kernel: splitk_reduce) when N gives
-// few tiles and the caller brought the workspace for it, as prefill_split_tiles decides.
+// few tiles and the caller brought the workspace for it, as mid_slice_tiles decides.
 hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
     GemmArgs a = a_in;
     a.split_k = 0;
@@ -462,8 +494,8 @@ hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
         return hipErrorInvalidValue;
     const int grid_n = (int)((a.N + mid::BN - 1) / mid::BN);
     int splits = 1;
-    const int64_t per = prefill_split_tiles(a.M, a.N, a.K);
-    const size_t need = gemm_split_ws_bytes(a.M, a.N, a.K);
+    const int64_t per = a.split_ws && a.kgroups <= 1 && !tuning().mid_nosplit
+                            ? mid_slice_tiles(a.M, a.N, a.K, a.split_ws_bytes) : 0;
     int gmode = 0;
     if (a.kgroups > 1) {  // the caller sized split_ws for one slice per K-group
         if (!a.split_ws || a.split_ws_bytes < (size_t)a.kgroups * a.M * a.N * 4)
@@ -472,7 +504,7 @@ hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
         // are long enough to be worth splitting over the workgroup's four themselves
         gmode = tuning().group_slices || tiles_k(a.K) >= 8 ? 1 : 2;
         splits = gmode == 2 ? (a.kgroups + 3) / 4 : a.kgroups;
-    } else if (per && a.split_ws && a.split_ws_bytes >= need && !tuning().mid_nosplit) {
+    } else if (per) {
         splits = (int)((tiles_k(a.K) + per - 1) / per);
         a.tk_pitch = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
         a.split_k = per * kChunkK;

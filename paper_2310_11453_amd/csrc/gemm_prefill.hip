@@ -849,9 +849,9 @@ static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes
     }
     return best;
 }
-// Room for the K-slices of the plan (M > 64): optional, without it K is not split.
+// Room for the K-slices of the plan: optional, without it K is not split (or in fewer slices).
 size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K) {
-    if (M <= 64) return 0;
+    if (M <= 64) return mid_split_bytes(M, N, K);
     const PrefillPlan p = prefill_plan(M, N, K, (size_t)1 << 40);
     const int64_t n = (tiles_k(K) + p.per - 1) / p.per;
     return n > 1 ? (size_t)n * M * N * 4 : 0;

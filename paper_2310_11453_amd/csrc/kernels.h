@@ -128,6 +128,7 @@ size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t K);
 size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K);
 size_t group_split_bytes(int64_t M, int64_t N, int64_t K, int groups);  // K: a group's
 int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K);
+size_t mid_split_bytes(int64_t M, int64_t N, int64_t K);
 void launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_read_probe(const void* src, size_t bytes, int workgroups, int threads,
                              uint32_t* sink, hipStream_t s);
