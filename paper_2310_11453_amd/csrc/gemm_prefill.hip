@@ -497,7 +497,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
 // has two stages or more (nst).  One wait for all but the last five covers all three; items of one
 // stage wait for everything.
 //
-// 1000 x 7168 x 28672 in 8 x 8 groups: the layer takes 250 us; with the ring drained and filled for every item
+// 1000 x 7168 x 28672 in 8 x 8 groups: the layer takes 240 us; with the ring drained and filled for every item
 // and the scales loaded behind it, 445 us.
 template <bool ETA>
 __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid_m, int grid_n) {
@@ -629,9 +629,11 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
     v4i bw[NI][2];
     v4i ax[MI], ay[MI], bx[NI], by[NI];
     float side[MI][NI][16] = {};  // the tile's sum over the groups so far
-    // acc += ac x b; meanwhile an = operands at `ad`, bn = plane i of half h (see gemm_prefill_kernel)
+    // acc += ac x b; meanwhile an = operands at `ad`, bn = plane i of half h (see gemm_prefill_kernel);
+    // between() goes behind the first two MFMAs: the cursors' scalar work would idle the matrix pipe of
+    // all waves at once if it stood right behind the barrier
     auto half_step = [&](const v4i(&ac)[MI], const v4i(&b)[NI], v4i(&bn)[NI], int h, int i, v4i(&an)[MI],
-                         uint32_t ad) {
+                         uint32_t ad, auto between) {
         lds_issue(an, ad);
         asm volatile("" : "+v"(bw[0][h]), "+v"(bw[1][h]));
         __builtin_amdgcn_sched_barrier(0);
@@ -648,6 +650,11 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
                 }
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                if (q == 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    between();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         asm volatile("" : "+v"(bn[0]), "+v"(bn[1]));
         __builtin_amdgcn_sched_barrier(0);
@@ -658,7 +665,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
     int slot = 0, rbuf = 0;  // the stage's ring slot; the buffer the current chunk's bits came from
     auto stage = [&](auto ic, bool last, bool first_chunk) {
         constexpr int i = decltype(ic)::value;
-        half_step(ax, bx, by, 1, i, ay, a_lane[1] + (uint32_t)(slot * STAGE_BYTES));
+        half_step(ax, bx, by, 1, i, ay, a_lane[1] + (uint32_t)(slot * STAGE_BYTES), []() {});
         if (one_stage) wait_vmcnt<0>();
         else wait_vmcnt<5>();
         block_barrier();
@@ -666,13 +673,14 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
             rbuf ^= 1;
             lds_read_bits(bw, b_lane + (uint32_t)(rbuf * BITS_BYTES));
         }
-        if constexpr (i == 0) {
-            if (first_chunk) issue_scales();
-            issue_bits();
-        }
-        issue_codes();
         slot = (slot + 1) & (NS - 1);
-        half_step(ay, by, bx, 0, last ? 0 : i + 1, ax, a_lane[0] + (uint32_t)(slot * STAGE_BYTES));
+        half_step(ay, by, bx, 0, last ? 0 : i + 1, ax, a_lane[0] + (uint32_t)(slot * STAGE_BYTES), [&]() {
+            if constexpr (i == 0) {
+                if (first_chunk) issue_scales();
+                issue_bits();
+            }
+            issue_codes();
+        });
     };
     auto clear = [&]() {
 #pragma unroll
