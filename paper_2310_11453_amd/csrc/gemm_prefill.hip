@@ -269,7 +269,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
     // read into an meanwhile (valid on return).  Against an asm block of the MFMAs with the
     // expansion ahead of it: 117 against 129 us on 2048 x 4096 x 16384, 1-2 % on the longer K.
     auto half_step = [&](const v4i(&ac)[MI], const v4i(&b)[NI], v4i(&bn)[NI], int h, int i,
-                          v4i(&an)[MI], uint32_t ad) {
+                          v4i(&an)[MI], uint32_t ad, auto between) {
         lds_issue(an, ad);
         // the bits pass through an (empty) asm placed after the reads, and the new operand through
         // one at the end: the expansion can neither be moved ahead of this half-step nor be left
@@ -290,6 +290,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                 }
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 2 * DW, 0);
+                if (q == 1) {  // the DMA of a stage: behind two MFMAs, not ahead of them
+                    __builtin_amdgcn_sched_barrier(0);
+                    between();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         asm volatile("" : "+v"(bn[0]), "+v"(bn[1]));
         __builtin_amdgcn_sched_barrier(0);
@@ -305,17 +310,18 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
     // right after that barrier.  Near the end of K nothing more is issued and the wait is for
     // everything outstanding (all of it is needed within the next NS-2 stages).
     auto stage = [&](int st, int i, bool clamp, bool half, bool ahead, bool bits_in_flight) {
-        half_step(ax, bx, by, 1, i, ay, a_addr(st, 1));
+        half_step(ax, bx, by, 1, i, ay, a_addr(st, 1), []() {});
         if (!ahead) wait_vmcnt<0>();
         else if (bits_in_flight && i >= 3 && i <= NS - 1 && i <= 6) wait_vmcnt<(NS - 3) * P + NBW>();
         else wait_vmcnt<(NS - 3) * P>();
         block_barrier();
         if (i == 7) lds_read_bits(bw, b_lane);  // bits of the next chunk (landed long ago)
-        if (i == 2 && (st >> 3) + 1 < TK) issue_bits((st >> 3) + 1);
-        if (ahead) issue(st + NS - 1, clamp);
-        if (!half) {
-            half_step(ay, by, bx, 0, (i + 1) & 7, ax, a_addr(st + 1, 0));
-        }
+        auto dma = [&]() {
+            if (i == 2 && (st >> 3) + 1 < TK) issue_bits((st >> 3) + 1);
+            if (ahead) issue(st + NS - 1, clamp);
+        };
+        if (!half) half_step(ay, by, bx, 0, (i + 1) & 7, ax, a_addr(st + 1, 0), dma);
+        else dma();
     };
 
     int t = (int)blockIdx.x, parity = 0;
