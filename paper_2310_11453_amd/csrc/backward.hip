@@ -559,7 +559,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
     // with WORDS the sign words at `adw` into wr (both valid on return).
     auto half_step = [&](const v4i(&ac)[MI], const v4i(&b)[NI], v4i(&bn)[NI], uint32_t(&ws)[NI],
                          int h, v4i(&an)[MI], uint32_t ad, auto words, uint32_t(&wr)[NI],
-                         uint32_t adw) {
+                         uint32_t adw, auto between) {
         constexpr bool WORDS = decltype(words)::value;
         a_issue(an, ad);
         if constexpr (WORDS) words_issue(wr, adw);
@@ -575,6 +575,11 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
                 bn[idx >> 2][idx & 3] = pm_one(ws[idx >> 2], h, idx & 3);
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                if (idx == 1) {  // the DMA of a stage: behind two MFMAs, not ahead of them
+                    __builtin_amdgcn_sched_barrier(0);
+                    between();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         asm volatile("" : "+v"(bn[0]), "+v"(bn[1]));
         __builtin_amdgcn_sched_barrier(0);
@@ -585,14 +590,17 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
     auto stage = [&](int st, bool ahead) {
         // MFMAs of (st, half 0); operand of (st, half 1) from this stage's words; the words of stage
         // st+1 (their group landed before the barrier that released stage st) are read meanwhile
-        half_step(ax, bx, by, wcur, 1, ay, a_lane[1] + ring(st), std::true_type{}, wraw, w_addr(st + 1));
+        half_step(ax, bx, by, wcur, 1, ay, a_lane[1] + ring(st), std::true_type{}, wraw, w_addr(st + 1),
+                  []() {});
         if (ahead) wait_vmcnt<(NS - 3) * P>();  // younger than stage st+1: stages st+2 .. st+NS-2
         else wait_vmcnt<0>();
         block_barrier();
-        if (ahead) issue(st + NS - 1, st + NS - 1);
 #pragma unroll
         for (int s = 0; s < NI; ++s) wnext[s] = wraw[s] >> (4 * g2);
-        half_step(ay, by, bx, wnext, 0, ax, a_lane[0] + ring(st + 1), std::false_type{}, wraw, 0u);
+        half_step(ay, by, bx, wnext, 0, ax, a_lane[0] + ring(st + 1), std::false_type{}, wraw, 0u,
+                  [&]() {
+                      if (ahead) issue(st + NS - 1, st + NS - 1);
+                  });
 #pragma unroll
         for (int s = 0; s < NI; ++s) wcur[s] = wnext[s];
     };
