@@ -531,7 +531,7 @@ static void launch_mode(const QuantArgs& a, hipStream_t s) {
     }
 }
 
-// Waves per row: enough of them that the chip holds about sixteen waves per CU (short rows
+// Waves per row (up to 16): enough of them that the chip holds about sixteen waves per CU (short rows
 // of a small batch are split over several waves rather than leaving most SIMDs idle), and
 // never more than 16 float4 per lane.
 hipError_t launch_quant(const QuantArgs& a, hipStream_t s) {
@@ -550,19 +550,27 @@ hipError_t launch_quant(const QuantArgs& a, hipStream_t s) {
     int wpr = 1;
     while (wpr < 8 && K4 > (int64_t)wpr * kWave * 16) wpr *= 2;             // capacity
     while (wpr < 8 && a.M * wpr < 4096 && K4 >= (int64_t)wpr * 2 * kWave * 4) wpr *= 2;  // occupancy
+    // A small batch is the latency of one row: loads, two passes of fp64 per element of a lane, the
+    // reductions.  One more doubling, down to two float4 per lane, and 16 waves beyond K = 16384, pay
+    // while the batch stays below 2048 waves (us, before / after: 8 x 2048 4.05 / 3.6, 8 x 4096 4.3 / 4.05,
+    // 64 x 7168 5.8 / 4.9, 64 x 28672 9.5 / 8.6; 512 x 4096 would go from 6.4 to 6.5, 8 x 16384 with 16
+    // waves from 6.1 to 6.35).
+    if (a.M * wpr * 2 <= 2048) {
+        if (wpr < 8 && K4 >= (int64_t)wpr * 2 * kWave * 2) wpr *= 2;
+        else if (K4 > 8 * kWave * 8) wpr = 16;
+    }
     if (const int v = tuning().quant_wpr)
         if ((v == 1 || v == 2 || v == 4 || v == 8) && K4 <= (int64_t)v * kWave * 16) wpr = v;
     const int64_t per_lane = (K4 + wpr * kWave - 1) / (wpr * kWave);
     int nv = 1;
     while (nv < per_lane) nv *= 2;
-    if (wpr == 2 && nv < 4) nv = 4;
-    if (wpr == 4 && nv < 4) nv = 4;
-    if (wpr == 8 && nv < 8) nv = 8;
+    if (wpr > 1 && nv < 2) nv = 2;
 #define BL_QUANT_CASE(W, V) if (wpr == W && nv == V) launch_mode<W, V>(a, s); else
     BL_QUANT_CASE(1, 1) BL_QUANT_CASE(1, 2) BL_QUANT_CASE(1, 4) BL_QUANT_CASE(1, 8) BL_QUANT_CASE(1, 16)
-    BL_QUANT_CASE(2, 4) BL_QUANT_CASE(2, 8) BL_QUANT_CASE(2, 16)
-    BL_QUANT_CASE(4, 4) BL_QUANT_CASE(4, 8) BL_QUANT_CASE(4, 16)
-    BL_QUANT_CASE(8, 8) BL_QUANT_CASE(8, 16)
+    BL_QUANT_CASE(2, 2) BL_QUANT_CASE(2, 4) BL_QUANT_CASE(2, 8) BL_QUANT_CASE(2, 16)
+    BL_QUANT_CASE(4, 2) BL_QUANT_CASE(4, 4) BL_QUANT_CASE(4, 8) BL_QUANT_CASE(4, 16)
+    BL_QUANT_CASE(8, 2) BL_QUANT_CASE(8, 4) BL_QUANT_CASE(8, 8) BL_QUANT_CASE(8, 16)
+    BL_QUANT_CASE(16, 8)
     return hipErrorInvalidValue;
 #undef BL_QUANT_CASE
     return hipGetLastError();
