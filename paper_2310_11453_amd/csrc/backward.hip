@@ -742,6 +742,10 @@ static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp) {
     int cus = bwd_num_cus();
     if (tuning().bwd_grid > 0) cus = tuning().bwd_grid;
     const int64_t ntiles = gi * gj, nst = Rp / 32;
+    if (ntiles == 0 || nst == 0) {  // no tokens: nothing to launch, nothing to cut (a size query asks)
+        p.sl = RingSlices{1, (int)nst};
+        return p;
+    }
     p.sl = ring_slices(ntiles, nst, (double)I * (double)J * 4.0, cus);
     if (const int n = tuning().bwd_splits) {
         const int64_t per = (nst + n - 1) / n;

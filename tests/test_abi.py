@@ -47,6 +47,27 @@ def test_host_size_queries(lib):
     assert bl.workspace_bytes(99, 8, 512, 256) == 0
 
 
+def test_size_queries_without_tokens(lib):
+    """M = 0 is a valid batch for every operation: the queries answer, with no more than one token needs, and
+    the backward is a no-op like the other calls."""
+    import paper_2310_11453_amd as bl
+    for N, K in [(512, 256), (16, 32), (8192, 2048)]:
+        for op in (bl.OP_QUANT, bl.OP_FORWARD, bl.OP_BACKWARD, bl.OP_LN_BACKWARD, bl.OP_FORWARD_NONNEG):
+            for per_tensor in (False, True):
+                assert 0 < bl.workspace_bytes(op, 0, N, K, per_tensor) <= bl.workspace_bytes(op, 1, N, K, per_tensor)
+        assert bl.workspace_bytes(bl.OP_MATMUL, 0, N, K) == 0
+    for op in (bl.OP_QUANT, bl.OP_FORWARD, bl.OP_LN_BACKWARD, bl.OP_FORWARD_NONNEG):
+        assert 0 < bl.workspace_bytes_grouped(op, 0, 512, 2048, 2, 4) <= bl.workspace_bytes_grouped(
+            op, 1, 512, 2048, 2, 4)
+    try:
+        for spec in (b"bwd_splits=3", b"bwd_grid=8"):
+            assert lib.bitlinear_set_tuning(spec) == 0
+            assert bl.workspace_bytes(bl.OP_BACKWARD, 0, 512, 256) > 0
+    finally:
+        lib.bitlinear_set_tuning(None)
+    assert lib.bitlinear_backward_ste(None, 0, 512, 256, None, None, 0, None, None, None, None, None, 0, None) == 0
+
+
 def test_argument_errors_are_found_on_the_host(lib):
     one = ctypes.c_void_p(256)  # never dereferenced: every call below fails before a launch
     assert lib.bitlinear_pack_weights(None, 8, 32, 0, one, one, one, one, 1 << 20, None) == -1

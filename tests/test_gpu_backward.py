@@ -162,3 +162,15 @@ def test_backward_slices_of_the_reduction_exact(bl, tuning, M, N, K, splits):
         dX, dW = bl.bitlinear_backward_ste(dev(dY), dev(q), g128, packed, one, True, workspace=ws)
         assert np.array_equal(dX.cpu().numpy(), dX_ref)
         assert np.array_equal(dW.cpu().numpy(), dW_ref)
+
+
+@pytest.mark.parametrize("per_tensor", [True, False])
+def test_backward_without_tokens(bl, per_tensor):
+    """A batch of zero tokens is a no-op through the binding too (which asks for the workspace first)."""
+    N, K = 512, 256
+    print(f"backward M=0 per_tensor={per_tensor}", flush=True)
+    packed, _, beta = bl.bitlinear_pack_weights(dev(wl.make_weight(N, K, 0.02, 5)))
+    dX, dW = bl.bitlinear_backward_ste(torch.empty((0, N), device="cuda"),
+                                       torch.empty((0, K), dtype=torch.int8, device="cuda"),
+                                       torch.ones(1, device="cuda"), packed, beta, per_tensor)
+    assert dX.shape == (0, K) and dW.shape == (N, K)
