@@ -747,7 +747,7 @@ static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp) {
         return p;
     }
     p.sl = ring_slices(ntiles, nst, (double)I * (double)J * 4.0, cus);
-    if (const int n = tuning().bwd_splits) {
+    if (const int n = tuning().bwd_splits; n > 0) {
         const int64_t per = (nst + n - 1) / n;
         p.sl = RingSlices{(int)((nst + per - 1) / per), (int)per};
     }

@@ -127,6 +127,14 @@ def test_tuning_switches_parse_on_the_host(lib):
     assert lib.bitlinear_set_tuning(b"no_such_switch=1") == -3
     assert lib.bitlinear_set_tuning(b"decode_nofuse") == -3
     assert lib.bitlinear_set_tuning(b"decode_nofuse=x") == -3
+    # a count below one is no override
+    import paper_2310_11453_amd as bl
+    assert lib.bitlinear_set_tuning(b"") == 0
+    plain = bl.workspace_bytes(bl.OP_BACKWARD, 1000, 512, 256)
+    for n in (b"-1", b"-5", b"-32"):
+        assert lib.bitlinear_set_tuning(b"bwd_splits=" + n) == 0
+        assert bl.workspace_bytes(bl.OP_BACKWARD, 1000, 512, 256) == plain
+        assert bl.workspace_bytes(bl.OP_BACKWARD, 8, 64, 256) > 0
     assert lib.bitlinear_set_tuning(b"") == 0
     assert lib.bitlinear_set_tuning(None) == 0
 
