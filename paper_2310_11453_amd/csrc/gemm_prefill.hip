@@ -833,7 +833,10 @@ struct PrefillPlan {
 static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
     const int64_t cus = num_cus(), TK = tiles_k(K), nst = (K + kStageK - 1) / kStageK;
     const int force = tuning().prefill_tile;
-    PrefillPlan best{2, TK};
+    const int64_t force_n = tuning().prefill_split > 0 ? tuning().prefill_split : 0;
+    // a forced tile stays that tile, unsliced, where its slices have no room; forced slices are
+    // as many as the chunks of K give in equal parts
+    PrefillPlan best{force >= 1 && force <= 4 ? force : 2, TK};
     double best_us = 1e30;
     auto offer = [&](int tile, int64_t per, double us) {
         if (us < best_us) {
@@ -851,11 +854,10 @@ static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes
             continue;
         }
         const int kg = tile == 3 ? 2 : 4;
-        for (int64_t want = 1; want <= 8; ++want) {
-            if (tuning().prefill_split && want != tuning().prefill_split) continue;
+        for (int64_t want = force_n ? force_n : 1; want <= (force_n ? force_n : 8); ++want) {
             const int64_t per = (TK + want - 1) / want, n = (TK + per - 1) / per;
             const double bytes = (double)n * (double)M * (double)N * 4.0;
-            if (n > 1 && (n != want || bytes > (double)ws_bytes)) continue;
+            if (n > 1 && ((n != want && !force_n) || bytes > (double)ws_bytes)) continue;
             const int64_t rounds = (tiles * n + cus - 1) / cus;
             offer(tile, per, (double)rounds * (5.0 + 4.2 * (double)((per + kg - 1) / kg)) +
                                  (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0));

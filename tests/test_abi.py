@@ -139,6 +139,23 @@ def test_tuning_switches_parse_on_the_host(lib):
     assert lib.bitlinear_set_tuning(None) == 0
 
 
+@pytest.mark.parametrize("K", [32, 1024, 2080, 3616, 4128])
+def test_forced_tiles_and_slices_are_planned(lib, K):
+    """M > 64: a forced tile with forced slices of K is what the plan holds (seen in the bytes it asks
+    for), in as many equal slices as the 512-wide chunks of K give; the large tiles take no slices."""
+    import paper_2310_11453_amd as bl
+    M, N, chunks = 257, 390, (K + 511) // 512
+    try:
+        for tile in (1, 2, 3, 4):
+            for n in (1, 2, 3, 4, 9):
+                bl.set_tuning(f"prefill_tile={tile},prefill_split={n}")
+                per = (chunks + n - 1) // n
+                slices = (chunks + per - 1) // per if tile >= 3 else 1
+                assert bl.workspace_bytes(bl.OP_MATMUL, M, N, K) == (slices * M * N * 4 if slices > 1 else 0)
+    finally:
+        bl.set_tuning(None)
+
+
 def test_size_limits_are_host_errors(lib):
     """K beyond what the GEMM kernels' int32 partial sums hold: refused before any launch."""
     one = ctypes.c_void_p(256)

@@ -205,9 +205,9 @@ def test_matmul_random_shapes(bl, M, K, N):
 
 # More than 64 tokens: every tile shape on every form of edge (rows, columns and K one past a tile, K
 # within one chunk, fewer chunks than K-groups or slices, N not a multiple of 4) and, for the tiles
-# that allow it, K in slices; the nonnegative quantiser's epilogue; a workspace without room for
-# the slices.
-TILE_SHAPES = [(65, 32, 33), (129, 544, 130), (192, 2080, 256), (257, 4128, 390), (100, 1024, 37)]
+# that allow it, K in slices (two to four where K has the chunks, the last one shorter); the
+# nonnegative quantiser's epilogue; the same tile without room for the slices (the forward always has it).
+TILE_SHAPES = [(65, 32, 33), (129, 544, 130), (192, 2080, 256), (257, 4128, 390), (100, 1024, 37), (130, 3616, 260)]
 
 
 @pytest.mark.parametrize("M,K,N", TILE_SHAPES)
@@ -229,6 +229,9 @@ def test_matmul_large_batch_tiles(bl, tuning, M, K, N):
         print(f"  {spec}", flush=True)
         tuning(spec)
         need = bl.workspace_bytes(bl.OP_MATMUL, M, N, K)
+        want, chunks = int(spec[-1]) if "split" in spec else 1, (K + 511) // 512
+        slices = -(-chunks // -(-chunks // want))
+        assert need == (slices * M * N * 4 if slices > 1 else 0)
         for ws in (None, torch.empty(need, dtype=torch.uint8, device="cuda") if need else None):
             acc = bl.bitlinear_matmul(codes, gamma, rowsum, packed, N, beta, flags=bl.FLAG_OUT_ACC_I32,
                                       workspace=ws)
