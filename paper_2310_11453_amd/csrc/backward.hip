@@ -193,15 +193,16 @@ struct RingSlices {
 };
 
 // ---- C[I][J] = scale * sum_r A[I][r] B[J][r], bf16 operands, fp32 accumulation -----------------
-// Workgroup tile 256 x 256, four waves of 128 x 128 (4 x 4 MFMA tiles), one workgroup per CU,
-// persistent over the tiles.  A stage is 32 reduction elements: 64-byte rows of A and of B,
-// streamed global -> LDS by global_load_lds_dwordx4 into a ring of NS stages; the 16-byte
+// Workgroup tile T x T, four waves of T/2 x T/2, persistent over the tiles.  T = 256: 4 x 4 MFMA tiles a
+// wave, one workgroup per CU; T = 128 (few stages or few tiles, dw_plan): 2 x 2, two workgroups per CU.
+// A stage is 32 reduction elements: 64-byte rows of A and of B, streamed global -> LDS by
+// global_load_lds_dwordx4 into a ring of NS stages; the 16-byte
 // segments of a row are XOR-swizzled with (row/4)%4, so the operand reads of 16 consecutive rows
 // touch every bank once.  Between the half-steps of stage st every wave waits for its own DMA of
 // stage st+1 (s_waitcnt vmcnt(n), n counted by hand), meets the others at a bare s_barrier, and
 // the DMA of stage st+NS-1 goes to the buffer stage st-1 has left.
 //
-// Why four waves.  With eight waves of 128 x 64 LDS sets the pace: every operand row is read by the
+// Why four waves (T = 256).  With eight waves of 128 x 64 LDS sets the pace: every operand row is read by the
 // waves that share it, 96 KiB of reads and 32 KiB of DMA writes a stage, at 128 bytes a cycle as
 // long as the MFMAs of the stage take (1024 cycles).  128 x 128 waves read 64 KiB.  There is one wave
 // per SIMD then: 256 accumulator registers (the compiler keeps them in the AGPR half of the file),
@@ -229,15 +230,29 @@ __device__ inline void wide_wait(v4i (&a)[4], v4i (&b)[4]) {
                    "+v"(b[3]));
 }
 
-template <int NS, bool SPLIT>
-__global__ __launch_bounds__(256, 1) void gemm_tn_bf16_wide(const uint16_t* __restrict__ A,
+// the same for 64 x 64 waves
+__device__ inline void wide_issue(v4i (&a)[2], v4i (&b)[2], uint32_t ad_a, uint32_t ad_b) {
+    asm volatile(
+        "ds_read_b128 %0, %4\n\t"
+        "ds_read_b128 %1, %4 offset:2048\n\t"
+        "ds_read_b128 %2, %5\n\t"
+        "ds_read_b128 %3, %5 offset:2048"
+        : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0]), "=&v"(b[1])
+        : "v"(ad_a), "v"(ad_b));
+}
+__device__ inline void wide_wait(v4i (&a)[2], v4i (&b)[2]) {
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]));
+}
+
+template <int T, int NS, bool SPLIT>
+__global__ __launch_bounds__(256, T == 256 ? 1 : 2) void gemm_tn_bf16_wide(const uint16_t* __restrict__ A,
                                                             const uint16_t* __restrict__ B,
                                                             int64_t I, int64_t J, int64_t Rp,
                                                             const float* __restrict__ scale_ptr,
                                                             float scale_mul, float* __restrict__ C,
                                                             int grid_i, int grid_j, int blk_i,
                                                             int blk_j, RingSlices sl) {
-    constexpr int BM = 256, BN = 256, WN = 2, THREADS = 256, WTM = 128, WTN = 128, MI = 4, NI = 4;
+    constexpr int BM = T, BN = T, WN = 2, THREADS = 256, WTM = T / 2, WTN = T / 2, MI = T / 64, NI = T / 64;
     constexpr int PA = BM * 4 / THREADS, PB = BN * 4 / THREADS, P = PA + PB;
     constexpr int A_BYTES = BM * 64, STAGE_BYTES = (BM + BN) * 64;
     static_assert((NS - 1) * P < 64, "vmcnt range");
@@ -708,24 +723,26 @@ static int bwd_num_cus() {
 // blk_i x blk_j = grid / 8 tiles out of its grid_i / 8 rows, as square as the divisors allow; 0 =
 // no such tiling; and the slices of the reduction.
 struct RingPlan {
-    int grid, gi, gj, blk_i, blk_j;
+    int tile, grid, gi, gj, blk_i, blk_j;
     RingSlices sl;
 };
 
-// Slices of a product of `tiles` tiles and nst stages on `cus` CUs: the count that costs least, in
-// units of 1 us, when a stage takes 0.6 us on a CU, an item 7 us besides, and the fp32 sums of a
-// slice (`bytes`) are written and read at 5 TB/s by a second launch of 4 us.  dX^ of M = 1000, N = 8192,
-// K = 2048 (32 tiles of 256 stages): 6 slices, 43 us and 11 us for the fold; in 64 tiles of
-// 256 x 128, each walking all of N, it took 185 us.
+// Cost in us of a product of `tiles` 256 x 256 tiles in slices of `per` of its nst stages on `cus` CUs: a
+// stage takes 0.6 us on a CU, an item 7 us besides, and the fp32 sums of a slice (`bytes`) are written
+// and read at 5 TB/s by a second launch of 4 us.
+static double ring_cost(int64_t tiles, int64_t nst, int64_t per, double bytes, int64_t cus) {
+    const int64_t n = (nst + per - 1) / per, rounds = (tiles * n + cus - 1) / cus;
+    return (double)rounds * (0.6 * (double)per + 7.0) + (n > 1 ? 4.0 + (double)n * bytes * 2.0 / 5e6 : 0.0);
+}
+// The slices that cost least.  dX^ of M = 1000, N = 8192, K = 2048 (32 tiles of 256 stages): 6 slices, 43 us
+// and 11 us for the fold; in 64 tiles of 256 x 128, each walking all of N, it took 185 us.
 static RingSlices ring_slices(int64_t tiles, int64_t nst, double bytes, int64_t cus) {
     RingSlices best{1, (int)nst};
     double best_cost = 1e30;
     for (int64_t want = 1; want <= 16; ++want) {
         const int64_t per = (nst + want - 1) / want, n = (nst + per - 1) / per;
         if (want > 1 && per < 8) break;
-        const int64_t rounds = (tiles * n + cus - 1) / cus;
-        const double cost = (double)rounds * (0.6 * (double)per + 7.0) +
-                            (n > 1 ? 4.0 + (double)n * bytes * 2.0 / 5e6 : 0.0);
+        const double cost = ring_cost(tiles, nst, per, bytes, cus);
         if (cost < best_cost * 0.97) {
             best_cost = cost;
             best = RingSlices{(int)n, (int)per};
@@ -734,25 +751,25 @@ static RingSlices ring_slices(int64_t tiles, int64_t nst, double bytes, int64_t 
     return best;
 }
 
-static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp) {
+static int ring_cus() { return tuning().bwd_grid > 0 ? tuning().bwd_grid : bwd_num_cus(); }
+
+// tile: 256, or 128 (dW only; not sliced)
+static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp, int tile) {
     RingPlan p{};
-    const int64_t gi = (I + 255) / 256, gj = (J + 255) / 256;
+    const int64_t gi = (I + tile - 1) / tile, gj = (J + tile - 1) / tile;
+    p.tile = tile;
     p.gi = (int)gi;
     p.gj = (int)gj;
-    int cus = bwd_num_cus();
-    if (tuning().bwd_grid > 0) cus = tuning().bwd_grid;
     const int64_t ntiles = gi * gj, nst = Rp / 32;
-    if (ntiles == 0 || nst == 0) {  // no tokens: nothing to launch, nothing to cut (a size query asks)
-        p.sl = RingSlices{1, (int)nst};
-        return p;
-    }
-    p.sl = ring_slices(ntiles, nst, (double)I * (double)J * 4.0, cus);
-    if (const int n = tuning().bwd_splits; n > 0) {
+    p.sl = RingSlices{1, (int)nst};
+    if (ntiles == 0 || nst == 0) return p;  // no tokens: nothing to launch (a size query asks)
+    if (tile == 256) p.sl = ring_slices(ntiles, nst, (double)I * (double)J * 4.0, ring_cus());
+    if (const int n = tuning().bwd_splits; n > 0 && tile == 256) {
         const int64_t per = (nst + n - 1) / n;
         p.sl = RingSlices{(int)((nst + per - 1) / per), (int)per};
     }
-    const int64_t items = ntiles * p.sl.splits;
-    const int grid = cus > items ? (int)items : cus;
+    const int64_t items = ntiles * p.sl.splits, cap = (int64_t)ring_cus() * (tile == 256 ? 1 : 2);
+    const int grid = (int)(cap > items ? items : cap);
     p.grid = grid;
     if (p.sl.splits == 1 && ntiles % 8 == 0 && grid % 8 == 0 && gi % 8 == 0 &&
         (ntiles / 8) % (grid / 8) == 0 && !tuning().bwd_rowmajor) {
@@ -791,18 +808,45 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
             part, p.sl.splits, count, scale_ptr, scale_mul, C);
 }
 
+// dW's plan: 256 x 256 tiles, or 128 x 128 where they cost less.  The fixed cost of a 256 x 256 tile (7 us: its
+// first DMA, its 64 K outputs stored by four waves) is what a product of a few stages consists of; the
+// 128 x 128 tile has a quarter of it and two workgroups per CU, but reads every operand twice as often:
+//   a round of up to one workgroup per CU    1.0 + 0.25 us per stage
+//   a round of two per CU                    2.5 + 0.38
+// The whole call (with the operand copies), 256 against 128: 8 x 512 x 256 18.2 / 10.5 us, 64 x 2048 x 2048
+// 21.3 / 13.2, 1000 x 2048 x 2048 44.6 / 25.7, 8 x 4096 x 16384 74.6 / 64.4; 4096 x 512 x 256 (16 slices of
+// 256 tiles) 33.9 / 44.5.  Past one full round the second read of the operands decides: beyond 32 stages (16 from two full
+// rounds on, 12 from nine), or with a B operand well beyond an XCD's 4 MB of L2, the large tile it is (512 x 7168 x
+// 7168 115 / 107, 1000 x 7168 x 7168 159 / 171, 512 x 21504 x 7168 261 / 287, 256 x 7168 x 28672 248 / 265).
+static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
+    const int force = tuning().bwd_ring;
+    if (force == 2) return ring_plan(I, J, Rp, 128);
+    const RingPlan p = ring_plan(I, J, Rp, 256);
+    if (force == 1 || tuning().bwd_splits > 0 || p.grid == 0) return p;
+    const int64_t cus = ring_cus(), nst = Rp / 32, ntiles = (I + 127) / 128 * ((J + 127) / 128);
+    const int64_t full = ntiles / (2 * cus), rest = ntiles % (2 * cus);
+    if (ntiles > 2 * cus && (nst > (full < 2 ? 32 : full < 9 ? 16 : 12) || J * Rp * 2 > 12000000)) return p;
+    const double wide = ring_cost((int64_t)p.gi * p.gj, nst, p.sl.per, (double)I * (double)J * 4.0, cus);
+    const double two = 2.5 + 0.38 * (double)nst, one = 1.0 + 0.25 * (double)nst;
+    const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);
+    return small < wide ? ring_plan(I, J, Rp, 128) : p;
+}
+
 // C[I][J] = scale * A[I][:] . B[J][:], in slices of r where the plan has them and `part` has room
 static void launch_gemm_tn(const uint16_t* A, const uint16_t* B, int64_t I, int64_t J, int64_t Rp,
                            const float* scale_ptr, float scale_mul, float* C, float* part,
                            size_t part_bytes, hipStream_t s) {
-    RingPlan p = ring_plan(I, J, Rp);
+    RingPlan p = dw_plan(I, J, Rp);
     if (slices_bytes(p, I, J) > part_bytes) p = unsliced(p, Rp);
     if (p.sl.splits > 1) {
-        gemm_tn_bf16_wide<4, true><<<(unsigned)p.grid, 256, 0, s>>>(A, B, I, J, Rp, nullptr, 1.0f, part,
-                                                                     p.gi, p.gj, 0, 0, p.sl);
+        gemm_tn_bf16_wide<256, 4, true><<<(unsigned)p.grid, 256, 0, s>>>(
+            A, B, I, J, Rp, nullptr, 1.0f, part, p.gi, p.gj, 0, 0, p.sl);
         launch_fold(part, p, I * J, scale_ptr, scale_mul, C, s);
+    } else if (p.tile == 256) {
+        gemm_tn_bf16_wide<256, 4, false><<<(unsigned)p.grid, 256, 0, s>>>(
+            A, B, I, J, Rp, scale_ptr, scale_mul, C, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
     } else {
-        gemm_tn_bf16_wide<4, false><<<(unsigned)p.grid, 256, 0, s>>>(
+        gemm_tn_bf16_wide<128, 4, false><<<(unsigned)p.grid, 256, 0, s>>>(
             A, B, I, J, Rp, scale_ptr, scale_mul, C, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
     }
 }
@@ -828,8 +872,8 @@ static BackwardWs backward_ws(int64_t M, int64_t N, int64_t K) {
 size_t backward_workspace_min_bytes(int64_t M, int64_t N, int64_t K) { return backward_ws(M, N, K).total; }
 // The same and room for the slices of whichever product is cut (one after the other): optional.
 size_t backward_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    const size_t dx = slices_bytes(ring_plan(M, K, pad32(N)), M, K);
-    const size_t dw = slices_bytes(ring_plan(N, K, pad32(M)), N, K);
+    const size_t dx = slices_bytes(ring_plan(M, K, pad32(N), 256), M, K);
+    const size_t dw = slices_bytes(dw_plan(N, K, pad32(M)), N, K);
     const size_t need = backward_ws(M, N, K).total + (dx > dw ? dx : dw);
     // never less than four bf16 copies of a small product's operands, which callers may have budgeted
     const size_t copies = 2 * ((size_t)M * pad32(N) * 2 + (size_t)K * pad32(N) + (size_t)K * pad32(M));
@@ -852,7 +896,7 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
     launch_cast_transpose<float>(a.dY, M, N, Np, Mp, a.per_tensor ? nullptr : a.gamma,
                                  a.dX ? g : nullptr, a.dW ? gwT : nullptr, s);
     if (a.dX) {  // +-1 from sign words inside the kernel: no bf16 copy of the weights
-        RingPlan p = ring_plan(M, K, Np);
+        RingPlan p = ring_plan(M, K, Np, 256);
         if (slices_bytes(p, M, K) > part_bytes) p = unsliced(p, Np);
         dim3 gb((unsigned)(Np / 32), (unsigned)tiles_k(K));
         bits_transpose_words<<<gb, 256, 0, s>>>(a.packed, N, K, Sw);

@@ -37,8 +37,8 @@ SHAPES = [(8, 512, 256), (12, 20, 64), (300, 200, 96), (64, 136, 1056), (257, 51
           (1024, 640, 512)]
 
 
-# The library picks the GEMM kernel from the shape (the persistent 256 x 256 ring kernel needs
-# many tiles); the bwd_ring switch forces either one so that both see the ragged shapes.
+# The library picks dW's tile from the shape (256 x 256, or 128 x 128 where that costs less); the bwd_ring
+# switch forces either one so that both see the ragged shapes.  dX has one tile.
 @pytest.mark.parametrize("M,N,K", SHAPES)
 @pytest.mark.parametrize("per_tensor", [True, False])
 @pytest.mark.parametrize("ring", ["2", "1"])
@@ -67,13 +67,16 @@ def test_backward_ste_matches_oracle(bl, tuning, M, N, K, per_tensor, ring):
     assert none is None and torch.equal(dW2, dW)
 
 
-def test_backward_ring_kernel_walks_several_tiles(bl, tuning):
-    """The persistent kernel with fewer workgroups than tiles (the bwd_grid switch): dX has 16
-    tiles on 8 workgroups (the tile order that groups tiles by L2 applies), dW 12 on 8."""
-    tuning("bwd_ring=1,bwd_grid=8")
-    M, N, K = 1024, 520, 1024
+@pytest.mark.parametrize("spec,N", [("bwd_ring=1,bwd_grid=8", 520), ("bwd_ring=2,bwd_grid=4", 520),
+                                    ("bwd_ring=2,bwd_grid=8", 1024)])
+def test_backward_ring_kernel_walks_several_tiles(bl, tuning, spec, N):
+    """The persistent kernels with fewer workgroups than tiles (the bwd_grid switch): dX has 16
+    tiles on 8 workgroups, dW 12 of 256 x 256 on 8, then 40 of 128 x 128 on 8 and 64 on 16 (the tile order
+    that groups tiles by L2)."""
+    tuning(spec)
+    M, K = 1024, 1024
     sd = wl.seed_for(4, 77)
-    print(f"backward ring grid=8 M={M} N={N} K={K}", flush=True)
+    print(f"backward ring {spec} M={M} N={N} K={K}", flush=True)
     W = wl.make_weight(N, K, 0.02, sd)
     X = wl.make_activation(M, K, sd)
     dY = wl.make_grad(M, N, sd)
