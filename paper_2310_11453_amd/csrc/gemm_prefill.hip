@@ -634,7 +634,17 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
     v16i acc[MI][NI];
     v4i bw[NI][2];
     v4i ax[MI], ay[MI], bx[NI], by[NI];
-    float side[MI][NI][16] = {};  // the tile's sum over the groups so far
+    // the tile's sum over the groups so far: from -0, which leaves the first term as it is (0 + -0 is 0)
+    float side[MI][NI][16];
+    auto clear_side = [&]() {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int s = 0; s < NI; ++s)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) side[mi][s][r] = -0.f;
+    };
+    clear_side();
     // acc += ac x b; meanwhile an = operands at `ad`, bn = plane i of half h (see gemm_prefill_kernel);
     // between() goes behind the first two MFMAs: the cursors' scalar work would idle the matrix pipe of
     // all waves at once if it stood right behind the barrier
@@ -766,12 +776,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
                         if (n < N) __builtin_nontemporal_store(side[mi][s][r], &a.Y[(int64_t)m * N + n]);
                     }
                 }
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int s = 0; s < NI; ++s)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) side[mi][s][r] = 0.f;
+            clear_side();
         }
         if (!next_item(cur)) break;
         fbuf ^= 1;

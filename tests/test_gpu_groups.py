@@ -177,6 +177,25 @@ def test_grouped_forward_large_batch_slices(bl, tuning, M, Kg, N, gn, gk):
         _check_forward(bl, M, Kg * gk, N, gn, gk, False, 800 + M)
 
 
+@pytest.mark.parametrize("M,Kg,N,gn,gk", [(130, 96, 272, 1, 2), (70, 544, 40, 1, 3)])
+def test_grouped_forward_zero_keeps_its_sign(bl, tuning, M, Kg, N, gn, gk):
+    """Weights of zero (beta_g = 0): every group's term is a zero with the sign of its integer sum, and the
+    sum of the groups, added in the order 0, 1, ..., has the same sign bits from either kernel."""
+    print(f"grouped zeros M={M} Kg={Kg} N={N} gn={gn} gk={gk}", flush=True)
+    X, _ = layer(M, Kg * gk, N, 900 + M)
+    packed, alpha, beta = bl.bitlinear_pack_weights_grouped(dev(np.zeros((N, Kg * gk), f32)), gn, gk)
+    _, gamma, rowsum, _ = bl.bitlinear_quant_act_grouped(dev(X), gk)
+    zeros = (-host(rowsum).reshape(M, gk)).astype(f32) * f32(0)  # all weights are -1: the integer sums are -rowsum
+    ref = zeros[:, 0]
+    for g in range(1, gk):
+        ref = zeros[:, g] + ref
+    assert np.signbit(ref).any() and not np.signbit(ref).all()
+    for tile in (1, 3, 4):
+        tuning(f"prefill_tile={tile}")
+        y = host(bl.bitlinear_forward_grouped(dev(X), packed, N, beta, gn, gk))
+        assert np.array_equal(y.view(np.uint32), np.repeat(ref[:, None], N, 1).view(np.uint32)), tile
+
+
 def test_grouped_forward_full_size_30b(bl):
     """A 30B-shaped layer (7168 -> 28672) with eight groups on each axis, decode and prefill batch:
     alpha_g, beta_g and all bits; codes and gamma_g given the normalised input the GPU dumped;
