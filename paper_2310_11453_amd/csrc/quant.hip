@@ -554,8 +554,11 @@ hipError_t launch_quant(const QuantArgs& a, hipStream_t s) {
     // reductions.  One more doubling, down to two float4 per lane, and 16 waves beyond K = 16384, pay
     // while the batch stays below 2048 waves (us, before / after: 8 x 2048 4.05 / 3.6, 8 x 4096 4.3 / 4.05,
     // 64 x 7168 5.8 / 4.9, 64 x 28672 9.5 / 8.6; 512 x 4096 would go from 6.4 to 6.5, 8 x 16384 with 16
-    // waves from 6.1 to 6.35).
-    if (a.M * wpr * 2 <= 2048) {
+    // waves from 6.1 to 6.35).  Not for short rows with a gamma per tensor from about 128 rows on: a workgroup
+    // sends one candidate for the maximum, and half the rows to a workgroup are twice the candidates on
+    // one address (both passes, without / with: 512 x 1024 9.2 / 10.2, 333 x 2048 10.1 / 11.8, but 33 x 2048 8.3 / 7.5
+    // and 512 x 3072 12.8 / 11.4).
+    if (a.M * wpr * 2 <= 2048 && !(a.per_tensor && a.M > 128 && K4 <= 512)) {
         if (wpr < 8 && K4 >= (int64_t)wpr * 2 * kWave * 2) wpr *= 2;
         else if (K4 > 8 * kWave * 8) wpr = 16;
     }

@@ -70,7 +70,7 @@ def test_pack_deterministic(bl):
 QUANT_SHAPES = [(8, 256), (1, 2048), (5, 96), (3, 544), (16, 8192), (33, 4096), (7, 7168),
                 (2, 28672), (4, 16384), (64, 1024),
                 # waves per row: 16 with a ragged tail, and the batches that take one doubling less
-                (40, 17024), (300, 7168), (130, 28672),
+                (40, 17024), (300, 7168), (130, 28672), (200, 2048), (129, 1056),
                 # rows longer than the registers hold: walked from memory in passes
                 (3, 36000), (2, 65536), (5, 32800)]
 
