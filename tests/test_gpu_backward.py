@@ -177,3 +177,29 @@ def test_backward_without_tokens(bl, per_tensor):
                                        torch.empty((0, K), dtype=torch.int8, device="cuda"),
                                        torch.ones(1, device="cuda"), packed, beta, per_tensor)
     assert dX.shape == (0, K) and dW.shape == (N, K)
+
+
+@pytest.mark.parametrize("M,N,K", [(290, 520, 288), (513, 2080, 544)])
+@pytest.mark.parametrize("per_tensor", [True, False])
+def test_backward_slices_are_within_tolerance_of_uncut(bl, tuning, M, N, K, per_tensor):
+    """Real values: slices change the order of the fp32 sums, so dX and dW may differ from the uncut ones in
+    the last bits; both are as close to the oracle.  A rounding is at most 2^-24 of the running sum; R of them, of
+    either sign, come to about sqrt(R) 2^-24 of the result's rms, 2.7e-6 at R = 2080, on each side: 1e-5."""
+    print(f"backward slices, real values M={M} N={N} K={K} per_tensor={per_tensor}", flush=True)
+    sd = wl.seed_for(4, M + N + K)
+    W, X, dY = wl.make_weight(N, K, 0.02, sd), wl.make_activation(M, K, sd), wl.make_grad(M, N, sd)
+    packed, alpha, beta = bl.bitlinear_pack_weights(dev(W))
+    codes, gamma, rowsum, _ = bl.bitlinear_quant_act(dev(X), per_tensor=per_tensor)
+    sign = oracle.unpack_canonical(
+        bl.bitlinear_packed_to_canonical(packed, N, K).cpu().numpy().view(np.uint32), K)
+    ref = oracle.backward_ste(dY, codes.cpu().numpy(), gamma.cpu().numpy(), sign, float(beta.cpu()[0]), per_tensor)
+    uncut = None
+    for splits in (1, 3):
+        tuning(f"bwd_splits={splits}")
+        got = [t.cpu().numpy().astype(np.float64)
+               for t in bl.bitlinear_backward_ste(dev(dY), codes, gamma, packed, beta, per_tensor)]
+        for g, r in zip(got, ref):
+            close(g, r)
+        for g, u in zip(got, uncut or got):
+            assert np.linalg.norm(g - u) <= 1e-5 * np.linalg.norm(u)
+        uncut = got

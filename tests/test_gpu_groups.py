@@ -108,8 +108,9 @@ def _check_forward(bl, M, K, N, gn, gk, per_tensor, seed):
 @pytest.mark.parametrize("gn,gk", GROUPS)
 @pytest.mark.parametrize("M", [8, 24, 48, 100])
 def test_grouped_forward(bl, M, gn, gk):
-    """One batch size for each of the four GEMM kernels (up to 16, 17-32, 33-64 tokens, large
-    tiles), per-token gamma."""
+    """One batch size for each of the four ranges of the batch (up to 16, 17-32, 33-64 tokens and, above
+    that, the small tiles, with K-groups as slices), per-token gamma.  The kernels for large layers have
+    tests of their own below."""
     K, N = 2048, 512
     print(f"grouped forward M={M} K={K} N={N} gn={gn} gk={gk}", flush=True)
     _check_forward(bl, M, K, N, gn, gk, False, 300 + gn * 10 + gk)
@@ -149,17 +150,39 @@ def test_grouped_forward_group_placement(bl, tuning, M, K, N, gn, gk):
     assert np.array_equal(y0, y1)
 
 
-@pytest.mark.parametrize("M,Kg,N,gn,gk,grid", [(130, 32, 272, 1, 5, 2), (300, 64, 528, 3, 8, 2),
-                                               (257, 96, 512, 1, 3, 1), (300, 160, 272, 1, 4, 3),
-                                               (129, 512, 288, 2, 2, 2), (200, 544, 520, 1, 4, 2),
-                                               (512, 576, 1024, 8, 2, 8), (150, 1120, 256, 1, 3, 1)])
-def test_grouped_forward_large_batch_stream(bl, tuning, M, Kg, N, gn, gk, grid):
-    """More than 64 tokens: the operand stream runs on across the ends of groups and tiles.  Groups of
-    one stage, two stages, one chunk, one stage past a chunk, an odd number of chunks and a K that ends
-    inside a stage, on few enough workgroups that each walks several tiles."""
-    print(f"grouped stream M={M} Kg={Kg} N={N} gn={gn} gk={gk} grid={grid}", flush=True)
-    tuning(f"prefill_grid={grid}")
-    _check_forward(bl, M, Kg * gk, N, gn, gk, False, 700 + M)
+def force_group_stream(bl, tuning, op, M, K, N, gn, gk, grid, per_tensor):
+    """Above 64 tokens: the kernel that walks a tile's K-groups, on `grid` workgroups, instead of the K-groups
+    as slices.  Seen in the workspace: the call then asks for no slices."""
+    tuning("prefill_tile=3")
+    sliced = bl.workspace_bytes_grouped(op, M, N, K, gn, gk, per_tensor)
+    tuning(f"prefill_tile=1,prefill_grid={grid}")
+    assert bl.workspace_bytes_grouped(op, M, N, K, gn, gk, per_tensor) == sliced - gk * M * N * 4
+
+
+# groups of one stage, two stages, one chunk, one stage past a chunk, an odd number of chunks and a K that
+# ends inside a stage, on few enough workgroups that each walks several tiles
+GROUP_STREAM_SHAPES = [(130, 32, 272, 1, 5, 2), (300, 64, 528, 3, 8, 2), (257, 96, 512, 1, 3, 1),
+                       (300, 160, 272, 1, 4, 3), (129, 512, 288, 2, 2, 2), (200, 544, 520, 1, 4, 2),
+                       (512, 576, 1024, 8, 2, 8), (150, 1120, 256, 1, 3, 1)]
+
+
+@pytest.mark.parametrize("per_tensor", [False, True])
+@pytest.mark.parametrize("M,Kg,N,gn,gk,grid", GROUP_STREAM_SHAPES)
+def test_grouped_forward_large_batch_stream(bl, tuning, M, Kg, N, gn, gk, grid, per_tensor):
+    """More than 64 tokens: the operand stream runs on across the ends of groups and tiles."""
+    print(f"grouped stream M={M} Kg={Kg} N={N} gn={gn} gk={gk} grid={grid} per_tensor={per_tensor}", flush=True)
+    force_group_stream(bl, tuning, bl.OP_FORWARD, M, Kg * gk, N, gn, gk, grid, per_tensor)
+    _check_forward(bl, M, Kg * gk, N, gn, gk, per_tensor, 700 + M)
+
+
+@pytest.mark.parametrize("per_tensor", [False, True])
+@pytest.mark.parametrize("tile", [1, 2])
+def test_grouped_forward_column_groups_large_tiles(bl, tuning, tile, per_tensor):
+    """The large tiles with a beta per column group (one K-group), several tiles per workgroup."""
+    M, K, N, gn = 300, 544, 528, 3
+    print(f"column groups M={M} K={K} N={N} gn={gn} tile={tile} per_tensor={per_tensor}", flush=True)
+    tuning(f"prefill_tile={tile},prefill_grid=2")
+    _check_forward(bl, M, K, N, gn, 1, per_tensor, 750)
 
 
 @pytest.mark.parametrize("M,Kg,N,gn,gk", [(65, 96, 272, 1, 5), (200, 544, 528, 3, 4), (130, 2080, 37, 1, 2)])

@@ -8,6 +8,7 @@ import torch
 
 import oracle
 import workloads as wl
+from test_gpu_groups import GROUP_STREAM_SHAPES, force_group_stream
 
 pytestmark = pytest.mark.gpu
 f32 = np.float32
@@ -124,14 +125,7 @@ def test_quant_nonneg_per_tensor_and_groups(bl, M, K, gk, mode, per_tensor):
         assert np.array_equal(rs_gpu[:, g], q_ref.astype(np.int32).sum(axis=1))
 
 
-@pytest.mark.parametrize("M", [1, 8, 24, 48, 100])
-@pytest.mark.parametrize("gn,gk,per_tensor", [(1, 1, True), (1, 4, False), (2, 2, True), (4, 4, False),
-                                              (8, 1, True), (1, 8, True)])
-def test_forward_nonneg_per_tensor_and_groups(bl, M, gn, gk, per_tensor):
-    """Every GEMM kernel's epilogue (1, up to 16, 17-32, 33-64 tokens, large tiles) with a
-    per-tensor eta and with eta_g per K-group."""
-    K, N = 2048, 512
-    print(f"forward nonneg M={M} gn={gn} gk={gk} per_tensor={per_tensor}", flush=True)
+def _check_forward(bl, M, K, N, gn, gk, per_tensor):
     X = wl.make_activation(M, K, seed=wl.seed_for(5, 700 + M + gn + gk), outlier_p=0.005, outlier_mul=8.0)
     X += f32(0.25)
     X[:, K // 2:] *= f32(1.7)
@@ -158,6 +152,36 @@ def test_forward_nonneg_per_tensor_and_groups(bl, M, gn, gk, per_tensor):
     assert err <= 1e-5, err
     if gk == 1:
         assert np.array_equal(y, given["y"])
+
+
+@pytest.mark.parametrize("M", [1, 8, 24, 48, 100])
+@pytest.mark.parametrize("gn,gk,per_tensor", [(1, 1, True), (1, 4, False), (2, 2, True), (4, 4, False),
+                                              (8, 1, True), (1, 8, True)])
+def test_forward_nonneg_per_tensor_and_groups(bl, M, gn, gk, per_tensor):
+    """The epilogues of the kernels that these batches take (1, up to 16, 17-32, 33-64 tokens and, above
+    that, the small tiles and the fold of K-groups) with a per-tensor eta and with eta_g per K-group."""
+    K, N = 2048, 512
+    print(f"forward nonneg M={M} gn={gn} gk={gk} per_tensor={per_tensor}", flush=True)
+    _check_forward(bl, M, K, N, gn, gk, per_tensor)
+
+
+@pytest.mark.parametrize("per_tensor", [False, True])
+@pytest.mark.parametrize("M,Kg,N,gn,gk,grid", GROUP_STREAM_SHAPES)
+def test_forward_nonneg_large_batch_stream(bl, tuning, M, Kg, N, gn, gk, grid, per_tensor):
+    """More than 64 tokens, the kernel that walks a tile's K-groups: eta_g and the row sums of the weights in
+    its scales, across the ends of groups and tiles."""
+    print(f"nonneg stream M={M} Kg={Kg} N={N} gn={gn} gk={gk} grid={grid} per_tensor={per_tensor}", flush=True)
+    force_group_stream(bl, tuning, bl.OP_FORWARD_NONNEG, M, Kg * gk, N, gn, gk, grid, per_tensor)
+    _check_forward(bl, M, Kg * gk, N, gn, gk, per_tensor)
+
+
+@pytest.mark.parametrize("per_tensor", [False, True])
+@pytest.mark.parametrize("tile", [1, 2])
+def test_forward_nonneg_column_groups_large_tiles(bl, tuning, tile, per_tensor):
+    M, K, N, gn = 300, 544, 528, 3
+    print(f"nonneg column groups M={M} K={K} N={N} gn={gn} tile={tile} per_tensor={per_tensor}", flush=True)
+    tuning(f"prefill_tile={tile},prefill_grid=2")
+    _check_forward(bl, M, K, N, gn, 1, per_tensor)
 
 
 def test_nonneg_errors(bl):
