@@ -76,7 +76,10 @@ size_t bitlinear_packed_bytes(int64_t N, int64_t K, unsigned flags);
  * is the one operation whose need may be 0 for a valid shape (its workspace is optional and
  * only some shapes have a use for it).  The sizes for the forward calls at M > 32, for
  * BL_OP_BACKWARD and for BL_OP_LN_BACKWARD include an optional part (partial sums of shapes that are
- * cut along the reduction to fill the chip): without it the same call runs uncut. */
+ * cut along the reduction to fill the chip): without it the same call runs uncut.  The forward's
+ * results are the same bits either way.  The fp32 sums of the backward and the fp64 sums of the
+ * LayerNorm backward's dgain and dbias are then added in another order, so their last bits depend
+ * on whether the optional part was brought (and, for the backward, on the bwd_* switches). */
 size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int granularity,
                                  unsigned flags);
 
@@ -114,9 +117,9 @@ int bitlinear_quant_act(const float* X, int64_t M, int64_t K, const float* ln_ga
  *   rowsum  in  int32 [M] as produced by bitlinear_quant_act (required)
  *   Y       out fp32 [M,N] (int32 accumulators with BL_FLAG_OUT_ACC_I32)
  *   workspace   optional (may be NULL): with bitlinear_workspace_bytes(BL_OP_MATMUL, ...) bytes
- *               the library may split K over more workgroups (M <= 16: K > 16384; 16 < M <= 64:
- *               whenever N alone supplies too few workgroups for the chip) and fold the int32
- *               slices afterwards; the result is the same bit for bit */
+ *               the library may split K over more workgroups (M <= 16: K > 16384; M > 16:
+ *               where the output alone supplies too few workgroups for the chip) and fold the
+ *               int32 slices afterwards; the result is the same bit for bit */
 int bitlinear_matmul(const int8_t* codes, const float* gamma, const int32_t* rowsum, int64_t M,
                      int64_t K, const void* packed, int64_t N, const float* beta, int granularity,
                      unsigned flags, float* Y, void* workspace, size_t workspace_bytes,
@@ -304,18 +307,19 @@ int bitlinear_layernorm_backward(const float* dXhat, const float* X, int64_t M, 
 int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int threads, uint32_t* sink,
                          void* stream);
 
-/* host: launch-time switches for tests and benchmarks; results never depend on them.
+/* host: launch-time switches for tests and benchmarks; results do not depend on them but for the
+ * order of floating-point sums (the quantiser's fp64 statistics, the backward's fp32 products).
  * spec = "name=value,name=value" (integers); every switch not named returns to 0 = the
  * library decides; NULL or "" resets all.  Process-wide, not thread-safe, takes effect on the
  * next call.  Unless this function has been called, the environment variable
- * BITLINEAR_TUNING (same syntax) is read once, at the first call that launches.
+ * BITLINEAR_TUNING (same syntax) is read once, at the first call that launches or asks for a size.
  *   decode_nofuse=1     bitlinear_forward at M = 1: quantiser and GEMM as two launches
  *   decode_nosplit=1    M <= 16: never split K over workgroups
  *   decode_tiles=t      M <= 16: weight tiles per workgroup
  *   mid_nosplit=1       16 < M <= 64: never split K over workgroups
  *   mid_split_tiles=c   16 < M <= 64: 512-element chunks of K per slice
  *   mid_only=1          16 < M <= 32: skip the register-streaming kernel
- *   mid_kernel=1        32 < M <= 64: the LDS-tiled kernel with the K split inside the workgroup
+ *   mid_kernel=1        accepted, without effect
  *   prefill_tile=1|2|3|4   M > 64: 128 x 256, 256 x 256, 128 x 128 or 64 x 128 output tiles
  *   prefill_split=n     M > 64, tiles 3 and 4: slices of K
  *   prefill_grid=g      M > 64: workgroups of the persistent kernel
@@ -325,7 +329,7 @@ int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int thre
  *   quant_wpr=w         quantiser: waves per row (1, 2, 4, 8)
  *   bwd_ring=1|2        backward, dW: 256 x 256 or 128 x 128 output tiles
  *   bwd_grid=g, bwd_rowmajor=1   backward ring kernel: workgroups, plain tile order
- *   bwd_splits=n        backward ring kernels: slices of the reduction
+ *   bwd_splits=n        backward ring kernels: slices of the reduction (256 x 256 tiles)
  * Returns BL_OK, or BL_ERR_UNSUPPORTED (unknown name or bad syntax; nothing changes). */
 int bitlinear_set_tuning(const char* spec);
 

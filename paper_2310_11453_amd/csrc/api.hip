@@ -129,7 +129,8 @@ QuantWs quant_ws_grouped(int64_t M, int groups_k, int granularity) {
     return quant_ws(M * groups_k, granularity);
 }
 // Up to 64 tokens all K-groups run in one launch, each group's int32 sums in a slice of its own
-// that a second kernel dequantises and adds (Eq. 13-14).
+// that a second kernel dequantises and adds (Eq. 13-14).  Above that slices are optional
+// (group_split_bytes).
 size_t group_slices_bytes(int64_t M, int64_t N, int groups_k) {
     return groups_k > 1 && M <= 64 ? (size_t)groups_k * (size_t)M * (size_t)N * 4 : 0;
 }
@@ -574,16 +575,17 @@ static int forward_grouped_impl(const float* X, int64_t M, int64_t K, const void
                                     flags & BL_FLAG_SKIP_LN, nonneg, codes, gamma, eta, rowsum,
                                     nullptr, base + ws.quant, workspace_bytes - ws.quant, stream);
     if (rc != BL_OK) return rc;
-    // one GEMM per K-group, each dequantised with its own beta_g * gamma_g (and shifted by its own
-    // eta_g, Eq. 14) and added (Eq. 13-14)
+    // each K-group is dequantised with its own beta_g * gamma_g (and shifted by its own eta_g, Eq. 14)
+    // and added (Eq. 13-14)
     const int64_t Kg = K / groups_k;
     const size_t blob_dwords = tiles_bytes(N, Kg) / 4;
     const bool per_tensor = granularity == BL_GAMMA_PER_TENSOR;
     if (groups_k > 1) {
-        // One launch for all K-groups.  Up to 64 tokens every K-group is a slice of the launch,
-        // and the fold that follows dequantises each group's sums with its own scales and adds
-        // them in the order 0, 1, ...; above that the large-tile kernel walks a tile's groups
-        // itself and keeps the fp32 sum in registers.  Y is written once.
+        // One launch for all K-groups.  Up to 64 tokens, and above where tiles are few and the
+        // workspace has the room, every K-group is a slice of the launch, and the fold that
+        // follows dequantises each group's sums with its own scales and adds them in the order
+        // 0, 1, ...; else gemm_group_kernel walks a tile's groups itself and keeps the fp32 sum in
+        // registers.  Y is written once.
         GemmArgs a{};
         a.codes = codes; a.gamma = gamma; a.rowsum = rowsum;
         a.M = M; a.K = Kg; a.N = N;

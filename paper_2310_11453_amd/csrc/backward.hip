@@ -205,8 +205,10 @@ struct RingSlices {
 // Why four waves (T = 256).  With eight waves of 128 x 64 LDS sets the pace: every operand row is read by the
 // waves that share it, 96 KiB of reads and 32 KiB of DMA writes a stage, at 128 bytes a cycle as
 // long as the MFMAs of the stage take (1024 cycles).  128 x 128 waves read 64 KiB.  There is one wave
-// per SIMD then: 256 accumulator registers (the compiler keeps them in the AGPR half of the file),
-// and only the wave's own instruction stream hides latency.  A half-step (16 r) is 16 MFMAs, 512
+// per SIMD then: 256 accumulator registers (the compiler keeps them in the AGPR half of the file, and the
+// other 256 are full: the epilogue's column indices, 8 registers sliced and 2 unsliced, are spilled ahead of the
+// tiles and read back behind the last stage, outside the counted waits), and only the wave's own
+// instruction stream hides latency.  A half-step (16 r) is 16 MFMAs, 512
 // cycles; the reads of the next one's operands go out behind its first four, the DMA of a stage (its
 // addresses and issue would idle the pipe) behind each row of four.  M = 8192, 4096 -> 16384: dW
 // 900 us, 946 us with eight waves; without any DMA in the loop (timing only) it takes 740 us.
@@ -813,7 +815,7 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
 // 128 x 128 tile has a quarter of it and two workgroups per CU, but reads every operand twice as often:
 //   a round of up to one workgroup per CU    1.0 + 0.25 us per stage
 //   a round of two per CU                    2.5 + 0.38
-// The whole call (with the operand copies), 256 against 128: 8 x 512 x 256 18.2 / 10.5 us, 64 x 2048 x 2048
+// The whole call (M x N x K, with the operand copies), 256 against 128: 8 x 512 x 256 18.2 / 10.5 us, 64 x 2048 x 2048
 // 21.3 / 13.2, 1000 x 2048 x 2048 44.6 / 25.7, 8 x 4096 x 16384 74.6 / 64.4; 4096 x 512 x 256 (16 slices of
 // 256 tiles) 33.9 / 44.5.  Past one full round the second read of the operands decides: beyond 32 stages (16 from two full
 // rounds on, 12 from nine), or with a B operand well beyond an XCD's 4 MB of L2, the large tile it is (512 x 7168 x

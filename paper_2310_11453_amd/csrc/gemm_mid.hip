@@ -1,12 +1,14 @@
 // 1-bit x 8-bit GEMM + dequantisation for a few dozen tokens (16 < M <= 64), Eq. 7 and Eq. 11
 // of arXiv 2310.11453: the batch between the weight-streaming kernel (M <= 16) and the large
-// MFMA tiles.  One 64 x 128 output tile per workgroup gives at most a few hundred workgroups,
-// each with a long serial walk over K, so the walk is split INSIDE the workgroup: eight waves,
-// four K-groups of two waves (64 x 64 each), each group streaming its own quarter of K through
-// its own LDS ring (codes and packed bits by global_load_lds, bits expanded in registers,
-// hand-counted vmcnt), all groups meeting at the same barriers.  The integer accumulators of
-// the four groups are added through LDS at the end and one epilogue dequantises: the same
-// integers as any other split of K, so the result does not depend on it.
+// MFMA tiles; and, walking row tiles of 64 or 128 tokens, for larger batches where the large
+// tiles leave CUs idle (gemm_prefill.hip chooses).  One 64 x 128 output tile per workgroup gives
+// at most a few hundred workgroups, each with a long serial walk over K, so the walk is split
+// INSIDE the workgroup: eight waves, four K-groups of two waves (64 x 64 each; with 128 rows two
+// K-groups of four waves), each group streaming its own part of K through its own LDS ring (codes
+// and packed bits by global_load_lds, bits expanded in registers, hand-counted vmcnt), all groups
+// meeting at the same barriers.  The integer accumulators of the groups are added through LDS at
+// the end and one epilogue dequantises: the same integers as any other split of K, so the result
+// does not depend on it.
 //
 // What bounds this shape is the stream of activation codes from L2 into LDS: every workgroup
 // reads all M x K of them (64 bytes per k against 16 bytes of packed weights), 100 MB per launch
@@ -438,8 +440,9 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
 // Small batches (16 < M <= 64) leave most of the chip idle when N supplies few 64 x 128 tiles: K is
 // then split over workgroups too, and splitk_reduce folds the slices.
 
-// 512-chunks of K per slice in the workspace that a call must bring (0 = no slices): about one work
-// item per CU, sums no larger than the packed weights.  256 CUs are assumed.
+// 512-chunks of K per slice of the workspace that a call must bring (0 = no slices): about one work
+// item per CU, sums no larger than the packed weights.  256 CUs are assumed.  This is only the size that
+// calls have always been required to bring; the launch decides by mid_slice_tiles what it makes of it.
 int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
     if (M <= 16 || M > 64) return 0;
     if (const int64_t per = tuning().mid_split_tiles) return per > 0 && per < tiles_k(K) ? per : 0;
@@ -456,8 +459,8 @@ int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
 
 // What the launch takes of ws_bytes: the slices of least cost, in us: a round of items 5 + 4.1 c (c
 // 512-chunks per K-group of the workgroup), the slices 4 and their sums written and read at 5 TB/s.  64 x
-// 7168 x 7168: 16.3 us in 4 slices, 18.9 in 3 (what the rule above gives); 48 x 16384 x 4096: 14.0 us
-// without, 17.7 in 2.  Returns 512-chunks per slice, 0 = no slices.
+// 7168 x 7168 (M x K x N, GEMM and fold): 15.9 us in 4 slices, 17.0 in 3 (what the rule above gives), 16.7 without;
+// 48 x 4096 x 16384: 11.5 us without, 16.4 in 2; 48 x 16384 x 4096: 16.0 in the 8 taken, 19.5 in 2, 26.5 without.  Returns 512-chunks per slice, 0 = no slices.
 static int64_t mid_slice_tiles(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
     const int64_t TK = tiles_k(K), tiles = (N + mid::BN - 1) / mid::BN;
     if (const int64_t per = tuning().mid_split_tiles)

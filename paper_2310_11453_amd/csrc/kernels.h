@@ -24,7 +24,7 @@ struct Tuning {
     int bwd_rowmajor;      // backward ring kernel: plain row-major tile order
     int bwd_splits;        // backward ring kernels: slices of the reduction
     int group_slices;      // grouped layer, M <= 64: every K-group a slice of the grid (work item) of its own
-    int mid_kernel;        // 32 < M <= 64: 1 = LDS-tiled kernel with the in-workgroup K split
+    int mid_kernel;        // accepted, without effect
 };
 const Tuning& tuning();
 
@@ -98,9 +98,10 @@ struct GemmArgs {
     // and a second kernel folds them and applies the epilogue.
     int64_t split_k;
     int32_t* split_ws;
-    size_t split_ws_bytes;  // what the caller offers; too small or nullptr: no split
-    // All K-groups of a grouped layer (Eq. 13-15) in one launch, M <= 64 (set by the caller
-    // together with split_ws of kgroups * M * N * 4 bytes): slice g of the launch is K-group g.
+    size_t split_ws_bytes;  // what the caller offers; as many slices as fit, too small or nullptr: no split
+    // All K-groups of a grouped layer (Eq. 13-15) in one launch (set by the caller; up to 64 tokens
+    // together with split_ws of kgroups * M * N * 4 bytes, above that it is optional): slice g of the launch is
+    // K-group g, or, without slices, gemm_group_kernel walks a tile's groups and adds them in registers.
     // codes, packed, K, gamma, rowsum, beta, eta, wsum describe group 0; group g reads codes + g * K,
     // packed + g * group_packed dwords, and the fold applies gamma[.. + g], rowsum[.. + g], beta[.. + g],
     // eta[.. + g], wsum[g * N + n] to its partial sums and adds the groups in the order 0, 1, ...
