@@ -458,9 +458,10 @@ int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
 }
 
 // What the launch takes of ws_bytes: the slices of least cost, in us: a round of items 5 + 4.1 c (c
-// 512-chunks per K-group of the workgroup), the slices 4 and their sums written and read at 5 TB/s.  64 x
-// 7168 x 7168 (M x K x N, GEMM and fold): 15.9 us in 4 slices, 17.0 in 3 (what the rule above gives), 16.7 without;
-// 48 x 4096 x 16384: 11.5 us without, 16.4 in 2; 48 x 16384 x 4096: 16.0 in the 8 taken, 19.5 in 2, 26.5 without.  Returns 512-chunks per slice, 0 = no slices.
+// 512-chunks per K-group of the workgroup), the slices 4 and their sums written and read at 5 TB/s.
+// GEMM and fold, M x K x N: 64 x 7168 x 7168 15.9 us in 4 slices, 17.0 in 3 (what the rule above
+// gives), 16.7 without; 48 x 4096 x 16384 11.5 us without, 16.4 in 2; 48 x 16384 x 4096 16.0 in the 8
+// taken, 19.5 in 2, 26.5 without.  Returns 512-chunks per slice, 0 = no slices.
 static int64_t mid_slice_tiles(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
     const int64_t TK = tiles_k(K), tiles = (N + mid::BN - 1) / mid::BN;
     if (const int64_t per = tuning().mid_split_tiles)
