@@ -126,17 +126,10 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
                     smf[1][wave] = mx;
                 }
                 __syncthreads();
-                s = smd[0][rw * WPR];
-                q = smd[1][rw * WPR];
-                mn = smf[0][rw * WPR];
-                mx = smf[1][rw * WPR];
-#pragma unroll
-                for (int i = 1; i < WPR; ++i) {
-                    s += smd[0][rw * WPR + i];
-                    q += smd[1][rw * WPR + i];
-                    mn = fminf(mn, smf[0][rw * WPR + i]);
-                    mx = fmaxf(mx, smf[1][rw * WPR + i]);
-                }
+                s = fold_slots<WPR>(smd[0] + rw * WPR, OpSum{});
+                q = fold_slots<WPR>(smd[1] + rw * WPR, OpSum{});
+                mn = fold_slots<WPR>(smf[0] + rw * WPR, OpMin{});
+                mx = fold_slots<WPR>(smf[1] + rw * WPR, OpMax{});
             }
             mu = s / (double)a.K;
             const double qs = q;
@@ -265,34 +258,14 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
     const float scale = 128.0f / gamma;
     int rs = 0;
     uint32_t* __restrict__ c4 = reinterpret_cast<uint32_t*>(a.codes + row * a.K);
-    // code = clamp(rne(x^ * scale), -128, 127), one fp32 operation per step.  The integral
-    // float plus 128 lies in 0..255 and goes straight into its byte of the output word;
-    // flipping the top bit of each byte turns that offset form into two's complement.
-    auto code_word_nonneg = [&](const float4& x) {  // Eq. 6: shift by eta, clamp to [0, 127]
-        const float q0 = fminf(fmaxf(rintf((x.x - lo) * scale), 0.f), 127.f);
-        const float q1 = fminf(fmaxf(rintf((x.y - lo) * scale), 0.f), 127.f);
-        const float q2 = fminf(fmaxf(rintf((x.z - lo) * scale), 0.f), 127.f);
-        const float q3 = fminf(fmaxf(rintf((x.w - lo) * scale), 0.f), 127.f);
-        uint32_t wd = __builtin_amdgcn_cvt_pk_u8_f32(q0, 0, 0u);
-        wd = __builtin_amdgcn_cvt_pk_u8_f32(q1, 1, wd);
-        wd = __builtin_amdgcn_cvt_pk_u8_f32(q2, 2, wd);
-        return __builtin_amdgcn_cvt_pk_u8_f32(q3, 3, wd);
-    };
-    auto code_word = [&](const float4& x) {
-        const float q0 = fminf(fmaxf(rintf(x.x * scale), -128.f), 127.f) + 128.f;
-        const float q1 = fminf(fmaxf(rintf(x.y * scale), -128.f), 127.f) + 128.f;
-        const float q2 = fminf(fmaxf(rintf(x.z * scale), -128.f), 127.f) + 128.f;
-        const float q3 = fminf(fmaxf(rintf(x.w * scale), -128.f), 127.f) + 128.f;
-        uint32_t wd = __builtin_amdgcn_cvt_pk_u8_f32(q0, 0, 0u);
-        wd = __builtin_amdgcn_cvt_pk_u8_f32(q1, 1, wd);
-        wd = __builtin_amdgcn_cvt_pk_u8_f32(q2, 2, wd);
-        wd = __builtin_amdgcn_cvt_pk_u8_f32(q3, 3, wd);
-        return wd ^ 0x80808080u;
-    };
+    // code = clamp(rne(x^ * scale), -128, 127) (Eq. 6: shifted by eta and clamped to [0, 127])
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int idx = t + j * RT;
-        const uint32_t wd = a.nonneg ? code_word_nonneg(v[j]) : code_word(v[j]);
+        const float4 x = v[j];
+        const uint32_t wd = a.nonneg ? code_word<0>((x.x - lo) * scale, (x.y - lo) * scale,
+                                                    (x.z - lo) * scale, (x.w - lo) * scale)
+                                     : code_word<-128>(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
         if (idx < K4) {
             rs = __builtin_amdgcn_sdot4((int)wd, 0x01010101, rs, false);  // sum of the four codes
             if (live) c4[idx] = wd;
@@ -465,26 +438,9 @@ __global__ __launch_bounds__(512) void ln_quant_long(QuantArgs a) {
     for (int64_t idx = t; idx < K4; idx += T) {
         const float4 x = xhat_at(idx);
         if (d4) d4[idx] = x;
-        uint32_t wd;
-        if (a.nonneg) {  // Eq. 6: shift by eta, clamp to [0, 127]
-            const float q0 = fminf(fmaxf(rintf((x.x - lo) * scale), 0.f), 127.f);
-            const float q1 = fminf(fmaxf(rintf((x.y - lo) * scale), 0.f), 127.f);
-            const float q2 = fminf(fmaxf(rintf((x.z - lo) * scale), 0.f), 127.f);
-            const float q3 = fminf(fmaxf(rintf((x.w - lo) * scale), 0.f), 127.f);
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q0, 0, 0u);
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q1, 1, wd);
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q2, 2, wd);
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q3, 3, wd);
-        } else {
-            const float q0 = fminf(fmaxf(rintf(x.x * scale), -128.f), 127.f) + 128.f;
-            const float q1 = fminf(fmaxf(rintf(x.y * scale), -128.f), 127.f) + 128.f;
-            const float q2 = fminf(fmaxf(rintf(x.z * scale), -128.f), 127.f) + 128.f;
-            const float q3 = fminf(fmaxf(rintf(x.w * scale), -128.f), 127.f) + 128.f;
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q0, 0, 0u);
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q1, 1, wd);
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q2, 2, wd);
-            wd = __builtin_amdgcn_cvt_pk_u8_f32(q3, 3, wd) ^ 0x80808080u;
-        }
+        const uint32_t wd = a.nonneg ? code_word<0>((x.x - lo) * scale, (x.y - lo) * scale,
+                                                    (x.z - lo) * scale, (x.w - lo) * scale)
+                                     : code_word<-128>(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
         rs = __builtin_amdgcn_sdot4((int)wd, 0x01010101, rs, false);
         c4[idx] = wd;
     }
