@@ -514,110 +514,84 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
     }
 }
 
-// Fold of a grouped layer's slices (Eq. 13-15), four consecutive columns per thread (N % 4 == 0):
-// each K-group's sums are dequantised with its own beta_g gamma_g / 128 (and shifted by its own
-// eta_g, Eq. 14) and the groups are added in the order 0, 1, ...
-__global__ __launch_bounds__(256) void groups_reduce4(GemmArgs a) {
-    const int64_t N4 = a.N >> 2;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= a.M * N4) return;
-    const int64_t m = idx / N4, n = (idx % N4) * 4;
-    const int G = a.kgroups;
-    uint32_t bg[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-        bg[c] = ((uint32_t)(n + c) / (uint32_t)a.beta_rows) * (uint32_t)a.beta_stride;
-    v4f y = {0.f, 0.f, 0.f, 0.f};
-    for (int g = 0; g < G; ++g) {
-        const v4i part = *reinterpret_cast<const v4i*>(a.split_ws + ((int64_t)g * a.M + m) * a.N + n);
-        const int rs = a.rowsum[m * a.gstride + g];
-        const float gm = a.gamma[a.per_tensor ? g : m * a.gstride + g];
-        const float eta = a.eta ? a.eta[a.per_tensor ? g : m * a.gstride + g] : 0.f;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float beta = a.beta[bg[c] + g];
-            float yg = (float)(part[c] - rs) * ((beta * gm) / 128.0f);
-            if (a.eta) yg = yg + (beta * eta) * (float)a.wsum[(int64_t)g * a.N + n + c];
-            y[c] = g ? yg + y[c] : yg;
-        }
-    }
-    *reinterpret_cast<v4f*>(a.Y + m * a.N + n) = y;
-}
-
-// Second step of a K split: Y[m,n] = epilogue(sum_s partial[s][m][n] - rowsum[m]).
+// Second step of a K split: Y[m,n] = epilogue(sum_s partial[s][m][n] - rowsum[m]).  V consecutive columns a
+// thread (V = 4: N % 4 == 0, split_ws and Y 16-byte aligned), rows m = blockIdx.y, + gridDim.y, ...
+// With the slices of a small batch this launch is latency: four slices are read at a time, and nothing
+// that can be a scalar (the row, and beta while the matrix has one) costs a vector instruction; read one
+// after another behind a 64-bit division the launch took 4.0 us at 8 x 7168 and 4.8 at 333 x 2048.
+template <int V>
 __global__ __launch_bounds__(256) void splitk_reduce(GemmArgs a, int splits) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= a.M * a.N) return;
-    const int64_t m = idx / a.N, n = idx % a.N;
-    if (a.kgroups > 1) {
-        // slices are K-groups (Eq. 13-15): each is dequantised with its own beta_g gamma_g / 128
-        // (and shifted by its own eta_g, Eq. 14); the groups are added in the order 0, 1, ...
-        const int G = a.kgroups;
-        const uint32_t bg = ((uint32_t)n / (uint32_t)a.beta_rows) * (uint32_t)a.beta_stride;
-        float y = 0.f;
-        for (int g = 0; g < G; ++g) {
-            const int pm = a.split_ws[((int64_t)g * a.M + m) * a.N + n] - a.rowsum[m * a.gstride + g];
-            const float beta = a.beta[bg + g];
-            const float gm = a.gamma[a.per_tensor ? g : m * a.gstride + g];
-            float yg = (float)pm * ((beta * gm) / 128.0f);
-            if (a.eta)
-                yg = yg + (beta * a.eta[a.per_tensor ? g : m * a.gstride + g]) *
-                              (float)a.wsum[(int64_t)g * a.N + n];
-            y = g ? yg + y : yg;
-        }
-        a.Y[idx] = y;
-        return;
-    }
-    int sum = 0;
-    for (int sp = 0; sp < splits; ++sp) sum += a.split_ws[((int64_t)sp * a.M + m) * a.N + n];
-    const int pm = sum - a.rowsum[m * a.gstride];
-    if (a.out_acc) {
-        reinterpret_cast<int*>(a.Y)[idx] = pm;
-        return;
-    }
-    const float beta = a.beta[((uint32_t)n / (uint32_t)a.beta_rows) * a.beta_stride];
-    const float gm = a.per_tensor ? a.gamma[0] : a.gamma[m * a.gstride];
-    float y = (float)pm * ((beta * gm) / 128.0f);
-    if (a.eta) y = y + (beta * a.eta[a.per_tensor ? 0 : m * a.gstride]) * (float)a.wsum[n];
-    if (a.accumulate) y += a.Y[idx];
-    a.Y[idx] = y;
-}
-
-// The same for four consecutive columns per thread (N % 4 == 0; split_ws and Y 16-byte aligned), a row
-// of the grid's y per token.  Bound by the slices' bytes, which mostly come out of the Infinity Cache;
-// below 2^20 outputs by latency, and four times the threads of the kernel above are the better use of
-// the chip (64 x 7168: 1 % of a layer).
-__global__ __launch_bounds__(256) void splitk_reduce4(GemmArgs a, int splits) {
-    const int64_t n = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    typedef int vi __attribute__((ext_vector_type(V)));
+    typedef float vf __attribute__((ext_vector_type(V)));
+    const int64_t n = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
     if (n >= a.N) return;
-    float beta[4], wsum[4];
+    float beta[V], wsum[V];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        beta[c] = a.beta[((uint32_t)(n + c) / (uint32_t)a.beta_rows) * a.beta_stride];
+    for (int c = 0; c < V; ++c) {
+        beta[c] = a.beta_rows >= a.N ? a.beta[0] : a.beta[((uint32_t)(n + c) / (uint32_t)a.beta_rows) * a.beta_stride];
         wsum[c] = a.eta ? (float)a.wsum[n + c] : 0.f;
     }
     const int64_t stride = a.M * a.N;
     for (int64_t m = blockIdx.y; m < a.M; m += gridDim.y) {
         const int32_t* p = a.split_ws + m * a.N + n;
-        v4i sum = *reinterpret_cast<const v4i*>(p);
-#pragma unroll 4
-        for (int sp = 1; sp < splits; ++sp) sum += *reinterpret_cast<const v4i*>(p + sp * stride);
-        const v4i pm = sum - a.rowsum[m * a.gstride];
+        vi sum = {};
+        for (int sp = 0; sp < splits; sp += 4) {
+            vi q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                q[i] = *reinterpret_cast<const vi*>(p + (sp + i < splits ? sp + i : splits - 1) * stride);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum += q[i] & -(int)(sp + i < splits);
+        }
+        const vi pm = sum - a.rowsum[m * a.gstride];
         if (a.out_acc) {
-            *reinterpret_cast<v4i*>(reinterpret_cast<int*>(a.Y) + m * a.N + n) = pm;
+            *reinterpret_cast<vi*>(reinterpret_cast<int*>(a.Y) + m * a.N + n) = pm;
             continue;
         }
         const float gm = a.gamma[a.per_tensor ? 0 : m * a.gstride];
         const float eta = a.eta ? a.eta[a.per_tensor ? 0 : m * a.gstride] : 0.f;
-        v4f* const o = reinterpret_cast<v4f*>(a.Y + m * a.N + n);
-        v4f y;
+        vf* const o = reinterpret_cast<vf*>(a.Y + m * a.N + n);
+        vf y;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < V; ++c) {
             y[c] = (float)pm[c] * ((beta[c] * gm) / 128.0f);
             if (a.eta) y[c] = y[c] + (beta[c] * eta) * wsum[c];
         }
         if (a.accumulate) y += *o;
         *o = y;
+    }
+}
+
+// The same where the slices are the K-groups of a layer (Eq. 13-15): each is dequantised with its own
+// beta_g gamma_g / 128 (and shifted by its own eta_g, Eq. 14) and the groups are added in the order 0, 1, ...
+template <int V>
+__global__ __launch_bounds__(256) void groups_reduce(GemmArgs a) {
+    typedef int vi __attribute__((ext_vector_type(V)));
+    typedef float vf __attribute__((ext_vector_type(V)));
+    const int64_t n = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
+    if (n >= a.N) return;
+    const int G = a.kgroups;
+    uint32_t bg[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+        bg[c] = ((uint32_t)(n + c) / (uint32_t)a.beta_rows) * (uint32_t)a.beta_stride;
+    for (int64_t m = blockIdx.y; m < a.M; m += gridDim.y) {
+        vf y = {};
+#pragma unroll 4
+        for (int g = 0; g < G; ++g) {
+            const vi part = *reinterpret_cast<const vi*>(a.split_ws + ((int64_t)g * a.M + m) * a.N + n);
+            const int rs = a.rowsum[m * a.gstride + g];
+            const float gm = a.gamma[a.per_tensor ? g : m * a.gstride + g];
+            const float eta = a.eta ? a.eta[a.per_tensor ? g : m * a.gstride + g] : 0.f;
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                const float beta = a.beta[bg[c] + g];
+                float yg = (float)(part[c] - rs) * ((beta * gm) / 128.0f);
+                if (a.eta) yg = yg + (beta * eta) * (float)a.wsum[(int64_t)g * a.N + n + c];
+                y[c] = g ? yg + y[c] : yg;
+            }
+        }
+        *reinterpret_cast<vf*>(a.Y + m * a.N + n) = y;
     }
 }
 
@@ -716,18 +690,23 @@ hipError_t launch_read_probe(const void* src, size_t bytes, int workgroups, int 
     return hipGetLastError();
 }
 
+// Four columns a thread from 2^18 outputs on, below that one, which reaches more CUs (us of the layer, one
+// column / four: 8 x 28672 -> 7168 19.1 / 19.3, 24 x 16384 -> 4096 19.05 / 19.2, 64 x 7168 -> 7168 22.9 / 22.8,
+// 333 x 8192 -> 2048 29.9 / 28.8).
 void launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s) {
-    if (a.kgroups > 1 && (a.N & 3) == 0 && ((uintptr_t)a.Y & 15) == 0) {
-        groups_reduce4<<<(unsigned)((a.M * (a.N >> 2) + 255) / 256), 256, 0, s>>>(a);
-        return;
+    const bool vec = a.M * a.N >= (1 << 18) && (a.N & 3) == 0 &&
+                     (((uintptr_t)a.Y | (uintptr_t)a.split_ws) & 15) == 0;
+    const int64_t cols = vec ? a.N / 4 : a.N;
+    const int threads = vec && a.M * a.N < (1 << 20) ? 64 : 256;
+    const dim3 grid((unsigned)((cols + threads - 1) / threads), (unsigned)(a.M < 65535 ? a.M : 65535));
+    if (a.kgroups > 1) {
+        if (vec) groups_reduce<4><<<grid, threads, 0, s>>>(a);
+        else groups_reduce<1><<<grid, threads, 0, s>>>(a);
+    } else if (vec) {
+        splitk_reduce<4><<<grid, threads, 0, s>>>(a, splits);
+    } else {
+        splitk_reduce<1><<<grid, threads, 0, s>>>(a, splits);
     }
-    if (a.kgroups <= 1 && a.M * a.N >= (1 << 20) && (a.N & 3) == 0 &&
-        (((uintptr_t)a.Y | (uintptr_t)a.split_ws) & 15) == 0) {
-        const dim3 grid((unsigned)((a.N / 4 + 255) / 256), (unsigned)(a.M < 65535 ? a.M : 65535));
-        splitk_reduce4<<<grid, 256, 0, s>>>(a, splits);
-        return;
-    }
-    splitk_reduce<<<(unsigned)((a.M * a.N + 255) / 256), 256, 0, s>>>(a, splits);
 }
 
 hipError_t launch_gemm_decode(const GemmArgs& a_in, hipStream_t s) {

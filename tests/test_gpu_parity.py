@@ -605,3 +605,27 @@ def test_forward_long_k_split_matches_single_pass(bl, M, K, N):
     sign = oracle.binarize(W, host(alpha)[0])
     ref = oracle.matmul_i32_sampled(host(codes), sign, rows, cols)
     assert np.array_equal(host(acc_split)[rows, cols], ref)
+
+
+# The fold of the slices: slice counts on either side of the four it reads at a time, and outputs on either
+# side of the 2^18 from which a thread takes four columns (or one, where N is no multiple of four).
+@pytest.mark.parametrize("M,K,N,spec", [(16, 40960, 1032, None), (3, 65536, 18, None),
+                                        (130, 4608, 2020, "prefill_tile=3,prefill_split=5"),
+                                        (130, 4608, 2021, "prefill_tile=3,prefill_split=9"),
+                                        (129, 4608, 2032, "prefill_tile=4,prefill_split=4")])
+def test_fold_of_slices(bl, tuning, M, K, N, spec):
+    print(f"fold M={M} K={K} N={N} {spec}", flush=True)
+    packed, _, beta = bl.bitlinear_pack_weights(dev(wl.make_weight(N, K, 0.02, seed=wl.seed_for(3, K + N))))
+    Xd = dev(wl.make_activation(M, K, seed=wl.seed_for(3, K + M)))
+    wsum = bl.bitlinear_weight_rowsums(packed, N, K)
+
+    def outputs():
+        return [bl.bitlinear_forward(Xd, packed, N, beta),
+                bl.bitlinear_forward(Xd, packed, N, beta, flags=bl.FLAG_OUT_ACC_I32),
+                bl.bitlinear_forward_nonneg(Xd, packed, N, beta, wsum)]
+
+    tuning(spec)
+    cut = outputs()
+    tuning("decode_nosplit=1" if spec is None else spec.split(",")[0] + ",prefill_split=1")
+    for y, ref in zip(cut, outputs()):
+        assert torch.equal(y, ref)
