@@ -76,7 +76,8 @@ size_t bitlinear_packed_bytes(int64_t N, int64_t K, unsigned flags);
  * is the one operation whose need may be 0 for a valid shape (its workspace is optional and
  * only some shapes have a use for it).  The sizes for the forward calls at M > 32, for
  * BL_OP_BACKWARD and for BL_OP_LN_BACKWARD include an optional part (partial sums of shapes that are
- * cut along the reduction to fill the chip): without it the same call runs uncut.  The forward's
+ * cut along the reduction to fill the chip): without it the same call runs uncut.  BL_OP_PACK's includes
+ * room (N * K / 128 bytes) that lets the call read W once instead of twice.  The forward's
  * results are the same bits either way.  The fp32 sums of the backward and the fp64 sums of the
  * LayerNorm backward's dgain and dbias are then added in another order, so their last bits depend
  * on whether the optional part was brought (and, for the backward, on the bwd_* switches). */

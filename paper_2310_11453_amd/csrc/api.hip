@@ -74,6 +74,17 @@ bool gran_ok(int g) { return g == BL_GAMMA_PER_TOKEN || g == BL_GAMMA_PER_TENSOR
 size_t tiles_bytes(int64_t rows, int64_t cols) { return (size_t)(tiles_n(rows) * tiles_k(cols)) * 1024; }
 
 // workspace layouts ------------------------------------------------------------
+// Weight prep: partial sums are `required`; with `full` bytes W is read once (launch_pack).  The blocks
+// of a grouped layer are packed one after another in the same bytes.
+struct PackWs {
+    size_t required, full;
+};
+PackWs pack_ws(int64_t N, int64_t K, int groups_n, int groups_k) {
+    PackWs w{};
+    w.required = align256((size_t)reduce_grid(N * K / 4) * 16);
+    w.full = std::max(w.required, align256(pack_scan_bytes(N / groups_n, K / groups_k)));
+    return w;
+}
 struct QuantWs {
     size_t rowstats, gmax, total;
 };
@@ -258,7 +269,7 @@ size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int gr
     switch (op) {
         case BL_OP_PACK:
             if (!shape_ok(N, K)) return 0;
-            return align256((size_t)reduce_grid(N * K / 4) * 16);
+            return pack_ws(N, K, 1, 1).full;
         case BL_OP_QUANT:
             if (M < 0 || M > kMaxDim || K <= 0 || K % 32) return 0;
             return quant_ws(M, granularity).total;
@@ -289,11 +300,10 @@ int bitlinear_pack_weights(const float* W, int64_t N, int64_t K, unsigned flags,
     if (!shape_ok(N, K)) return BL_ERR_SHAPE;
     if (flags & ~BL_FLAG_BETA_CENTERED) return BL_ERR_UNSUPPORTED;
     if (!W || !packed || !alpha || !beta) return BL_ERR_NULL;
-    const size_t need = bitlinear_workspace_bytes(BL_OP_PACK, 0, N, K, 0, flags);
-    if (!workspace || workspace_bytes < need) return BL_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < pack_ws(N, K, 1, 1).required) return BL_ERR_WORKSPACE;
     return check_hip(launch_pack(W, N, K, K, (flags & BL_FLAG_BETA_CENTERED) != 0,
                                  (uint32_t*)packed, alpha, beta, (double*)workspace,
-                                 (hipStream_t)stream));
+                                 workspace_bytes, (hipStream_t)stream));
 }
 
 int bitlinear_packed_to_canonical(const void* packed, int64_t N, int64_t K, uint32_t* canonical,
@@ -441,7 +451,7 @@ size_t bitlinear_workspace_bytes_grouped(int op, int64_t M, int64_t N, int64_t K
     if (groups_status(N, K, groups_n, groups_k) != BL_OK) return 0;
     switch (op) {
         case BL_OP_PACK:
-            return align256((size_t)reduce_grid(N * K / 4) * 16);
+            return pack_ws(N, K, groups_n, groups_k).full;
         case BL_OP_QUANT:
             return quant_ws_grouped(M, groups_k, granularity).total;
         case BL_OP_FORWARD:
@@ -463,8 +473,8 @@ int bitlinear_pack_weights_grouped(const float* W, int64_t N, int64_t K, int gro
     if (int st = groups_status(N, K, groups_n, groups_k)) return st;
     if (flags & ~BL_FLAG_BETA_CENTERED) return BL_ERR_UNSUPPORTED;
     if (!W || !packed || !alpha || !beta) return BL_ERR_NULL;
-    const size_t need = bitlinear_workspace_bytes_grouped(BL_OP_PACK, 0, N, K, groups_n, groups_k, 0);
-    if (!workspace || workspace_bytes < need) return BL_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < pack_ws(N, K, groups_n, groups_k).required)
+        return BL_ERR_WORKSPACE;
     const int64_t Ng = N / groups_n, Kg = K / groups_k;
     const size_t blob_dwords = tiles_bytes(N, Kg) / 4;
     for (int gk = 0; gk < groups_k; ++gk)
@@ -476,7 +486,8 @@ int bitlinear_pack_weights_grouped(const float* W, int64_t N, int64_t K, int gro
             const int idx = gn * groups_k + gk;
             hipError_t e = launch_pack(W + gn * Ng * K + gk * Kg, Ng, Kg, K,
                                        (flags & BL_FLAG_BETA_CENTERED) != 0, dst, alpha + idx,
-                                       beta + idx, (double*)workspace, (hipStream_t)stream);
+                                       beta + idx, (double*)workspace, workspace_bytes,
+                                       (hipStream_t)stream);
             if (e != hipSuccess) return BL_ERR_HIP;
         }
     return BL_OK;

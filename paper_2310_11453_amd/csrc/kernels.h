@@ -32,8 +32,11 @@ const Tuning& tuning();
 // A block of `rows` x `cols` weights inside a matrix whose rows are `ldw` floats apart
 // (ldw == cols: the whole matrix).  `packed` receives tiles_n(rows) x tiles_k(cols) tiles.
 int reduce_grid(int64_t count4);
+// partials: at least reduce_grid(rows * cols / 4) * 16 bytes; with pack_scan_bytes W is read once.
+size_t pack_scan_bytes(int64_t rows, int64_t cols);
 hipError_t launch_pack(const float* W, int64_t rows, int64_t cols, int64_t ldw, bool beta_centered,
-                       uint32_t* packed, float* alpha, float* beta, double* partials, hipStream_t s);
+                       uint32_t* packed, float* alpha, float* beta, double* partials,
+                       size_t partials_bytes, hipStream_t s);
 // canonical words of the block go to canonical[n * ldc + kw], ldc in words
 hipError_t launch_weight_rowsums(const uint32_t* packed, int64_t N, int64_t K, int32_t* wsum,
                                  hipStream_t s);

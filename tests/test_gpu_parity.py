@@ -66,6 +66,31 @@ def test_pack_deterministic(bl):
     assert torch.equal(p1, p2) and torch.equal(a1, a2) and torch.equal(b1, b2)
 
 
+@pytest.mark.parametrize("N,K", [(1, 32), (17, 544), (40, 992), (300, 4128), (4100, 2048)])
+def test_pack_weights_near_alpha(bl, N, K):
+    """W is read once and only the rows of a tile with a weight within |alpha| of zero are packed again: zeros
+    of either sign, weights at +-alpha and next to it, rows without any.  With the workspace that only holds
+    the sums, the same bits by the two readings."""
+    print(f"pack near alpha N={N} K={K}", flush=True)
+    W = wl.make_weight(N, K, 0.02, seed=wl.seed_for(0, 3 * N + K))
+    W[np.abs(W) < 1e-4] = 1e-4
+    W[0, :2] = [0.0, -0.0]
+    for _ in range(3):  # plants weights at the alpha that the matrix then has, or very nearly so
+        a, _ = oracle.weight_stats(W)
+        W[-1, 4:8] = [a, -a, np.nextafter(a, f32(1)), np.nextafter(a, f32(-1))]
+        W[N // 2, K - 1] = a
+    a, b = oracle.weight_stats(W)
+    words = oracle.pack_canonical(oracle.binarize(W, a))
+    sums_only = -(-16 * min(1024, max(1, -(-(N * K // 4) // 2048))) // 256) * 256
+    full = bl.workspace_bytes(bl.OP_PACK, 0, N, K)
+    assert full >= sums_only
+    for size in (full, sums_only):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        packed, alpha, beta = bl.bitlinear_pack_weights(dev(W), workspace=ws)
+        assert host(alpha)[0] == a and host(beta)[0] == b
+        assert np.array_equal(host(bl.bitlinear_packed_to_canonical(packed, N, K)).view(np.uint32), words)
+
+
 # ------------------------------------------------------------------ activations (Eq. 12, 4, 5)
 QUANT_SHAPES = [(8, 256), (1, 2048), (5, 96), (3, 544), (16, 8192), (33, 4096), (7, 7168),
                 (2, 28672), (4, 16384), (64, 1024),
