@@ -531,7 +531,7 @@ __global__ __launch_bounds__(256) void splitk_reduce(GemmArgs a, int splits) {
         beta[c] = a.beta_rows >= a.N ? a.beta[0] : a.beta[((uint32_t)(n + c) / (uint32_t)a.beta_rows) * a.beta_stride];
         wsum[c] = a.eta ? (float)a.wsum[n + c] : 0.f;
     }
-    const int64_t stride = a.M * a.N;
+    const int64_t stride = a.M * a.N, ldy = a.ldy ? a.ldy : a.N;
     for (int64_t m = blockIdx.y; m < a.M; m += gridDim.y) {
         const int32_t* p = a.split_ws + m * a.N + n;
         vi sum = {};
@@ -545,12 +545,12 @@ __global__ __launch_bounds__(256) void splitk_reduce(GemmArgs a, int splits) {
         }
         const vi pm = sum - a.rowsum[m * a.gstride];
         if (a.out_acc) {
-            *reinterpret_cast<vi*>(reinterpret_cast<int*>(a.Y) + m * a.N + n) = pm;
+            *reinterpret_cast<vi*>(reinterpret_cast<int*>(a.Y) + m * ldy + n) = pm;
             continue;
         }
         const float gm = a.gamma[a.per_tensor ? 0 : m * a.gstride];
         const float eta = a.eta ? a.eta[a.per_tensor ? 0 : m * a.gstride] : 0.f;
-        vf* const o = reinterpret_cast<vf*>(a.Y + m * a.N + n);
+        vf* const o = reinterpret_cast<vf*>(a.Y + m * ldy + n);
         vf y;
 #pragma unroll
         for (int c = 0; c < V; ++c) {
@@ -694,7 +694,7 @@ hipError_t launch_read_probe(const void* src, size_t bytes, int workgroups, int 
 // column / four: 8 x 28672 -> 7168 19.1 / 19.3, 24 x 16384 -> 4096 19.05 / 19.2, 64 x 7168 -> 7168 22.9 / 22.8,
 // 333 x 8192 -> 2048 29.9 / 28.8).
 void launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s) {
-    const bool vec = a.M * a.N >= (1 << 18) && (a.N & 3) == 0 &&
+    const bool vec = a.M * a.N >= (1 << 18) && ((a.N | a.ldy) & 3) == 0 &&
                      (((uintptr_t)a.Y | (uintptr_t)a.split_ws) & 15) == 0;
     const int64_t cols = vec ? a.N / 4 : a.N;
     const int threads = vec && a.M * a.N < (1 << 20) ? 64 : 256;

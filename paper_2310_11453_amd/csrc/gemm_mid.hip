@@ -399,7 +399,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         const int* p0 = red + (er + ER * h) * BN + (threadIdx.x & 31) * 4;
         v4i s4 = *reinterpret_cast<const v4i*>(p0);
         if constexpr (REG == 2) s4 += *reinterpret_cast<const v4i*>(p0 + BM * BN);
-        const bool vec = (N & 3) == 0;  // then nq + 3 < N and the row starts 16-byte aligned
+        const bool vec = ((N | a.ldy) & 3) == 0;  // then nq + 3 < N and the row starts 16-byte aligned
         if (to_slices) {
             int* o = a.split_ws + ((int64_t)sp * M + m) * N + nq;
             const v4i t = s4 * 2;
@@ -411,14 +411,14 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         }
         const v4i pm = s4 * 2 - e_rs[h];
         if (a.out_acc) {
-            int* o = reinterpret_cast<int*>(a.Y) + m * N + nq;
+            int* o = reinterpret_cast<int*>(a.Y) + m * a.ldy + nq;
             if (vec) *reinterpret_cast<v4i*>(o) = pm;
             else
                 for (int c = 0; c < 4; ++c)
                     if (nq + c < N) o[c] = pm[c];
             continue;
         }
-        float* o = a.Y + m * N + nq;
+        float* o = a.Y + m * a.ldy + nq;
         const float sc = e_gamma[h] * 0.0078125f;  // gamma / 128, exact
         v4f y;
 #pragma unroll
@@ -494,6 +494,7 @@ size_t mid_split_bytes(int64_t M, int64_t N, int64_t K) {
 hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
     GemmArgs a = a_in;
     a.split_k = 0;
+    if (!a.ldy) a.ldy = a.N;
     if (a.M > 64 || a.K >= ((int64_t)1 << 22) || a.ldq >= ((int64_t)1 << 22))
         return hipErrorInvalidValue;
     const int grid_n = (int)((a.N + mid::BN - 1) / mid::BN);

@@ -454,7 +454,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                         float y = GEN ? (float)pm * (bcol[s] * sc4[rr]) : (float)pm * sc4[rr];
                         if (special) {  // uniform
                             if (a.out_acc) {
-                                reinterpret_cast<int*>(a.Y)[m * a.N + n] = pm;
+                                reinterpret_cast<int*>(a.Y)[m * a.ldy + n] = pm;
                                 continue;
                             }
                             if (GEN && a.eta) {  // Eq. 6: + (beta * eta_m) * sum_k s[n,k]
@@ -462,11 +462,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                                     (uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi + 8 * rq + 4 * g2 + rr]);
                                 y = y + (bcol[s] * e) * wcol[s];
                             }
-                            if (GEN && a.accumulate) y += a.Y[m * a.N + n];  // a later K-group
+                            if (GEN && a.accumulate) y += a.Y[m * a.ldy + n];  // a later K-group
                         }
                         // streaming store: the output is not read again soon, and keeping it out
                         // of L2 leaves the codes and bits there (3-4 % of the kernel)
-                        __builtin_nontemporal_store(y, &a.Y[m * a.N + n]);
+                        __builtin_nontemporal_store(y, &a.Y[m * a.ldy + n]);
                     }
                 }
             }
@@ -831,23 +831,21 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 // ones win: 333 x 2048 x 2048 9.8 us (64 x 128) against 19.4 us (128 x 256), 200 x 4096 x 16384
 // 22.1 (128 x 128) against 30, 333 x 8192 x 2048 18.5 (64 x 128 in 2 slices) against 50; 1000 x 2048
 // x 8192 stays with 128 x 256: 21.3 against 28.4.
-struct PrefillPlan {
+struct TilePlan {
     int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
     int64_t per;  // 512-chunks of K per slice (3 and 4)
+    double us;
 };
-static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+static double large_round_us(int tile, int64_t nst) { return tile == 1 ? 8.0 + 0.37 * nst : 14.0 + 0.62 * nst; }
+static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
     const int64_t cus = num_cus(), TK = tiles_k(K), nst = (K + kStageK - 1) / kStageK;
     const int force = tuning().prefill_tile;
     const int64_t force_n = tuning().prefill_split > 0 ? tuning().prefill_split : 0;
     // a forced tile stays that tile, unsliced, where its slices have no room; forced slices are
     // as many as the chunks of K give in equal parts
-    PrefillPlan best{force >= 1 && force <= 4 ? force : 2, TK};
-    double best_us = 1e30;
+    TilePlan best{force >= 1 && force <= 4 ? force : 2, TK, 1e30};
     auto offer = [&](int tile, int64_t per, double us) {
-        if (us < best_us) {
-            best_us = us;
-            best = PrefillPlan{tile, per};
-        }
+        if (us < best.us) best = TilePlan{tile, per, us};
     };
     for (int tile = 1; tile <= 4; ++tile) {
         if (force && tile != force) continue;
@@ -855,7 +853,7 @@ static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes
         const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         if (tile <= 2) {
             const int64_t rounds = (tiles + cus - 1) / cus;
-            offer(tile, TK, (double)rounds * (tile == 1 ? 8.0 + 0.37 * nst : 14.0 + 0.62 * nst));
+            offer(tile, TK, (double)rounds * large_round_us(tile, nst));
             continue;
         }
         const int kg = tile == 3 ? 2 : 4;
@@ -870,12 +868,43 @@ static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes
     }
     return best;
 }
+
+// The last round of large tiles may be nearly empty (4096 x 7168 x 21504: 1344 tiles are 5.25 rounds of 256
+// CUs, run as 6).  Then the columns that fill the rounds before it keep the large tiles, and the rest
+// is a launch of its own with whatever costs least there, 3 us between the two.  us of the layer, one launch /
+// two: 4096 x 7168 x 21504 553 / 528 (a quarter-filled round runs at a higher clock, or it would be more),
+// 300 x 4096 x 24000 57.9 / 52.3, 2048 x 3072 x 12288 88.6 / 85.7, 4096 x 2048 x 6144 70.7 / 69.6.
+struct PrefillPlan {
+    TilePlan first, rest;
+    int64_t cut;  // columns of the first launch, a multiple of 256; 0: one launch
+};
+static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool may_cut) {
+    PrefillPlan best{tile_plan(M, N, K, ws_bytes), {}, 0};
+    if (!may_cut || tuning().prefill_tile || tuning().prefill_split || tuning().prefill_grid) return best;
+    const int64_t cus = num_cus(), nst = (K + kStageK - 1) / kStageK;
+    double best_us = best.first.us;
+    for (int tile = 1; tile <= 2; ++tile) {
+        const int64_t bm = tile == 1 ? 128 : 256;
+        const int64_t grid_m = (M + bm - 1) / bm, grid_n = (N + 255) / 256;
+        const int64_t rounds = grid_m * grid_n / cus;
+        const int64_t cols = rounds * cus / grid_m;  // columns of tiles that the full rounds hold
+        if (cols < 1 || cols >= grid_n) continue;
+        const TilePlan rest = tile_plan(M, N - cols * 256, K, ws_bytes);
+        const double first_us = (double)rounds * large_round_us(tile, nst), us = first_us + 3.0 + rest.us;
+        if (us < best_us) {
+            best_us = us;
+            best = PrefillPlan{{tile, tiles_k(K), first_us}, rest, cols * 256};
+        }
+    }
+    return best;
+}
+static int64_t plan_slices(const TilePlan& p, int64_t K) { return (tiles_k(K) + p.per - 1) / p.per; }
 // Room for the K-slices of the plan: optional, without it K is not split (or in fewer slices).
 size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K) {
     if (M <= 64) return mid_split_bytes(M, N, K);
-    const PrefillPlan p = prefill_plan(M, N, K, (size_t)1 << 40);
-    const int64_t n = (tiles_k(K) + p.per - 1) / p.per;
-    return n > 1 ? (size_t)n * M * N * 4 : 0;
+    const PrefillPlan p = prefill_plan(M, N, K, (size_t)1 << 40, true);
+    const int64_t n = plan_slices(p.cut ? p.rest : p.first, K);
+    return n > 1 ? (size_t)n * M * (N - p.cut) * 4 : 0;
 }
 
 // The same choice for a grouped layer (K = a group's): 0 = the stream kernel, 3 or 4 = the tiles of
@@ -915,6 +944,7 @@ size_t group_split_bytes(int64_t M, int64_t N, int64_t K, int groups) {
 hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
     GemmArgs a = a_in;
     a.split_k = 0;  // set here only
+    if (!a.ldy) a.ldy = a.N;
     if (a.K >= ((int64_t)1 << 22) || a.ldq >= ((int64_t)1 << 22)) return hipErrorInvalidValue;
     if (a.M <= 64) {  // up to 32 tokens: gemm_stream.hip where it takes the shape; else gemm_mid.hip
         if (!tuning().mid_only && a_in.kgroups <= 1 && launch_gemm_stream(a_in, s)) return hipGetLastError();
@@ -931,11 +961,23 @@ hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
         else gemm_group_kernel<false><<<(unsigned)grid, 512, 0, s>>>(a, grid_m, grid_n);
         return hipGetLastError();
     }
-    const PrefillPlan p = prefill_plan(a.M, a.N, a.K, a.split_ws ? a.split_ws_bytes : 0);
-    if (p.tile >= 3) return launch_gemm_mid_tiles(a, p.tile == 3 ? 128 : 64, p.per, s);
-    if (p.tile == 1) launch_tile<128, 256, 2, 4, 8>(a, s);
-    else launch_tile<256, 256, 2, 4, 8>(a, s);
-    return hipGetLastError();
+    // (columns in groups with a beta of their own are not cut)
+    const PrefillPlan p = prefill_plan(a.M, a.N, a.K, a.split_ws ? a.split_ws_bytes : 0, a.beta_rows >= a.N);
+    auto launch = [&](const GemmArgs& b, const TilePlan& t) {
+        if (t.tile >= 3) return launch_gemm_mid_tiles(b, t.tile == 3 ? 128 : 64, t.per, s);
+        if (t.tile == 1) launch_tile<128, 256, 2, 4, 8>(b, s);
+        else launch_tile<256, 256, 2, 4, 8>(b, s);
+        return hipGetLastError();
+    };
+    if (!p.cut) return launch(a, p.first);
+    GemmArgs b = a;
+    a.N = a.beta_rows = p.cut;
+    b.N = b.beta_rows = b.N - p.cut;
+    b.Y += p.cut;
+    b.packed += tile_dword_offset(p.cut / kTileN, 0, b.tk_pitch ? b.tk_pitch : tiles_k(b.K));
+    if (b.wsum) b.wsum += p.cut;
+    if (const hipError_t e = launch(a, p.first); e != hipSuccess) return e;
+    return launch(b, p.rest);
 }
 
 }  // namespace bl

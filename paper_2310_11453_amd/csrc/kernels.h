@@ -85,6 +85,7 @@ struct GemmArgs {
     bool out_acc;
     float* Y;
     // Group quantisation (Eq. 13-15); plain layer: ldq = K, gstride = 1, beta_rows = N.
+    int64_t ldy;          // floats between consecutive rows of Y (0: N); more than N: a range of columns
     int64_t ldq;          // bytes between consecutive rows of codes (>= K: a K-slice of wider rows)
     int64_t gstride;      // gamma[m * gstride], rowsum[m * gstride] belong to token m
     int64_t beta_rows;    // output columns n per beta group (a multiple of 16, or N)

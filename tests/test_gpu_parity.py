@@ -654,3 +654,25 @@ def test_fold_of_slices(bl, tuning, M, K, N, spec):
     tuning("decode_nosplit=1" if spec is None else spec.split(",")[0] + ",prefill_split=1")
     for y, ref in zip(cut, outputs()):
         assert torch.equal(y, ref)
+
+
+# Large layers whose last round of tiles is nearly empty run as two launches over ranges of columns (the rest
+# by small tiles, or by 128 x 256 ones with a ragged K): the bits of one launch, in every form of the epilogue.
+@pytest.mark.parametrize("M,K,N", [(2050, 2048, 8333), (4100, 1536, 4610), (1030, 2080, 16650)])
+def test_forward_in_two_ranges_of_columns(bl, tuning, M, K, N):
+    print(f"two ranges M={M} K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    packed, _, beta = bl.bitlinear_pack_weights(torch.randn(N, K, device="cuda", generator=g))
+    X = torch.randn(M, K, device="cuda", generator=g)
+    wsum = bl.bitlinear_weight_rowsums(packed, N, K)
+
+    def outputs():
+        return [bl.bitlinear_forward(X, packed, N, beta),
+                bl.bitlinear_forward(X, packed, N, beta, per_tensor=True),
+                bl.bitlinear_forward(X, packed, N, beta, flags=bl.FLAG_OUT_ACC_I32),
+                bl.bitlinear_forward_nonneg(X, packed, N, beta, wsum)]
+
+    two = outputs()
+    tuning("prefill_tile=2")
+    for y, ref in zip(two, outputs()):
+        assert torch.equal(y, ref)
