@@ -14,10 +14,14 @@
 //    chunk each lane copies the 16-byte groups of its own columns to registers (16 bytes
 //    cover 16 k in each of the eight 64-wide sub-blocks of the chunk) and expands them
 //    right before use, never as bytes in LDS:
-//        b = (w >> i) & 0x01010101           four {0,1} bytes, two VALU operations
+//        b = (w << (7 - i)) & 0x80808080     four {0,-128} bytes, two VALU operations
 //    amortised over the WTM/32 MFMAs that reuse the operand.  The MFMA accumulates
-//    sum_k q b; the epilogue restores sum_k q s = 2 sum_k q b - sum_k q with the row sums
-//    of the codes that the quantiser already produced.
+//    -128 sum_k q b (K <= 65536: below 2^30); the epilogue restores sum_k q s = 2 sum_k q b - sum_k q
+//    with the row sums of the codes that the quantiser already produced.
+//  * Which operand is which, and the value a set bit has, cost power, and at large batches power is
+//    what the clock is made of: a register-resident loop over these operands reaches 4.65 POP/s with the
+//    codes as the first operand and {0,-128} weights, 4.4 with {0,1}, 3.8 with +-1 or with the
+//    weights as the first operand.
 //  * A 128 x 64 wave tile keeps LDS traffic (one 1 KiB operand read per two MFMAs) and
 //    expansion cost (16 VALU per 8 MFMAs) well below the MFMA time.
 //  * Eight waves share a 256 x 256 (or 128 x 256) block, one block per CU.  The L2 -> LDS
@@ -254,12 +258,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
 
     v16i acc[MI][NI];
     v4i bw[NI][2];  // packed bits of the current chunk
-    // bit plane i of half h as {0,1} bytes; the epilogue turns sum_k q b into sum_k q (2b - 1)
+    // bit plane i of half h as {0,-128} bytes; the epilogue turns -128 sum_k q b into sum_k q (2b - 1)
     auto expand = [&](v4i (&b)[NI], int h, int i) {
 #pragma unroll
         for (int s = 0; s < NI; ++s)
 #pragma unroll
-            for (int d = 0; d < 4; ++d) b[s][d] = (int)(((uint32_t)bw[s][h][d] >> i) & 0x01010101u);
+            for (int d = 0; d < 4; ++d) b[s][d] = (int)(((uint32_t)bw[s][h][d] << (7 - i)) & 0x80808080u);
     };
     v4i ax[MI], ay[MI], bx[NI], by[NI];
     // One half-step (32 k of a stage): acc += ac x b, MI * NI MFMAs, with the next half-step's
@@ -286,7 +290,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
 #pragma unroll
                 for (int e = 0; e < DW; ++e) {
                     const int idx = q * DW + e;  // 0 .. NI*4-1
-                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] >> i) & 0x01010101u);
+                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] << (7 - i)) & 0x80808080u);
                 }
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 2 * DW, 0);
@@ -413,7 +417,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
         }
 
         // ---- epilogue (Eq. 11): lane (j, g2) holds column n, rows 8*(r/4) + 4*g2 + r%4 ----
-        //   sum_k q s = 2 sum_k q b - sum_k q ;  y = that * (beta_n * gamma_m / 128)
+        //   sum_k q s = 2 sum_k q b - sum_k q, the accumulators holding -128 sum_k q b ;  y = that * (beta_n * gamma_m / 128)
         float bcol[NI];
 #pragma unroll
         for (int s = 0; s < NI; ++s)
@@ -448,7 +452,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                     for (int s = 0; s < NI; ++s) {
                         const int64_t n = n0 + wn * WTN + 32 * s + j;
                         if (n >= a.N) continue;
-                        const int pm = 2 * acc[mi][s][r] - rs4[rr];
+                        const int pm = -(acc[mi][s][r] >> 6) - rs4[rr];  // exact: a multiple of 128
                         // y = acc * ((beta * gamma) / 128)
                         // (GEN: sc4 holds gamma / 128, else the whole scale)
                         float y = GEN ? (float)pm * (bcol[s] * sc4[rr]) : (float)pm * sc4[rr];
@@ -662,7 +666,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const int idx = q * 2 + e;
-                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] >> i) & 0x01010101u);
+                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] << (7 - i)) & 0x80808080u);
                 }
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
@@ -720,7 +724,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
 #pragma unroll
     for (int s = 0; s < NI; ++s)
 #pragma unroll
-        for (int d = 0; d < 4; ++d) bx[s][d] = (int)((uint32_t)bw[s][0][d] & 0x01010101u);
+        for (int d = 0; d < 4; ++d) bx[s][d] = (int)(((uint32_t)bw[s][0][d] << 7) & 0x80808080u);
     clear();
 
     int fbuf = 0;  // the scales of the item being folded
@@ -757,7 +761,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
                     const float e = ETA ? lds_read_f32(eta_base + (32 * mi + 8 * rq + rr) * 4) : 0.f;
 #pragma unroll
                     for (int s = 0; s < NI; ++s) {
-                        float y = (float)(2 * acc[mi][s][r] - rs4[rr]) * (bcol[s] * sc);
+                        float y = (float)(-(acc[mi][s][r] >> 6) - rs4[rr]) * (bcol[s] * sc);
                         if constexpr (ETA) y = y + (bcol[s] * e) * wcol[s];
                         side[mi][s][r] = y + side[mi][s][r];
                     }
