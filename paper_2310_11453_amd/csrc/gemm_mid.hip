@@ -17,6 +17,12 @@
 // every line was requested twice, half of it each time, and the kernel ran at the L2's request
 // rate: 1.79 M requests of 128 bytes per launch for 128 MB of operands.)
 //
+// The walk is two thirds matrix time, at 1.9 GHz (the clock falls from 2.4 within it); the rest of a launch
+// of one or two chunks is what stands before and after, and is kept short: integer indices, one row or one
+// column of scales a thread, the groups' sums added from their registers' layout, rows stored by adding the
+// pitch.  us of the layer before / after that: 200 x 4096 x 16384 27.4 / 25.4, 333 x 2048 x 2048 15.4 / 14.0,
+// 333 x 2048 x 6144 19.9 / 17.8, 64 x 7168 x 28672 26.2 / 24.8, 64 x 7168 x 7168 22.5 / 21.7.
+//
 // A wave expands its weight bits to {0,1} operand bytes with two vector ALU operations per dword,
 // for an operand that only two MFMAs use.  That work sits between the MFMAs of the half-step
 // before (the compiler's scheduler is told so with sched_group_barrier), two half-steps ahead of
@@ -91,12 +97,10 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     constexpr int GT = GW * kWave;              // threads of a K-group
     constexpr int STAGE_BYTES = BM * STAGE_K;   // 8 or 16 KiB
     constexpr int NBW = (BN / 16) / GW;         // packed tiles per wave and chunk
-    constexpr int REG = KG / 2;                 // BM x BN int32 sums that meet in LDS
     static_assert(P == BM * (STAGE_K / 16) / GT && NBW * GW * 16 == BN, "tile shape");
-    // rings of the K-groups; after the walk the same bytes hold REG sums
+    // rings of the K-groups; after the walk the groups' sums meet in the same bytes
     __shared__ __attribute__((aligned(1024))) uint8_t smA[KG * NS * STAGE_BYTES];
     __shared__ __attribute__((aligned(1024))) uint8_t smB[KG * (BN / 16) * 1024];
-    static_assert(KG * NS * STAGE_BYTES >= REG * BM * BN * 4, "room for the reduction");
     static_assert(NS >= 4, "the wait bookkeeping below: a stage's codes are requested NS-1 >= 3 stages ahead");
 
     // wave-uniform values in scalar registers: the loop below branches on them
@@ -107,16 +111,17 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     const int64_t M = a.M, N = a.N;
     const int64_t TN = tiles_n(N);
     const int64_t TKp = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
-    int item = (int)blockIdx.x, tm = 0;
+    int tm = 0, tcol = (int)blockIdx.x, sp = (int)blockIdx.y;
     if constexpr (ROWS) {  // the host rounds the grid up to a multiple of 8
-        item = (item & 7) * (int)(gridDim.x >> 3) + (item >> 3);
-        if (item >= grid_m * grid_n * splits) return;  // uniform for the workgroup
-        tm = item % grid_m;
-        item /= grid_m;
+        const uint32_t item = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+        if (item >= (uint32_t)(grid_m * grid_n * splits)) return;  // uniform for the workgroup
+        const uint32_t rest = item / (uint32_t)grid_m;
+        tm = (int)(item - rest * grid_m);
+        sp = splits > 1 ? (int)(rest / (uint32_t)grid_n) : 0;
+        tcol = (int)rest - sp * grid_n;
     }
-    const int sp = item / grid_n;
     const int64_t m0 = ROWS ? (int64_t)tm * BM : 0;
-    const int64_t n0 = (int64_t)(item % grid_n) * BN;
+    const int64_t n0 = (int64_t)tcol * BN;
 
     // ---- this item's slice of K, then this group's chunks of it ----------------------------
     int64_t ki0 = 0, Ki = a.K;
@@ -130,48 +135,34 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         ki0 = (int64_t)sp * a.split_k;
         Ki = a.K - ki0 < a.split_k ? a.K - ki0 : a.split_k;
     }
-    const int64_t TKi = tiles_k(Ki);
+    const int TKi = (int)tiles_k(Ki);  // K < 2^22
     // gmode 2: the whole group (nothing for a group past the layer's last)
-    const int64_t c0 = gmode == 2 ? 0 : TKi * kg / KG;
-    const int64_t c1 = gmode == 2 ? (lgrp < a.kgroups ? TKi : 0) : TKi * (kg + 1) / KG;
-    const int64_t TK = c1 - c0;
-    const int64_t k0 = ki0 + c0 * kChunkK;
-    int64_t K = Ki - c0 * kChunkK;  // this group's K
+    const int c0 = gmode == 2 ? 0 : TKi * kg / KG;
+    const int c1 = gmode == 2 ? (lgrp < a.kgroups ? TKi : 0) : TKi * (kg + 1) / KG;
+    const int TK = c1 - c0;
+    const int64_t k0 = ki0 + (int64_t)c0 * kChunkK;
+    int K = (int)Ki - c0 * kChunkK;  // this group's K
     if (K > TK * kChunkK) K = TK * kChunkK;
     // Every group walks the same number of stages, whole chunks of the longest group; what lies
     // past a group's own K meets zero bits (padding of its last chunk, or a zero mask past its
     // last chunk), so it adds nothing.
-    int64_t TKmax = 0;
-#pragma unroll
-    for (int g = 0; g < KG; ++g) {
-        const int64_t d = TKi * (g + 1) / KG - TKi * g / KG;
-        TKmax = d > TKmax ? d : TKmax;
-    }
-    if (gmode == 2) TKmax = TKi;
-    const int nrun = (int)TKmax * SPC;
+    const int TKmax = gmode == 2 ? TKi : (TKi + KG - 1) / KG;
+    const int nrun = TKmax * SPC;
 
-    // ---- epilogue operands of this thread's outputs, requested now ---------------------------
-    // thread -> columns nq .. nq+3 of the tile, rows er + 16 h
-    constexpr int EH = BM * (BN / 4) / THREADS;  // 4 or 8
-    constexpr int ER = THREADS / (BN / 4);       // 16
-    const int er = (int)threadIdx.x >> 5;
-    const int64_t nq = n0 + (threadIdx.x & 31) * 4;
-    float e_gamma[EH], e_eta[EH];
-    int e_rs[EH];
-#pragma unroll
-    for (int h = 0; h < EH; ++h) {
-        const int64_t m = m0 + er + ER * h < M ? m0 + er + ER * h : M - 1;
-        e_gamma[h] = a.gamma[a.per_tensor ? 0 : m * a.gstride];
-        e_rs[h] = a.rowsum[m * a.gstride];
-        e_eta[h] = *(a.eta ? a.eta + (a.per_tensor ? 0 : m * a.gstride) : a.gamma);
-    }
-    float e_beta[4];
-    int e_ws[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int64_t n = nq + c < N ? nq + c : N - 1;
-        e_beta[c] = a.beta[((uint32_t)n / (uint32_t)a.beta_rows) * a.beta_stride];
-        e_ws[c] = *(a.eta ? a.wsum + n : a.rowsum);
+    // ---- epilogue operands, requested now: thread -> one row, or one column, of the tile ------
+    // (waves 0 .. BM/64 - 1 the rows, waves 4 and 5 the columns; nothing for sums that go to slices)
+    int e0 = 0, e1 = 0, e2 = 0;
+    if (!to_slices) {
+        if (w < BM / kWave) {
+            const int64_t r = m0 + (int)threadIdx.x, m = r < M ? r : M - 1, mg = a.per_tensor ? 0 : m * a.gstride;
+            e0 = __float_as_int(a.gamma[mg]);
+            e1 = a.rowsum[m * a.gstride];
+            if (a.eta) e2 = __float_as_int(a.eta[mg]);
+        } else if (w == 4 || w == 5) {
+            const int64_t c = n0 + (int)threadIdx.x - 4 * kWave, n = c < N ? c : N - 1;
+            e0 = __float_as_int(a.beta[a.beta_rows >= N ? 0 : (uint32_t)n / (uint32_t)a.beta_rows * a.beta_stride]);
+            if (a.eta) e1 = a.wsum[n];
+        }
     }
 
     // ---- DMA of this group.  A stage is BM rows of 128 bytes; thread -> four 16-byte pieces of
@@ -214,11 +205,11 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
 #pragma unroll
         for (int q = 0; q < P; ++q) issue_piece(st, q);
     };
-    auto issue_bits = [&](int64_t tk) {
+    auto issue_bits = [&](int tk) {
 #pragma unroll
         for (int q = 0; q < NBW; ++q)
             __builtin_amdgcn_global_load_lds(
-                (const void*)(bsrc[q] + tk * 256),
+                (const void*)(bsrc[q] + (int64_t)tk * 256),
                 (__attribute__((address_space(3))) void*)(ringB + (wi + q * GW) * 1024), 16, 0, 0);
     };
 
@@ -270,12 +261,12 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // every wave has read the current chunk's bits, one barrier earlier), so they are younger than
     // what the waits of stages 1 and 2 are for, and the wait of stage 3, which is for a group
     // requested after them, covers them: three stages for a trip to HBM, then they are read.
-    for (int64_t c = 0; c < TKmax; ++c) {
+    for (int c = 0; c < TKmax; ++c) {
         const bool bits_next = c + 1 < TK;
         static_for<0, 16>([&](auto uc) {
             constexpr int u = decltype(uc)::value;
             constexpr int s = u >> 2, hs = u & 3;
-            const int st = (int)c * SPC + s;
+            const int st = c * SPC + s;
             if constexpr (hs == 2) {  // mid-stage: stage st+1 becomes readable, stage st-1's buffer free
                 const bool ahead = st + NS - 1 < nrun;
                 if (!ahead) wait_vmcnt<0>();
@@ -338,103 +329,123 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     wait_vmcnt<0>();
     __syncthreads();  // every group is done with its ring
 
-    // ---- add the groups: lane (j, g2) of wave (wm, wn) holds columns 64*wn + 32*s + j, rows
-    // 64*wm + 32*mi + 8*(r/4) + 4*g2 + r%4; the upper half of the groups writes, the lower half
-    // adds theirs, then all threads read the REG sums ------------------------------------------
-    int* red = reinterpret_cast<int*>(smA);
-    auto red_at = [&](int region, int mi, int s2, int r) {
-        return red + region * (BM * BN) + (wm * 64 + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3)) * BN + wn * 64 +
-               32 * s2 + j;
+    // ---- add the groups.  Lane (j, g2) of wave (wm, wn) holds columns 64 wn + 32 s + j, rows 64 wm +
+    // 32 mi + 8 q + 4 g2 + 0..3 as pieces (mi, s, q) of four; the waves (wm, wn) of the KG groups hold sums
+    // of the same 64 x 64 outputs.  Group g finishes 16 / KG of the pieces: every wave leaves the
+    // others' in LDS as they lie in its registers (16 bytes a lane, no conflicts), and after one
+    // barrier reads its own from the other groups.  (Adding in the tile's layout, half of the waves after the
+    // other and then all of them reading it back, took 1.1 us of a 20 us launch and a barrier more.)
+    constexpr int OWN = 16 / KG;
+    v4i own[OWN];
+    int* const red = reinterpret_cast<int*>(smA);
+    // where group `from` of waves wi leaves piece i of group `to`
+    auto slot = [&](int from, int to, int i) {
+        const int rank = to < from ? to : to - 1;  // of the KG - 1 groups it writes to
+        return red + ((((wi * KG + from) * (KG - 1) + rank) * OWN + i) * kWave + l) * 4;
     };
-    if constexpr (BM == 64) if (gmode == 2) {  // four K-groups of the layer: each group's sums to its own slice
-        static_assert(NS * STAGE_BYTES >= BM * BN * 4, "room for the four groups' sums");
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) *red_at(kg, mi, s2, r) = acc[mi][s2][r];
-        __syncthreads();
-        const bool vec = (N & 3) == 0;
-#pragma unroll
-        for (int h = 0; h < BM * (BN / 4) / THREADS; ++h) {
-            const int64_t m = er + (THREADS / (BN / 4)) * h;
-            if (m >= M || nq >= N) continue;
-            for (int rg = 0; rg < KG && sp * KG + rg < a.kgroups; ++rg) {
-                const v4i t = *reinterpret_cast<const v4i*>(red + rg * (BM * BN) + (int)m * BN +
-                                                             (threadIdx.x & 31) * 4) * 2;
-                int* o = a.split_ws + ((int64_t)(sp * KG + rg) * M + m) * N + nq;
-                if (vec) *reinterpret_cast<v4i*>(o) = t;
-                else
-                    for (int c = 0; c < 4; ++c)
-                        if (nq + c < N) o[c] = t[c];
+    static_assert(GW * KG * (KG - 1) * OWN * kWave * 16 + 4096 <= KG * NS * STAGE_BYTES, "room beside the scales");
+    auto piece = [&](int q) {
+        const v16i& t = acc[q >> 3][(q >> 2) & 1];
+        const int r = (q & 3) * 4;
+        return (v4i){t[r], t[r + 1], t[r + 2], t[r + 3]};
+    };
+    int* const scales = red + GW * KG * (KG - 1) * OWN * kWave * 4;  // gamma, row sums, eta; beta, column sums
+    const bool add_groups = gmode != 2;
+    if (add_groups) {
+        static_for<0, KG>([&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            if (kg == g) {  // uniform for the wave
+                static_for<0, 16>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    if constexpr (q / OWN == g) own[q % OWN] = piece(q);
+                    else *reinterpret_cast<v4i*>(slot(g, q / OWN, q % OWN)) = piece(q);
+                });
+            }
+        });
+        if (!to_slices) {
+            if (w < BM / kWave) {
+                scales[threadIdx.x] = e0;
+                scales[BM + threadIdx.x] = e1;
+                scales[2 * BM + threadIdx.x] = e2;
+            } else if (w == 4 || w == 5) {
+                scales[3 * BM + threadIdx.x - 4 * kWave] = e0;
+                scales[3 * BM + BN + threadIdx.x - 4 * kWave] = e1;
             }
         }
+        __syncthreads();
+#pragma unroll
+        for (int d = 1; d < KG; ++d) {
+            const int from = (kg + d) % KG;
+#pragma unroll
+            for (int i = 0; i < OWN; ++i) own[i] += *reinterpret_cast<const v4i*>(slot(from, kg, i));
+        }
+    }
+
+    // ---- store: sum_k q s = 2 sum_k q b - sum_k q ; y = that * (beta gamma / 128) (Eq. 11) --------
+    // 32 consecutive columns of two rows an instruction, whole lines.  What a store costs here is the
+    // instructions around it (3 us a tile with a row's bounds, branches and 64-bit product at each): the rows
+    // are walked by adding the pitch, with a count of the valid ones where the tile is ragged.
+    const bool inside = m0 + BM <= M && n0 + BN <= N;  // uniform
+    const int prow = wm * 64 + 4 * g2, pcol = wn * 64 + j;  // of piece q: + 32 (q / 8) + 8 (q % 4), + 32 (q / 4 % 2)
+    auto store_sums = [&](const v4i& p, int q, int64_t grp) {
+        const int64_t m = m0 + prow + 32 * (q >> 3) + 8 * (q & 3), n = n0 + pcol + 32 * ((q >> 2) & 1);
+        int32_t* o = a.split_ws + (grp * M + m) * N + n;
+        const int rows = n < N ? (int)(M - m < 4 ? M - m : 4) : 0;
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr, o += N)
+            if (inside || rr < rows) *o = 2 * p[rr];
+    };
+    if (!add_groups) {  // each group's sums to its layer group's slice
+        if (lgrp < a.kgroups)
+            static_for<0, 16>([&](auto qc) {
+                store_sums(piece(decltype(qc)::value), decltype(qc)::value, lgrp);
+            });
         return;
     }
-    if (kg >= REG) {
+    if (to_slices) {
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) *red_at(kg - REG, mi, s2, r) = acc[mi][s2][r];
+        for (int i = 0; i < OWN; ++i) store_sums(own[i], kg * OWN + i, sp);
+        return;
     }
-    __syncthreads();
-    if (kg < REG) {
+    // kind 0: a tile inside the output; 1: a ragged one; 2: a ragged one or any, with the options below
+    auto store = [&](auto with_eta, auto kind) {
+        constexpr bool ETA = decltype(with_eta)::value;
+        constexpr int KIND = decltype(kind)::value;
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
+        for (int i = 0; i < OWN; ++i) {
+            const int q = kg * OWN + i;
+            const int row = prow + 32 * (q >> 3) + 8 * (q & 3), col = pcol + 32 * ((q >> 2) & 1);
+            const v4f gm = *reinterpret_cast<const v4f*>(scales + row);
+            const v4i rs = *reinterpret_cast<const v4i*>(scales + BM + row);
+            v4f eta = {};
+            if constexpr (ETA) eta = *reinterpret_cast<const v4f*>(scales + 2 * BM + row);
+            const float beta = __int_as_float(scales[3 * BM + col]);
+            const float ws = ETA ? (float)scales[3 * BM + BN + col] : 0.f;
+            float* o = a.Y + (m0 + row) * a.ldy + n0 + col;
+            const int64_t left = M - m0 - row;
+            const int rows = n0 + col < N ? (int)(left < 4 ? left : 4) : 0;
 #pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) *red_at(kg, mi, s2, r) += acc[mi][s2][r];
-    }
-    __syncthreads();
-
-    // ---- epilogue (Eq. 11): sum_k q s = 2 sum_k q b - sum_k q ; y = that * (beta gamma / 128) ----
-#pragma unroll
-    for (int h = 0; h < EH; ++h) {
-        const int64_t m = m0 + er + ER * h;
-        if (m >= M || nq >= N) continue;
-        const int* p0 = red + (er + ER * h) * BN + (threadIdx.x & 31) * 4;
-        v4i s4 = *reinterpret_cast<const v4i*>(p0);
-        if constexpr (REG == 2) s4 += *reinterpret_cast<const v4i*>(p0 + BM * BN);
-        const bool vec = ((N | a.ldy) & 3) == 0;  // then nq + 3 < N and the row starts 16-byte aligned
-        if (to_slices) {
-            int* o = a.split_ws + ((int64_t)sp * M + m) * N + nq;
-            const v4i t = s4 * 2;
-            if (vec) *reinterpret_cast<v4i*>(o) = t;
-            else
-                for (int c = 0; c < 4; ++c)
-                    if (nq + c < N) o[c] = t[c];
-            continue;
+            for (int rr = 0; rr < 4; ++rr, o += a.ldy) {
+                const int pm = 2 * own[i][rr] - rs[rr];
+                if (KIND == 2 && a.out_acc) {
+                    if (rr < rows) *reinterpret_cast<int*>(o) = pm;
+                    continue;
+                }
+                // beta * (gamma / 128) has the bits of (beta * gamma) / 128 (gamma / 128 is exact)
+                float y = (float)pm * (beta * (gm[rr] * 0.0078125f));
+                if constexpr (ETA) y = y + (beta * eta[rr]) * ws;  // Eq. 6
+                if (KIND == 2 && a.accumulate && rr < rows) y += *o;  // a later K-group (Eq. 13-15)
+                if (KIND == 0 || rr < rows) *o = y;
+            }
         }
-        const v4i pm = s4 * 2 - e_rs[h];
-        if (a.out_acc) {
-            int* o = reinterpret_cast<int*>(a.Y) + m * a.ldy + nq;
-            if (vec) *reinterpret_cast<v4i*>(o) = pm;
-            else
-                for (int c = 0; c < 4; ++c)
-                    if (nq + c < N) o[c] = pm[c];
-            continue;
-        }
-        float* o = a.Y + m * a.ldy + nq;
-        const float sc = e_gamma[h] * 0.0078125f;  // gamma / 128, exact
-        v4f y;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            // beta * (gamma / 128) has the bits of (beta * gamma) / 128
-            y[c] = (float)pm[c] * (e_beta[c] * sc);
-            if (a.eta) y[c] = y[c] + (e_beta[c] * e_eta[h]) * (float)e_ws[c];  // Eq. 6
-        }
-        if (vec) {
-            if (a.accumulate) y += *reinterpret_cast<const v4f*>(o);  // a later K-group (Eq. 13-15)
-            *reinterpret_cast<v4f*>(o) = y;
-        } else {
-            for (int c = 0; c < 4; ++c)
-                if (nq + c < N) o[c] = a.accumulate ? y[c] + o[c] : y[c];
-        }
-    }
+    };
+    auto store_kind = [&](auto with_eta) {
+        if (a.out_acc || a.accumulate) store(with_eta, std::integral_constant<int, 2>{});
+        else if (inside) store(with_eta, std::integral_constant<int, 0>{});
+        else store(with_eta, std::integral_constant<int, 1>{});
+    };
+    if (a.eta) store_kind(std::true_type{});
+    else store_kind(std::false_type{});
 }
 
 // Small batches (16 < M <= 64) leave most of the chip idle when N supplies few 64 x 128 tiles: K is
@@ -457,11 +468,11 @@ int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
     return (TK + per - 1) / per >= 2 ? per : 0;
 }
 
-// What the launch takes of ws_bytes: the slices of least cost, in us: a round of items 5 + 4.1 c (c
-// 512-chunks per K-group of the workgroup), the slices 4 and their sums written and read at 5 TB/s.
-// GEMM and fold, M x K x N: 64 x 7168 x 7168 15.9 us in 4 slices, 17.0 in 3 (what the rule above
-// gives), 16.7 without; 48 x 4096 x 16384 11.5 us without, 16.4 in 2; 48 x 16384 x 4096 16.0 in the 8
-// taken, 19.5 in 2, 26.5 without.  Returns 512-chunks per slice, 0 = no slices.
+// What the launch takes of ws_bytes: the slices of least cost, in us: a round of items 3.5 + 4.1 c (c
+// 512-chunks per K-group of the workgroup), the slices 6.5 and their sums written and read at 5 TB/s.
+// The layer, M x K x N: 64 x 7168 x 7168 20.4 us in 4 slices, 20.2 in 2, 20.8 without; 48 x 4096 x 12288
+// 15.2 us without, 20.6 in 2; 48 x 16384 x 4096 22.3 in the 8 taken, 24.5 in 4, 32.6 without; 40 x 8192 x
+// 2048 16.3 in 4, 20.6 without.  Returns 512-chunks per slice, 0 = no slices.
 static int64_t mid_slice_tiles(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
     const int64_t TK = tiles_k(K), tiles = (N + mid::BN - 1) / mid::BN;
     if (const int64_t per = tuning().mid_split_tiles)
@@ -472,8 +483,8 @@ static int64_t mid_slice_tiles(int64_t M, int64_t N, int64_t K, size_t ws_bytes)
         const int64_t per = (TK + want - 1) / want, n = (TK + per - 1) / per;
         const double bytes = (double)n * (double)M * (double)N * 4.0;
         if (n > 1 && bytes > (double)ws_bytes) continue;
-        const double us = (double)((tiles * n + 255) / 256) * (5.0 + 4.1 * (double)((per + 3) / 4)) +
-                          (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0);
+        const double us = (double)((tiles * n + 255) / 256) * (3.5 + 4.1 * (double)((per + 3) / 4)) +
+                          (n > 1 ? 6.5 + bytes * 2.0 / 5e6 : 0.0);
         if (us < best_us) {
             best_us = us;
             best = n > 1 ? per : 0;
@@ -514,7 +525,7 @@ hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
         a.tk_pitch = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
         a.split_k = per * kChunkK;
     }
-    gemm_mid_kernel<64, 4, false><<<(unsigned)(grid_n * splits), mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
+    gemm_mid_kernel<64, 4, false><<<dim3((unsigned)grid_n, (unsigned)splits), mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
     if (splits > 1 || gmode) launch_splitk_reduce(a, gmode ? a.kgroups : splits, s);
     return hipGetLastError();
 }

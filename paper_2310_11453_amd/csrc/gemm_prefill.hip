@@ -829,12 +829,12 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 // replays (n stages of 64 k, c 512-chunks per K-group of the workgroup):
 //   a round of 128 x 256 tiles   8 + 0.37 n     (n = 32: 19.5, 64: 30, 128: 50, 256: 89 to 112)
 //   a round of 256 x 256 tiles  14 + 0.62 n     (n = 32: 33, 64: 51 to 58, 112: 82, 256: 158)
-//   a round of the 128 x 128 and 64 x 128 tiles  5 + 4.2 c   (c = 1: 9, 2: 14, 4: 22, 8: 32 to 36)
-//   slices of K                  4 + the int32 sums written and read at 5 TB/s
+//   a round of the 128 x 128 and 64 x 128 tiles  3.5 + 4.2 c   (c = 1: 7.5, 2: 12, 4: 20)
+//   slices of K                  6.5 + the int32 sums written and read at 5 TB/s
 // The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
-// ones win: 333 x 2048 x 2048 9.8 us (64 x 128) against 19.4 us (128 x 256), 200 x 4096 x 16384
-// 22.1 (128 x 128) against 30, 333 x 8192 x 2048 18.5 (64 x 128 in 2 slices) against 50; 1000 x 2048
-// x 8192 stays with 128 x 256: 21.3 against 28.4.
+// ones win; the layer, us: 333 x 2048 x 2048 13.6 (64 x 128) against 24.1 (128 x 256), 200 x 4096 x 16384
+// 24.9 (128 x 128) against 34, 333 x 8192 x 2048 25.5 (64 x 128; in 2 slices 26.2) against 56, 200 x 16384 x
+// 4096 32.6 (64 x 128 in 2 slices; without 37); 1000 x 2048 x 8192 stays with 128 x 256: 26.1 against 33.6.
 struct TilePlan {
     int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
     int64_t per;  // 512-chunks of K per slice (3 and 4)
@@ -866,8 +866,8 @@ static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
             const double bytes = (double)n * (double)M * (double)N * 4.0;
             if (n > 1 && ((n != want && !force_n) || bytes > (double)ws_bytes)) continue;
             const int64_t rounds = (tiles * n + cus - 1) / cus;
-            offer(tile, per, (double)rounds * (5.0 + 4.2 * (double)((per + kg - 1) / kg)) +
-                                 (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0));
+            offer(tile, per, (double)rounds * (3.5 + 4.2 * (double)((per + kg - 1) / kg)) +
+                                 (n > 1 ? 6.5 + bytes * 2.0 / 5e6 : 0.0));
         }
     }
     return best;
@@ -929,8 +929,8 @@ static int group_plan(int64_t M, int64_t N, int64_t K, int groups, size_t ws_byt
         if ((force && tile != force) || bytes > (double)ws_bytes) continue;
         const int64_t bm = tile == 4 ? 64 : 128, kg = tile == 3 ? 2 : 4;
         const int64_t items = ((M + bm - 1) / bm) * ((N + 127) / 128) * groups;
-        const double us = (double)((items + cus - 1) / cus) * (5.0 + 4.2 * (double)((TK + kg - 1) / kg)) +
-                          4.0 + bytes * 2.0 / 5e6;
+        const double us = (double)((items + cus - 1) / cus) * (3.5 + 4.2 * (double)((TK + kg - 1) / kg)) +
+                          5.0 + bytes * 2.0 / 5e6;
         if (us < best_us || force) {
             best_us = us;
             best = tile;
