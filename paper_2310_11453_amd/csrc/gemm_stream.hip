@@ -19,10 +19,9 @@
 // kernel is as fast.  Long K is split over workgroups (second kernel: splitk_reduce) when the
 // caller brought the workspace.
 
-#include <type_traits>
-
 #include "common.h"
 #include "kernels.h"
+#include "ring.h"
 
 namespace bl {
 
@@ -44,8 +43,8 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     // per wave: one chunk of the codes of 32 tokens on its way from row-major memory (read as
     // whole 512-byte rows) to the MFMA's operand layout (16-byte pieces of 32 tokens at one k)
     __shared__ __attribute__((aligned(16))) uint8_t stage[kMaxWaves * kStageBytes];
-    __shared__ int tok_sum[kTokens];
-    __shared__ float tok_sc[kTokens], tok_eta[kTokens];
+    __shared__ int tok_sum[kWave];
+    __shared__ float tok_gamma[kWave], tok_eta[kWave];
 
     const int W = (int)blockDim.x / kWave;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
@@ -55,7 +54,7 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     const int64_t TN = tiles_n(N);
     const int64_t TKp = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
     const int sp = (int)blockIdx.y;
-    int64_t k0 = 0, K = a.K;
+    int64_t k0 = 0, K = a.K;  // K, ldq < 2^22, M <= 32: offsets into the codes fit 32 bits
     if (a.split_k) {
         k0 = (int64_t)sp * a.split_k;
         K = a.K - k0 < a.split_k ? a.K - k0 : a.split_k;
@@ -63,29 +62,43 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     const int TK = (int)tiles_k(K);
 
     // this workgroup's pairs of tile rows
-    const int64_t TP = (TN + 1) / 2;
+    const uint32_t TP = (uint32_t)(TN + 1) / 2;  // <= kMaxPairs workgroups' worth
     const int p0 = (int)(TP * blockIdx.x / gridDim.x), p1 = (int)(TP * (blockIdx.x + 1) / gridDim.x);
     const int np = p1 - p0;  // <= kMaxPairs (the launcher sees to it)
 
-    for (int i = threadIdx.x; i < np * 32 * kPitch; i += blockDim.x) red[i] = 0;
-    // per-token factors of the epilogue, fetched now so that it waits on no load of theirs
-    if ((int)threadIdx.x < M && !a.split_k) {
-        const int m = threadIdx.x;
-        tok_sum[m] = a.rowsum[m * a.gstride];
-        // gamma / 128 is exact
-        tok_sc[m] = a.out_acc ? 0.f : a.gamma[a.per_tensor ? 0 : m * a.gstride] * 0.0078125f;
-        tok_eta[m] = a.eta && !a.out_acc ? a.eta[a.per_tensor ? 0 : m * a.gstride] : 0.f;
+    // Factors of the epilogue, requested now and straight into LDS, so that nothing waits on a load of theirs:
+    // a token's by wave 0, beta as a scalar while the matrix has one.  Neither they nor the clearing of the
+    // sums stand ahead of the first chunk's requests, and the indices of those are 32 bits: 64-bit divisions,
+    // products and a barrier behind the factors' loads were 1.5 us of a launch.
+    if (w == 0 && !a.split_k) {
+        const int64_t m = l < M ? l : M - 1, mg = a.per_tensor ? 0 : m * a.gstride;
+        auto to_lds = [](const void* src, void* dst) {
+            __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+        };
+        to_lds(a.rowsum + m * a.gstride, tok_sum);
+        to_lds(a.gamma + mg, tok_gamma);
+        if (a.eta) to_lds(a.eta + mg, tok_eta);
     }
-    __syncthreads();
+    const bool one_beta = a.beta_rows >= N;
+    const float beta0 = a.beta[0];
+    auto clear_sums = [&]() {  // every thread, once: it synchronises
+        for (int i = threadIdx.x; i < np * 32 * kPitch; i += blockDim.x) red[i] = 0;
+        // a bare barrier behind the LDS writes: a fence would also wait for the chunk's loads
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        block_barrier();
+    };
 
     // lane -> weight row (tok is also the row index of the A operand) and its 16-byte slot:
     // tile 2p + row/16, slot (2 mf + half) * 16 + row % 16
     const int wrow = tok;
     const uint32_t slot_dw = (uint32_t)((half * 16 + (wrow & 15)) * 4);  // + 128 dwords for mf = 1
-    auto pair_ptr = [&](int p, int c) {
-        int64_t tn = (int64_t)(p0 + p) * 2 + (wrow >> 4);
-        if (tn > TN - 1) tn = TN - 1;  // its rows are never stored
-        return a.packed + tile_dword_offset(tn, k0 / kChunkK + c, TKp) + slot_dw;
+    // uniform bases, 32-bit offsets (a tile row is at most 128 KiB here, a row of codes less than 4 MiB)
+    const uint32_t* const wbase = a.packed + tile_dword_offset((int64_t)p0 * 2, k0 / kChunkK, TKp);
+    const int8_t* const cbase = a.codes + k0;
+    const int last_row = (int)(TN - 1) - 2 * p0;  // rows behind it are never stored
+    auto pair_off = [&](int p) {
+        const int row = 2 * p + (wrow >> 4);
+        return __umul24((uint32_t)(row < last_row ? row : last_row), (uint32_t)TKp * 256) + slot_dw;
     };
 
     // NP = pairs of this workgroup, a compile-time count so that the tiles sit in registers
@@ -97,24 +110,27 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
         auto load_q = [&](v4i (&dst)[NP][2], int c) {
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                const uint32_t* s = pair_ptr(p, c);
-                dst[p][0] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(s));
-                dst[p][1] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(s + 128));
+                const uint32_t* s = wbase + (int64_t)c * 256;
+                const uint32_t off = pair_off(p);
+                dst[p][0] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(s + off));
+                dst[p][1] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(s + off + 128));
             }
         };
         // wave-load jj brings tokens 2 jj and 2 jj + 1: lane -> (token, 16-byte piece), whole rows
         auto load_raw = [&](int c) {
+            uint32_t k = (uint32_t)c * kChunkK + 16 * tok;
+            if (k > (uint32_t)K - 16) k = (uint32_t)K - 16;  // the packed bits there are zero
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj) {
                 const int t = 2 * jj + half;
-                const int m = t < M ? t : M - 1;
-                int64_t k = (int64_t)c * kChunkK + 16 * tok;
-                if (k > K - 16) k = K - 16;  // the packed bits there are zero
-                raw[jj] = *reinterpret_cast<const v4i*>(a.codes + (int64_t)m * a.ldq + k0 + k);
+                raw[jj] = *reinterpret_cast<const v4i*>(
+                    cbase + (__umul24((uint32_t)(t < M ? t : M - 1), (uint32_t)a.ldq) + k));
             }
         };
         load_q(q, w);
         load_raw(w);
+        __builtin_amdgcn_sched_barrier(0);
+        clear_sums();
         // the first tiles are waited for here, once: inside the loop a wait for them would have to
         // count the conditional fetches behind them as absent, and so wait for those as well
 #pragma unroll
@@ -175,68 +191,68 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
         }
     };
 
-    if (w < TK) {  // uniform per wave; nothing in there synchronises across waves
-        switch (np) {
+    if (w >= TK) {  // uniform per wave
+        clear_sums();
+    } else {
+        switch (np) {  // np >= 1: there are no more workgroups than pairs
             case 1: wave_chunks(std::integral_constant<int, 1>{}); break;
             case 2: wave_chunks(std::integral_constant<int, 2>{}); break;
             case 3: wave_chunks(std::integral_constant<int, 3>{}); break;
             case 4: wave_chunks(std::integral_constant<int, 4>{}); break;
-            default: break;
+            default: clear_sums(); break;
         }
     }
+    wait_vmcnt<0>();  // the tokens' factors
     __syncthreads();
 
     // ---- epilogue (Eq. 11): sum_k q s = 2 sum_k q b - sum_k q ; y = that * (beta gamma / 128) ----
-    // thread -> four consecutive weight rows of every pair and every (blockDim / 8)-th token
-    const int nl0 = (threadIdx.x & 7) * 4, MG = blockDim.x >> 3;
-    const bool raw_out = a.split_k || a.out_acc;
-    uint32_t* const out = a.split_k ? reinterpret_cast<uint32_t*>(a.split_ws) + (int64_t)sp * M * N
-                                    : reinterpret_cast<uint32_t*>(a.Y);
-    const bool vec = (N & 3) == 0;  // then n0 + 3 < N and the row starts 16-byte aligned
-    float beta[kMaxPairs][4], wsum[kMaxPairs][4];
+    // item -> four consecutive weight rows of a pair and a token, eight items to a line of the output.
+    // kind 0: one beta and none of the options; 1: sums (a slice, or int32 output); 2: the rest
+    const bool vec = (N & 3) == 0;  // then n + 3 < N and the row starts 16-byte aligned
+    auto finish = [&](auto kind) {
+        constexpr int KIND = decltype(kind)::value;
+        uint32_t* const out = KIND == 1 && a.split_k
+                                  ? reinterpret_cast<uint32_t*>(a.split_ws) + (int64_t)sp * M * N
+                                  : reinterpret_cast<uint32_t*>(a.Y);
+        for (int i = threadIdx.x; i < np * 8 * kTokens; i += blockDim.x) {
+            const int nl = (i >> 8) * 32 + (i & 7) * 4, m = (i >> 3) & (kTokens - 1);
+            const int64_t n = (int64_t)p0 * 32 + nl;
+            if (m >= M || n >= N) continue;
+            int sum[4];
 #pragma unroll
-    for (int p = 0; p < kMaxPairs; ++p)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t n = ((int64_t)(p0 + p) * 2) * kTileN + nl0 + j;
-            const bool live = p < np && n < N && !raw_out;
-            beta[p][j] = live ? a.beta[((uint32_t)n / (uint32_t)a.beta_rows) * a.beta_stride] : 0.f;
-            wsum[p][j] = live && a.eta ? (float)a.wsum[n] : 0.f;
-        }
-#pragma unroll
-    for (int p = 0; p < kMaxPairs; ++p) {
-        const int64_t n0 = ((int64_t)(p0 + p) * 2) * kTileN + nl0;
-        if (p >= np || n0 >= N) continue;
-        for (int m = threadIdx.x >> 3; m < M; m += MG) {
+            for (int j = 0; j < 4; ++j) sum[j] = 2 * red[(nl + j) * kPitch + m];
+            uint32_t* const dst = out + (int64_t)m * N + n;
             uint32_t o[4];
+            if constexpr (KIND == 1) {
+                const int rs = a.split_k ? 0 : tok_sum[m];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int s2 = 2 * red[(p * 32 + nl0 + j) * kPitch + m];
-                if (a.split_k) {
-                    o[j] = (uint32_t)s2;
-                    continue;
+                for (int j = 0; j < 4; ++j) o[j] = (uint32_t)(sum[j] - rs);
+            } else {
+                const float sc = tok_gamma[m] * 0.0078125f;  // gamma / 128, exact
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int64_t nj = n + j < N ? n + j : N - 1;
+                    const float beta =
+                        KIND == 0 || one_beta ? beta0 : a.beta[((uint32_t)nj / (uint32_t)a.beta_rows) * a.beta_stride];
+                    // beta * (gamma / 128) has the bits of (beta * gamma) / 128
+                    float y = (float)(sum[j] - tok_sum[m]) * (beta * sc);
+                    if (KIND == 2 && a.eta) y = y + (beta * tok_eta[m]) * (float)a.wsum[nj];       // Eq. 6
+                    if (KIND == 2 && a.accumulate && n + j < N) y += __uint_as_float(dst[j]);  // a later K-group
+                    o[j] = __float_as_uint(y);
                 }
-                const int pm = s2 - tok_sum[m];
-                if (a.out_acc) {
-                    o[j] = (uint32_t)pm;
-                    continue;
-                }
-                // beta * (gamma / 128) has the bits of (beta * gamma) / 128
-                float y = (float)pm * (beta[p][j] * tok_sc[m]);
-                if (a.eta) y = y + (beta[p][j] * tok_eta[m]) * wsum[p][j];  // Eq. 6
-                if (a.accumulate && n0 + j < N) y += a.Y[m * N + n0 + j];    // a later K-group (Eq. 13-15)
-                o[j] = __float_as_uint(y);
             }
-            uint32_t* const dst = out + (int64_t)m * N + n0;
             if (vec) {
                 *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (n0 + j < N) dst[j] = o[j];
+                    if (n + j < N) dst[j] = o[j];
             }
         }
-    }
+    };
+    if (a.split_k || a.out_acc) finish(std::integral_constant<int, 1>{});
+    else if (one_beta && !a.eta && !a.accumulate) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, 2>{});
 }
 
 static int stream_cus() {
