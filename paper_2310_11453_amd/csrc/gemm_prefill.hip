@@ -148,7 +148,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
     __shared__ __attribute__((aligned(16))) float smBeta[2][GEN ? BN : 4];  // beta of each column's group
     __shared__ __attribute__((aligned(16))) float smEta[2][GEN ? BM : 4];   // Eq. 6 only: eta_m
     __shared__ __attribute__((aligned(16))) int smWsum[2][GEN ? BN : 4];    // Eq. 6 only: sum_k s[n,k]
-    __shared__ __attribute__((aligned(16))) int smRowsum[2][BM];   // sum_k q[m,k]
+    __shared__ __attribute__((aligned(16))) int smRowsum[2][BM];   // -sum_k q[m,k]
 
     const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
     const int wm = w / WN, wn = w % WN;
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                 if (i < BM) {
                     // gamma / 128 is exact, so beta * (gamma / 128) has the bits of (beta * gamma) / 128
                     lds_write_b32((uint32_t)(uintptr_t)&smScale[parity][i], __float_as_uint(gm * 0.0078125f));
-                    lds_write_b32((uint32_t)(uintptr_t)&smRowsum[parity][i], (uint32_t)rs);
+                    lds_write_b32((uint32_t)(uintptr_t)&smRowsum[parity][i], (uint32_t)-rs);
                     lds_write_b32((uint32_t)(uintptr_t)&smEta[parity][i], __float_as_uint(e));
                 }
                 if (i < BN) {
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                     rs = a.rowsum[m];
                 }
                 lds_write_b32((uint32_t)(uintptr_t)&smScale[parity][r], __float_as_uint(sc));
-                lds_write_b32((uint32_t)(uintptr_t)&smRowsum[parity][r], (uint32_t)rs);
+                lds_write_b32((uint32_t)(uintptr_t)&smRowsum[parity][r], (uint32_t)-rs);
             }
         }
 #pragma unroll
@@ -432,10 +432,50 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
             wcol[s] = (GEN && a.eta) ? (float)__float_as_int(lds_read_f32(
                                   (uint32_t)(uintptr_t)&smWsum[parity][wn * WTN + 32 * s + j]))
                             : 0.f;
+        // A tile inside the output, which nearly all are: a row's address is a scalar that walks by the
+        // pitch (hidden from the optimiser, which would compute all of them ahead and spill), a lane's offset in
+        // it one register, so a store is a conversion, a product and itself.  With a row's bounds, its 64-bit
+        // product and the branches of the general form below at every store the instructions around the
+        // stores took as long as a sixth of the products.
+        const bool inside = m0 + BM <= M && n0 + BN <= a.N && !a.out_acc && !a.accumulate && a.ldy < (1 << 24);
+        auto store_inside = [&](auto with_eta) {
+            constexpr bool ETA = decltype(with_eta)::value;
+            const int ws = __builtin_amdgcn_readfirstlane(w);
+            typedef __attribute__((address_space(1))) float* gptr;  // a scalar base needs the address space
+            gptr rowp = (gptr)(uintptr_t)(a.Y + (m0 + ws / WN * WTM) * a.ldy + n0 + ws % WN * WTN);
+            const uint32_t lane = (uint32_t)(4 * g2) * (uint32_t)a.ldy + j;
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq) {
+                    v4f sc4;
+                    v4i rs4;
+                    lds_read_rows(sc4, rs4, sc_base + (32 * mi + 8 * rq) * 4, rs_base + (32 * mi + 8 * rq) * 4);
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        asm volatile("" : "+s"(rowp));
+                        const float e = ETA ? lds_read_f32((uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi +
+                                                                                              8 * rq + 4 * g2 + rr])
+                                            : 0.f;
+#pragma unroll
+                        for (int s = 0; s < NI; ++s) {
+                            const int pm = rs4[rr] - (acc[mi][s][rq * 4 + rr] >> 6);  // exact: a multiple of 128
+                            float y = GEN ? (float)pm * (bcol[s] * sc4[rr]) : (float)pm * sc4[rr];
+                            if constexpr (ETA) y = y + (bcol[s] * e) * wcol[s];
+                            __builtin_nontemporal_store(y, rowp + (lane + 32 * s));
+                        }
+                        rowp += rr == 3 ? 5 * a.ldy : a.ldy;
+                    }
+                }
+        };
         // Register allocation here is at the limit of 256 and sensitive to the form of these
         // loops: hoisting the uniform branches into a second copy of the loops, or naming the
         // row index as a 32-bit temporary, makes the compiler precompute the store addresses and
         // spill over a hundred registers.  Check the resource usage after any change.
+        if (inside) {  // uniform
+            if (GEN && a.eta) store_inside(std::integral_constant<bool, GEN>{});
+            else store_inside(std::false_type{});
+        } else
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -452,7 +492,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                     for (int s = 0; s < NI; ++s) {
                         const int64_t n = n0 + wn * WTN + 32 * s + j;
                         if (n >= a.N) continue;
-                        const int pm = -(acc[mi][s][r] >> 6) - rs4[rr];  // exact: a multiple of 128
+                        const int pm = rs4[rr] - (acc[mi][s][r] >> 6);  // exact: a multiple of 128
                         // y = acc * ((beta * gamma) / 128)
                         // (GEN: sc4 holds gamma / 128, else the whole scale)
                         float y = GEN ? (float)pm * (bcol[s] * sc4[rr]) : (float)pm * sc4[rr];
