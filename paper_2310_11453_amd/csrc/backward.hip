@@ -414,19 +414,25 @@ __global__ __launch_bounds__(256, T == 256 ? 1 : 2) void gemm_tn_bf16_wide(const
             issue_tile_start();
         }
 
-        // lane (j, g2) holds column j0 + .. + j, rows 8*(r/4) + 4*g2 + r%4 of each sub-tile
+        {
+            const int64_t ib = i0 + __builtin_amdgcn_readfirstlane(wm * WTM), jb = j0 + __builtin_amdgcn_readfirstlane(wn * WTN);
+            if constexpr (T < 256) {
+                store_tile<MI, NI, true>(Cs + ib * J + jb, J, I - ib, J - jb, j, g2, [](int, int) {},
+                                         [&](int mi, int r, int s) { return scale * acc[mi][s][r]; });
+            } else  // with 256 accumulators the walk of store_tile spills 29 registers and gains nothing
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+                for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t i = i0 + wm * WTM + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3);
-                if (i >= I) continue;
+                    for (int r = 0; r < 16; ++r) {
+                        const int64_t i = i0 + wm * WTM + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3);
+                        if (i >= I) continue;
 #pragma unroll
-                for (int s = 0; s < NI; ++s) {
-                    const int64_t jj = j0 + wn * WTN + 32 * s + j;
-                    if (jj < J) __builtin_nontemporal_store(scale * acc[mi][s][r], &Cs[i * J + jj]);  // streaming
-                }
-            }
+                        for (int s = 0; s < NI; ++s) {
+                            const int64_t jj = j0 + wn * WTN + 32 * s + j;
+                            if (jj < J) __builtin_nontemporal_store(scale * acc[mi][s][r], &Cs[i * J + jj]);
+                        }
+                    }
+        }
         if (i0n < 0) break;
         t = t_next;
         i0 = i0n;
@@ -667,18 +673,11 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
             issue_tile_start();
         }
 
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t i = i0 + wm * WTM + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3);
-                if (i >= I) continue;
-#pragma unroll
-                for (int s = 0; s < NI; ++s) {
-                    const int64_t jj = j0 + wn * WTN + 32 * s + j;
-                    if (jj < J) __builtin_nontemporal_store(scale * acc[mi][s][r], &Cs[i * J + jj]);
-                }
-            }
+        {
+            const int64_t ib = i0 + __builtin_amdgcn_readfirstlane(wm * WTM), jb = j0 + __builtin_amdgcn_readfirstlane(wn * WTN);
+            store_tile<MI, NI, true>(Cs + ib * J + jb, J, I - ib, J - jb, j, g2, [](int, int) {},
+                               [&](int mi, int r, int s) { return scale * acc[mi][s][r]; });
+        }
         if (i0n < 0) break;
         t = t_next;
         i0 = i0n;

@@ -432,18 +432,38 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
             wcol[s] = (GEN && a.eta) ? (float)__float_as_int(lds_read_f32(
                                   (uint32_t)(uintptr_t)&smWsum[parity][wn * WTN + 32 * s + j]))
                             : 0.f;
-        // A tile inside the output, which nearly all are: a row's address is a scalar that walks by the
-        // pitch (hidden from the optimiser, which would compute all of them ahead and spill), a lane's offset in
-        // it one register, so a store is a conversion, a product and itself.  With a row's bounds, its 64-bit
-        // product and the branches of the general form below at every store the instructions around the
-        // stores took as long as a sixth of the products.
-        const bool inside = m0 + BM <= M && n0 + BN <= a.N && !a.out_acc && !a.accumulate && a.ldy < (1 << 24);
-        auto store_inside = [&](auto with_eta) {
+        const int wrow = __builtin_amdgcn_readfirstlane(wm * WTM), wcolumn = __builtin_amdgcn_readfirstlane(wn * WTN);
+        auto store_plain = [&](auto with_eta) {
             constexpr bool ETA = decltype(with_eta)::value;
-            const int ws = __builtin_amdgcn_readfirstlane(w);
-            typedef __attribute__((address_space(1))) float* gptr;  // a scalar base needs the address space
-            gptr rowp = (gptr)(uintptr_t)(a.Y + (m0 + ws / WN * WTM) * a.ldy + n0 + ws % WN * WTN);
-            const uint32_t lane = (uint32_t)(4 * g2) * (uint32_t)a.ldy + j;
+            v4f sc4;
+            v4i rs4;
+            float e = 0.f;
+            store_tile<MI, NI, (BM < 256)>(
+                a.Y + (m0 + wrow) * a.ldy + n0 + wcolumn, a.ldy, M - m0 - wrow, a.N - n0 - wcolumn, j, g2,
+                [&](int mi, int rq) {
+                    lds_read_rows(sc4, rs4, sc_base + (32 * mi + 8 * rq) * 4, rs_base + (32 * mi + 8 * rq) * 4);
+                },
+                [&](int mi, int r, int s) {
+                    const int pm = rs4[r & 3] - (acc[mi][s][r] >> 6);  // exact: a multiple of 128
+                    float y = GEN ? (float)pm * (bcol[s] * sc4[r & 3]) : (float)pm * sc4[r & 3];
+                    if constexpr (ETA) {  // Eq. 6: + (beta * eta_m) * sum_k s[n,k]
+                        if (s == 0)
+                            e = lds_read_f32((uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi + 8 * (r >> 2) +
+                                                                                 4 * g2 + (r & 3)]);
+                        y = y + (bcol[s] * e) * wcol[s];
+                    }
+                    return y;
+                });
+        };
+        if (!a.out_acc && !a.accumulate &&  // uniform
+            (BM < 256 || (m0 + BM <= M && n0 + BN <= a.N && a.ldy < (1 << 24)))) {
+            if (GEN && a.eta) store_plain(std::integral_constant<bool, GEN>{});
+            else store_plain(std::false_type{});
+        } else {
+            // a 256-row tile at an edge, int32 output, or a later K-group added.  Register allocation here is at the limit of 256 and
+            // sensitive to the form of these loops: hoisting the uniform branches into a second copy of the
+            // loops, or naming the row index as a 32-bit temporary, makes the compiler precompute the
+            // store addresses and spill over a hundred registers.
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -453,67 +473,32 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                     lds_read_rows(sc4, rs4, sc_base + (32 * mi + 8 * rq) * 4, rs_base + (32 * mi + 8 * rq) * 4);
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) {
-                        asm volatile("" : "+s"(rowp));
-                        const float e = ETA ? lds_read_f32((uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi +
-                                                                                              8 * rq + 4 * g2 + rr])
-                                            : 0.f;
+                        const int r = rq * 4 + rr;
+                        const int64_t m = m0 + wm * WTM + 32 * mi + 8 * rq + 4 * g2 + rr;
+                        if (m >= M) continue;
 #pragma unroll
                         for (int s = 0; s < NI; ++s) {
-                            const int pm = rs4[rr] - (acc[mi][s][rq * 4 + rr] >> 6);  // exact: a multiple of 128
+                            const int64_t n = n0 + wn * WTN + 32 * s + j;
+                            if (n >= a.N) continue;
+                            const int pm = rs4[rr] - (acc[mi][s][r] >> 6);
                             float y = GEN ? (float)pm * (bcol[s] * sc4[rr]) : (float)pm * sc4[rr];
-                            if constexpr (ETA) y = y + (bcol[s] * e) * wcol[s];
-                            __builtin_nontemporal_store(y, rowp + (lane + 32 * s));
+                            if (special) {  // uniform
+                                if (a.out_acc) {
+                                    reinterpret_cast<int*>(a.Y)[m * a.ldy + n] = pm;
+                                    continue;
+                                }
+                                if (GEN && a.eta) {
+                                    const float e = lds_read_f32(
+                                        (uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi + 8 * rq + 4 * g2 + rr]);
+                                    y = y + (bcol[s] * e) * wcol[s];
+                                }
+                                if (GEN && a.accumulate) y += a.Y[m * a.ldy + n];
+                            }
+                            __builtin_nontemporal_store(y, &a.Y[m * a.ldy + n]);
                         }
-                        rowp += rr == 3 ? 5 * a.ldy : a.ldy;
                     }
                 }
-        };
-        // Register allocation here is at the limit of 256 and sensitive to the form of these
-        // loops: hoisting the uniform branches into a second copy of the loops, or naming the
-        // row index as a 32-bit temporary, makes the compiler precompute the store addresses and
-        // spill over a hundred registers.  Check the resource usage after any change.
-        if (inside) {  // uniform
-            if (GEN && a.eta) store_inside(std::integral_constant<bool, GEN>{});
-            else store_inside(std::false_type{});
-        } else
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                v4f sc4;
-                v4i rs4;
-                lds_read_rows(sc4, rs4, sc_base + (32 * mi + 8 * rq) * 4, rs_base + (32 * mi + 8 * rq) * 4);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = rq * 4 + rr;
-                    const int64_t m = m0 + wm * WTM + 32 * mi + 8 * rq + 4 * g2 + rr;
-                    if (m >= M) continue;
-#pragma unroll
-                    for (int s = 0; s < NI; ++s) {
-                        const int64_t n = n0 + wn * WTN + 32 * s + j;
-                        if (n >= a.N) continue;
-                        const int pm = rs4[rr] - (acc[mi][s][r] >> 6);  // exact: a multiple of 128
-                        // y = acc * ((beta * gamma) / 128)
-                        // (GEN: sc4 holds gamma / 128, else the whole scale)
-                        float y = GEN ? (float)pm * (bcol[s] * sc4[rr]) : (float)pm * sc4[rr];
-                        if (special) {  // uniform
-                            if (a.out_acc) {
-                                reinterpret_cast<int*>(a.Y)[m * a.ldy + n] = pm;
-                                continue;
-                            }
-                            if (GEN && a.eta) {  // Eq. 6: + (beta * eta_m) * sum_k s[n,k]
-                                const float e = lds_read_f32(
-                                    (uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi + 8 * rq + 4 * g2 + rr]);
-                                y = y + (bcol[s] * e) * wcol[s];
-                            }
-                            if (GEN && a.accumulate) y += a.Y[m * a.ldy + n];  // a later K-group
-                        }
-                        // streaming store: the output is not read again soon, and keeping it out
-                        // of L2 leaves the codes and bits there (3-4 % of the kernel)
-                        __builtin_nontemporal_store(y, &a.Y[m * a.ldy + n]);
-                    }
-                }
-            }
+        }
         if (m0n < 0) break;
         t = t_next;
         m0 = m0n;
@@ -808,18 +793,9 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
                 }
             }
         if (cur.grp + 1 == ngroups) {
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int m = cur.m0 + wm * WTM + 32 * mi + 8 * (r >> 2) + 4 * g2 + (r & 3);
-                    if (m >= M) continue;
-#pragma unroll
-                    for (int s = 0; s < NI; ++s) {
-                        const int n = cur.n0 + wn * WTN + 32 * s + j;
-                        if (n < N) __builtin_nontemporal_store(side[mi][s][r], &a.Y[(int64_t)m * N + n]);
-                    }
-                }
+            const int row = cur.m0 + wm * WTM, col = cur.n0 + wn * WTN;
+            store_tile<MI, NI, true>(a.Y + (int64_t)row * N + col, N, M - row, N - col, j, g2, [](int, int) {},
+                               [&](int mi, int r, int s) { return side[mi][s][r]; });
             clear_side();
         }
         if (!next_item(cur)) break;
