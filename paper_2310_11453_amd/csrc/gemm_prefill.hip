@@ -691,7 +691,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const int idx = q * 2 + e;
-                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] << (7 - i)) & 0x80808080u);
+                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] >> i) & 0x01010101u);
                 }
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
 #pragma unroll
     for (int s = 0; s < NI; ++s)
 #pragma unroll
-        for (int d = 0; d < 4; ++d) bx[s][d] = (int)(((uint32_t)bw[s][0][d] << 7) & 0x80808080u);
+        for (int d = 0; d < 4; ++d) bx[s][d] = (int)((uint32_t)bw[s][0][d] & 0x01010101u);
     clear();
 
     int fbuf = 0;  // the scales of the item being folded
@@ -783,10 +783,11 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
                 for (int rr = 0; rr < 4; ++rr) {
                     const int r = rq * 4 + rr;
                     const float sc = sc4[rr] * 0.0078125f;  // gamma / 128, exact
+                    const int nrs = -rs4[rr];
                     const float e = ETA ? lds_read_f32(eta_base + (32 * mi + 8 * rq + rr) * 4) : 0.f;
 #pragma unroll
                     for (int s = 0; s < NI; ++s) {
-                        float y = (float)(-(acc[mi][s][r] >> 6) - rs4[rr]) * (bcol[s] * sc);
+                        float y = (float)((int)((uint32_t)acc[mi][s][r] << 1) + nrs) * (bcol[s] * sc);
                         if constexpr (ETA) y = y + (bcol[s] * e) * wcol[s];
                         side[mi][s][r] = y + side[mi][s][r];
                     }
