@@ -369,8 +369,8 @@ def main():
     d0 = layers[0]
     pws = torch.empty(bl.workspace_bytes(bl.OP_PACK, 0, up.N, up.K), dtype=torch.uint8, device=dev)
     t_pack = event_ms(lambda: bl.bitlinear_pack_weights(d0["Wd"], workspace=pws), 10, torch)
-    prep = dict(ms=t_pack, gbs=(2 * 4 + 0.125) * up.N * up.K / (t_pack * 1e-3) / 1e9,
-                note="two passes over fp32 W (stats, then compare+pack)")
+    prep = dict(ms=t_pack, gbs=(4 + 0.125) * up.N * up.K / (t_pack * 1e-3) / 1e9,
+                note="one reading of fp32 W, and again the rows of tiles with a weight within |alpha| of zero")
 
     # ---- parity guard: a fast-but-wrong kernel must not report a number ----------------------
     # Both layers of the step: sampled rows of codes (given the normalised input the GPU dumped)

@@ -188,7 +188,7 @@ __device__ inline float quant_token(const GemmArgs& a, uint32_t* lds_codes, Toke
 // one workgroup.  a.K is one group's K; the waves are dealt to the groups (W / kgroups consecutive
 // waves each, C chunks of the group's K per wave), every group reads its own columns of the codes
 // and its own blob of tiles, and a tile's sums are added per group and written to the group's slice
-// of split_ws (2 * sum_k q b, as a K split does), for splitk_reduce to dequantise group by group.
+// of split_ws (2 * sum_k q b, as a K split does), for groups_reduce to dequantise group by group.
 template <int C, int T, int MAXT, bool ONE_ROUND, int FUSED = 0, bool KGRP = false>
 __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) {
     static_assert(!FUSED || ONE_ROUND, "the fused quantiser covers K in one round");

@@ -7,8 +7,8 @@
 // K-groups of four waves), each group streaming its own part of K through its own LDS ring (codes
 // and packed bits by global_load_lds, bits expanded in registers, hand-counted vmcnt), all groups
 // meeting at the same barriers.  The integer accumulators of the groups are added through LDS at
-// the end and one epilogue dequantises: the same integers as any other split of K, so the result
-// does not depend on it.
+// the end, each group finishing its share of the tile: the same integers as any other split of K, so the
+// result does not depend on it.
 //
 // What bounds this shape is the stream of activation codes from L2 into LDS: every workgroup
 // reads all M x K of them (64 bytes per k against 16 bytes of packed weights), 100 MB per launch
