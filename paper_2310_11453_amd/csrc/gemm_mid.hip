@@ -435,7 +435,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
                 float y = (float)pm * (beta * (gm[rr] * 0.0078125f));
                 if constexpr (ETA) y = y + (beta * eta[rr]) * ws;  // Eq. 6
                 if (KIND == 2 && a.accumulate && rr < rows) y += *o;  // a later K-group (Eq. 13-15)
-                if (KIND == 0 || rr < rows) *o = y;
+                if (KIND == 0 || rr < rows) __builtin_nontemporal_store(y, o);  // streaming, as in the large tiles
             }
         }
     };
