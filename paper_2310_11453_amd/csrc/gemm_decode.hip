@@ -505,7 +505,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             }
             if ((a.N & 3) == 0) {
                 if (a.accumulate) o += *reinterpret_cast<const v4f*>(y);  // a later K-group
-                *reinterpret_cast<v4f*>(y) = o;
+                __builtin_nontemporal_store(o, reinterpret_cast<v4f*>(y));  // not read again soon
             } else {
                 for (int r = 0; r < 4; ++r)
                     if (n + r < a.N) y[r] = a.accumulate ? y[r] + o[r] : o[r];
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(256) void splitk_reduce(GemmArgs a, int splits) {
             if (a.eta) y[c] = y[c] + (beta[c] * eta) * wsum[c];
         }
         if (a.accumulate) y += *o;
-        *o = y;
+        __builtin_nontemporal_store(y, o);  // not read again soon
     }
 }
 
@@ -591,7 +591,7 @@ __global__ __launch_bounds__(256) void groups_reduce(GemmArgs a) {
                 y[c] = g ? yg + y[c] : yg;
             }
         }
-        *reinterpret_cast<vf*>(a.Y + m * a.N + n) = y;
+        __builtin_nontemporal_store(y, reinterpret_cast<vf*>(a.Y + m * a.N + n));
     }
 }
 

@@ -242,7 +242,10 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
                 }
             }
             if (vec) {
-                *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
+                const v4i v = {(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
+                // the output is not read again soon; a slice is, by the fold
+                if (KIND == 1) *reinterpret_cast<v4i*>(dst) = v;
+                else __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(dst));
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
