@@ -393,7 +393,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         const int rows = n < N ? (int)(M - m < 4 ? M - m : 4) : 0;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr, o += N)
-            if (inside || rr < rows) *o = 2 * p[rr];
+            if (inside || rr < rows) __builtin_nontemporal_store(2 * p[rr], o);
     };
     if (!add_groups) {  // each group's sums to its layer group's slice
         if (lgrp < a.kgroups)
