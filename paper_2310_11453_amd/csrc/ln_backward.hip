@@ -140,7 +140,8 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_backward_ro
         o.y = r * ((g[j].y - m1) - x[j].y * m2);
         o.z = r * ((g[j].z - m1) - x[j].z * m2);
         o.w = r * ((g[j].w - m1) - x[j].w * m2);
-        if (idx < K4 && live) d4[idx] = o;
+        if (idx < K4 && live)  // streaming: not read again soon
+            __builtin_nontemporal_store((v4f){o.x, o.y, o.z, o.w}, reinterpret_cast<v4f*>(d4 + idx));
     }
 }
 
