@@ -77,10 +77,11 @@ size_t bitlinear_packed_bytes(int64_t N, int64_t K, unsigned flags);
  * only some shapes have a use for it).  The sizes for the forward calls at M > 32, for
  * BL_OP_BACKWARD and for BL_OP_LN_BACKWARD include an optional part (partial sums of shapes that are
  * cut along the reduction to fill the chip): without it the same call runs uncut.  BL_OP_PACK's includes
- * room (N * K / 128 bytes) that lets the call read W once instead of twice.  The forward's
- * results are the same bits either way.  The fp32 sums of the backward and the fp64 sums of the
- * LayerNorm backward's dgain and dbias are then added in another order, so their last bits depend
- * on whether the optional part was brought (and, for the backward, on the bwd_* switches). */
+ * room (64 bytes per tile of 16 x 512 weights, N * K / 128 for whole tiles) that lets the call read W once
+ * instead of twice.  The forward's results are the same bits either way.  The fp32 sums of the backward,
+ * the fp64 sums of the LayerNorm backward's dgain and dbias and those behind alpha and beta are then added
+ * in another order, so their last bits can depend on whether the optional part was brought (and, for the
+ * backward, on the bwd_* switches). */
 size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int granularity,
                                  unsigned flags);
 

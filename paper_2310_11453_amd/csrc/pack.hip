@@ -7,7 +7,8 @@
 // weights it separates from zero are few: pack_scan reads W once, packs the bits of W > 0, and keeps
 // the smallest |w| of every row of a tile (512 weights); a row's bits are those of W > alpha whenever
 // |alpha| is below that, and pack_fix reads again only the rows where it is not (about one in 20 of a
-// zero-mean 16384 x 4096 matrix; all of them if the mean is large, which costs what a second pass does).
+// zero-mean 16384 x 4096 matrix; all of them if the mean is a fiftieth of the deviation or more, which costs what
+// a second pass does).
 #include "common.h"
 #include "kernels.h"
 #include "rowops.h"
@@ -31,69 +32,74 @@ __device__ inline uint32_t row_dword(const float4 (&w)[2], const bool (&valid)[2
     return (uint32_t)(lo | hi);
 }
 
+// Stores the dwords of four rows of a tile: every lane has all four rows' for q = l % 16 and stores row l / 16's.
+// By value: a choice between array elements would put the arrays into LDS and make the kernel read its
+// workgroup size out of the dispatch packet, in host memory (13 us a launch).
+__device__ inline void store_rows(uint32_t* tile, int l, uint32_t dw0, uint32_t dw1, uint32_t dw2, uint32_t dw3,
+                                  int c0, int c1, int c2, int c3) {
+    const bool odd = l & 16, high = l & 32;
+    const uint32_t dw = high ? (odd ? dw3 : dw2) : (odd ? dw1 : dw0);
+    const int c = high ? (odd ? c3 : c2) : (odd ? c1 : c0);
+    tile[(((l & 15) >> 2) * 16 + c) * 4 + (l & 3)] = dw;
+}
+
 // ---- one reading of W: sums for alpha and beta, bits of W > 0, smallest |w| of a tile's rows ------
-// One wave per tile, tiles dealt over a fixed grid; kRows rows of a tile are in flight at a time and the
-// two halves of a tile are kept apart (together they take 193 registers and half the waves).
-// partials[2*b] = sum of W, partials[2*b+1] = sum of |W| over workgroup b's tiles.
-// The whole call, us, against two readings of W with the fold of the sums as a launch between them:
-// 16384 x 4096 92 -> 62, 8192 x 2048 33 -> 22, 28672 x 7168 321 -> 183, 512 x 256 15 -> 12.5; with a mean of
-// half the standard deviation, where pack_fix reads everything again, 94 -> 99 and 33 -> 30.
+// One wave per half tile (8 rows, all in flight at once), dealt over a fixed grid.
+// partials[2*b] = sum of W, partials[2*b+1] = sum of |W| over workgroup b's rows.
+// The whole call, us: two readings of W with the fold of the sums as a launch between them / this with a zero mean /
+// this with a mean of half the deviation, where pack_fix reads everything again: 64 x 32 10.6 / 8.6 / 8.7,
+// 512 x 256 11.9 / 9.1 / 9.0, 2048 x 2048 20.4 / 10.8 / 11.7, 8192 x 2048 31 / 21.7 / 28.7, 16384 x 4096 88 / 52 / 89,
+// 28672 x 7168 318 / 177 / 317; 3 to 5 % slower than two readings only where W is 100 to 200 MB and all of it is
+// repacked (8192 x 4096 46.5 / 31 / 48, 50257 x 1024 69 / 44 / 72.5).
 __global__ __launch_bounds__(256, 4) void pack_scan(const float* __restrict__ W, int64_t N, int64_t K,
                                                  int64_t ldw, uint32_t* __restrict__ packed,
                                                  float* __restrict__ rowmin,
                                                  double* __restrict__ partials) {
     constexpr int kRows = 8;
-    __shared__ __attribute__((aligned(16))) uint32_t sm[4][256];
     __shared__ double smd[4];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
-    const int64_t TN = tiles_n(N), TK = tiles_k(K);
+    const uint32_t TK = (uint32_t)tiles_k(K), items = (uint32_t)tiles_n(N) * TK * (kTileN / kRows);  // < 2^31
     double s = 0.0, a = 0.0;
-    for (int64_t task = (int64_t)blockIdx.x * 4 + wave; task < TN * TK; task += (int64_t)gridDim.x * 4) {
-        const int64_t tn = task / TK, tk = task % TK;
-        float keep = 0.f;  // lane c keeps row c's smallest |w|
-        const int64_t k0 = tk * kChunkK + 4 * l;
-#pragma unroll 1
-        for (int cb = 0; cb < kTileN; cb += kRows) {
-            float4 w[kRows][2];
+    for (uint32_t item = blockIdx.x * 4 + wave; item < items; item += gridDim.x * 4) {
+        const uint32_t tile = item >> 1, tn = tile / TK, tk = tile - tn * TK;
+        const int cb = (int)(item & 1) * kRows;
+        const int64_t n0 = (int64_t)tn * kTileN + cb, k0 = (int64_t)tk * kChunkK + 4 * l;
+        float keep = 0.f;  // lane r keeps row cb + r's smallest |w|
+        float4 w[kRows][2];
 #pragma unroll
-            for (int r = 0; r < kRows; ++r) {
-                const int64_t n = tn * kTileN + cb + r < N ? tn * kTileN + cb + r : N - 1;
+        for (int r = 0; r < kRows; ++r) {
+            const int64_t n = n0 + r < N ? n0 + r : N - 1;
 #pragma unroll
-                for (int it = 0; it < 2; ++it) {
-                    const int64_t k = k0 + 256 * it < K ? k0 + 256 * it : K - 4;
-                    w[r][it] = *reinterpret_cast<const float4*>(W + n * ldw + k);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) {
-                const bool row = tn * kTileN + cb + r < N;
-                const bool valid[2] = {row && k0 < K, row && k0 + 256 < K};
-                float mn = __builtin_inff();
-#pragma unroll
-                for (int it = 0; it < 2; ++it) {
-                    float4 v = w[r][it];
-                    const float m4 = fminf(fminf(fabsf(v.x), fabsf(v.y)), fminf(fabsf(v.z), fabsf(v.w)));
-                    if (!valid[it]) v = make_float4(0.f, 0.f, 0.f, 0.f);
-                    else mn = fminf(mn, m4);
-                    const double x = (double)v.x, y = (double)v.y, z = (double)v.z, u = (double)v.w;
-                    s += (x + y) + (z + u);
-                    a += (fabs(x) + fabs(y)) + (fabs(z) + fabs(u));
-                }
-                mn = wave_reduce(mn, OpMin{});
-                if (l == cb + r) keep = mn;
-                const uint32_t dw = row_dword(w[r], valid, 0.f, l);
-                if (l < 16) sm[wave][((l >> 2) * 16 + cb + r) * 4 + (l & 3)] = dw;
+            for (int it = 0; it < 2; ++it) {
+                const int64_t k = k0 + 256 * it < K ? k0 + 256 * it : K - 4;
+                w[r][it] = *reinterpret_cast<const float4*>(W + n * ldw + k);
             }
         }
-        // a wave's own part of sm: LDS serves a wave in order, so the compiler keeping the order of the lanes'
-        // writes, this read and the next tile's writes is all it takes
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const uint4 v = *reinterpret_cast<const uint4*>(&sm[wave][l * 4]);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        *reinterpret_cast<uint4*>(packed + tile_dword_offset(tn, tk, TK) + l * 4) = v;
-        if (l < kTileN) rowmin[task * kTileN + l] = keep;
+        uint32_t dw[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const bool row = n0 + r < N;
+            const bool valid[2] = {row && k0 < K, row && k0 + 256 < K};
+            float mn = __builtin_inff();
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                float4 v = w[r][it];
+                const float m4 = fminf(fminf(fabsf(v.x), fabsf(v.y)), fminf(fabsf(v.z), fabsf(v.w)));
+                if (!valid[it]) v = make_float4(0.f, 0.f, 0.f, 0.f);
+                else mn = fminf(mn, m4);
+                const double x = (double)v.x, y = (double)v.y, z = (double)v.z, u = (double)v.w;
+                s += (x + y) + (z + u);
+                a += (fabs(x) + fabs(y)) + (fabs(z) + fabs(u));
+            }
+            mn = wave_reduce(mn, OpMin{});
+            if (l == r) keep = mn;
+            dw[r] = row_dword(w[r], valid, 0.f, l);
+        }
+        uint32_t* const at = packed + tile_dword_offset(tn, tk, TK);
+#pragma unroll
+        for (int r = 0; r < kRows; r += 4)
+            store_rows(at, l, dw[r], dw[r + 1], dw[r + 2], dw[r + 3], cb + r, cb + r + 1, cb + r + 2, cb + r + 3);
+        if (l < kRows) rowmin[(int64_t)item * kRows + l] = keep;
     }
     s = block_sum<4>(s, smd);
     a = block_sum<4>(a, smd);
@@ -105,11 +111,11 @@ __global__ __launch_bounds__(256, 4) void pack_scan(const float* __restrict__ W,
 
 // ---- alpha, beta, and the rows of tiles whose bits depend on alpha --------------------------------
 // Every workgroup folds the partials for itself (the same sums in the same order, out of L2); workgroup 0
-// writes the two scalars.  A wave looks at the 16 rows of a tile at once and repacks the ones with a
-// weight within |alpha| of zero, four at a time.
+// writes the two scalars.  A wave looks at `nrows` rows of a tile at once (4, 8 or 16) and repacks the ones with
+// a weight within |alpha| of zero, four at a time and two such fours in flight.
 __global__ __launch_bounds__(256) void pack_fix(const float* __restrict__ W, int64_t N, int64_t K,
                                                 int64_t ldw, const double* __restrict__ partials,
-                                                int nparts, double count,
+                                                int nparts, double count, int nrows, bool backwards,
                                                 const float* __restrict__ rowmin,
                                                 uint32_t* __restrict__ packed,
                                                 float* __restrict__ alpha_out,
@@ -130,19 +136,23 @@ __global__ __launch_bounds__(256) void pack_fix(const float* __restrict__ W, int
             *beta_out = (float)(a / count);
         }
     }
-    const int64_t TN = tiles_n(N), TK = tiles_k(K);
-    for (int64_t task = (int64_t)blockIdx.x * 4 + wave; task < TN * TK; task += (int64_t)gridDim.x * 4) {
-        const float mn = l < kTileN ? rowmin[task * kTileN + l] : __builtin_inff();
-        const int64_t tn = task / TK, tk = task % TK, k0 = tk * kChunkK + 4 * l;
-        const int64_t rows = N - tn * kTileN < kTileN ? N - tn * kTileN : kTileN;
-        uint32_t redo = (uint32_t)__ballot(!(mn > fabsf(alpha))) & ((1u << rows) - 1u);
-        while (redo) {  // uniform for the wave
-            int c[4];
-            float4 w[4][2];
-            const bool valid[2] = {k0 < K, k0 + 256 < K};
+    const uint32_t TK = (uint32_t)tiles_k(K), per = kTileN / nrows;  // items of a tile
+    const uint32_t items = (uint32_t)tiles_n(N) * TK * per;           // < 2^31
+    for (uint32_t i = blockIdx.x * 4 + wave; i < items; i += gridDim.x * 4) {
+        const uint32_t item = backwards ? items - 1 - i : i, tile = item / per, tk = tile % TK;
+        const int64_t tn = tile / TK, k0 = (int64_t)tk * kChunkK + 4 * l;
+        const int c0 = (int)(item % per) * nrows;
+        const int64_t left = N - tn * kTileN - c0;
+        const int rows = (int)(left < nrows ? left : nrows);  // may be negative: nothing
+        const float mn = l < rows ? rowmin[(int64_t)tile * kTileN + c0 + l] : __builtin_inff();
+        // a NaN or infinite alpha repacks every row
+        uint32_t redo = (uint32_t)__ballot(l < rows && !(mn > fabsf(alpha)));
+        const bool valid[2] = {k0 < K, k0 + 256 < K};
+        // the next (up to) four rows to repack; a missing one repeats the one before it
+        auto take4 = [&](float4 (&w)[4][2], int (&c)[4]) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                c[r] = redo ? __builtin_ctz(redo) : c[r ? r - 1 : 0];
+                c[r] = redo ? c0 + __builtin_ctz(redo) : c[r ? r - 1 : 0];
                 redo &= redo - 1;
 #pragma unroll
                 for (int it = 0; it < 2; ++it) {
@@ -150,12 +160,21 @@ __global__ __launch_bounds__(256) void pack_fix(const float* __restrict__ W, int
                     w[r][it] = *reinterpret_cast<const float4*>(W + (tn * kTileN + c[r]) * ldw + k);
                 }
             }
+        };
+        auto store4 = [&](const float4 (&w)[4][2], const int (&c)[4]) {
+            uint32_t dw[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t dw = row_dword(w[r], valid, alpha, l);
-                if (l < 16)
-                    packed[tile_dword_offset(tn, tk, TK) + ((l >> 2) * 16 + c[r]) * 4 + (l & 3)] = dw;
-            }
+            for (int r = 0; r < 4; ++r) dw[r] = row_dword(w[r], valid, alpha, l);
+            store_rows(packed + tile_dword_offset(tn, tk, TK), l, dw[0], dw[1], dw[2], dw[3], c[0], c[1], c[2], c[3]);
+        };
+        while (redo) {  // uniform for the wave
+            float4 w0[4][2], w1[4][2];
+            int r0[4], r1[4] = {};
+            take4(w0, r0);
+            const bool more = redo != 0;
+            if (more) take4(w1, r1);
+            store4(w0, r0);
+            if (more) store4(w1, r1);
         }
     }
 }
@@ -322,7 +341,10 @@ int reduce_grid(int64_t count4) {
     return (int)g;
 }
 
-static int scan_grid(int64_t tiles) { return (int)((tiles + 3) / 4 < 1024 ? (tiles + 3) / 4 : 1024); }
+static int scan_grid(int64_t tiles) {
+    const int64_t blocks = (tiles + 1) / 2;  // of four waves with one half tile each
+    return (int)(blocks < 1024 ? blocks : 1024);
+}
 // workspace with which W is read once: the scan's partial sums, then the tiles' smallest |w|
 size_t pack_scan_bytes(int64_t N, int64_t K) {
     const int64_t tiles = tiles_n(N) * tiles_k(K);
@@ -339,8 +361,14 @@ hipError_t launch_pack(const float* W, int64_t N, int64_t K, int64_t ldw, bool b
         const int G = scan_grid(tiles);
         float* rowmin = reinterpret_cast<float*>(partials + 2 * G);
         pack_scan<<<G, 256, 0, s>>>(W, N, K, ldw, packed, rowmin, partials);
-        pack_fix<<<(unsigned)((tiles + 3) / 4 < 2048 ? (tiles + 3) / 4 : 2048), 256, 0, s>>>(W, N, K, ldw, partials, G, (double)N * (double)K, rowmin, packed,
-                                   alpha, beta);
+        // Few tiles: more, shorter items.  W beyond the Infinity Cache: last tiles first, they are still in it
+        // (28672 x 7168 all repacked 333 us -> 317); else in the scan's order, which finds them in the XCD's
+        // own L2 (4096 x 2048 16.0 / 18.9 -> 13.3 / 13.8).
+        const int nrows = tiles <= 512 ? 4 : tiles <= 1024 ? 8 : kTileN;
+        const bool backwards = N * K * 4 > (int64_t)256 << 20;
+        const int64_t blocks = (tiles * (kTileN / nrows) + 3) / 4;
+        pack_fix<<<(unsigned)(blocks < 1280 ? blocks : 1280), 256, 0, s>>>(
+            W, N, K, ldw, partials, G, (double)N * (double)K, nrows, backwards, rowmin, packed, alpha, beta);
         return hipGetLastError();
     }
     const int G = reduce_grid(count4);

@@ -66,29 +66,86 @@ def test_pack_deterministic(bl):
     assert torch.equal(p1, p2) and torch.equal(a1, a2) and torch.equal(b1, b2)
 
 
-@pytest.mark.parametrize("N,K", [(1, 32), (17, 544), (40, 992), (300, 4128), (4100, 2048)])
-def test_pack_weights_near_alpha(bl, N, K):
-    """W is read once and only the rows of a tile with a weight within |alpha| of zero are packed again: zeros
-    of either sign, weights at +-alpha and next to it, rows without any.  With the workspace that only holds
-    the sums, the same bits by the two readings."""
-    print(f"pack near alpha N={N} K={K}", flush=True)
-    W = wl.make_weight(N, K, 0.02, seed=wl.seed_for(0, 3 * N + K))
+def smallest_pack_workspace(bl, W):
+    """What the call requires: the two readings of W.  Smaller sizes are refused on the host."""
+    for size in range(256, bl.workspace_bytes(bl.OP_PACK, 0, *W.shape) + 1, 256):
+        try:
+            bl.bitlinear_pack_weights(W, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+            return size
+        except bl.BitLinearError:
+            pass
+    raise AssertionError("the workspace asked for was refused")
+
+
+def near_alpha_weight(N, K, seed):
+    """Zeros of either sign, weights at +-alpha and next to it, rows without any."""
+    W = wl.make_weight(N, K, 0.02, seed=seed)
     W[np.abs(W) < 1e-4] = 1e-4
     W[0, :2] = [0.0, -0.0]
     for _ in range(3):  # plants weights at the alpha that the matrix then has, or very nearly so
         a, _ = oracle.weight_stats(W)
         W[-1, 4:8] = [a, -a, np.nextafter(a, f32(1)), np.nextafter(a, f32(-1))]
         W[N // 2, K - 1] = a
+    return W
+
+
+# 4, 8 and 16 rows of a tile to an item of the second kernel (up to 512, up to 1024 and more tiles)
+@pytest.mark.parametrize("N,K", [(1, 32), (17, 544), (40, 992), (300, 4128), (4000, 2048), (4100, 2048)])
+def test_pack_weights_near_alpha(bl, N, K):
+    """W is read once and only the rows of a tile with a weight within |alpha| of zero are packed again.  With
+    the workspace that only holds the sums, the same bits by the two readings."""
+    print(f"pack near alpha N={N} K={K}", flush=True)
+    W = near_alpha_weight(N, K, wl.seed_for(0, 3 * N + K))
     a, b = oracle.weight_stats(W)
     words = oracle.pack_canonical(oracle.binarize(W, a))
-    sums_only = -(-16 * min(1024, max(1, -(-(N * K // 4) // 2048))) // 256) * 256
-    full = bl.workspace_bytes(bl.OP_PACK, 0, N, K)
-    assert full >= sums_only
-    for size in (full, sums_only):
+    sizes = {bl.workspace_bytes(bl.OP_PACK, 0, N, K), smallest_pack_workspace(bl, dev(W))}
+    assert len(sizes) == (1 if (N, K) == (1, 32) else 2)  # one tile: the sums' 256 bytes hold its minima too
+    for size in sizes:
         ws = torch.empty(size, dtype=torch.uint8, device="cuda")
         packed, alpha, beta = bl.bitlinear_pack_weights(dev(W), workspace=ws)
         assert host(alpha)[0] == a and host(beta)[0] == b
         assert np.array_equal(host(bl.bitlinear_packed_to_canonical(packed, N, K)).view(np.uint32), words)
+
+
+@pytest.mark.parametrize("N,K,gn,gk", [(96, 2112, 2, 2), (64, 1088, 4, 2), (4128, 1088, 1, 2)])
+def test_pack_grouped_near_alpha(bl, N, K, gn, gk):
+    """The blocks of a grouped matrix (rows further apart than they are long), each with its own alpha."""
+    print(f"pack grouped near alpha N={N} K={K} gn={gn} gk={gk}", flush=True)
+    Ng, Kg = N // gn, K // gk
+    W = np.empty((N, K), f32)
+    for i in range(gn):
+        for j in range(gk):
+            W[i * Ng:(i + 1) * Ng, j * Kg:(j + 1) * Kg] = near_alpha_weight(Ng, Kg, wl.seed_for(0, N + 7 * i + j))
+    a, b = oracle.weight_stats_grouped(W, gn, gk)
+    packed, alpha, beta = bl.bitlinear_pack_weights_grouped(dev(W), gn, gk)
+    assert np.array_equal(host(alpha), a) and np.array_equal(host(beta), b)
+    canon = host(bl.bitlinear_packed_to_canonical_grouped(packed, N, K, gk)).view(np.uint32)
+    assert np.array_equal(canon, oracle.pack_canonical(oracle.binarize_grouped(W, a)))
+
+
+@pytest.mark.parametrize("mean", [0.0, 0.1])
+def test_pack_beyond_the_cache(bl, mean):
+    """More than 256 MB: the second kernel starts at the last tile.  The bits of the two readings."""
+    N, K = 8200, 8224
+    print(f"pack beyond the cache mean={mean}", flush=True)
+    W = torch.randn(N, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(9)) + mean
+    p1, a1, b1 = bl.bitlinear_pack_weights(W)
+    small = torch.empty(smallest_pack_workspace(bl, W), dtype=torch.uint8, device="cuda")
+    p2, a2, b2 = bl.bitlinear_pack_weights(W, workspace=small)
+    assert torch.equal(a1, a2) and torch.equal(b1, b2) and torch.equal(p1, p2)
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+def test_pack_not_finite(bl, value):
+    """Undefined by the interface; here both paths still compare every weight with the alpha they wrote."""
+    print(f"pack with {value}", flush=True)
+    W = dev(wl.make_weight(80, 1056, 0.02, seed=11))
+    W[33, 700] = value
+    small = torch.empty(smallest_pack_workspace(bl, W), dtype=torch.uint8, device="cuda")
+    assert small.numel() < bl.workspace_bytes(bl.OP_PACK, 0, 80, 1056)
+    p1, a1, _ = bl.bitlinear_pack_weights(W)
+    p2, a2, _ = bl.bitlinear_pack_weights(W, workspace=small)
+    assert torch.equal(p1, p2) and torch.equal(torch.isnan(a1), torch.isnan(a2))
 
 
 # ------------------------------------------------------------------ activations (Eq. 12, 4, 5)
