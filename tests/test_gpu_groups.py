@@ -200,6 +200,35 @@ def test_grouped_forward_large_batch_slices(bl, tuning, M, Kg, N, gn, gk):
         _check_forward(bl, M, Kg * gk, N, gn, gk, False, 800 + M)
 
 
+# The fold of the K-groups' sums: one column a thread below 2^18 outputs, four from there on where N is a multiple of
+# four; one row, rows that end inside a workgroup, more groups than columns of scales in a line.
+@pytest.mark.parametrize("per_tensor", [False, True])
+@pytest.mark.parametrize("M,Kg,N,gn,gk", [(1, 64, 48, 3, 2), (16, 160, 16384, 4, 3), (64, 96, 4097, 1, 4),
+                                          (63, 96, 4160, 4, 4), (64, 96, 4100, 1, 9), (130, 544, 2032, 1, 2)])
+def test_fold_of_groups(bl, tuning, M, Kg, N, gn, gk, per_tensor):
+    print(f"fold of groups M={M} Kg={Kg} N={N} gn={gn} gk={gk} per_tensor={per_tensor}", flush=True)
+    K, Ng = Kg * gk, N // gn
+    X, W = layer(M, K, N, 900 + M + gk)
+    packed, _, beta = bl.bitlinear_pack_weights_grouped(dev(W), gn, gk)
+    if M > 64:
+        tuning("prefill_tile=4")
+    y = bl.bitlinear_forward_grouped(dev(X), packed, N, beta, gn, gk, per_tensor=per_tensor)
+    # each block by itself, its terms added in fp32 in the order of the groups: the same bits
+    codes, gamma, rowsum, _ = bl.bitlinear_quant_act_grouped(dev(X), gk, per_tensor=per_tensor)
+    ref = None
+    for g in range(gk):
+        sl = slice(g * Kg, (g + 1) * Kg)
+        gam = gamma.reshape(-1, gk)[:, g].contiguous()
+        cols = []
+        for n in range(gn):
+            p, _, b = bl.bitlinear_pack_weights(dev(W[n * Ng:(n + 1) * Ng, sl]))
+            cols.append(bl.bitlinear_matmul(codes[:, sl].contiguous(), gam, rowsum.reshape(M, gk)[:, g].contiguous(),
+                                            p, Ng, b, per_tensor=per_tensor))
+        term = torch.cat(cols, 1)
+        ref = term if ref is None else term + ref
+    assert torch.equal(y, ref)
+
+
 @pytest.mark.parametrize("M,Kg,N,gn,gk", [(130, 96, 272, 1, 2), (70, 544, 40, 1, 3)])
 def test_grouped_forward_zero_keeps_its_sign(bl, tuning, M, Kg, N, gn, gk):
     """Weights of zero (beta_g = 0): every group's term is a zero with the sign of its integer sum, and the
