@@ -87,8 +87,8 @@ __device__ inline void lds_wait(v4i (&a)[2]) {
 // its own blob) and its sums go, without being added, to that group's slice of a.split_ws.
 // gmode 1: a work item is (column tile, one K-group of the layer), split over the workgroup's four.
 // NS = stages in each group's ring.
-// ROWS = false: one row tile (M <= BM).
-template <int BM, int NS, bool ROWS>
+// ROWS = false: one row tile (M <= BM).  STREAM: streaming stores (streaming_stores below).
+template <int BM, int NS, bool ROWS, bool STREAM>
 __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int grid_m, int grid_n,
                                                                 int splits, int gmode) {
     using namespace mid;
@@ -387,13 +387,17 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // are walked by adding the pitch, with a count of the valid ones where the tile is ragged.
     const bool inside = m0 + BM <= M && n0 + BN <= N;  // uniform
     const int prow = wm * 64 + 4 * g2, pcol = wn * 64 + j;  // of piece q: + 32 (q / 8) + 8 (q % 4), + 32 (q / 4 % 2)
+    auto put = [](auto v, auto* at) {
+        if constexpr (STREAM) __builtin_nontemporal_store(v, at);
+        else *at = v;
+    };
     auto store_sums = [&](const v4i& p, int q, int64_t grp) {
         const int64_t m = m0 + prow + 32 * (q >> 3) + 8 * (q & 3), n = n0 + pcol + 32 * ((q >> 2) & 1);
         int32_t* o = a.split_ws + (grp * M + m) * N + n;
         const int rows = n < N ? (int)(M - m < 4 ? M - m : 4) : 0;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr, o += N)
-            if (inside || rr < rows) __builtin_nontemporal_store(2 * p[rr], o);
+            if (inside || rr < rows) put(2 * p[rr], o);
     };
     if (!add_groups) {  // each group's sums to its layer group's slice
         if (lgrp < a.kgroups)
@@ -435,7 +439,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
                 float y = (float)pm * (beta * (gm[rr] * 0.0078125f));
                 if constexpr (ETA) y = y + (beta * eta[rr]) * ws;  // Eq. 6
                 if (KIND == 2 && a.accumulate && rr < rows) y += *o;  // a later K-group (Eq. 13-15)
-                if (KIND == 0 || rr < rows) __builtin_nontemporal_store(y, o);  // streaming, as in the large tiles
+                if (KIND == 0 || rr < rows) put(y, o);
             }
         }
     };
@@ -500,6 +504,15 @@ size_t mid_split_bytes(int64_t M, int64_t N, int64_t K) {
     return bytes > gemm_split_ws_bytes(M, N, K) ? bytes : 0;
 }
 
+// Whether a launch's stores are streaming: whole lines only (others 1 % slower), the slices of a K split (64 x 7168 ->
+// 7168 21.3 us / 20.6), and outputs from 4 MiB on (200 x 4096 -> 16384 22.5 / 21.15; of layers at 65 to 4096
+// tokens 1.3 % by themselves and still 0.7 % with a pass over Y behind; smaller outputs lose 0.5 % with that pass).
+// Slices of K-groups are not: their fold gets slower by more (64 x 6144 -> 21860 in four groups 36 / 31).
+static bool streaming_stores(const GemmArgs& a, int splits, bool grouped) {
+    if (grouped || (a.N | a.ldy) & 31) return false;
+    return splits > 1 || a.M * a.ldy >= (int64_t)1 << 20;
+}
+
 // 16 < M <= 64.  K is also split over workgroups (second kernel: splitk_reduce) when N gives
 // few tiles and the caller brought the workspace for it, as mid_slice_tiles decides.
 hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
@@ -525,7 +538,11 @@ hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
         a.tk_pitch = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
         a.split_k = per * kChunkK;
     }
-    gemm_mid_kernel<64, 4, false><<<dim3((unsigned)grid_n, (unsigned)splits), mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
+    const dim3 grid((unsigned)grid_n, (unsigned)splits);
+    if (streaming_stores(a, splits, gmode != 0))
+        gemm_mid_kernel<64, 4, false, true><<<grid, mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
+    else
+        gemm_mid_kernel<64, 4, false, false><<<grid, mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
     if (splits > 1 || gmode) launch_splitk_reduce(a, gmode ? a.kgroups : splits, s);
     return hipGetLastError();
 }
@@ -547,10 +564,12 @@ hipError_t launch_gemm_mid_tiles(const GemmArgs& a_in, int bm, int64_t per, hipS
     int64_t items = (int64_t)grid_m * grid_n * splits;
     if (items > ((int64_t)1 << 30)) return hipErrorInvalidValue;
     items = (items + 7) / 8 * 8;
-    if (bm == 64)
-        gemm_mid_kernel<64, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, grouped);
-    else
-        gemm_mid_kernel<128, 4, true><<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, grouped);
+    auto launch = [&](auto kernel) {
+        kernel<<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, grouped);
+    };
+    const bool streaming = streaming_stores(a, splits, grouped);
+    if (bm == 64) launch(streaming ? gemm_mid_kernel<64, 4, true, true> : gemm_mid_kernel<64, 4, true, false>);
+    else launch(streaming ? gemm_mid_kernel<128, 4, true, true> : gemm_mid_kernel<128, 4, true, false>);
     if (splits > 1) launch_splitk_reduce(a, splits, s);
     return hipGetLastError();
 }
