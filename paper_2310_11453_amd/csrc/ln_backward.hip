@@ -13,11 +13,30 @@
 
 namespace bl {
 
+// Sum over a wave for these kernels: the four row totals are read back as scalars.  Two sums of doubles are
+// too few to hide the lane swaps of wave_reduce: 33 to 128 rows of 2048 take 4.3 us this way, 4.6 with those.
+template <int CTRL>
+__device__ inline double dpp_row(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false));
+}
+__device__ inline double lane_value(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ inline double row_sum(double v) {
+    v += dpp_row<0xB1>(v);   // quad_perm [1,0,3,2]
+    v += dpp_row<0x4E>(v);   // quad_perm [2,3,0,1]
+    v += dpp_row<0x141>(v);  // row_half_mirror
+    v += dpp_row<0x140>(v);  // row_mirror
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
 // One to eight waves own one row (a token, or one K-group of a token); x and g of the row
 // stay in registers (NV float4 per lane each).  Statistics and the two means are fp64, as in
 // the forward kernel.  Rows are the consecutive K-element pieces of X, so a K-group of a
-// token is simply a row of its own.
-template <int WPR, int NV>
+// token is simply a row of its own.  STREAM: streaming stores of dX (launch_ln_backward).
+template <int WPR, int NV, bool STREAM>
 __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_backward_rows(LnBackwardArgs a) {
     constexpr int NW = WPR < 4 ? 4 : WPR;
     constexpr int RT = WPR * kWave;
@@ -69,8 +88,8 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_backward_ro
             q = fma(dw - c, dw - c, q);
         }
     }
-    s = wave_reduce(s, OpSum{});
-    q = wave_reduce(q, OpSum{});
+    s = row_sum(s);
+    q = row_sum(q);
     if constexpr (WPR > 1) {
         if ((threadIdx.x & (kWave - 1)) == 0) {
             smd[0][wave] = s;
@@ -113,8 +132,8 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_backward_ro
             c2 = fma((double)g[j].w, (double)x[j].w, c2);
         }
     }
-    c1 = wave_reduce(c1, OpSum{});
-    c2 = wave_reduce(c2, OpSum{});
+    c1 = row_sum(c1);
+    c2 = row_sum(c2);
     if constexpr (WPR > 1) {
         if ((threadIdx.x & (kWave - 1)) == 0) {
             smd[2][wave] = c1;
@@ -140,8 +159,11 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_backward_ro
         o.y = r * ((g[j].y - m1) - x[j].y * m2);
         o.z = r * ((g[j].z - m1) - x[j].z * m2);
         o.w = r * ((g[j].w - m1) - x[j].w * m2);
-        if (idx < K4 && live)  // streaming: not read again soon
-            __builtin_nontemporal_store((v4f){o.x, o.y, o.z, o.w}, reinterpret_cast<v4f*>(d4 + idx));
+        if (idx < K4 && live) {
+            if constexpr (STREAM)
+                __builtin_nontemporal_store((v4f){o.x, o.y, o.z, o.w}, reinterpret_cast<v4f*>(d4 + idx));
+            else d4[idx] = o;
+        }
     }
 }
 
@@ -172,8 +194,8 @@ __global__ __launch_bounds__(512) void ln_backward_long(LnBackwardArgs a) {
         q = fma(dz - c, dz - c, q);
         q = fma(dw - c, dw - c, q);
     }
-    s = wave_reduce(s, OpSum{});
-    q = wave_reduce(q, OpSum{});
+    s = row_sum(s);
+    q = row_sum(q);
     if (lead) {
         smd[0][wave] = s;
         smd[1][wave] = q;
@@ -217,8 +239,8 @@ __global__ __launch_bounds__(512) void ln_backward_long(LnBackwardArgs a) {
         c2 = fma((double)gh.z, (double)xn.z, c2);
         c2 = fma((double)gh.w, (double)xn.w, c2);
     }
-    c1 = wave_reduce(c1, OpSum{});
-    c2 = wave_reduce(c2, OpSum{});
+    c1 = row_sum(c1);
+    c2 = row_sum(c2);
     if (lead) {
         smd[2][wave] = c1;
         smd[3][wave] = c2;
@@ -346,7 +368,13 @@ int ln_backward_chunks(int64_t tokens, int64_t width) {
 template <int WPR, int NV>
 static void launch_rows(const LnBackwardArgs& a, hipStream_t s) {
     constexpr int NW = WPR < 4 ? 4 : WPR, RPW = NW / WPR;
-    ln_backward_rows<WPR, NV><<<(unsigned)((a.M + RPW - 1) / RPW), NW * kWave, 0, s>>>(a);
+    // Streaming stores of dX where they pay with a reader behind them, us with a pass over dX: 1000 x 2048 11.9 /
+    // 11.3 with them, 333 x 7168 14.2 / 13.0, 1200 x 4096 19.6 / 19.0; but 64 x 2048 6.2 / 6.6, 3000 x 2048 20.8 / 22.4,
+    // 8192 x 4096 124 / 128 (there the call by itself 75 / 61, and the reader pays for it).
+    const int64_t out = a.M * a.K;
+    const auto kernel = out >= (int64_t)1 << 20 && out <= (int64_t)5 << 20 ? ln_backward_rows<WPR, NV, true>
+                                                                          : ln_backward_rows<WPR, NV, false>;
+    kernel<<<(unsigned)((a.M + RPW - 1) / RPW), NW * kWave, 0, s>>>(a);
 }
 
 // a.M counts rows of a.K elements (tokens * groups); a.rowstats must be given when dgain or

@@ -44,7 +44,10 @@ SHAPES = [(1, 32, 1), (5, 96, 1), (33, 256, 1), (100, 2048, 1), (17, 4096, 1), (
           (5, 28672, 1), (3, 36000, 1), (2, 65536, 1), (4, 57344, 2),
           # column sums over several chunks of tokens, the last one short, and a width that is not
           # a multiple of a workgroup's 256 columns
-          (1000, 288, 1), (531, 2048, 1), (65, 1184, 37)]
+          (1000, 288, 1), (531, 2048, 1), (65, 1184, 37),
+          # outputs of 4 to 20 MB are streaming stores: two rows to a workgroup with the last one alone, eight
+          # waves to a row, and the sizes around the upper line
+          (257, 4096, 1), (65, 16384, 1), (2560, 2048, 8), (2561, 2048, 8)]
 
 
 @pytest.mark.parametrize("M,K,groups", SHAPES)
