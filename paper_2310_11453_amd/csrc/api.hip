@@ -57,9 +57,6 @@ bool parse_tuning(const char* spec, Tuning& out) {
 }
 
 constexpr int64_t kMaxDim = (int64_t)1 << 30;
-// The GEMM kernels keep partial sums scaled by up to 2^14 per element of K in int32 and byte
-// offsets into a block of rows in 32 bits: both hold up to this K.
-constexpr int64_t kMaxGemmK = 65536;
 constexpr int kMaxGroups = 64;
 constexpr unsigned kKnownFlags = BL_FLAG_SKIP_LN | BL_FLAG_OUT_ACC_I32 | BL_FLAG_BETA_CENTERED;
 

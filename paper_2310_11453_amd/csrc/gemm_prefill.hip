@@ -16,7 +16,7 @@
 //    right before use, never as bytes in LDS:
 //        b = (w << (7 - i)) & 0x80808080     four {0,-128} bytes, two VALU operations
 //    amortised over the WTM/32 MFMAs that reuse the operand.  The MFMA accumulates
-//    -128 sum_k q b (K <= 65536: below 2^30); the epilogue restores sum_k q s = 2 sum_k q b - sum_k q
+//    -128 sum_k q b (K <= kMaxGemmK: at most 2^30); the epilogue restores sum_k q s = 2 sum_k q b - sum_k q
 //    with the row sums of the codes that the quantiser already produced.
 //  * Which operand is which, and the value a set bit has, cost power, and at large batches power is
 //    what the clock is made of: a register-resident loop over these operands reaches 4.65 POP/s with the
@@ -961,12 +961,13 @@ size_t group_split_bytes(int64_t M, int64_t N, int64_t K, int groups) {
     return (size_t)groups * M * N * 4;
 }
 
-// K < 2^22 is required (the per-lane offset into a block of 256 rows is kept in 32 bits).
+// K <= kMaxGemmK (a group's K: the large tiles sum up to 2^14 per element of it in int32) and rows of codes below
+// 2^22 bytes (the per-lane offset into a block of 256 of them is kept in 32 bits).
 hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
     GemmArgs a = a_in;
     a.split_k = 0;  // set here only
     if (!a.ldy) a.ldy = a.N;
-    if (a.K >= ((int64_t)1 << 22) || a.ldq >= ((int64_t)1 << 22)) return hipErrorInvalidValue;
+    if (a.K > kMaxGemmK || a.ldq >= ((int64_t)1 << 22)) return hipErrorInvalidValue;
     if (a.M <= 64) {  // up to 32 tokens: gemm_stream.hip where it takes the shape; else gemm_mid.hip
         if (!tuning().mid_only && a_in.kgroups <= 1 && launch_gemm_stream(a_in, s)) return hipGetLastError();
         return launch_gemm_mid(a_in, s);

@@ -5,6 +5,10 @@
 
 namespace bl {
 
+// The GEMM kernels keep partial sums scaled by up to 2^14 per element of K in int32 and byte
+// offsets into a block of rows in 32 bits: both hold up to this K (of a K-group).
+constexpr int64_t kMaxGemmK = 65536;
+
 // Launch-time switches for tests and benchmarks (bitlinear_set_tuning in the C ABI; defaults:
 // everything 0 = the launchers decide).  One process-wide instance, defined in api.hip.
 struct Tuning {

@@ -251,6 +251,26 @@ def test_matmul_acc_bit_exact_and_y(bl, M, K, N):
     assert np.array_equal(host(acc), np.repeat((-128 * sign.astype(np.int64).sum(1))[None], M, 0))
 
 
+# the longest K: sums of 2^14 per element, 2^30 in all, in the large tiles
+@pytest.mark.parametrize("spec", ["prefill_tile=1", "prefill_tile=2", "prefill_tile=3", "prefill_tile=4"])
+def test_matmul_longest_k(bl, tuning, spec):
+    print(f"longest K {spec}", flush=True)
+    M, K, N = 130, 65536, 272
+    W = torch.ones(N, K, device="cuda")
+    W[1::2] = -1.0
+    packed, alpha, beta = bl.bitlinear_pack_weights(W)
+    assert host(alpha)[0] == 0.0
+    ones = torch.ones(M, device="cuda")
+    tuning(spec)
+    for q in (-128, 127):
+        codes = torch.full((M, K), q, dtype=torch.int8, device="cuda")
+        rowsum = torch.full((M,), q * K, dtype=torch.int32, device="cuda")
+        acc = bl.bitlinear_matmul(codes, ones, rowsum, packed, N, beta, flags=bl.FLAG_OUT_ACC_I32)
+        assert torch.equal(acc, (q * K * W[:, 0].int())[None].expand(M, N))
+        y = bl.bitlinear_matmul(codes, ones, rowsum, packed, N, beta)
+        assert torch.equal(y, acc.float() / 128.0)
+
+
 def _random_shapes(n, seed):
     """Seeded shapes across the three GEMM kernels' ranges of M, with K a multiple of 32 and any N."""
     rng = np.random.default_rng(seed)
