@@ -474,9 +474,10 @@ int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K) {
 
 // What the launch takes of ws_bytes: the slices of least cost, in us: a round of items 3.5 + 4.1 c (c
 // 512-chunks per K-group of the workgroup), the slices 6.5 and their sums written and read at 5 TB/s.
-// The layer, M x K x N: 64 x 7168 x 7168 20.4 us in 4 slices, 20.2 in 2, 20.8 without; 48 x 4096 x 12288
-// 15.2 us without, 20.6 in 2; 48 x 16384 x 4096 22.3 in the 8 taken, 24.5 in 4, 32.6 without; 40 x 8192 x
-// 2048 16.3 in 4, 20.6 without.  Returns 512-chunks per slice, 0 = no slices.
+// The layer, us, M x K x N: 64 x 7168 x 7168 18.8 in 4 slices, 19.7 in 2, 19.9 without; 48 x 4096 x 12288
+// 14.5 without, 17.0 in 2; 48 x 16384 x 4096 20.1 in the 8 taken, 20.7 in 4, 31.4 without; 48 x 8192 x
+// 2048 15.6 in the 4 taken, 17.8 in 2, 20.1 without.  Over 54 shapes (18 K x N, 33 to 64 tokens) the slices taken
+// are at most 1.2 % slower than the best number of them.  Returns 512-chunks per slice, 0 = no slices.
 static int64_t mid_slice_tiles(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
     const int64_t TK = tiles_k(K), tiles = (N + mid::BN - 1) / mid::BN;
     if (const int64_t per = tuning().mid_split_tiles)

@@ -849,9 +849,10 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 //   a round of the 128 x 128 and 64 x 128 tiles  3.5 + 4.2 c   (c = 1: 7.5, 2: 12, 4: 20)
 //   slices of K                  6.5 + the int32 sums written and read at 5 TB/s
 // The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
-// ones win; the layer, us: 333 x 2048 x 2048 13.6 (64 x 128) against 24.1 (128 x 256), 200 x 4096 x 16384
-// 24.9 (128 x 128) against 34, 333 x 8192 x 2048 25.5 (64 x 128; in 2 slices 26.2) against 56, 200 x 16384 x
-// 4096 32.6 (64 x 128 in 2 slices; without 37); 1000 x 2048 x 8192 stays with 128 x 256: 26.1 against 33.6.
+// ones win; the layer, us, M x K x N: 333 x 2048 x 2048 12.8 (64 x 128) against 19.4 (128 x 256), 200 x 4096 x
+// 16384 22.3 (128 x 128) against 30.2, 333 x 8192 x 2048 25.4 (64 x 128; in 2 slices 25.0) against 51.9, 200 x
+// 16384 x 4096 31.3 (64 x 128 in 2 slices; without 36.1).  Over 126 shapes of 65 to 512 tokens the plan is 0.6 %
+// slower than the best of all these on average, 6.4 % at most (333 x 7168 x 28672 82.9, 77.9 as 128 x 128).
 struct TilePlan {
     int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
     int64_t per;  // 512-chunks of K per slice (3 and 4)
