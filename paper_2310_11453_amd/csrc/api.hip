@@ -208,7 +208,6 @@ void plain_fields(GemmArgs& a) {
     a.gstride = 1;
     a.beta_rows = a.N;
     a.beta_stride = 0;
-    a.accumulate = false;
 }
 
 // ---- scratch memory the library owns (bitlinear_forward_static) ------------------------
@@ -586,51 +585,29 @@ static int forward_grouped_impl(const float* X, int64_t M, int64_t K, const void
     // each K-group is dequantised with its own beta_g * gamma_g (and shifted by its own eta_g, Eq. 14)
     // and added (Eq. 13-14)
     const int64_t Kg = K / groups_k;
-    const size_t blob_dwords = tiles_bytes(N, Kg) / 4;
-    const bool per_tensor = granularity == BL_GAMMA_PER_TENSOR;
+    GemmArgs a{};
+    a.codes = codes; a.gamma = gamma; a.rowsum = rowsum;
+    a.M = M; a.K = Kg; a.N = N;
+    a.packed = (const uint32_t*)packed; a.beta = beta;
+    a.per_tensor = granularity == BL_GAMMA_PER_TENSOR;
+    a.Y = Y;
+    a.ldq = K; a.gstride = groups_k; a.beta_rows = N / groups_n; a.beta_stride = groups_k;
+    if (nonneg) {
+        a.eta = eta;
+        a.wsum = wsum;
+    }
     if (groups_k > 1) {
         // One launch for all K-groups.  Up to 64 tokens, and above where tiles are few and the
         // workspace has the room, every K-group is a slice of the launch, and the fold that
         // follows dequantises each group's sums with its own scales and adds them in the order
         // 0, 1, ...; else gemm_group_kernel walks a tile's groups itself and keeps the fp32 sum in
         // registers.  Y is written once.
-        GemmArgs a{};
-        a.codes = codes; a.gamma = gamma; a.rowsum = rowsum;
-        a.M = M; a.K = Kg; a.N = N;
-        a.packed = (const uint32_t*)packed; a.beta = beta;
-        a.per_tensor = per_tensor;
-        a.Y = Y;
-        a.ldq = K; a.gstride = groups_k; a.beta_rows = N / groups_n; a.beta_stride = groups_k;
-        if (nonneg) {
-            a.eta = eta;
-            a.wsum = wsum;
-        }
-        a.kgroups = groups_k; a.group_packed = (int64_t)blob_dwords;
+        a.kgroups = groups_k; a.group_packed = (int64_t)(tiles_bytes(N, Kg) / 4);
         a.split_ws = (int32_t*)(base + ws.split); a.split_ws_bytes = ws.split_bytes;
-        if (M > 64) offer_slices(a, base, ws.total, workspace_bytes);
-        return check_hip(M <= 16 ? launch_gemm_decode(a, (hipStream_t)stream)
-                                 : launch_gemm_prefill(a, (hipStream_t)stream));
     }
-    for (int gk = 0; gk < groups_k; ++gk) {
-        GemmArgs a{};
-        a.codes = codes + gk * Kg; a.gamma = gamma + gk; a.rowsum = rowsum + gk;
-        a.M = M; a.K = Kg; a.N = N;
-        a.packed = (const uint32_t*)packed + gk * blob_dwords; a.beta = beta + gk;
-        a.per_tensor = per_tensor;
-        a.out_acc = false;
-        a.Y = Y;
-        a.ldq = K; a.gstride = groups_k; a.beta_rows = N / groups_n; a.beta_stride = groups_k;
-        a.accumulate = gk > 0;
-        if (nonneg) {
-            a.eta = eta + gk;
-            a.wsum = wsum + (int64_t)gk * N;
-        }
-        if (M > 32) offer_slices(a, base, ws.total, workspace_bytes);
-        const hipError_t e = M <= 16 ? launch_gemm_decode(a, (hipStream_t)stream)
-                                     : launch_gemm_prefill(a, (hipStream_t)stream);
-        if (e != hipSuccess) return BL_ERR_HIP;
-    }
-    return BL_OK;
+    if (M > (groups_k > 1 ? 64 : 32)) offer_slices(a, base, ws.total, workspace_bytes);
+    return check_hip(M <= 16 ? launch_gemm_decode(a, (hipStream_t)stream)
+                             : launch_gemm_prefill(a, (hipStream_t)stream));
 }
 
 int bitlinear_forward_grouped(const float* X, int64_t M, int64_t K, const void* packed, int64_t N,

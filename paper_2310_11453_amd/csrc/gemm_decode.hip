@@ -512,13 +512,12 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                     o[r] = o[r] + be * (float)a.wsum[n + r < a.N ? n + r : a.N - 1];
             }
             if ((a.N & 3) == 0) {
-                if (a.accumulate) o += *reinterpret_cast<const v4f*>(y);  // a later K-group
                 // not a streaming store: no faster for whole lines, 0.3 us slower for others (8 x 6144 -> 21860 11.3 ->
                 // 11.7 us), and the next reader of Y pays (2048 -> 2048 and a pass over Y: 5.9 us -> 6.3)
                 *reinterpret_cast<v4f*>(y) = o;
             } else {
                 for (int r = 0; r < 4; ++r)
-                    if (n + r < a.N) y[r] = a.accumulate ? y[r] + o[r] : o[r];
+                    if (n + r < a.N) y[r] = o[r];
             }
         }
     }
@@ -567,7 +566,6 @@ __global__ __launch_bounds__(256) void splitk_reduce(GemmArgs a, int splits) {
             y[c] = (float)pm[c] * ((beta[c] * gm) / 128.0f);
             if (a.eta) y[c] = y[c] + (beta[c] * eta) * wsum[c];
         }
-        if (a.accumulate) y += *o;
         *o = y;
     }
 }

@@ -411,7 +411,7 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         for (int i = 0; i < OWN; ++i) store_sums(own[i], kg * OWN + i, sp);
         return;
     }
-    // kind 0: a tile inside the output; 1: a ragged one; 2: a ragged one or any, with the options below
+    // kind 0: a tile inside the output; 1: a ragged one; 2: either, int32 output
     auto store = [&](auto with_eta, auto kind) {
         constexpr bool ETA = decltype(with_eta)::value;
         constexpr int KIND = decltype(kind)::value;
@@ -431,24 +431,23 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr, o += a.ldy) {
                 const int pm = 2 * own[i][rr] - rs[rr];
-                if (KIND == 2 && a.out_acc) {
+                if constexpr (KIND == 2) {
                     if (rr < rows) *reinterpret_cast<int*>(o) = pm;
                     continue;
                 }
                 // beta * (gamma / 128) has the bits of (beta * gamma) / 128 (gamma / 128 is exact)
                 float y = (float)pm * (beta * (gm[rr] * 0.0078125f));
                 if constexpr (ETA) y = y + (beta * eta[rr]) * ws;  // Eq. 6
-                if (KIND == 2 && a.accumulate && rr < rows) y += *o;  // a later K-group (Eq. 13-15)
                 if (KIND == 0 || rr < rows) put(y, o);
             }
         }
     };
     auto store_kind = [&](auto with_eta) {
-        if (a.out_acc || a.accumulate) store(with_eta, std::integral_constant<int, 2>{});
-        else if (inside) store(with_eta, std::integral_constant<int, 0>{});
+        if (inside) store(with_eta, std::integral_constant<int, 0>{});
         else store(with_eta, std::integral_constant<int, 1>{});
     };
-    if (a.eta) store_kind(std::true_type{});
+    if (a.out_acc) store(std::false_type{}, std::integral_constant<int, 2>{});
+    else if (a.eta) store_kind(std::true_type{});
     else store_kind(std::false_type{});
 }
 

@@ -425,7 +425,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                           : 1.f;
         const uint32_t sc_base = (uint32_t)(uintptr_t)&smScale[parity][wm * WTM + 4 * g2];
         const uint32_t rs_base = (uint32_t)(uintptr_t)&smRowsum[parity][wm * WTM + 4 * g2];
-        const bool special = a.out_acc || (GEN && (a.eta != nullptr || a.accumulate));
+        const bool special = a.out_acc || (GEN && a.eta != nullptr);
         float wcol[NI];  // Eq. 6 only
 #pragma unroll
         for (int s = 0; s < NI; ++s)
@@ -455,12 +455,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                     return y;
                 });
         };
-        if (!a.out_acc && !a.accumulate &&  // uniform
+        if (!a.out_acc &&  // uniform
             (BM < 256 || (m0 + BM <= M && n0 + BN <= a.N && a.ldy < (1 << 24)))) {
             if (GEN && a.eta) store_plain(std::integral_constant<bool, GEN>{});
             else store_plain(std::false_type{});
         } else {
-            // a 256-row tile at an edge, int32 output, or a later K-group added.  Register allocation here is at the limit of 256 and
+            // a 256-row tile at an edge, or int32 output.  Register allocation here is at the limit of 256 and
             // sensitive to the form of these loops: hoisting the uniform branches into a second copy of the
             // loops, or naming the row index as a 32-bit temporary, makes the compiler precompute the
             // store addresses and spill over a hundred registers.
@@ -492,7 +492,6 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
                                         (uint32_t)(uintptr_t)&smEta[parity][wm * WTM + 32 * mi + 8 * rq + 4 * g2 + rr]);
                                     y = y + (bcol[s] * e) * wcol[s];
                                 }
-                                if (GEN && a.accumulate) y += a.Y[m * a.ldy + n];
                             }
                             __builtin_nontemporal_store(y, &a.Y[m * a.ldy + n]);
                         }
@@ -820,7 +819,7 @@ static int num_cus() {
 
 template <int BM, int BN, int WM, int WN, int NS>
 static void launch_tile(const GemmArgs& a, hipStream_t s) {
-    const bool plain = a.beta_rows >= a.N && a.gstride == 1 && !a.eta && !a.accumulate;
+    const bool plain = a.beta_rows >= a.N && a.gstride == 1 && !a.eta;
     const int grid_m = (int)((a.M + BM - 1) / BM), grid_n = (int)((a.N + BN - 1) / BN);
     const int ntiles = grid_m * grid_n;
     int grid = num_cus();  // one workgroup per CU

@@ -237,7 +237,6 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
                     // beta * (gamma / 128) has the bits of (beta * gamma) / 128
                     float y = (float)(sum[j] - tok_sum[m]) * (beta * sc);
                     if (KIND == 2 && a.eta) y = y + (beta * tok_eta[m]) * (float)a.wsum[nj];       // Eq. 6
-                    if (KIND == 2 && a.accumulate && n + j < N) y += __uint_as_float(dst[j]);  // a later K-group
                     o[j] = __float_as_uint(y);
                 }
             }
@@ -253,7 +252,7 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
         }
     };
     if (a.split_k || a.out_acc) finish(std::integral_constant<int, 1>{});
-    else if (one_beta && !a.eta && !a.accumulate) finish(std::integral_constant<int, 0>{});
+    else if (one_beta && !a.eta) finish(std::integral_constant<int, 0>{});
     else finish(std::integral_constant<int, 2>{});
 }
 

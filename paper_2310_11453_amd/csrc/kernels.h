@@ -94,7 +94,6 @@ struct GemmArgs {
     int64_t gstride;      // gamma[m * gstride], rowsum[m * gstride] belong to token m
     int64_t beta_rows;    // output columns n per beta group (a multiple of 16, or N)
     int64_t beta_stride;  // beta[(n / beta_rows) * beta_stride] scales column n
-    bool accumulate;      // Y += result (a later K-group) instead of Y = result
     // Eq. 6: Y += (beta * eta[m * gstride]) * wsum[n] (eta[0] per tensor), wsum[n] = sum_k s[n,k];
     // nullptr otherwise
     const float* eta;
