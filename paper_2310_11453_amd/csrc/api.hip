@@ -117,7 +117,7 @@ ForwardWs forward_ws(int64_t M, int64_t N, int64_t K, int granularity) {
     w.xhat = off;  // one token: the normalised row, fp32 [K] (what the codes were rounded from)
     off += M == 1 ? align256((size_t)K * 4) : 0;
     w.total = off;
-    w.full = off + prefill_split_bytes(M, N, K);
+    w.full = off + prefill_split_bytes(M, N, K, true);
     return w;
 }
 
@@ -142,7 +142,7 @@ QuantWs quant_ws_grouped(int64_t M, int groups_k, int granularity) {
 size_t group_slices_bytes(int64_t M, int64_t N, int groups_k) {
     return groups_k > 1 && M <= 64 ? (size_t)groups_k * (size_t)M * (size_t)N * 4 : 0;
 }
-ForwardWs forward_ws_grouped(int64_t M, int64_t N, int64_t K, int groups_k, int granularity) {
+ForwardWs forward_ws_grouped(int64_t M, int64_t N, int64_t K, int groups_n, int groups_k, int granularity) {
     ForwardWs w{};
     size_t off = 0;
     w.codes = off;
@@ -157,7 +157,7 @@ ForwardWs forward_ws_grouped(int64_t M, int64_t N, int64_t K, int groups_k, int 
     w.split_bytes = group_slices_bytes(M, N, groups_k);
     off += align256(w.split_bytes);
     w.total = off;
-    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K)
+    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K, groups_n == 1)
                                   : group_split_bytes(M, N, K / groups_k, groups_k));
     return w;
 }
@@ -175,7 +175,7 @@ LnBackwardWs ln_backward_ws(int64_t M, int64_t K, int groups_k) {
     return w;
 }
 // Eq. 6: codes, then gamma and (xhat field) eta, row sums, the quantiser's own scratch
-ForwardWs forward_ws_nonneg(int64_t M, int64_t N, int64_t K, int groups_k, int granularity) {
+ForwardWs forward_ws_nonneg(int64_t M, int64_t N, int64_t K, int groups_n, int groups_k, int granularity) {
     ForwardWs w{};
     size_t off = 0;
     w.codes = off;
@@ -192,7 +192,7 @@ ForwardWs forward_ws_nonneg(int64_t M, int64_t N, int64_t K, int groups_k, int g
     w.split_bytes = group_slices_bytes(M, N, groups_k);
     off += align256(w.split_bytes);
     w.total = off;
-    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K)
+    w.full = off + (groups_k == 1 ? prefill_split_bytes(M, N, K, groups_n == 1)
                                   : group_split_bytes(M, N, K / groups_k, groups_k));
     return w;
 }
@@ -280,11 +280,11 @@ size_t bitlinear_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int gr
             return ln_backward_ws(M, K, 1).total;
         case BL_OP_FORWARD_NONNEG:
             if (M < 0 || M > kMaxDim || !shape_ok(N, K)) return 0;
-            return forward_ws_nonneg(M, N, K, 1, granularity).full;
+            return forward_ws_nonneg(M, N, K, 1, 1, granularity).full;
         case BL_OP_MATMUL:
             if (M < 0 || M > kMaxDim || !shape_ok(N, K)) return 0;
             // 0 for most shapes: nothing is needed
-            return std::max(M <= 64 ? gemm_split_ws_bytes(M, N, K) : 0, prefill_split_bytes(M, N, K));
+            return std::max(M <= 64 ? gemm_split_ws_bytes(M, N, K) : 0, prefill_split_bytes(M, N, K, true));
         default:
             return 0;
     }
@@ -451,11 +451,11 @@ size_t bitlinear_workspace_bytes_grouped(int op, int64_t M, int64_t N, int64_t K
         case BL_OP_QUANT:
             return quant_ws_grouped(M, groups_k, granularity).total;
         case BL_OP_FORWARD:
-            return forward_ws_grouped(M, N, K, groups_k, granularity).full;
+            return forward_ws_grouped(M, N, K, groups_n, groups_k, granularity).full;
         case BL_OP_LN_BACKWARD:
             return ln_backward_ws(M, K, groups_k).total;
         case BL_OP_FORWARD_NONNEG:
-            return forward_ws_nonneg(M, N, K, groups_k, granularity).full;
+            return forward_ws_nonneg(M, N, K, groups_n, groups_k, granularity).full;
         default:
             return 0;
     }
@@ -570,8 +570,8 @@ static int forward_grouped_impl(const float* X, int64_t M, int64_t K, const void
     if (K / groups_k > kMaxGemmK) return BL_ERR_UNSUPPORTED;
     if (M == 0) return BL_OK;
     if (!X || !packed || !beta || !Y || (nonneg && !wsum)) return BL_ERR_NULL;
-    const ForwardWs ws = nonneg ? forward_ws_nonneg(M, N, K, groups_k, granularity)
-                                : forward_ws_grouped(M, N, K, groups_k, granularity);
+    const ForwardWs ws = nonneg ? forward_ws_nonneg(M, N, K, groups_n, groups_k, granularity)
+                                : forward_ws_grouped(M, N, K, groups_n, groups_k, granularity);
     if (!workspace || workspace_bytes < ws.total) return BL_ERR_WORKSPACE;
     char* base = (char*)workspace;
     int8_t* codes = (int8_t*)(base + ws.codes);

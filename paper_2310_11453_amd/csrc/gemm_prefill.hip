@@ -899,9 +899,10 @@ struct PrefillPlan {
     TilePlan first, rest;
     int64_t cut;  // columns of the first launch, a multiple of 256; 0: one launch
 };
-static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool may_cut) {
+// (one_beta: columns in groups with a beta of their own are not cut)
+static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool one_beta) {
     PrefillPlan best{tile_plan(M, N, K, ws_bytes), {}, 0};
-    if (!may_cut || tuning().prefill_tile || tuning().prefill_split || tuning().prefill_grid) return best;
+    if (!one_beta || tuning().prefill_tile || tuning().prefill_split || tuning().prefill_grid) return best;
     const int64_t cus = num_cus(), nst = (K + kStageK - 1) / kStageK;
     double best_us = best.first.us;
     for (int tile = 1; tile <= 2; ++tile) {
@@ -921,9 +922,9 @@ static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes
 }
 static int64_t plan_slices(const TilePlan& p, int64_t K) { return (tiles_k(K) + p.per - 1) / p.per; }
 // Room for the K-slices of the plan: optional, without it K is not split (or in fewer slices).
-size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K) {
+size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K, bool one_beta) {
     if (M <= 64) return mid_split_bytes(M, N, K);
-    const PrefillPlan p = prefill_plan(M, N, K, (size_t)1 << 40, true);
+    const PrefillPlan p = prefill_plan(M, N, K, (size_t)1 << 40, one_beta);
     const int64_t n = plan_slices(p.cut ? p.rest : p.first, K);
     return n > 1 ? (size_t)n * M * (N - p.cut) * 4 : 0;
 }
@@ -983,7 +984,6 @@ hipError_t launch_gemm_prefill(const GemmArgs& a_in, hipStream_t s) {
         else gemm_group_kernel<false><<<(unsigned)grid, 512, 0, s>>>(a, grid_m, grid_n);
         return hipGetLastError();
     }
-    // (columns in groups with a beta of their own are not cut)
     const PrefillPlan p = prefill_plan(a.M, a.N, a.K, a.split_ws ? a.split_ws_bytes : 0, a.beta_rows >= a.N);
     auto launch = [&](const GemmArgs& b, const TilePlan& t) {
         if (t.tile >= 3) return launch_gemm_mid_tiles(b, t.tile == 3 ? 128 : 64, t.per, s);

@@ -133,7 +133,7 @@ struct GemmArgs {
 };
 bool gemm_decode_fuses_quant(int64_t M, int64_t K, int64_t N);
 size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t K);
-size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K);
+size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K, bool one_beta);
 size_t group_split_bytes(int64_t M, int64_t N, int64_t K, int groups);  // K: a group's
 int64_t prefill_split_tiles(int64_t M, int64_t N, int64_t K);
 size_t mid_split_bytes(int64_t M, int64_t N, int64_t K);

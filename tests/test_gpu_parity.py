@@ -6,6 +6,8 @@ separately, x^ itself is compared with the oracle's fp64 LayerNorm.  fp32 output
 given shared codes/gamma/beta (the epilogue is one fp32 multiply on both sides), and
 within 1e-3 relative (Frobenius, and max error against rms) end to end.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -733,6 +735,18 @@ def test_fold_of_slices(bl, tuning, M, K, N, spec):
         assert torch.equal(y, ref)
 
 
+def kernel_launches(bl, call):
+    """How many kernels a call launches: the nodes of its captured graph."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    count = ctypes.c_size_t()
+    assert bl.load_library().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
 # Large layers whose last round of tiles is nearly empty run as two launches over ranges of columns (the rest
 # by small tiles, or by 128 x 256 ones with a ragged K): the bits of one launch, in every form of the epilogue.
 @pytest.mark.parametrize("M,K,N", [(2050, 2048, 8333), (4100, 1536, 4610), (1030, 2080, 16650)])
@@ -753,3 +767,19 @@ def test_forward_in_two_ranges_of_columns(bl, tuning, M, K, N):
     tuning("prefill_tile=2")
     for y, ref in zip(two, outputs()):
         assert torch.equal(y, ref)
+
+
+def test_groups_of_columns_are_not_cut(bl, tuning):
+    """Columns with a beta of their own a group stay one launch, and the workspace asked for is that launch's."""
+    M, K, N = 261, 6144, 21856
+    print(f"groups of columns M={M} K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    packed, _, beta = bl.bitlinear_pack_weights_grouped(torch.randn(N, K, device="cuda", generator=g), 2, 1)
+    X = torch.randn(M, K, device="cuda", generator=g)
+    whole = bl.workspace_bytes_grouped(bl.OP_FORWARD, M, N, K, 1, 1)
+    assert bl.workspace_bytes_grouped(bl.OP_FORWARD, M, N, K, 2, 1) < whole
+    forward = lambda: bl.bitlinear_forward_grouped(X, packed, N, beta, 2, 1)
+    assert kernel_launches(bl, forward) == 2  # the quantiser and one product
+    y = forward()
+    tuning("prefill_tile=2")
+    assert torch.equal(y, forward())
