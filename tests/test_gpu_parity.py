@@ -747,24 +747,36 @@ def kernel_launches(bl, call):
     return count.value
 
 
-# Large layers whose last round of tiles is nearly empty run as two launches over ranges of columns (the rest
-# by small tiles, or by 128 x 256 ones with a ragged K): the bits of one launch, in every form of the epilogue.
-@pytest.mark.parametrize("M,K,N", [(2050, 2048, 8333), (4100, 1536, 4610), (1030, 2080, 16650)])
-def test_forward_in_two_ranges_of_columns(bl, tuning, M, K, N):
+# Large layers whose last round of tiles is nearly empty run as two launches over ranges of columns: the bits of
+# one launch, in every form of the epilogue.  The rest as 128 x 128 tiles, 128 x 256 ones with a ragged K, 64 x 128
+# ones, and 64 x 128 or 128 x 128 ones in slices of K, whose sums a third launch folds into rows of Y that are longer
+# than the range (one column a thread, or four).
+@pytest.mark.parametrize("M,K,N,sliced", [(2050, 2048, 8333, False), (4100, 1536, 4610, False),
+                                          (1030, 2080, 16650, False), (660, 1056, 22617, False),
+                                          (261, 6144, 21860, True), (260, 6144, 22864, True),
+                                          (669, 6176, 11436, True), (262, 4160, 22277, True)])
+def test_forward_in_two_ranges_of_columns(bl, tuning, M, K, N, sliced):
     print(f"two ranges M={M} K={K} N={N}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(M + N)
     packed, _, beta = bl.bitlinear_pack_weights(torch.randn(N, K, device="cuda", generator=g))
     X = torch.randn(M, K, device="cuda", generator=g)
     wsum = bl.bitlinear_weight_rowsums(packed, N, K)
+    codes, gamma, rowsum, _ = bl.bitlinear_quant_act(X)
+    ws = torch.empty(bl.workspace_bytes(bl.OP_MATMUL, M, N, K), dtype=torch.uint8, device="cuda")
+
+    def product(workspace):
+        return bl.bitlinear_matmul(codes, gamma, rowsum, packed, N, beta, workspace=workspace)
 
     def outputs():
         return [bl.bitlinear_forward(X, packed, N, beta),
                 bl.bitlinear_forward(X, packed, N, beta, per_tensor=True),
                 bl.bitlinear_forward(X, packed, N, beta, flags=bl.FLAG_OUT_ACC_I32),
-                bl.bitlinear_forward_nonneg(X, packed, N, beta, wsum)]
+                bl.bitlinear_forward_nonneg(X, packed, N, beta, wsum), product(ws)]
 
+    assert kernel_launches(bl, lambda: product(ws)) == (3 if sliced else 2)
     two = outputs()
     tuning("prefill_tile=2")
+    assert kernel_launches(bl, lambda: product(ws)) == 1
     for y, ref in zip(two, outputs()):
         assert torch.equal(y, ref)
 
