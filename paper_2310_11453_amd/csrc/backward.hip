@@ -415,7 +415,8 @@ __global__ __launch_bounds__(256, T == 256 ? 1 : 2) void gemm_tn_bf16_wide(const
         }
 
         {
-            const int64_t ib = i0 + __builtin_amdgcn_readfirstlane(wm * WTM), jb = j0 + __builtin_amdgcn_readfirstlane(wn * WTN);
+            const int64_t ib = i0 + __builtin_amdgcn_readfirstlane(wm * WTM);
+            const int64_t jb = j0 + __builtin_amdgcn_readfirstlane(wn * WTN);
             if constexpr (T < 256) {
                 store_tile<MI, NI, true>(Cs + ib * J + jb, J, I - ib, J - jb, j, g2, [](int, int) {},
                                          [&](int mi, int r, int s) { return scale * acc[mi][s][r]; });
@@ -674,7 +675,8 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
         }
 
         {
-            const int64_t ib = i0 + __builtin_amdgcn_readfirstlane(wm * WTM), jb = j0 + __builtin_amdgcn_readfirstlane(wn * WTN);
+            const int64_t ib = i0 + __builtin_amdgcn_readfirstlane(wm * WTM);
+            const int64_t jb = j0 + __builtin_amdgcn_readfirstlane(wn * WTN);
             store_tile<MI, NI, true>(Cs + ib * J + jb, J, I - ib, J - jb, j, g2, [](int, int) {},
                                [&](int mi, int r, int s) { return scale * acc[mi][s][r]; });
         }
@@ -816,9 +818,9 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
 //   a round of two per CU                    2.5 + 0.38
 // The whole call (M x N x K, with the operand copies), 256 against 128: 8 x 512 x 256 18.2 / 10.5 us, 64 x 2048 x 2048
 // 21.3 / 13.2, 1000 x 2048 x 2048 44.6 / 25.7, 8 x 4096 x 16384 74.6 / 64.4; 4096 x 512 x 256 (16 slices of
-// 256 tiles) 33.9 / 44.5.  Past one full round the second read of the operands decides: beyond 32 stages (16 from two full
-// rounds on, 12 from nine), or with a B operand well beyond an XCD's 4 MB of L2, the large tile it is (512 x 7168 x
-// 7168 115 / 107, 1000 x 7168 x 7168 159 / 171, 512 x 21504 x 7168 261 / 287, 256 x 7168 x 28672 248 / 265).
+// 256 tiles) 33.9 / 44.5.  Past one full round the second read of the operands decides: beyond 32 stages (16 from two
+// full rounds on, 12 from nine), or with a B operand well beyond an XCD's 4 MB of L2, the large tile it is (512 x
+// 7168 x 7168 115 / 107, 1000 x 7168 x 7168 159 / 171, 512 x 21504 x 7168 261 / 287, 256 x 7168 x 28672 248 / 265).
 static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int force = tuning().bwd_ring;
     if (force == 2) return ring_plan(I, J, Rp, 128);

@@ -417,7 +417,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
         }
 
         // ---- epilogue (Eq. 11): lane (j, g2) holds column n, rows 8*(r/4) + 4*g2 + r%4 ----
-        //   sum_k q s = 2 sum_k q b - sum_k q, the accumulators holding -128 sum_k q b ;  y = that * (beta_n * gamma_m / 128)
+        //   sum_k q s = 2 sum_k q b - sum_k q, the accumulators holding -128 sum_k q b ;
+        //   y = that * (beta_n * gamma_m / 128)
         float bcol[NI];
 #pragma unroll
         for (int s = 0; s < NI; ++s)

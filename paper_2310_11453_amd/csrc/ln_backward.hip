@@ -369,8 +369,8 @@ template <int WPR, int NV>
 static void launch_rows(const LnBackwardArgs& a, hipStream_t s) {
     constexpr int NW = WPR < 4 ? 4 : WPR, RPW = NW / WPR;
     // Streaming stores of dX where they pay with a reader behind them, us with a pass over dX: 1000 x 2048 11.9 /
-    // 11.3 with them, 333 x 7168 14.2 / 13.0, 1200 x 4096 19.6 / 19.0; but 64 x 2048 6.2 / 6.6, 3000 x 2048 20.8 / 22.4,
-    // 8192 x 4096 124 / 128 (there the call by itself 75 / 61, and the reader pays for it).
+    // 11.3 with them, 333 x 7168 14.2 / 13.0, 1200 x 4096 19.6 / 19.0; but 64 x 2048 6.2 / 6.6, 3000 x 2048 20.8 /
+    // 22.4, 8192 x 4096 124 / 128 (there the call by itself 75 / 61, and the reader pays for it).
     const int64_t out = a.M * a.K;
     const auto kernel = out >= (int64_t)1 << 20 && out <= (int64_t)5 << 20 ? ln_backward_rows<WPR, NV, true>
                                                                           : ln_backward_rows<WPR, NV, false>;
