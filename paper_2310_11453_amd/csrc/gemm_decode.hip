@@ -460,7 +460,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
     }
     for (int t = w; t < tpb; t += W) {
         v4i sum = (v4i){0, 0, 0, 0};
-        if ((FUSED == 1 || (!FUSED && MAXW == 8)) && W >= 4) {  // uniform
+        if ((FUSED == 1 || (!FUSED && MAXW == 8)) && W >= 3) {  // uniform
             // four waves' sums at a time, read independently of one another (the regions of absent waves are
             // not read: another wave's is, masked)
 #pragma unroll
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                 for (int i = 0; i < 4; ++i) sum += p[i] & -(int)(w0 + i < W);
             }
         } else {
-            // with fewer waves, with 16, or behind the long row's quantiser, the plain loop is the faster one: from
+            // with one or two waves, with 16, or behind the long row's quantiser, the plain loop is the faster one: from
             // codes 1 x 256 -> 512 2.47 us for 2.56, 1 x 16384 -> 4096 4.4 for 4.7; 1 x 28672 -> 7168 in one
             // launch 15.9 for 16.5
             for (int ww = 0; ww < W; ++ww)
