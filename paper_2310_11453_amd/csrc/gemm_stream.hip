@@ -207,7 +207,11 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
 
     // ---- epilogue (Eq. 11): sum_k q s = 2 sum_k q b - sum_k q ; y = that * (beta gamma / 128) ----
     // item -> four consecutive weight rows of a pair and a token, eight items to a line of the output.
-    // kind 0: one beta and none of the options; 1: sums (a slice, or int32 output); 2: the rest
+    // kind 0: one beta and none of the options; 1: sums (a slice, or int32 output); 2: the rest; 3: 0 with streaming
+    // stores, for outputs of whole lines from 768 KB on.  There they pay with a pass over Y behind them as well (us of
+    // the layer with that pass, ordinary / streaming: 24 x 4096 -> 12288 14.45 / 14.34, 32 x 2048 -> 6144 10.76 /
+    // 10.56, 32 x 4096 -> 16384 15.27 / 15.21; without it 11.71 / 11.54, 7.93 / 7.86, 12.10 / 11.84); below, the
+    // reader pays more than they gain (24 x 2048 -> 2048 9.17 / 9.79, 20 x 1408 -> 5632 10.34 / 10.64).
     const bool vec = (N & 3) == 0;  // then n + 3 < N and the row starts 16-byte aligned
     auto finish = [&](auto kind) {
         constexpr int KIND = decltype(kind)::value;
@@ -233,16 +237,17 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
                 for (int j = 0; j < 4; ++j) {
                     const int64_t nj = n + j < N ? n + j : N - 1;
                     const float beta =
-                        KIND == 0 || one_beta ? beta0 : a.beta[((uint32_t)nj / (uint32_t)a.beta_rows) * a.beta_stride];
+                        KIND != 2 || one_beta ? beta0 : a.beta[((uint32_t)nj / (uint32_t)a.beta_rows) * a.beta_stride];
                     // beta * (gamma / 128) has the bits of (beta * gamma) / 128
                     float y = (float)(sum[j] - tok_sum[m]) * (beta * sc);
                     if (KIND == 2 && a.eta) y = y + (beta * tok_eta[m]) * (float)a.wsum[nj];       // Eq. 6
                     o[j] = __float_as_uint(y);
                 }
             }
-            if (vec) {
-                // not a streaming store: no faster, and the next reader of Y pays (2048 -> 2048 at 17 to 32 tokens
-                // and a pass over Y: 9.4 us -> 9.7)
+            if constexpr (KIND == 3) {
+                const v4i v = {(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
+                __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(dst));
+            } else if (vec) {
                 *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
             } else {
 #pragma unroll
@@ -252,8 +257,9 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
         }
     };
     if (a.split_k || a.out_acc) finish(std::integral_constant<int, 1>{});
-    else if (one_beta && !a.eta) finish(std::integral_constant<int, 0>{});
-    else finish(std::integral_constant<int, 2>{});
+    else if (!one_beta || a.eta) finish(std::integral_constant<int, 2>{});
+    else if (M * N >= (int64_t)3 << 16 && (N & 31) == 0) finish(std::integral_constant<int, 3>{});
+    else finish(std::integral_constant<int, 0>{});
 }
 
 static int stream_cus() {

@@ -735,6 +735,17 @@ def test_fold_of_slices(bl, tuning, M, K, N, spec):
         assert torch.equal(y, ref)
 
 
+# Up to 32 tokens: streaming stores from 768 KB of output on, in whole lines; both sides of each line.
+@pytest.mark.parametrize("M,K,N", [(24, 96, 8192), (23, 96, 8192), (32, 544, 6176), (32, 544, 6160), (17, 4128, 11616)])
+def test_streaming_stores_up_to_32_tokens(bl, tuning, M, K, N):
+    print(f"streaming stores M={M} K={K} N={N}", flush=True)
+    packed, _, beta = bl.bitlinear_pack_weights(dev(wl.make_weight(N, K, 0.02, seed=wl.seed_for(3, K + N))))
+    X = dev(wl.make_activation(M, K, seed=wl.seed_for(3, K + M)))
+    y = bl.bitlinear_forward(X, packed, N, beta)
+    tuning("mid_only=1")
+    assert torch.equal(y, bl.bitlinear_forward(X, packed, N, beta))
+
+
 def kernel_launches(bl, call):
     """How many kernels a call launches: the nodes of its captured graph."""
     call()
