@@ -34,7 +34,7 @@ I8_MFMA_PEAK_TOPS = 5000.0
 # HBM bytes per launch of the dominant kernel (the 4096->16384 GEMM at M=2048) measured with
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, each scaled by what the same counter reads for a
 # plain 256 MiB device copy (x2.000 and x1.000): profiles/gemm_prefill_6p7b_counters.txt.
-TRAFFIC_BYTES = {"gemm_prefill_up": int((41190 * 2.000 + 131073 * 1.000) * 1024)}
+TRAFFIC_BYTES = {"gemm_prefill_up": int((41129 * 2.000 + 131200 * 1.000) * 1024)}
 
 
 def gemm_bytes(M, K, N):

@@ -512,8 +512,10 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                     o[r] = o[r] + be * (float)a.wsum[n + r < a.N ? n + r : a.N - 1];
             }
             if ((a.N & 3) == 0) {
-                // not a streaming store: no faster for whole lines, 0.3 us slower for others (8 x 6144 -> 21860 11.3 ->
-                // 11.7 us), and the next reader of Y pays (2048 -> 2048 and a pass over Y: 5.9 us -> 6.3)
+                // not a streaming store: what reads Y next pays more than it gains (2048 -> 2048 and a pass over Y 5.9
+                // us, 6.3 streaming; a step of 24 layers of width 1408 at 16 tokens with an addition to every Y 992,
+                // 1019 streaming, though 809 and 768 with nothing that reads Y); rows that are no whole lines lose by
+                // themselves (8 x 6144 -> 21860 11.3 us, 11.7 streaming)
                 *reinterpret_cast<v4f*>(y) = o;
             } else {
                 for (int r = 0; r < 4; ++r)
