@@ -125,8 +125,7 @@ __device__ inline void lds_write_b32(uint32_t ad, uint32_t v) {
 // NS = stages in the LDS ring (4 or 8: it must divide the 8 stages of a chunk).
 // Persistent: gridDim.x workgroups (one per CU) walk the tiles t = blockIdx.x, + gridDim.x, ...
 // GEN = false: the plain layer (one beta, Y = result): nothing of what follows costs anything.
-// GEN = true adds beta per column group (Eq. 13), accumulation over K-groups, the shift term of
-// Eq. 6.
+// GEN = true adds beta per column group (Eq. 13) and the shift term of Eq. 6.
 template <int BM, int BN, int WM, int WN, int NS, bool GEN>
 __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs a, int grid_m,
                                                                         int grid_n, int xbm) {

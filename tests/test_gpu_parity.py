@@ -746,6 +746,30 @@ def test_streaming_stores_up_to_32_tokens(bl, tuning, M, K, N):
     assert torch.equal(y, bl.bitlinear_forward(X, packed, N, beta))
 
 
+# Small MFMA tiles: streaming stores of outputs from 2^20 values on, in whole lines, and of K slices; both sides of each line,
+# against the rows sixteen at a time (another kernel).
+@pytest.mark.parametrize("M,K,N,spec", [(64, 96, 16384, None), (63, 96, 16384, None), (64, 96, 16400, None),
+                                        (64, 4128, 512, "mid_split_tiles=3"), (64, 4128, 528, "mid_split_tiles=3"),
+                                        (130, 96, 8192, "prefill_tile=3"), (130, 96, 8192, "prefill_tile=4"),
+                                        (127, 96, 8224, "prefill_tile=4"), (130, 96, 8208, "prefill_tile=3"),
+                                        (130, 1056, 544, "prefill_tile=3,prefill_split=3")])
+def test_streaming_stores_of_small_tiles(bl, tuning, M, K, N, spec):
+    print(f"streaming stores of small tiles M={M} K={K} N={N} {spec}", flush=True)
+    packed, _, beta = bl.bitlinear_pack_weights(dev(wl.make_weight(N, K, 0.02, seed=wl.seed_for(3, K + N))))
+    X = dev(wl.make_activation(M, K, seed=wl.seed_for(3, K + M)))
+    codes, gamma, rowsum, _ = bl.bitlinear_quant_act(X)
+    wsum = bl.bitlinear_weight_rowsums(packed, N, K)
+    eta = torch.linspace(-3, 0, M, device="cuda")
+    tuning(spec)
+    ws = torch.empty(bl.workspace_bytes(bl.OP_MATMUL, M, N, K) + 4 * M * N * 4, dtype=torch.uint8, device="cuda")
+    y = bl.bitlinear_matmul(codes, gamma, rowsum, packed, N, beta, workspace=ws)
+    shifted = bl.bitlinear_matmul_nonneg(codes, gamma, eta, rowsum, packed, N, beta, wsum)
+    rows = [slice(i, min(i + 16, M)) for i in range(0, M, 16)]
+    assert torch.equal(y, torch.cat([bl.bitlinear_matmul(codes[r], gamma[r], rowsum[r], packed, N, beta) for r in rows]))
+    assert torch.equal(shifted, torch.cat([bl.bitlinear_matmul_nonneg(codes[r], gamma[r], eta[r], rowsum[r], packed, N, beta,
+                                                                      wsum) for r in rows]))
+
+
 def kernel_launches(bl, call):
     """How many kernels a call launches: the nodes of its captured graph."""
     call()
