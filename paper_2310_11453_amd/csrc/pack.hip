@@ -48,9 +48,9 @@ __device__ inline void store_rows(uint32_t* tile, int l, uint32_t dw0, uint32_t 
 // partials[2*b] = sum of W, partials[2*b+1] = sum of |W| over workgroup b's rows.
 // The whole call, us: two readings of W with the fold of the sums as a launch between them / this with a zero mean /
 // this with a mean of half the deviation, where pack_fix reads everything again: 64 x 32 10.6 / 8.6 / 8.7,
-// 512 x 256 11.9 / 9.1 / 9.0, 2048 x 2048 20.4 / 10.8 / 11.7, 8192 x 2048 31 / 21.7 / 28.7, 16384 x 4096 88 / 52 / 89,
-// 28672 x 7168 318 / 177 / 317; 3 to 5 % slower than two readings only where W is 100 to 200 MB and all of it is
-// repacked (8192 x 4096 46.5 / 31 / 48, 50257 x 1024 69 / 44 / 72.5).
+// 512 x 256 12.0 / 9.0 / 9.0, 2048 x 2048 20.5 / 10.5 / 11.4, 8192 x 2048 31 / 19.6 / 27.8, 16384 x 4096 88 / 54 / 87,
+// 28672 x 7168 314 / 179 / 311; up to 3 % slower than two readings only where W is 100 to 200 MB and all of it is
+// repacked (8192 x 4096 46.4 / 30.8 / 48, 50257 x 1024 69 / 42.5 / 70.5).
 __global__ __launch_bounds__(256, 4) void pack_scan(const float* __restrict__ W, int64_t N, int64_t K,
                                                  int64_t ldw, uint32_t* __restrict__ packed,
                                                  float* __restrict__ rowmin,
@@ -343,7 +343,7 @@ int reduce_grid(int64_t count4) {
 
 static int scan_grid(int64_t tiles) {
     const int64_t blocks = (tiles + 1) / 2;  // of four waves with one half tile each
-    return (int)(blocks < 1024 ? blocks : 1024);
+    return (int)(blocks < 512 ? blocks : 512);  // 2 a CU: with 4, 64 MB matrices took 0.6 us more (20.2 / 19.6)
 }
 // workspace with which W is read once: the scan's partial sums, then the tiles' smallest |w|
 size_t pack_scan_bytes(int64_t N, int64_t K) {
@@ -361,10 +361,11 @@ hipError_t launch_pack(const float* W, int64_t N, int64_t K, int64_t ldw, bool b
         const int G = scan_grid(tiles);
         float* rowmin = reinterpret_cast<float*>(partials + 2 * G);
         pack_scan<<<G, 256, 0, s>>>(W, N, K, ldw, packed, rowmin, partials);
-        // Few tiles: more, shorter items.  W beyond the Infinity Cache: last tiles first, they are still in it
+        // Few tiles: more, shorter items (8 rows / 16, repacked as a whole: 4500 x 2048, 1128 tiles, 17.7 us / 20.7;
+        // 3840 x 3840, 1920 tiles, 26.6 / 26.1).  W beyond the Infinity Cache: last tiles first, they are still in it
         // (28672 x 7168 all repacked 333 us -> 317); else in the scan's order, which finds them in the XCD's
         // own L2 (4096 x 2048 16.0 / 18.9 -> 13.3 / 13.8).
-        const int nrows = tiles <= 512 ? 4 : tiles <= 1024 ? 8 : kTileN;
+        const int nrows = tiles <= 512 ? 4 : tiles <= 1600 ? 8 : kTileN;
         const bool backwards = N * K * 4 > (int64_t)256 << 20;
         const int64_t blocks = (tiles * (kTileN / nrows) + 3) / 4;
         pack_fix<<<(unsigned)(blocks < 1280 ? blocks : 1280), 256, 0, s>>>(

@@ -91,8 +91,9 @@ def near_alpha_weight(N, K, seed):
     return W
 
 
-# 4, 8 and 16 rows of a tile to an item of the second kernel (up to 512, up to 1024 and more tiles)
-@pytest.mark.parametrize("N,K", [(1, 32), (17, 544), (40, 992), (300, 4128), (4000, 2048), (4100, 2048)])
+# 4, 8 and 16 rows of a tile to an item of the second kernel (up to 512, up to 1600 and more tiles)
+@pytest.mark.parametrize("N,K", [(1, 32), (17, 544), (40, 992), (300, 4128), (4000, 2048), (4100, 2048),
+                                 (6400, 2048), (6401, 2048)])
 def test_pack_weights_near_alpha(bl, N, K):
     """W is read once and only the rows of a tile with a weight within |alpha| of zero are packed again.  With
     the workspace that only holds the sums, the same bits by the two readings."""
