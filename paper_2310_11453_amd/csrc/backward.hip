@@ -51,14 +51,11 @@ __host__ __device__ inline int64_t block_offset(int64_t row, int64_t r, int64_t 
 // the transpose goes through LDS (row pitch 66 halfwords: the 4-row steps of the 16 lanes that
 // build one output row fall on distinct banks) and leaves as 8-byte pieces too.
 // VEC: C % 4 == 0 and `in` 16-byte aligned, so that a thread's 4 elements are one load.
+typedef uint16_t CastTile[64][66];
 template <typename IN, bool VEC>
-__global__ __launch_bounds__(256) void cast_transpose_bf16(const IN* __restrict__ in, int64_t R,
-                                                           int64_t C, int64_t Cp, int64_t Rp,
-                                                           const float* __restrict__ row_gamma,
-                                                           uint16_t* __restrict__ rows,
-                                                           uint16_t* __restrict__ tr) {
-    __shared__ __attribute__((aligned(8))) uint16_t tile[64][66];
-    const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
+__device__ inline void cast_transpose_tile(const IN* __restrict__ in, int64_t R, int64_t C, int64_t Cp, int64_t Rp,
+                                           const float* __restrict__ row_gamma, uint16_t* __restrict__ rows,
+                                           uint16_t* __restrict__ tr, int64_t r0, int64_t c0, CastTile& tile) {
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int idx = it * 256 + threadIdx.x;
@@ -107,19 +104,6 @@ __global__ __launch_bounds__(256) void cast_transpose_bf16(const IN* __restrict_
     }
 }
 
-template <typename IN>
-static void launch_cast_transpose(const IN* in, int64_t R, int64_t C, int64_t Cp, int64_t Rp,
-                                  const float* row_gamma, uint16_t* rows, uint16_t* tr, hipStream_t s) {
-    // the grid covers the padded extents of whichever outputs are written
-    const int64_t cols = rows ? Cp : C, rws = tr ? Rp : R;
-    dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rws + 63) / 64));
-    const bool vec = C % 4 == 0 && ((uintptr_t)in & 15) == 0;
-    if (vec)
-        cast_transpose_bf16<IN, true><<<grid, 256, 0, s>>>(in, R, C, Cp, Rp, row_gamma, rows, tr);
-    else
-        cast_transpose_bf16<IN, false><<<grid, 256, 0, s>>>(in, R, C, Cp, Rp, row_gamma, rows, tr);
-}
-
 // ---- Sw[Np/32][K]: the signs of 32 consecutive weight rows of one column k in one word -------
 // What the ring kernel below reads as the B operand of dX (reduction over n): a stage of 32 n is
 // one word per column, 1 KiB for a 256-column tile instead of 16 KiB of bf16.  Bit layout of a
@@ -127,12 +111,9 @@ static void launch_cast_transpose(const IN* in, int64_t R, int64_t C, int64_t Cp
 // n = 32 sw + r sits at bit 8 (r/16) + 4 ((r%16)/8) + (r%8)/2 + 16 (r%2), and holds 1 for -1
 // (the bf16 sign bit), 0 for +1.  Rows past N: their columns of g are zero, any bit does.
 // One workgroup transposes two tiles (32 rows) x 512 columns.
-__global__ __launch_bounds__(256) void bits_transpose_words(const uint32_t* __restrict__ packed,
-                                                            int64_t N, int64_t K,
-                                                            uint32_t* __restrict__ Sw) {
-    __shared__ uint32_t sm[2][256];
+__device__ inline void bits_transpose_tile(const uint32_t* __restrict__ packed, int64_t N, int64_t K,
+                                           uint32_t* __restrict__ Sw, int64_t sw, int64_t tk, uint32_t (&sm)[2][256]) {
     const int64_t TN = tiles_n(N), TK = tiles_k(K);
-    const int64_t sw = blockIdx.x, tk = blockIdx.y;
     for (int t = 0; t < 2; ++t) {
         uint32_t v = 0;
         if (2 * sw + t < TN) v = packed[tile_dword_offset(2 * sw + t, tk, TK) + threadIdx.x];
@@ -153,6 +134,75 @@ __global__ __launch_bounds__(256) void bits_transpose_words(const uint32_t* __re
         }
         Sw[sw * K + k] = word;
     }
+}
+
+// All of it in one launch: 64 x 64 tiles of dY, of the codes, and 32 x 512 pieces of the sign matrix are the items of
+// one grid.  Each part alone is HBM-bound when large, but at a thousand tokens the two small ones are launches of
+// latency (whole call, us, three launches / one, M x N x K: 256 x 1024 x 1024 32.0 / 26.5, 333 x 2048 x 2048 40.5 / 36.0,
+// 1000 x 8192 x 2048 108.9 / 104.2; 8192 x 16384 x 4096 1752 / 1752).  The small parts come first: behind dY they
+// would be the tail.
+struct PrepareArgs {
+    const float* dY;
+    const int8_t* codes;
+    const uint32_t* packed;
+    const float* row_gamma;  // null: per tensor
+    uint16_t *g, *gwT, *qT;  // what is not wanted is null
+    uint32_t* Sw;
+    int64_t M, N, K, Np, Mp;
+    uint32_t bits_items, code_items, items;  // items: of all three parts
+    uint32_t bits_x, code_x, dy_x;           // items in a row of each part
+};
+template <bool VECY, bool VECQ>
+__global__ __launch_bounds__(256) void prepare_operands(PrepareArgs a) {
+    __shared__ __attribute__((aligned(8))) union {
+        CastTile tile;
+        uint32_t words[2][256];
+    } sm;
+    for (uint32_t it = blockIdx.x; it < a.items; it += gridDim.x) {
+        if (it != blockIdx.x) __syncthreads();  // the item before has been read
+        uint32_t i = it;
+        if (i < a.bits_items) {
+            bits_transpose_tile(a.packed, a.N, a.K, a.Sw, i % a.bits_x, i / a.bits_x, sm.words);
+            continue;
+        }
+        i -= a.bits_items;
+        if (i < a.code_items) {
+            cast_transpose_tile<int8_t, VECQ>(a.codes, a.M, a.K, a.K, a.Mp, nullptr, nullptr, a.qT,
+                                              (int64_t)(i / a.code_x) * 64, (int64_t)(i % a.code_x) * 64, sm.tile);
+            continue;
+        }
+        i -= a.code_items;
+        cast_transpose_tile<float, VECY>(a.dY, a.M, a.N, a.Np, a.Mp, a.row_gamma, a.g, a.gwT,
+                                         (int64_t)(i / a.dy_x) * 64, (int64_t)(i % a.dy_x) * 64, sm.tile);
+    }
+}
+
+static void launch_prepare(const BackwardArgs& b, uint16_t* g, uint32_t* Sw, uint16_t* gwT, uint16_t* qT, int64_t Np,
+                           int64_t Mp, hipStream_t s) {
+    PrepareArgs a{b.dY, b.codes, b.packed, b.per_tensor ? nullptr : b.gamma, g, gwT, qT, Sw, b.M, b.N, b.K, Np, Mp,
+                  0, 0, 0, 1, 1, 1};
+    auto tiles = [](int64_t v) { return (v + 63) / 64; };
+    int64_t items = 0;
+    if (Sw) {
+        a.bits_x = (uint32_t)(Np / 32);
+        items = (Np / 32) * tiles_k(b.K);
+        a.bits_items = (uint32_t)items;
+    }
+    if (qT) {
+        a.code_x = (uint32_t)tiles(b.K);
+        a.code_items = (uint32_t)(tiles(b.K) * tiles(Mp));
+        items += tiles(b.K) * tiles(Mp);
+    }
+    // the items cover the padded extents of whichever copies are written
+    a.dy_x = (uint32_t)tiles(g ? Np : b.N);
+    items += tiles(g ? Np : b.N) * tiles(gwT ? Mp : b.M);
+    a.items = (uint32_t)items;
+    const unsigned grid = (unsigned)(items < (1 << 23) ? items : (1 << 23));
+    const bool vy = b.N % 4 == 0 && ((uintptr_t)b.dY & 15) == 0, vq = b.K % 4 == 0 && ((uintptr_t)b.codes & 15) == 0;
+    if (vy && vq) prepare_operands<true, true><<<grid, 256, 0, s>>>(a);
+    else if (vy) prepare_operands<true, false><<<grid, 256, 0, s>>>(a);
+    else if (vq) prepare_operands<false, true><<<grid, 256, 0, s>>>(a);
+    else prepare_operands<false, false><<<grid, 256, 0, s>>>(a);
 }
 
 // Tile order of the persistent bf16 kernels.  Workgroups are dealt round-robin to the 8 XCDs (one
@@ -443,7 +493,7 @@ __global__ __launch_bounds__(256, T == 256 ? 1 : 2) void gemm_tn_bf16_wide(const
 
 // ---- dX^: the same persistent kernel with the +-1 operand built from sign words ----------------
 // C[I][J] = scale * sum_r A[I][r] S[r][J], A = g (bf16 rows, as above), S given as Sw[r / 32][J]
-// (bits_transpose_words).  Only A goes through the big ring (16 KiB a stage, half the bytes the
+// (bits_transpose_tile).  Only A goes through the big ring (16 KiB a stage, half the bytes the
 // bf16 copy of S would add); a stage of S is one word per column, which each wave fetches for
 // its own 64 columns (one 4-byte DMA per lane) into a ring of its own, one stage ahead of A, so
 // that the words of stage st+1 can be read while stage st is being multiplied.  A lane turns its
@@ -896,13 +946,10 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
     const size_t part_bytes = a.workspace_bytes > ws.total ? a.workspace_bytes - ws.total : 0;
 
     // dY is read once: g for dX and gwT for dW come out of the same pass when both are wanted
-    launch_cast_transpose<float>(a.dY, M, N, Np, Mp, a.per_tensor ? nullptr : a.gamma,
-                                 a.dX ? g : nullptr, a.dW ? gwT : nullptr, s);
+    launch_prepare(a, a.dX ? g : nullptr, a.dX ? Sw : nullptr, a.dW ? gwT : nullptr, a.dW ? qT : nullptr, Np, Mp, s);
     if (a.dX) {  // +-1 from sign words inside the kernel: no bf16 copy of the weights
         RingPlan p = ring_plan(M, K, Np, 256);
         if (slices_bytes(p, M, K) > part_bytes) p = unsliced(p, Np);
-        dim3 gb((unsigned)(Np / 32), (unsigned)tiles_k(K));
-        bits_transpose_words<<<gb, 256, 0, s>>>(a.packed, N, K, Sw);
         if (p.sl.splits > 1) {
             gemm_tn_signs_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(g, Sw, M, K, Np, nullptr, 1.0f, part,
                                                                           p.gi, p.gj, 0, 0, p.sl);
@@ -913,7 +960,6 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
         }
     }
     if (a.dW) {
-        launch_cast_transpose<int8_t>(a.codes, M, K, K, Mp, nullptr, nullptr, qT, s);
         launch_gemm_tn(gwT, qT, N, K, Mp, a.per_tensor ? a.gamma : nullptr,
                        a.per_tensor ? 1.0f / 128.0f : 1.0f, a.dW, part, part_bytes, s);
     }

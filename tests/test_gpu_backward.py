@@ -67,6 +67,24 @@ def test_backward_ste_matches_oracle(bl, tuning, M, N, K, per_tensor, ring):
     assert none is None and torch.equal(dW2, dW)
 
 
+# The copies of the operands come out of one launch, with four elements a load where rows and pointer allow it: the
+# four combinations of that for dY and the codes give the same bits.
+@pytest.mark.parametrize("M,N,K", [(70, 68, 96), (33, 1000, 544), (130, 66, 32)])
+@pytest.mark.parametrize("per_tensor", [True, False])
+def test_backward_operands_at_any_alignment(bl, M, N, K, per_tensor):
+    def moved(t):  # the same values one element behind an aligned address
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:]
+        return flat.copy_(t.reshape(-1)).view(t.shape)
+
+    packed, _, beta = bl.bitlinear_pack_weights(dev(wl.make_weight(N, K, 0.02, 5)))
+    codes, gamma, _, _ = bl.bitlinear_quant_act(dev(wl.make_activation(M, K, 6)), per_tensor=per_tensor)
+    dY = dev(wl.make_grad(M, N, 7))
+    dX, dW = bl.bitlinear_backward_ste(dY, codes, gamma, packed, beta, per_tensor)
+    for y, c in ((moved(dY), codes), (dY, moved(codes)), (moved(dY), moved(codes))):
+        dX2, dW2 = bl.bitlinear_backward_ste(y, c, gamma, packed, beta, per_tensor)
+        assert torch.equal(dX2, dX) and torch.equal(dW2, dW)
+
+
 @pytest.mark.parametrize("spec,N", [("bwd_ring=1,bwd_grid=8", 520), ("bwd_ring=2,bwd_grid=4", 520),
                                     ("bwd_ring=2,bwd_grid=8", 1024)])
 def test_backward_ring_kernel_walks_several_tiles(bl, tuning, spec, N):
