@@ -128,11 +128,11 @@ int bitlinear_matmul(const int8_t* codes, const float* gamma, const int32_t* row
                      void* stream);
 
 /* Eq. 11, the whole layer: bitlinear_quant_act into the workspace, then
- * bitlinear_matmul.  Arguments as above.  For one token (M = 1, K <= 32768 and
- * an N that one round of workgroups covers) both steps run in one launch: the
- * GEMM kernel normalises and quantises the row itself, with the quantiser's
- * arithmetic but its own summation order, so a code can differ from
- * bitlinear_quant_act's where x^ * 128 / gamma sits on a rounding tie.  The
+ * bitlinear_matmul.  Arguments as above.  For one token (K <= 32768 and an N that one
+ * round of workgroups covers) and for up to eight tokens of short rows with gamma per token
+ * both steps run in one launch: the GEMM kernel normalises and quantises the rows itself.  With
+ * two to eight tokens the codes are the same bits as bitlinear_quant_act's; with one the summation
+ * order is its own, so a code can differ where x^ * 128 / gamma sits on a rounding tie.  The
  * workspace is required in every case
  * (bitlinear_workspace_bytes(BL_OP_FORWARD, ...)).  Afterwards it holds the codes,
  * gamma and row sums the matmul step read and, for M = 1, the normalised row x^ the
@@ -315,7 +315,7 @@ int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int thre
  * library decides; NULL or "" resets all.  Process-wide, not thread-safe, takes effect on the
  * next call.  Unless this function has been called, the environment variable
  * BITLINEAR_TUNING (same syntax) is read once, at the first call that launches or asks for a size.
- *   decode_nofuse=1     bitlinear_forward at M = 1: quantiser and GEMM as two launches
+ *   decode_nofuse=1     bitlinear_forward of a few tokens: quantiser and GEMM always as two launches
  *   decode_nosplit=1    M <= 16: never split K over workgroups
  *   decode_tiles=t      M <= 16: weight tiles per workgroup
  *   mid_nosplit=1       16 < M <= 64: never split K over workgroups

@@ -371,9 +371,9 @@ int bitlinear_forward(const float* X, int64_t M, int64_t K, const void* packed, 
     int8_t* codes = (int8_t*)(base + ws.codes);
     float* gamma = (float*)(base + ws.gamma);
     int32_t* rowsum = (int32_t*)(base + ws.rowsum);
-    // one token: the GEMM kernel quantises the row itself and the layer is one launch (codes,
-    // gamma and rowsum still land in the workspace)
-    const bool fuse = gemm_decode_fuses_quant(M, K, N);
+    // a few tokens of a short row: the GEMM kernel quantises them itself and the layer is one launch
+    // (codes, gamma and rowsum still land in the workspace)
+    const bool fuse = (M == 1 || granularity == BL_GAMMA_PER_TOKEN) && gemm_tokens_fuses_quant(M, K, N);
     if (!fuse) {
         int rc = bitlinear_quant_act(X, M, K, ln_gain, ln_bias, ln_eps, granularity,
                                      flags & BL_FLAG_SKIP_LN, codes, gamma, rowsum,
@@ -396,6 +396,7 @@ int bitlinear_forward(const float* X, int64_t M, int64_t K, const void* packed, 
     plain_fields(a);
     a.split_ws = ws.split_bytes ? (int32_t*)(base + ws.split) : nullptr;
     a.split_ws_bytes = ws.split_bytes;
+    if (fuse) return check_hip(launch_gemm_tokens(a, (hipStream_t)stream));
     if (M > 32) offer_slices(a, base, ws.total, workspace_bytes);
     if (M <= 16) return check_hip(launch_gemm_decode(a, (hipStream_t)stream));
     return check_hip(launch_gemm_prefill(a, (hipStream_t)stream));

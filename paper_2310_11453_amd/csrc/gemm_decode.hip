@@ -22,184 +22,20 @@
 
 namespace bl {
 
-// LayerNorm (Eq. 12) and the 8-bit absmax quantiser (Eq. 4-5) of ONE token by a whole workgroup,
-// with the arithmetic of the stand-alone quantiser: sums in fp64 about an element of the row,
-// the normalised value rounded once to fp32, then scale = 128 / gamma, rne, clamp - one fp32
-// operation per step.  The codes go to `lds_codes` (K bytes), the waves' parts of sum_k codes to smi; returns gamma.
-// Every thread of the workgroup must call it (it synchronises), K <= 4 * NV * blockDim.
-// `after_loads` runs once the row's loads are issued: loads return in order, so whatever else
-// the caller wants in flight meanwhile has to queue behind the row, not ahead of it.
-//
-// What bounds it is the length of the chain, not work: a launch of the one-token layer is this chain
-// and little else.  So the waves' values are folded by a butterfly after one read of LDS a wave (the slots
-// of absent waves hold the neutral element), not in a loop over the waves whose every step waits for
-// LDS, and the row sum of the codes, which only the epilogue wants, is left in smi for it.  In a graph of
-// such layers 2048 -> 2048 takes 3.9 us a launch (4.4 before), 8192 -> 2048 5.7 (6.3), 7168 -> 7168 6.5 (7.3),
-// of which an empty launch is 1.6.
-template <int MAXW>
-struct TokenShared {
-    double s[MAXW], q[MAXW];
-    float mn[MAXW], mx[MAXW], amax[MAXW];
-};
-template <int NV, int MAXW, class F>
-__device__ inline float quant_token(const GemmArgs& a, uint32_t* lds_codes, TokenShared<MAXW>& sh,
-                                    int* smi, F&& after_loads) {
-    const int T = blockDim.x, t = threadIdx.x, W = T / kWave, wave = t / kWave;
-    const bool lead = (t & (kWave - 1)) == 0;
-    const int K4 = (int)(a.K / 4);
-    const float4* __restrict__ x4 = reinterpret_cast<const float4*>(a.x_row);
-    float4 v[NV];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int idx = t + j * T;
-        v[j] = x4[idx < K4 ? idx : K4 - 1];
-    }
-    const float first = a.x_row[0];
-    after_loads();
-    if (t >= W && t < MAXW) {  // slots of absent waves
-        sh.s[t] = 0.0;
-        sh.q[t] = 0.0;
-        sh.mn[t] = __builtin_inff();
-        sh.mx[t] = -__builtin_inff();
-        sh.amax[t] = 0.f;
-        smi[t] = 0;
-    }
-    const bool affine = a.ln_gain != nullptr || a.ln_bias != nullptr;
-    bool have_amax = false;
-    float amax = 0.f;
-    if (!a.skip_ln) {
-        const double c = (double)first;
-        double s = 0.0, q = 0.0;
-        float mn = v[0].x, mx = v[0].x;  // always an element of the row (clamped index)
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            if (t + j * T < K4) {
-                const double dx = (double)v[j].x, dy = (double)v[j].y;
-                const double dz = (double)v[j].z, dw = (double)v[j].w;
-                s += (dx + dy) + (dz + dw);
-                q = fma(dx - c, dx - c, q);
-                q = fma(dy - c, dy - c, q);
-                q = fma(dz - c, dz - c, q);
-                q = fma(dw - c, dw - c, q);
-                mn = fminf(fminf(mn, v[j].x), fminf(fminf(v[j].y, v[j].z), v[j].w));
-                mx = fmaxf(fmaxf(mx, v[j].x), fmaxf(fmaxf(v[j].y, v[j].z), v[j].w));
-            }
-        }
-        // long rows: hidden from the optimiser here, or it keeps every element's fp64 copy for the
-        // normalisation and spills (28672 -> 7168 23 us instead of 17.4); short ones have the registers and
-        // are 0.1 us faster with the copies
-        if constexpr (NV > 4) {
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-                asm volatile("" : "+v"(v[j].x), "+v"(v[j].y), "+v"(v[j].z), "+v"(v[j].w));
-        }
-        s = wave_reduce(s, OpSum{});
-        q = wave_reduce(q, OpSum{});
-        mn = wave_reduce(mn, OpMin{});
-        mx = wave_reduce(mx, OpMax{});
-        if (lead) {
-            sh.s[wave] = s;
-            sh.q[wave] = q;
-            sh.mn[wave] = mn;
-            sh.mx[wave] = mx;
-        }
-        __syncthreads();
-        s = fold_slots<MAXW>(sh.s, OpSum{});
-        q = fold_slots<MAXW>(sh.q, OpSum{});
-        mn = fold_slots<MAXW>(sh.mn, OpMin{});
-        mx = fold_slots<MAXW>(sh.mx, OpMax{});
-        const double mu = s / (double)a.K;
-        const double var = fmax(q / (double)a.K - (mu - c) * (mu - c), 0.0);
-        const double rstd = 1.0 / sqrt(var + (double)a.ln_eps);
-        if (!affine) {
-            // x -> fl32((x - mu) * rstd) is monotone: the largest magnitude sits at min or max
-            const float lo = (float)(((double)mn - mu) * rstd);
-            const float hi = (float)(((double)mx - mu) * rstd);
-            amax = fmaxf(fabsf(lo), fabsf(hi));
-            have_amax = true;
-        }
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            const int idx = t + j * T;
-            float4 o;
-            o.x = (float)(((double)v[j].x - mu) * rstd);
-            o.y = (float)(((double)v[j].y - mu) * rstd);
-            o.z = (float)(((double)v[j].z - mu) * rstd);
-            o.w = (float)(((double)v[j].w - mu) * rstd);
-            if (idx < K4) {
-                if (a.ln_gain) {
-                    const float4 g = reinterpret_cast<const float4*>(a.ln_gain)[idx];
-                    o.x = o.x * g.x; o.y = o.y * g.y; o.z = o.z * g.z; o.w = o.w * g.w;
-                }
-                if (a.ln_bias) {
-                    const float4 b = reinterpret_cast<const float4*>(a.ln_bias)[idx];
-                    o.x = o.x + b.x; o.y = o.y + b.y; o.z = o.z + b.z; o.w = o.w + b.w;
-                }
-                v[j] = o;
-            }
-        }
-    }
-    if (!have_amax) {  // uniform: no LayerNorm, or a gain / bias after it
-        float m = 0.f;
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            if (t + j * T < K4)
-                m = fmaxf(m, fmaxf(fmaxf(fabsf(v[j].x), fabsf(v[j].y)), fmaxf(fabsf(v[j].z), fabsf(v[j].w))));
-        }
-        m = wave_reduce(m, OpMax{});
-        if (lead) sh.amax[wave] = m;
-        __syncthreads();
-        amax = fold_slots<MAXW>(sh.amax, OpMax{});
-    }
-    const float gamma = fmaxf(amax, 1e-5f);
-    const float scale = 128.0f / gamma;
-    const bool keep = blockIdx.x == 0 && blockIdx.y == 0;  // uniform: this workgroup leaves the row behind
-    if (keep && a.xhat_out) {
-        float4* __restrict__ d4 = reinterpret_cast<float4*>(a.xhat_out);
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-            if (t + j * T < K4) d4[t + j * T] = v[j];
-    }
-    int rs = 0;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int idx = t + j * T;
-        const uint32_t wd = code_word<-128>(v[j].x * scale, v[j].y * scale, v[j].z * scale, v[j].w * scale);
-        if (idx < K4) {
-            rs = __builtin_amdgcn_sdot4((int)wd, 0x01010101, rs, false);  // sum of the four codes
-            lds_codes[idx] = wd;
-            if (keep && a.codes_out) reinterpret_cast<uint32_t*>(a.codes_out)[idx] = wd;
-        }
-    }
-    rs = wave_reduce(rs, OpSum{});
-    if (lead) smi[wave] = rs;
-    __syncthreads();  // the codes and the waves' parts of their sum are in LDS
-    return gamma;
-}
-
 // C = K-chunks per wave and round, T = weight tiles per workgroup (compile-time bound; `tpb`
 // <= T of them are used), MAXT = launch bound.  ONE_ROUND: the waves of the group cover K in a
 // single round, so a tile's partial sum goes straight to LDS and no per-tile registers are
 // kept - this is what lets a wave keep eight 1 KiB weight loads in flight.
-// FUSED (one round, M = 1): the codes come from quant_token, not from memory.  1: a wave keeps
-// its slice of them in registers like codes read from memory; 2 (long K, many chunks per wave):
-// every MFMA takes its operand from LDS.
 // KGRP (one round, codes from memory): the a.kgroups K-groups of a grouped layer (Eq. 13-15) inside
 // one workgroup.  a.K is one group's K; the waves are dealt to the groups (W / kgroups consecutive
 // waves each, C chunks of the group's K per wave), every group reads its own columns of the codes
 // and its own blob of tiles, and a tile's sums are added per group and written to the group's slice
 // of split_ws (2 * sum_k q b, as a K split does), for groups_reduce to dequantise group by group.
-template <int C, int T, int MAXT, bool ONE_ROUND, int FUSED = 0, bool KGRP = false>
+template <int C, int T, int MAXT, bool ONE_ROUND, bool KGRP = false>
 __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) {
-    static_assert(!FUSED || ONE_ROUND, "the fused quantiser covers K in one round");
-    static_assert(!KGRP || (ONE_ROUND && !FUSED), "K-groups inside the workgroup: one round, codes from memory");
-    constexpr bool kActLds = FUSED == 2;
-    constexpr int kRowBytes = FUSED == 2 ? 32768 : 16384;  // longest row the fused kernels take
+    static_assert(!KGRP || ONE_ROUND, "K-groups inside the workgroup: one round");
     __shared__ __attribute__((aligned(16))) int red[(MAXT / kWave) * T * 256];  // [W][T][64][4]
-    __shared__ __attribute__((aligned(16))) uint32_t row_codes[FUSED ? kRowBytes / 4 : 1];
     constexpr int MAXW = MAXT / kWave;
-    __shared__ __attribute__((aligned(16))) TokenShared<FUSED ? MAXW : 1> token_sh;
-    __shared__ __attribute__((aligned(16))) int smi[FUSED ? MAXW : 1];
     const int W = blockDim.x / kWave;
     // the wave's index as a scalar: which chunks and tiles it owns is then scalar arithmetic and
     // the tile loads take a scalar base, instead of 64-bit compares and selects in every lane
@@ -236,7 +72,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
     const int mc = m < M ? m : M - 1;
     int rs = 0;
     float gm = 0.f, eta = 0.f;
-    if constexpr (!FUSED && !KGRP) {
+    if constexpr (!KGRP) {
         rs = a.rowsum[mc * a.gstride];
         gm = a.per_tensor ? a.gamma[0] : a.gamma[mc * a.gstride];
         // Eq. 6 only; without it the load goes to gamma (always valid) and the value is not used
@@ -262,9 +98,8 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // activation operand: lane (m, g) holds codes[m][512*tk + 64*i + 16*g .. +15].  Rows
         // m >= M read row M-1 (their outputs are never stored); columns k >= K read the last 16
         // valid bytes (the packed bits there are zero, so they contribute nothing).
-        v4i act[kActLds ? 1 : C][8];
+        v4i act[C][8];
         auto load_act = [&](const int8_t* arow) {
-            if constexpr (kActLds) return;
 #pragma unroll
             for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -286,20 +121,18 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // at slot ^ (r % 16).
         constexpr int kStageRows = T < 8 ? T : 8;
         constexpr int kStagePasses = (16 + kStageRows - 1) / kStageRows;
-        const bool staged = !FUSED && ONE_ROUND && (M <= kStageRows || T >= 4);
+        const bool staged = ONE_ROUND && (M <= kStageRows || T >= 4);
         const bool stage_lane = l < C * 32;
         v4i rowv[16];
-        if constexpr (!FUSED) {
-            if (staged) {
-                int kl = (int)tk0 * kChunkK + 16 * l;  // this lane's 16 bytes of a row slice
-                kl = kl > (int)a.K - 16 ? (int)a.K - 16 : kl;
+        if (staged) {
+            int kl = (int)tk0 * kChunkK + 16 * l;  // this lane's 16 bytes of a row slice
+            kl = kl > (int)a.K - 16 ? (int)a.K - 16 : kl;
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (r < M && stage_lane)
-                        rowv[r] = *reinterpret_cast<const v4i*>(a.codes + (int64_t)r * a.ldq + kl);
-            } else {
-                load_act(a.codes + (int64_t)(m < M ? m : M - 1) * a.ldq);
-            }
+            for (int r = 0; r < 16; ++r)
+                if (r < M && stage_lane)
+                    rowv[r] = *reinterpret_cast<const v4i*>(a.codes + (int64_t)r * a.ldq + kl);
+        } else {
+            load_act(a.codes + (int64_t)(m < M ? m : M - 1) * a.ldq);
         }
 
         // Weight tiles: a software pipeline of depth kDepth per wave.  Asking for everything at
@@ -309,9 +142,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // CU, enough to cover the latency) tiles arrive in order and compute overlaps the stream.
         // Tiles past the end re-read the last tile (never stored); chunks past the end are
         // masked to zero arithmetically (no branch around a load).
-        // FUSED: the waves spend the next microseconds on the token, not on MFMAs, so every tile
-        // is requested now and the stream runs under the quantiser.
-        constexpr int kDepth = FUSED ? T : T < 3 ? T : 3;
+        constexpr int kDepth = T < 3 ? T : 3;
         v4i wt[T][C];
         // chunk c of this wave: valid index and all-ones / all-zeros mask
         int64_t tkc[C];
@@ -334,40 +165,27 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             for (int c = 0; c < C; ++c)  // read once: streaming loads leave L2 to the codes (3-6 %)
                 wt[t][c] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(wbase[c] + off));
         };
-        if constexpr (FUSED) {
-            // the row is normalised and quantised while the tiles are on their way; every column
-            // of the MFMA then holds the one token
-            // (a chunk is 128 float4, 2 a lane; kActLds: eight chunks a wave)
-            gm = quant_token<2 * C, MAXW>(a, row_codes, token_sh, smi, [&]() {
-                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int t = 0; t < kDepth; ++t) load_tile(t);
-                __builtin_amdgcn_sched_barrier(0);
-            });
-            load_act(reinterpret_cast<const int8_t*>(row_codes));
-        } else {
+        for (int t = 0; t < kDepth; ++t) load_tile(t);
+        if (staged) {  // rows past M repeat row M-1 (never stored)
+            int* stage = &red[w * T * 256];
+            const int mr = m < M ? m : M - 1;
 #pragma unroll
-            for (int t = 0; t < kDepth; ++t) load_tile(t);
-            if (staged) {  // rows past M repeat row M-1 (never stored)
-                int* stage = &red[w * T * 256];
-                const int mr = m < M ? m : M - 1;
+            for (int p = 0; p < kStagePasses; ++p) {
+                if (p * kStageRows < M) {  // uniform
 #pragma unroll
-                for (int p = 0; p < kStagePasses; ++p) {
-                    if (p * kStageRows < M) {  // uniform
+                    for (int r = 0; r < kStageRows; ++r)
+                        if (p * kStageRows + r < 16 && p * kStageRows + r < M && stage_lane)
+                            *reinterpret_cast<v4i*>(&stage[r * 256 + (l ^ (r & 15)) * 4]) =
+                                rowv[p * kStageRows + r < 16 ? p * kStageRows + r : 15];
+                    if (mr / kStageRows == p) {
+                        const int rr = mr - p * kStageRows;
 #pragma unroll
-                        for (int r = 0; r < kStageRows; ++r)
-                            if (p * kStageRows + r < 16 && p * kStageRows + r < M && stage_lane)
-                                *reinterpret_cast<v4i*>(&stage[r * 256 + (l ^ (r & 15)) * 4]) =
-                                    rowv[p * kStageRows + r < 16 ? p * kStageRows + r : 15];
-                        if (mr / kStageRows == p) {
-                            const int rr = mr - p * kStageRows;
+                        for (int c = 0; c < C; ++c)
 #pragma unroll
-                            for (int c = 0; c < C; ++c)
-#pragma unroll
-                                for (int i = 0; i < 8; ++i)
-                                    act[c][i] = *reinterpret_cast<const v4i*>(
-                                        &stage[rr * 256 + ((c * 32 + 4 * i + g) ^ (rr & 15)) * 4]);
-                        }
+                            for (int i = 0; i < 8; ++i)
+                                act[c][i] = *reinterpret_cast<const v4i*>(
+                                    &stage[rr * 256 + ((c * 32 + 4 * i + g) ^ (rr & 15)) * 4]);
                     }
                 }
             }
@@ -383,26 +201,14 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             // chunks past the end of K are masked here, at the point of use (masking at the load
             // would tie a wait for the whole stream to the first tile), and inside the plane mask,
             // a scalar: it costs no instruction of its own
-            // kActLds: an offset of zero the compiler cannot see through, so that each tile reads
-            // its operands again instead of all C * 8 of them being kept in registers
-            int again = 0;
-            if constexpr (kActLds) asm volatile("" : "+v"(again));
 #pragma unroll
             for (int c = 0; c < C; ++c)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int mask = (int)(0x01010101u << i) & livem[c];
                     const v4i plane = wt[t][c] & mask;
-                    v4i cols;
-                    if constexpr (kActLds) {
-                        int k = (int)(tk0 + c) * kChunkK + 64 * i + 16 * g;
-                        if (k > (int)a.K - 16) k = (int)a.K - 16;
-                        cols = *reinterpret_cast<const v4i*>(reinterpret_cast<const int8_t*>(row_codes) + k + again);
-                    } else {
-                        cols = act[c][i];
-                    }
                     // rows of the MFMA = weights (n), columns = tokens (m)
-                    acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(plane, cols, acc[i], 0, 0, 0);
+                    acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(plane, act[c][i], acc[i], 0, 0, 0);
                 }
             // fold the planes, scaled by 128 so that one shift-add per plane does it:
             //   128 * sum_k q b = sum_{i<7} acc_i * 2^(7-i) - acc_7      (|.| < 2^24 per chunk)
@@ -451,16 +257,9 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         }
         return;
     }
-    if constexpr (FUSED) {
-        rs = fold_slots<MAXW>(smi, OpSum{});
-        if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0) {
-            if (a.gamma_out) a.gamma_out[0] = gm;
-            if (a.rowsum_out) a.rowsum_out[0] = rs;
-        }
-    }
     for (int t = w; t < tpb; t += W) {
         v4i sum = (v4i){0, 0, 0, 0};
-        if ((FUSED == 1 || (!FUSED && MAXW == 8)) && W >= 3) {  // uniform
+        if (MAXW == 8 && W >= 3) {  // uniform
             // four waves' sums at a time, read independently of one another (the regions of absent waves are
             // not read: another wave's is, masked)
 #pragma unroll
@@ -476,9 +275,8 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                 for (int i = 0; i < 4; ++i) sum += p[i] & -(int)(w0 + i < W);
             }
         } else {
-            // with one or two waves, with 16, or behind the long row's quantiser, the plain loop is the faster one: from
-            // codes 1 x 256 -> 512 2.47 us for 2.56, 1 x 16384 -> 4096 4.4 for 4.7; 1 x 28672 -> 7168 in one
-            // launch 15.9 for 16.5
+            // with one or two waves, or with 16, the plain loop is the faster one (from codes 1 x 256 -> 512 2.47 us
+            // for 2.56, 1 x 16384 -> 4096 4.4 for 4.7)
             for (int ww = 0; ww < W; ++ww)
                 sum += *reinterpret_cast<const v4i*>(&red[((ww * T + t) * kWave + l) * 4]);
         }
@@ -607,7 +405,7 @@ __global__ __launch_bounds__(256) void groups_reduce(GemmArgs a) {
     *reinterpret_cast<vf*>(a.Y + m * a.N + n) = y;
 }
 
-static int num_cus() {
+int num_cus() {
     static int n = 0;
     if (n == 0) {
         int dev = 0;
@@ -619,40 +417,28 @@ static int num_cus() {
     return n;
 }
 
-template <int C, int T, int MAXT, bool ONE_ROUND, int FUSED = 0, bool KGRP = false>
+template <int C, int T, int MAXT, bool ONE_ROUND, bool KGRP = false>
 static void launch_one(const GemmArgs& a, int W, int tpb, hipStream_t s) {
     const int64_t TN = tiles_n(a.N);
     const unsigned splits = KGRP ? 1u : a.kgroups > 1 ? (unsigned)a.kgroups
                             : a.split_k ? (unsigned)((a.K + a.split_k - 1) / a.split_k) : 1u;
     const dim3 grid((unsigned)((TN + tpb - 1) / tpb), splits);
-    gemm_decode_kernel<C, T, MAXT, ONE_ROUND, FUSED, KGRP><<<grid, W * kWave, 0, s>>>(a, tpb);
+    gemm_decode_kernel<C, T, MAXT, ONE_ROUND, KGRP><<<grid, W * kWave, 0, s>>>(a, tpb);
 }
 
 // one round, up to 8 waves, exactly tpb = 1..8 tiles per group
-template <int C, int FUSED, bool KGRP = false>
+template <int C, bool KGRP = false>
 static void launch_tiles(const GemmArgs& a, int W, int tpb, hipStream_t s) {
     switch (tpb) {
-        case 1: launch_one<C, 1, 512, true, FUSED, KGRP>(a, W, 1, s); break;
-        case 2: launch_one<C, 2, 512, true, FUSED, KGRP>(a, W, 2, s); break;
-        case 3: launch_one<C, 3, 512, true, FUSED, KGRP>(a, W, 3, s); break;
-        case 4: launch_one<C, 4, 512, true, FUSED, KGRP>(a, W, 4, s); break;
-        case 5: launch_one<C, 5, 512, true, FUSED, KGRP>(a, W, 5, s); break;
-        case 6: launch_one<C, 6, 512, true, FUSED, KGRP>(a, W, 6, s); break;
-        case 7: launch_one<C, 7, 512, true, FUSED, KGRP>(a, W, 7, s); break;
-        default: launch_one<C, 8, 512, true, FUSED, KGRP>(a, W, 8, s); break;
+        case 1: launch_one<C, 1, 512, true, KGRP>(a, W, 1, s); break;
+        case 2: launch_one<C, 2, 512, true, KGRP>(a, W, 2, s); break;
+        case 3: launch_one<C, 3, 512, true, KGRP>(a, W, 3, s); break;
+        case 4: launch_one<C, 4, 512, true, KGRP>(a, W, 4, s); break;
+        case 5: launch_one<C, 5, 512, true, KGRP>(a, W, 5, s); break;
+        case 6: launch_one<C, 6, 512, true, KGRP>(a, W, 6, s); break;
+        case 7: launch_one<C, 7, 512, true, KGRP>(a, W, 7, s); break;
+        default: launch_one<C, 8, 512, true, KGRP>(a, W, 8, s); break;
     }
-}
-
-// One token and a K that one round of waves covers: the small-batch kernel can quantise the row
-// itself.  Up to 32 chunks a wave holds one or two of them as register operands; up to 64 it
-// walks eight, with the operands read from LDS.  Every workgroup repeats the quantiser, so it
-// pays only while one round of workgroups covers N (8, 2 or 3 tiles a group at most, as the
-// launcher below chooses): K = N = 28672 measured 58 us fused against 44 us in two launches.
-bool gemm_decode_fuses_quant(int64_t M, int64_t K, int64_t N) {
-    const int64_t TK = tiles_k(K);
-    if (M != 1 || TK > 64 || tuning().decode_nofuse) return false;
-    const int64_t cap = TK <= 16 ? 8 : TK <= 32 ? 2 : 3;
-    return tiles_n(N) <= cap * num_cus();
 }
 
 // K > 16384 with a workspace: split K over workgroups so that every slice takes the one-round
@@ -727,10 +513,9 @@ hipError_t launch_gemm_decode(const GemmArgs& a_in, hipStream_t s) {
     const int64_t TN = tiles_n(a.N);
     int64_t TK = tiles_k(a.K);
     int splits = 1;
-    const bool fused = a.x_row != nullptr;  // the caller asked gemm_decode_fuses_quant
     const size_t need = gemm_split_ws_bytes(a.M, a.N, a.K);
     if (a.kgroups > 1) {  // one slice per K-group; the caller sized split_ws for it
-        if (fused || !a.split_ws || a.split_ws_bytes < (size_t)a.kgroups * a.M * a.N * 4)
+        if (!a.split_ws || a.split_ws_bytes < (size_t)a.kgroups * a.M * a.N * 4)
             return hipErrorInvalidValue;
         a.split_k = 0;
         // All groups inside a workgroup when their chunks fit the waves of one (up to 8 waves of
@@ -745,14 +530,14 @@ hipError_t launch_gemm_decode(const GemmArgs& a_in, hipStream_t s) {
         };
         bool done = true;
         if (tuning().group_slices) done = false;  // (tests: the K-groups as slices of the grid)
-        else if (TK % 2 == 0 && V / 2 <= 8) launch_tiles<2, 0, true>(a, (int)(V / 2), tiles_for(8), s);
-        else if (V <= 8) launch_tiles<1, 0, true>(a, (int)V, tiles_for(8), s);
+        else if (TK % 2 == 0 && V / 2 <= 8) launch_tiles<2, true>(a, (int)(V / 2), tiles_for(8), s);
+        else if (V <= 8) launch_tiles<1, true>(a, (int)V, tiles_for(8), s);
         else if (TK % 2 == 0 && V / 2 <= 16) {
-            if (tiles_for(2) <= 1) launch_one<2, 1, 1024, true, 0, true>(a, (int)(V / 2), 1, s);
-            else launch_one<2, 2, 1024, true, 0, true>(a, (int)(V / 2), 2, s);
+            if (tiles_for(2) <= 1) launch_one<2, 1, 1024, true, true>(a, (int)(V / 2), 1, s);
+            else launch_one<2, 2, 1024, true, true>(a, (int)(V / 2), 2, s);
         } else if (V <= 16) {
-            if (tiles_for(2) <= 1) launch_one<1, 1, 1024, true, 0, true>(a, (int)V, 1, s);
-            else launch_one<1, 2, 1024, true, 0, true>(a, (int)V, 2, s);
+            if (tiles_for(2) <= 1) launch_one<1, 1, 1024, true, true>(a, (int)V, 1, s);
+            else launch_one<1, 2, 1024, true, true>(a, (int)V, 2, s);
         } else {
             done = false;
         }
@@ -761,7 +546,7 @@ hipError_t launch_gemm_decode(const GemmArgs& a_in, hipStream_t s) {
             return hipGetLastError();
         }
         splits = a.kgroups;  // else: the K-groups as slices of the grid
-    } else if (need && !fused && a.split_ws && a.split_ws_bytes >= need && !tuning().decode_nosplit) {
+    } else if (need && a.split_ws && a.split_ws_bytes >= need && !tuning().decode_nosplit) {
         splits = (int)((TK + 15) / 16);
         const int64_t per = (TK + splits - 1) / splits;  // tiles per slice, evenly
         splits = (int)((TK + per - 1) / per);            // slices that actually hold tiles
@@ -784,36 +569,19 @@ hipError_t launch_gemm_decode(const GemmArgs& a_in, hipStream_t s) {
         // K < 4096: one K-chunk per wave, W = TK waves cover K in one round
         const int W = (int)TK;
         const int tpb = tiles_per_group(8);
-        if (fused) launch_tiles<1, 1>(a, W, tpb, s);
-        else launch_tiles<1, 0>(a, W, tpb, s);
+        launch_tiles<1>(a, W, tpb, s);
     } else if (TK <= 16) {
         // 4096 <= K <= 8192: two chunks per wave (the fold of the bit planes, once per tile and
         // wave, is then shared by two chunks), W = ceil(TK/2) <= 8 waves, one round
         const int W = (int)((TK + 1) / 2);
         const int tpb = tiles_per_group(8);
-        if (fused) launch_tiles<2, 1>(a, W, tpb, s);
-        else launch_tiles<2, 0>(a, W, tpb, s);
+        launch_tiles<2>(a, W, tpb, s);
     } else if (TK <= 32) {
         // K <= 16384: up to 16 waves of two chunks, one round; 128 registers per lane
         const int W = (int)((TK + 1) / 2);
         const int tpb = tiles_per_group(2);
-        if (fused) {
-            if (tpb <= 1) launch_one<2, 1, 1024, true, 1>(a, W, 1, s);
-            else launch_one<2, 2, 1024, true, 1>(a, W, 2, s);
-        } else if (tpb <= 1) {
-            launch_one<2, 1, 1024, true>(a, W, 1, s);
-        } else {
-            launch_one<2, 2, 1024, true>(a, W, 2, s);
-        }
-    } else if (fused) {
-        // one token, K <= 32768: eight chunks per wave (the last ones masked), up to 8 waves, one
-        // round, up to three tiles per group in registers (96 of them)
-        const int W = (int)((TK + 7) / 8);
-        switch (tiles_per_group(3)) {
-            case 1: launch_one<8, 1, 512, true, 2>(a, W, 1, s); break;
-            case 2: launch_one<8, 2, 512, true, 2>(a, W, 2, s); break;
-            default: launch_one<8, 3, 512, true, 2>(a, W, 3, s); break;
-        }
+        if (tpb <= 1) launch_one<2, 1, 1024, true>(a, W, 1, s);
+        else launch_one<2, 2, 1024, true>(a, W, 2, s);
     } else {
         // longer K: two chunks per wave and round, up to 16 waves, several rounds
         const int64_t slots = (TK + 1) / 2;

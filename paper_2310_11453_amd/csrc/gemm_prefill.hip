@@ -805,18 +805,6 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
     wait_vmcnt<0>();
 }
 
-static int num_cus() {
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            n = prop.multiProcessorCount;
-        if (n <= 0) n = 256;
-    }
-    return n;
-}
-
 template <int BM, int BN, int WM, int WN, int NS>
 static void launch_tile(const GemmArgs& a, hipStream_t s) {
     const bool plain = a.beta_rows >= a.N && a.gstride == 1 && !a.eta;

@@ -12,7 +12,7 @@ constexpr int64_t kMaxGemmK = 65536;
 // Launch-time switches for tests and benchmarks (bitlinear_set_tuning in the C ABI; defaults:
 // everything 0 = the launchers decide).  One process-wide instance, defined in api.hip.
 struct Tuning {
-    int decode_nofuse;     // forward at one token: quantiser and GEMM as two launches
+    int decode_nofuse;     // forward of a few tokens: quantiser and GEMM always as two launches
     int decode_nosplit;    // M <= 16: never split K over workgroups
     int decode_tiles;      // M <= 16: weight tiles per workgroup (1..8)
     int mid_nosplit;       // 16 < M <= 64: never split K over workgroups
@@ -73,8 +73,14 @@ struct QuantArgs {
     // [groups] per tensor).
     bool nonneg;
     float* eta;
+    double inv_k;  // 1 / K (set by the launcher)
 };
 bool quant_supported(int64_t K);
+// how a row is split: wpr waves, nv float4 a lane (K <= 32768)
+struct QuantShape {
+    int wpr, nv;
+};
+QuantShape quant_shape(int64_t M, int64_t K, bool per_tensor);
 hipError_t launch_quant(const QuantArgs& a, hipStream_t s);
 
 // gemm_decode.hip / gemm_prefill.hip
@@ -115,12 +121,10 @@ struct GemmArgs {
     // 0 or 1: off.
     int kgroups;
     int64_t group_packed;
-    // One token (M = 1, K <= 32768) straight from fp32, small-batch kernel only: every workgroup
-    // normalises and quantises the row for itself (Eq. 12, Eq. 4-5) while its first weight tiles
-    // are on their way, instead of reading codes / gamma / rowsum, so the layer is one launch.
-    // Workgroup 0 also writes the three to codes_out / gamma_out / rowsum_out and the normalised
-    // row to xhat_out.  nullptr: codes
-    // are read.
+    // A few tokens of a short row straight from fp32 (launch_gemm_tokens, and only it): every workgroup normalises and
+    // quantises the rows for itself (Eq. 12, Eq. 4-5) while its weight tiles are on their way, so the layer is
+    // one launch.  Workgroup 0 also writes codes, gamma and row sums to codes_out / gamma_out / rowsum_out and, of
+    // one token, the normalised row to xhat_out.
     const float* x_row;
     const float* ln_gain;  // [K] or nullptr
     const float* ln_bias;  // [K] or nullptr
@@ -131,7 +135,6 @@ struct GemmArgs {
     int32_t* rowsum_out;
     float* xhat_out;  // [K]: the normalised row the codes were rounded from
 };
-bool gemm_decode_fuses_quant(int64_t M, int64_t K, int64_t N);
 size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t K);
 size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K, bool one_beta);
 size_t group_split_bytes(int64_t M, int64_t N, int64_t K, int groups);  // K: a group's
@@ -141,6 +144,9 @@ void launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_read_probe(const void* src, size_t bytes, int workgroups, int threads,
                              uint32_t* sink, hipStream_t s);
 hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t s);
+bool gemm_tokens_fuses_quant(int64_t M, int64_t K, int64_t N);  // gamma per token
+hipError_t launch_gemm_tokens(const GemmArgs& a, hipStream_t s);
+int num_cus();
 hipError_t launch_gemm_prefill(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_mid(const GemmArgs& a, hipStream_t s);  // 16 < M <= 64
 hipError_t launch_gemm_mid_tiles(const GemmArgs& a, int bm, int64_t per, hipStream_t s);  // M > 64

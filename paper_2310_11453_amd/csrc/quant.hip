@@ -48,8 +48,8 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
     constexpr int NW = WPR < 4 ? 4 : WPR;  // waves per workgroup
     constexpr int RPW = NW / WPR;          // rows per workgroup
     constexpr int RT = WPR * kWave;        // lanes per row
-    __shared__ double smd[2][NW];
-    __shared__ float smf[4][NW];
+    __shared__ double sm_k[2 * NW];
+    __shared__ float sm_f[2 * NW], smf[2][NW];
     __shared__ int smi[NW];
 
     const int wave = threadIdx.x / kWave;
@@ -88,79 +88,61 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
     float lo = 0.f, hi_row = 0.f;  // Eq. 6 only: the row's minimum (eta) and maximum; amax = max - min
 
     if (!a.skip_ln) {
-        double mu, rstd;
+        const float cf = stats_centre(a.X[row * a.K]);
+        const double c = (double)cf;
+        RowNorm n;
         if constexpr (MODE == kApply) {
-            mu = a.rowstats[2 * row];
-            rstd = a.rowstats[2 * row + 1];
+            n.shift = a.rowstats[2 * row];
+            n.rstd = a.rowstats[2 * row + 1];
         } else {
-            // One pass for the mean and the variance: sums of x and of (x - c)^2 in fp64, with
-            // c an element of the row, so that var = E[(x-c)^2] - (mu-c)^2 loses no digits to
-            // a large common offset.  Minimum and maximum ride along for the absmax.
-            const double c = (double)a.X[row * a.K];
-            double s = 0.0, q = 0.0;
-            float mn = v[0].x, mx = v[0].x;  // always an element of the row (clamped index)
+            RowStats rs;
+            rs.mx = cf;
+            rs.nmn = -cf;
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
-                if (t + j * RT < K4) {
-                    const double dx = (double)v[j].x, dy = (double)v[j].y;
-                    const double dz = (double)v[j].z, dw = (double)v[j].w;
-                    s += (dx + dy) + (dz + dw);
-                    q = fma(dx - c, dx - c, q);
-                    q = fma(dy - c, dy - c, q);
-                    q = fma(dz - c, dz - c, q);
-                    q = fma(dw - c, dw - c, q);
-                    mn = fminf(fminf(mn, v[j].x), fminf(fminf(v[j].y, v[j].z), v[j].w));
-                    mx = fmaxf(fmaxf(mx, v[j].x), fmaxf(fmaxf(v[j].y, v[j].z), v[j].w));
+                if (K4 < (j + 1) * RT) {  // uniform: this piece of the row is ragged
+                    const bool in = t + j * RT < K4;
+                    v[j].x = in ? v[j].x : cf;
+                    v[j].y = in ? v[j].y : cf;
+                    v[j].z = in ? v[j].z : cf;
+                    v[j].w = in ? v[j].w : cf;
                 }
+                double d[4];
+                stats_add(rs, v[j], c, d);
             }
             // one barrier for the four values
-            s = wave_reduce(s, OpSum{});
-            q = wave_reduce(q, OpSum{});
-            mn = wave_reduce(mn, OpMin{});
-            mx = wave_reduce(mx, OpMax{});
+            PairStats st = stats_wave(rs);
             if constexpr (WPR > 1) {
-                if ((threadIdx.x & (kWave - 1)) == 0) {
-                    smd[0][wave] = s;
-                    smd[1][wave] = q;
-                    smf[0][wave] = mn;
-                    smf[1][wave] = mx;
-                }
+                stats_leave(st, sm_k, sm_f, wave);
                 __syncthreads();
-                s = fold_slots<WPR>(smd[0] + rw * WPR, OpSum{});
-                q = fold_slots<WPR>(smd[1] + rw * WPR, OpSum{});
-                mn = fold_slots<WPR>(smf[0] + rw * WPR, OpMin{});
-                mx = fold_slots<WPR>(smf[1] + rw * WPR, OpMax{});
+                st = stats_fold(sm_k + 2 * rw * WPR, sm_f + 2 * rw * WPR, WPR);
             }
-            mu = s / (double)a.K;
-            const double qs = q;
-            const double var = fmax(qs / (double)a.K - (mu - c) * (mu - c), 0.0);
-            rstd = 1.0 / sqrt(var + (double)a.eps);
+            float hi;
+            n = stats_finish(st, c, a.inv_k, (double)a.eps, lo, hi);
             if constexpr (MODE == kStats) {
                 if (t == 0 && live) {
-                    a.rowstats[2 * row] = mu;
-                    a.rowstats[2 * row + 1] = rstd;
+                    a.rowstats[2 * row] = n.shift;
+                    a.rowstats[2 * row + 1] = n.rstd;
                 }
             }
             if (!affine) {
-                // x -> fl32((x - mu) * rstd) is monotone, so the largest magnitude of the
-                // normalised row is reached at the row's minimum or maximum.
-                lo = (float)(((double)mn - mu) * rstd);
-                const float hi = (float)(((double)mx - mu) * rstd);
+                // x -> x^ is monotone, so the largest magnitude of the normalised row is reached at the row's
+                // minimum or maximum.
                 hi_row = hi;
                 amax = a.nonneg ? hi - lo : fmaxf(fabsf(lo), fabsf(hi));
                 have_amax = true;
             }
         }
         if (MODE != kStats || affine) {
-            forget();
+            if constexpr (NV > 4) forget();
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
                 const int idx = t + j * RT;
                 float4 o;
-                o.x = (float)(((double)v[j].x - mu) * rstd);
-                o.y = (float)(((double)v[j].y - mu) * rstd);
-                o.z = (float)(((double)v[j].z - mu) * rstd);
-                o.w = (float)(((double)v[j].w - mu) * rstd);
+                o.x = normalised(n, (double)v[j].x - c);
+                o.y = normalised(n, (double)v[j].y - c);
+                o.z = normalised(n, (double)v[j].z - c);
+                o.w = normalised(n, (double)v[j].w - c);
                 if (idx < K4) {
                     if (a.gain) {
                         const float4 g = reinterpret_cast<const float4*>(a.gain + grp * a.K)[idx];
@@ -204,7 +186,7 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
                     m = fmaxf(m, fmaxf(fmaxf(fabsf(v[j].x), fabsf(v[j].y)),
                                        fmaxf(fabsf(v[j].z), fabsf(v[j].w))));
             }
-            amax = row_reduce<WPR>(m, OpMax{}, smf[2], rw, wr);
+            amax = row_reduce<WPR>(m, OpMax{}, smf[0], rw, wr);
         } else if (!have_amax) {  // Eq. 6 on such a row: minimum and maximum of the values
             float mn = v[0].x, mx = v[0].x;  // lane 0's first element always exists
 #pragma unroll
@@ -218,8 +200,8 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
                 mn = __builtin_inff();
                 mx = -__builtin_inff();
             }
-            lo = row_reduce<WPR>(mn, OpMin{}, smf[2], rw, wr);
-            hi_row = row_reduce<WPR>(mx, OpMax{}, smf[3], rw, wr);
+            lo = row_reduce<WPR>(mn, OpMin{}, smf[0], rw, wr);
+            hi_row = row_reduce<WPR>(mx, OpMax{}, smf[1], rw, wr);
             amax = hi_row - lo;
         }
         if constexpr (MODE == kStats) {
@@ -490,8 +472,35 @@ static void launch_mode(const QuantArgs& a, hipStream_t s) {
 // Waves per row (up to 16): enough of them that the chip holds about sixteen waves per CU (short rows
 // of a small batch are split over several waves rather than leaving most SIMDs idle), and
 // never more than 16 float4 per lane.
-hipError_t launch_quant(const QuantArgs& a, hipStream_t s) {
-    const int64_t K4 = a.K / 4;
+QuantShape quant_shape(int64_t M, int64_t K, bool per_tensor) {
+    const int64_t K4 = K / 4;
+    int wpr = 1;
+    while (wpr < 8 && K4 > (int64_t)wpr * kWave * 16) wpr *= 2;             // capacity
+    while (wpr < 8 && M * wpr < 4096 && K4 >= (int64_t)wpr * 2 * kWave * 4) wpr *= 2;  // occupancy
+    // A small batch is the latency of one row: loads, two passes of fp64 per element of a lane, the
+    // reductions.  One more doubling, down to two float4 per lane, and 16 waves beyond K = 16384, pay
+    // while the batch stays below 2048 waves (us, before / after: 8 x 2048 4.05 / 3.6, 8 x 4096 4.3 / 4.05,
+    // 64 x 7168 5.8 / 4.9, 64 x 28672 9.5 / 8.6; 512 x 4096 would go from 6.4 to 6.5, 8 x 16384 with 16
+    // waves from 6.1 to 6.35).  Not for short rows with a gamma per tensor from about 128 rows on: a workgroup
+    // sends one candidate for the maximum, and half the rows to a workgroup are twice the candidates on
+    // one address (both passes, without / with: 512 x 1024 9.2 / 10.2, 333 x 2048 10.1 / 11.8, but 33 x 2048 8.3 / 7.5
+    // and 512 x 3072 12.8 / 11.4).
+    if (M * wpr * 2 <= 2048 && !(per_tensor && M > 128 && K4 <= 512)) {
+        if (wpr < 8 && K4 >= (int64_t)wpr * 2 * kWave * 2) wpr *= 2;
+        else if (K4 > 8 * kWave * 8) wpr = 16;
+    }
+    if (const int v = tuning().quant_wpr)
+        if ((v == 1 || v == 2 || v == 4 || v == 8) && K4 <= (int64_t)v * kWave * 16) wpr = v;
+    const int64_t per_lane = (K4 + wpr * kWave - 1) / (wpr * kWave);
+    int nv = 1;
+    while (nv < per_lane) nv *= 2;
+    if (wpr > 1 && nv < 2) nv = 2;
+    return {wpr, nv};
+}
+
+hipError_t launch_quant(const QuantArgs& a_in, hipStream_t s) {
+    QuantArgs a = a_in;
+    a.inv_k = 1.0 / (double)a.K;
     if (!quant_in_registers(a.K)) {
         const unsigned grid = (unsigned)a.M;
         if (!a.per_tensor) {
@@ -503,27 +512,8 @@ hipError_t launch_quant(const QuantArgs& a, hipStream_t s) {
         }
         return hipGetLastError();
     }
-    int wpr = 1;
-    while (wpr < 8 && K4 > (int64_t)wpr * kWave * 16) wpr *= 2;             // capacity
-    while (wpr < 8 && a.M * wpr < 4096 && K4 >= (int64_t)wpr * 2 * kWave * 4) wpr *= 2;  // occupancy
-    // A small batch is the latency of one row: loads, two passes of fp64 per element of a lane, the
-    // reductions.  One more doubling, down to two float4 per lane, and 16 waves beyond K = 16384, pay
-    // while the batch stays below 2048 waves (us, before / after: 8 x 2048 4.05 / 3.6, 8 x 4096 4.3 / 4.05,
-    // 64 x 7168 5.8 / 4.9, 64 x 28672 9.5 / 8.6; 512 x 4096 would go from 6.4 to 6.5, 8 x 16384 with 16
-    // waves from 6.1 to 6.35).  Not for short rows with a gamma per tensor from about 128 rows on: a workgroup
-    // sends one candidate for the maximum, and half the rows to a workgroup are twice the candidates on
-    // one address (both passes, without / with: 512 x 1024 9.2 / 10.2, 333 x 2048 10.1 / 11.8, but 33 x 2048 8.3 / 7.5
-    // and 512 x 3072 12.8 / 11.4).
-    if (a.M * wpr * 2 <= 2048 && !(a.per_tensor && a.M > 128 && K4 <= 512)) {
-        if (wpr < 8 && K4 >= (int64_t)wpr * 2 * kWave * 2) wpr *= 2;
-        else if (K4 > 8 * kWave * 8) wpr = 16;
-    }
-    if (const int v = tuning().quant_wpr)
-        if ((v == 1 || v == 2 || v == 4 || v == 8) && K4 <= (int64_t)v * kWave * 16) wpr = v;
-    const int64_t per_lane = (K4 + wpr * kWave - 1) / (wpr * kWave);
-    int nv = 1;
-    while (nv < per_lane) nv *= 2;
-    if (wpr > 1 && nv < 2) nv = 2;
+    const QuantShape q = quant_shape(a.M, a.K, a.per_tensor);
+    const int wpr = q.wpr, nv = q.nv;
 #define BL_QUANT_CASE(W, V) if (wpr == W && nv == V) launch_mode<W, V>(a, s); else
     BL_QUANT_CASE(1, 1) BL_QUANT_CASE(1, 2) BL_QUANT_CASE(1, 4) BL_QUANT_CASE(1, 8) BL_QUANT_CASE(1, 16)
     BL_QUANT_CASE(2, 2) BL_QUANT_CASE(2, 4) BL_QUANT_CASE(2, 8) BL_QUANT_CASE(2, 16)

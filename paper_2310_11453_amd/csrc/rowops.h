@@ -76,6 +76,123 @@ __device__ inline T wave_reduce(T v, Op op) {
     return op(lo, hi);
 }
 
+// ---- LayerNorm statistics of a row in one pass ---------------------------------------------
+// Sums in fp64 of d = x - c and of d^2 about an element c of the row, so that mean = c + sum / K and var =
+// E[d^2] - E[d]^2 lose nothing to a large common offset, and the extremes, for the absmax: x -> x^ is
+// monotone.  A launch of a few rows is the length of this chain: a wave issues one instruction in four cycles
+// whatever its kind (2.5 ns at the clock of such launches), so what counts here is how many there are.
+// Elements past the row hold c and add nothing.  The smallest value is kept negated: both are maxima then.
+struct RowStats {
+    double s = 0.0, q = 0.0;
+    float mx, nmn;
+};
+// the row's own element, or 0 where that is not finite (inf - inf would lose an infinity elsewhere in the row)
+__device__ inline float stats_centre(float first) {
+    return (__float_as_uint(first) & 0x7f800000u) == 0x7f800000u ? 0.f : first;
+}
+// plain instructions: fmaxf quietens both operands first, three more instructions each
+__device__ inline float max_raw(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ inline void stats_add(RowStats& st, const float4& v, double c, double (&d)[4]) {
+    d[0] = (double)v.x - c;
+    d[1] = (double)v.y - c;
+    d[2] = (double)v.z - c;
+    d[3] = (double)v.w - c;
+    st.s += (d[0] + d[1]) + (d[2] + d[3]);
+    st.q = fma(d[0], d[0], st.q);
+    st.q = fma(d[1], d[1], st.q);
+    st.q = fma(d[2], d[2], st.q);
+    st.q = fma(d[3], d[3], st.q);
+    asm("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4" : "+v"(st.mx) : "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
+    asm("v_max3_f32 %0, %0, -%1, -%2\n\tv_max3_f32 %0, %0, -%3, -%4"
+        : "+v"(st.nmn) : "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
+}
+// The wave's totals with the even lanes carrying the sum and the maximum, the odd ones the sum of squares and the
+// negated minimum: two reductions instead of four.
+struct PairStats {
+    double k;
+    float f;
+};
+template <int CTRL>
+__device__ inline void pair_step(PairStats& p) {
+    p.k += dpp_mov<CTRL>(p.k);
+    p.f = max_raw(p.f, dpp_mov<CTRL>(p.f));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kRor4 = 0x124, kRor8 = 0x128;  // DPP: lane ^ 1, lane ^ 2, rotations of 16
+constexpr int kEven = 0xA0, kOdd = 0xF5;                                 // the pair's even, odd lane in both
+__device__ inline PairStats stats_wave(const RowStats& st) {
+    const bool odd = threadIdx.x & 1;
+    PairStats p;
+    p.k = (odd ? st.q : st.s) + dpp_mov<kXor1>(odd ? st.s : st.q);
+    p.f = max_raw(odd ? st.nmn : st.mx, dpp_mov<kXor1>(odd ? st.mx : st.nmn));
+    pair_step<kXor2>(p);
+    pair_step<kRor4>(p);
+    pair_step<kRor8>(p);
+    double lo, hi;
+    float flo, fhi;
+    lane_swap<false>(p.k, lo, hi);
+    lane_swap<false>(p.f, flo, fhi);
+    p.k = lo + hi;
+    p.f = max_raw(flo, fhi);
+    lane_swap<true>(p.k, lo, hi);
+    lane_swap<true>(p.f, flo, fhi);
+    p.k = lo + hi;
+    p.f = max_raw(flo, fhi);
+    return p;
+}
+// `parts` waves share the row (a power of two up to 16, uniform): lanes 0 and 1 of each leave their pair in slots
+// 2 * part, 2 * part + 1, and behind a barrier every wave folds them.
+__device__ inline void stats_leave(const PairStats& p, double* k, float* f, int part) {
+    const int l = threadIdx.x & (kWave - 1);
+    if (l < 2) {
+        k[2 * part + l] = p.k;
+        f[2 * part + l] = p.f;
+    }
+}
+__device__ inline PairStats stats_fold(const double* k, const float* f, int parts) {
+    const int i = threadIdx.x & (2 * parts - 1);
+    PairStats p{k[i], f[i]};
+    pair_step<kXor2>(p);
+    if (parts > 2) pair_step<kRor4>(p);
+    if (parts > 4) pair_step<kRor8>(p);
+    if (parts > 8) {
+        double lo, hi;
+        float flo, fhi;
+        lane_swap<false>(p.k, lo, hi);
+        lane_swap<false>(p.f, flo, fhi);
+        p.k = lo + hi;
+        p.f = max_raw(flo, fhi);
+    }
+    return p;
+}
+// x^ = fl32(d * rstd + shift), d = x - c
+struct RowNorm {
+    double rstd, shift;
+};
+__device__ inline float normalised(const RowNorm& n, double d) { return (float)fma(d, n.rstd, n.shift); }
+// 1 / sqrt(v) for v >= 0: the hardware's estimate (a relative error below 2^-22) and one step of third order, good to
+// the last bit or two; a square root and a division are four times the instructions, one after another
+__device__ inline double rsqrt64(double v) {
+    const double y = __builtin_amdgcn_rsq(v);
+    const double e = fma(-(v * y), y, 1.0);
+    const double r = fma(y * e, fma(e, 0.375, 0.5), y);
+    return v > 0.0 ? r : y;
+}
+// inv_k = 1 / K.  lo and hi: the row's smallest and largest x^.
+__device__ inline RowNorm stats_finish(const PairStats& p, double c, double inv_k, double eps, float& lo, float& hi) {
+    const double dm = dpp_mov<kEven>(p.k) * inv_k;
+    const double var = fmax(fma(-dm, dm, dpp_mov<kOdd>(p.k) * inv_k), 0.0);
+    RowNorm n;
+    n.rstd = rsqrt64(var + eps);
+    n.shift = -(dm * n.rstd);
+    lo = normalised(n, -(double)dpp_mov<kOdd>(p.f) - c);
+    hi = normalised(n, (double)dpp_mov<kEven>(p.f) - c);
+    return n;
+}
+
 // ---- rounding to codes -------------------------------------------------------------------
 // clamp(rne(t), LO, 127) as the low byte of the result.  The bounds are integers, so clamping before
 // the rounding is the same thing; 1.5 * 2^23 has an ulp of one and is even, so adding it rounds half to

@@ -487,6 +487,43 @@ def test_forward_few_tokens(bl, M, K, N, variant):
     assert np.array_equal(y, y_ref)
 
 
+# five to eight tiles a workgroup, with one chunk of K a wave and with two
+@pytest.mark.parametrize("K,N", [(2080, 16390), (3104, 28688), (4096, 32761), (4640, 24560), (8192, 32768)])
+def test_forward_single_token_many_tiles(bl, K, N, tuning):
+    test_forward_single_token(bl, K, N, "plain", tuning)
+
+
+# Two to eight tokens of short rows, one launch: the same codes, gamma, row sums and outputs, bit for bit, as the
+# quantiser and the GEMM in two.  One (row, part) pair a wave or two, one to four float4 a lane with ragged last
+# pieces, one chunk of K a wave or two (an odd number of them), one to eight tiles of a workgroup, ragged N.
+@pytest.mark.parametrize("M,K,N", [(2, 32, 1), (8, 256, 512), (5, 544, 4100), (3, 992, 16), (8, 1024, 8195),
+                                   (7, 1568, 300), (4, 2048, 12304), (2, 2080, 16372), (3, 2528, 70), (2, 4096, 16381),
+                                   (2, 4640, 48), (2, 8192, 16384)])
+@pytest.mark.parametrize("variant", ["plain", "affine", "skip_ln", "acc", "inf"])
+def test_forward_tokens_in_one_launch(bl, M, K, N, variant, tuning):
+    print(f"tokens in one launch M={M} K={K} N={N} {variant}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + K + N)
+    packed, _, beta = bl.bitlinear_pack_weights(torch.randn(N, K, device="cuda", generator=g) * 0.02)
+    X = torch.randn(M, K, device="cuda", generator=g) * 3 + 1
+    X[M - 1] *= 5.0
+    if variant == "inf":
+        X[0, 0], X[1, K // 2], X[M - 1, K - 1] = float("inf"), float("-inf"), float("nan")
+    kw = dict(flags={"skip_ln": bl.FLAG_SKIP_LN, "acc": bl.FLAG_OUT_ACC_I32}.get(variant, 0))
+    if variant == "affine":
+        kw.update(ln_gain=1 + 0.1 * torch.randn(K, device="cuda", generator=g),
+                  ln_bias=0.1 * torch.randn(K, device="cuda", generator=g))
+    lay, got = bl.forward_workspace_layout(M, N, K), []
+    for spec in (None, "decode_nofuse=1"):
+        tuning(spec)
+        ws = torch.zeros(bl.workspace_bytes(bl.OP_FORWARD, M, N, K), dtype=torch.uint8, device="cuda")
+        call = lambda: bl.bitlinear_forward(X, packed, N, beta, workspace=ws, **kw)
+        assert kernel_launches(bl, call) == (1 if spec is None else 2)
+        got.append([host(call().view(torch.int32))] +
+                   [host(ws[lay[k]:lay[k] + n]) for k, n in (("codes", M * K), ("gamma", 4 * M), ("rowsum", 4 * M))])
+    for one, two in zip(*got):
+        assert np.array_equal(one, two)
+
+
 def test_empty_batch_and_errors(bl):
     W = dev(wl.make_weight(32, 64, 0.02, 1))
     packed, alpha, beta = bl.bitlinear_pack_weights(W)
