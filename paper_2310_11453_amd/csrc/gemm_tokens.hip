@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kTokWaves* kWave) void gemm_tokens_kernel(TokArgs a
         for (int j = 0; j < NV; ++j) {
             const int idx = t[p] + j * RT;
             const float4 x = v[p][j];
-            const uint32_t wd = code_word<-128>(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
+            const uint32_t wd = code_word(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
             if (idx < K4 && live[p]) {
                 rs = __builtin_amdgcn_sdot4((int)wd, 0x01010101, rs, false);  // sum of the four codes
                 *reinterpret_cast<uint32_t*>(codes + row[p] * pitch + ((idx * 4) ^ (row[p] * 16))) = wd;

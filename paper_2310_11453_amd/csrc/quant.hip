@@ -36,6 +36,10 @@ __device__ inline void offer_extremes(const QuantArgs& a, int g, float lo, float
         atomicMax(a.gmax_bits + g, kh);
 }
 
+// A batch of a few rows is the length of one row's instruction stream (a wave issues one in four cycles, 2.5 ns in a graph
+// of short launches): the row's address is scalar, whole pieces of it go without masks, gain, bias and the shift
+// of Eq. 6 stand behind one branch each.  us in a layer's two launches, with these in every element's path and the
+// address in 64-bit vector arithmetic / now: 8 x 7168 4.2 / 3.4, 8 x 28672 7.7 / 6.7, 16 x 2048 3.4 / 3.2.
 // WPR waves share one token (row); a lane holds NV float4 of it.  Workgroups have at least
 // four waves, so short rows are handled four (or two) to a workgroup, one per wave, with no
 // barrier at all.
@@ -52,7 +56,8 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
     __shared__ float sm_f[2 * NW], smf[2][NW];
     __shared__ int smi[NW];
 
-    const int wave = threadIdx.x / kWave;
+    // the wave's index, and with it the row and its address, as scalars
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int rw = wave / WPR, wr = wave % WPR;
     const int t = wr * kWave + (threadIdx.x & (kWave - 1));
     int64_t row = (int64_t)blockIdx.x * RPW + rw;
@@ -63,8 +68,8 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
         if (!live) row = a.M - 1;
     }
     const int K4 = (int)(a.K / 4);
-    const float4* __restrict__ x4 = reinterpret_cast<const float4*>(a.X + row * a.K);
-    const int grp = a.groups > 1 ? (int)(row % a.groups) : 0;  // K-group of this row (Eq. 14-15)
+    const float* __restrict__ xrow = a.X + row * a.K;
+    const float4* __restrict__ x4 = reinterpret_cast<const float4*>(xrow);
 
     // The loads are unconditional (clamped index, value masked afterwards) so that all of
     // them are in flight before the first is needed.
@@ -72,8 +77,10 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int idx = t + j * RT;
-        v[j] = x4[idx < K4 ? idx : K4 - 1];
+        v[j] = x4[(uint32_t)(idx < K4 ? idx : K4 - 1)];
     }
+    const float first = *xrow;
+    const int grp = a.groups > 1 ? (int)((uint32_t)row % (uint32_t)a.groups) : 0;  // K-group of this row (Eq. 14-15)
     // Each pass over the row converts its elements to fp64 again: `forget` hides the values
     // from the optimiser between passes, or it would keep all the converted copies alive
     // (two registers per element) and the kernel would run at minimal occupancy.
@@ -88,7 +95,7 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
     float lo = 0.f, hi_row = 0.f;  // Eq. 6 only: the row's minimum (eta) and maximum; amax = max - min
 
     if (!a.skip_ln) {
-        const float cf = stats_centre(a.X[row * a.K]);
+        const float cf = stats_centre(first);
         const double c = (double)cf;
         RowNorm n;
         if constexpr (MODE == kApply) {
@@ -136,23 +143,28 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
         if (MODE != kStats || affine) {
             if constexpr (NV > 4) forget();
 #pragma unroll
-            for (int j = 0; j < NV; ++j) {
-                const int idx = t + j * RT;
-                float4 o;
-                o.x = normalised(n, (double)v[j].x - c);
-                o.y = normalised(n, (double)v[j].y - c);
-                o.z = normalised(n, (double)v[j].z - c);
-                o.w = normalised(n, (double)v[j].w - c);
-                if (idx < K4) {
-                    if (a.gain) {
-                        const float4 g = reinterpret_cast<const float4*>(a.gain + grp * a.K)[idx];
-                        o.x = o.x * g.x; o.y = o.y * g.y; o.z = o.z * g.z; o.w = o.w * g.w;
+            for (int j = 0; j < NV; ++j) {  // (elements past the row too: nothing is stored of them)
+                v[j].x = normalised(n, (double)v[j].x - c);
+                v[j].y = normalised(n, (double)v[j].y - c);
+                v[j].z = normalised(n, (double)v[j].z - c);
+                v[j].w = normalised(n, (double)v[j].w - c);
+            }
+            if (affine) {  // uniform
+#pragma unroll
+                for (int j = 0; j < NV; ++j) {
+                    const int idx = t + j * RT;
+                    if (idx < K4) {
+                        float4 o = v[j];
+                        if (a.gain) {
+                            const float4 g = reinterpret_cast<const float4*>(a.gain + grp * a.K)[idx];
+                            o.x = o.x * g.x; o.y = o.y * g.y; o.z = o.z * g.z; o.w = o.w * g.w;
+                        }
+                        if (a.bias) {
+                            const float4 b = reinterpret_cast<const float4*>(a.bias + grp * a.K)[idx];
+                            o.x = o.x + b.x; o.y = o.y + b.y; o.z = o.z + b.z; o.w = o.w + b.w;
+                        }
+                        v[j] = o;
                     }
-                    if (a.bias) {
-                        const float4 b = reinterpret_cast<const float4*>(a.bias + grp * a.K)[idx];
-                        o.x = o.x + b.x; o.y = o.y + b.y; o.z = o.z + b.z; o.w = o.w + b.w;
-                    }
-                    v[j] = o;
                 }
             }
         }
@@ -241,16 +253,24 @@ __global__ __launch_bounds__((WPR < 4 ? 4 : WPR) * kWave, 4) void ln_quant_rows(
     int rs = 0;
     uint32_t* __restrict__ c4 = reinterpret_cast<uint32_t*>(a.codes + row * a.K);
     // code = clamp(rne(x^ * scale), -128, 127) (Eq. 6: shifted by eta and clamped to [0, 127])
+    if (a.nonneg) {  // uniform
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            v[j].x = v[j].x - lo;
+            v[j].y = v[j].y - lo;
+            v[j].z = v[j].z - lo;
+            v[j].w = v[j].w - lo;
+        }
+    }
+    const float least = a.nonneg ? 0.f : -128.f;
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int idx = t + j * RT;
         const float4 x = v[j];
-        const uint32_t wd = a.nonneg ? code_word<0>((x.x - lo) * scale, (x.y - lo) * scale,
-                                                    (x.z - lo) * scale, (x.w - lo) * scale)
-                                     : code_word<-128>(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
+        const uint32_t wd = code_word(x.x * scale, x.y * scale, x.z * scale, x.w * scale, least);
         if (idx < K4) {
             rs = __builtin_amdgcn_sdot4((int)wd, 0x01010101, rs, false);  // sum of the four codes
-            if (live) c4[idx] = wd;
+            if (live) c4[(uint32_t)idx] = wd;
         }
     }
     if (a.rowsum) {
@@ -420,9 +440,9 @@ __global__ __launch_bounds__(512) void ln_quant_long(QuantArgs a) {
     for (int64_t idx = t; idx < K4; idx += T) {
         const float4 x = xhat_at(idx);
         if (d4) d4[idx] = x;
-        const uint32_t wd = a.nonneg ? code_word<0>((x.x - lo) * scale, (x.y - lo) * scale,
-                                                    (x.z - lo) * scale, (x.w - lo) * scale)
-                                     : code_word<-128>(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
+        const uint32_t wd = a.nonneg ? code_word((x.x - lo) * scale, (x.y - lo) * scale, (x.z - lo) * scale,
+                                                 (x.w - lo) * scale, 0.f)
+                                     : code_word(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
         rs = __builtin_amdgcn_sdot4((int)wd, 0x01010101, rs, false);
         c4[idx] = wd;
     }

@@ -194,18 +194,16 @@ __device__ inline RowNorm stats_finish(const PairStats& p, double c, double inv_
 }
 
 // ---- rounding to codes -------------------------------------------------------------------
-// clamp(rne(t), LO, 127) as the low byte of the result.  The bounds are integers, so clamping before
-// the rounding is the same thing; 1.5 * 2^23 has an ulp of one and is even, so adding it rounds half to
+// clamp(rne(t), least, 127) as the low byte of the result (least = -128, or 0 for Eq. 6).  The bounds are integers, so
+// clamping before the rounding is the same thing; 1.5 * 2^23 has an ulp of one and is even, so adding it rounds half to
 // even and leaves the integer, in two's complement, in the low bits of the mantissa.
-template <int LO>
-__device__ inline uint32_t code_bits(float t) {
-    return __float_as_uint(__builtin_amdgcn_fmed3f(t, (float)LO, 127.f) + 12582912.f);
+__device__ inline uint32_t code_bits(float t, float least) {
+    return __float_as_uint(__builtin_amdgcn_fmed3f(t, least, 127.f) + 12582912.f);
 }
 // four codes, the first in the low byte
-template <int LO>
-__device__ inline uint32_t code_word(float t0, float t1, float t2, float t3) {
-    const uint32_t lo = __builtin_amdgcn_perm(code_bits<LO>(t1), code_bits<LO>(t0), 0x0C0C0400u);
-    const uint32_t hi = __builtin_amdgcn_perm(code_bits<LO>(t3), code_bits<LO>(t2), 0x04000C0Cu);
+__device__ inline uint32_t code_word(float t0, float t1, float t2, float t3, float least = -128.f) {
+    const uint32_t lo = __builtin_amdgcn_perm(code_bits(t1, least), code_bits(t0, least), 0x0C0C0400u);
+    const uint32_t hi = __builtin_amdgcn_perm(code_bits(t3, least), code_bits(t2, least), 0x04000C0Cu);
     return lo | hi;
 }
 
