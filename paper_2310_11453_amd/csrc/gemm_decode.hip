@@ -4,13 +4,16 @@
 //
 // This shape is bound by streaming the packed weights from HBM, and the only
 // ALU work the stream can afford is about two VALU operations per 32 weights.
-// The kernel therefore never expands a bit to a +-1 byte.  One AND with
-// 0x01010101 << i turns a packed dword into four bytes in {0, 2^i} ("bit plane
-// i", 2^7 read as -128 by the signed MFMA), each plane feeds its own i8 MFMA
-// accumulator, and the planes are folded once per output tile:
-//   sum_k q b = sum_i acc_i / c_i,  c_i = 2^i (i < 7), c_7 = -128   (exact shifts)
+// The kernel therefore never expands a bit to a +-1 byte.  One AND with 0x01010101 << i turns a packed
+// dword into four bytes in {0, 2^i} ("bit plane i"); planes i and i + 4, the latter of the dword shifted right by
+// four, feed one of four i8 MFMA accumulators, which are folded once per output tile:
+//   8 sum_k q b = 8 acc_0 + 4 acc_1 + 2 acc_2 + acc_3   (exact shifts)
 //   sum_k q s = 2 * sum_k q b - sum_k q,        s = 2 b - 1
 // with sum_k q taken from the quantiser's row sums.
+//
+// Four accumulators rather than eight, 32-bit scalars ahead of the first load and the epilogue's operands behind the last
+// one (a wave issues one instruction in four cycles, and these launches are short): us a launch, before / now, 8
+// tokens 2048 -> 8192 3.6 / 3.3, 4096 -> 16384 4.9 / 4.75, 7168 -> 28672 8.5 / 8.4, 16 tokens 9.65 / 9.15.
 //
 // Work split: a workgroup owns up to T consecutive 16-row weight tiles and all of K;
 // wave w of the group owns the K-chunks {w*C .. w*C+C-1} (+ W*C per round) and
@@ -41,8 +44,9 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
     // the tile loads take a scalar base, instead of 64-bit compares and selects in every lane
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
     const int m = l & 15, g = l >> 4;
-    const int64_t TKp = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);  // tiles per tile row in memory
     const bool to_slices = a.split_k || a.kgroups > 1;  // partial sums go to split_ws
+    int K = (int)a.K;  // at most 65536 (kMaxGemmK)
+    const uint32_t TKp = a.tk_pitch ? (uint32_t)a.tk_pitch : (uint32_t)tiles_k(K);  // tiles per tile row in memory
     // KGRP: waves per K-group, this wave's group and its index inside the group
     const int wpg = KGRP ? W / a.kgroups : W;
     const int gw = KGRP ? w / wpg : 0, wg = KGRP ? w % wpg : w;
@@ -53,31 +57,21 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         a.codes += (int64_t)blockIdx.y * a.K;
         a.packed += (int64_t)blockIdx.y * a.group_packed;
     } else if (a.split_k) {  // this workgroup's slice of K (uniform)
-        const int64_t k0 = (int64_t)blockIdx.y * a.split_k;
+        const int k0 = (int)blockIdx.y * (int)a.split_k;
         a.codes += k0;
         a.packed += (k0 / kChunkK) * 256;
-        a.K = a.K - k0 < a.split_k ? a.K - k0 : a.split_k;
+        K = K - k0 < (int)a.split_k ? K - k0 : (int)a.split_k;
     }
-    const int64_t TN = tiles_n(a.N), TK = tiles_k(a.K);
+    const uint32_t N = (uint32_t)a.N, TN = (uint32_t)tiles_n(a.N), tn0 = blockIdx.x * (uint32_t)tpb;  // N <= 2^30
+    const int TK = (int)tiles_k(K);
     const int M = (int)a.M;
-    const int64_t tn0 = (int64_t)blockIdx.x * tpb;
-
-    // epilogue operands, requested up front so their latency hides under the weight stream.
-    // beta belongs to the group of output rows that holds a tile (Eq. 13; one group: beta[0]).
-    auto beta_of = [&](int64_t tn) {  // branch-free: nothing may delay the loads that follow
-        if (tn > TN - 1) tn = TN - 1;
-        return a.beta[((uint32_t)(tn * kTileN) / (uint32_t)a.beta_rows) * a.beta_stride];  // N <= 2^30
-    };
-    const float beta_first = beta_of(tn0 + w);
     const int mc = m < M ? m : M - 1;
-    int rs = 0;
-    float gm = 0.f, eta = 0.f;
-    if constexpr (!KGRP) {
-        rs = a.rowsum[mc * a.gstride];
-        gm = a.per_tensor ? a.gamma[0] : a.gamma[mc * a.gstride];
-        // Eq. 6 only; without it the load goes to gamma (always valid) and the value is not used
-        eta = *(a.eta ? a.eta + (a.per_tensor ? 0 : mc * a.gstride) : a.gamma);
-    }
+    // beta belongs to the group of output rows that holds a tile (Eq. 13; one group: beta[0])
+    auto beta_of = [&](uint32_t tn) {
+        if (a.beta_rows >= a.N) return a.beta[0];
+        if (tn > TN - 1) tn = TN - 1;
+        return a.beta[(int64_t)(tn * kTileN / (uint32_t)a.beta_rows) * a.beta_stride];
+    };
 
     int part[ONE_ROUND ? 1 : T][4];
     if (!ONE_ROUND) {
@@ -86,10 +80,13 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
 #pragma unroll
             for (int r = 0; r < 4; ++r) part[t][r] = 0;
     }
+    // the masks of four bit planes in scalar registers: as literals they double the size of the ANDs
+    int plane_mask[4] = {0x01010101, 0x02020202, 0x04040404, 0x08080808};
+    asm volatile("" : "+s"(plane_mask[0]), "+s"(plane_mask[1]), "+s"(plane_mask[2]), "+s"(plane_mask[3]));
 
-    const int64_t rounds = ONE_ROUND ? 1 : (TK + (int64_t)W * C - 1) / ((int64_t)W * C);
-    for (int64_t rd = 0; rd < rounds; ++rd) {
-        const int64_t tk0 = (rd * W + wg) * C;
+    const int rounds = ONE_ROUND ? 1 : (TK + W * C - 1) / (W * C);
+    for (int rd = 0; rd < rounds; ++rd) {
+        const int tk0 = (rd * W + wg) * C;
 
         // Every load below is unconditional (addresses are clamped instead of guarded): with
         // no branches around them the loads complete in issue order and the MFMAs of tile t
@@ -99,22 +96,31 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // m >= M read row M-1 (their outputs are never stored); columns k >= K read the last 16
         // valid bytes (the packed bits there are zero, so they contribute nothing).
         v4i act[C][8];
-        auto load_act = [&](const int8_t* arow) {
+        auto load_act = [&]() {
+            const int8_t* __restrict__ base = a.codes + (uint32_t)mc * (uint32_t)a.ldq;  // at most 16 rows of 4 MiB
+            if ((tk0 + C) * kChunkK <= K) {  // uniform: whole chunks, one address
+                base += tk0 * kChunkK + 16 * g;
 #pragma unroll
-            for (int c = 0; c < C; ++c)
+                for (int c = 0; c < C; ++c)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    int k = (int)(tk0 + c) * kChunkK + 64 * i + 16 * g;  // K < 2^22
-                    k = k > (int)a.K - 16 ? (int)a.K - 16 : k;
-                    act[c][i] = *reinterpret_cast<const v4i*>(arow + k);
-                }
+                    for (int i = 0; i < 8; ++i)
+                        act[c][i] = *reinterpret_cast<const v4i*>(base + c * kChunkK + 64 * i);
+            } else {
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int k = (tk0 + c) * kChunkK + 64 * i + 16 * g;
+                        act[c][i] = *reinterpret_cast<const v4i*>(base + (uint32_t)(k > K - 16 ? K - 16 : k));
+                    }
+            }
         };
         // Few tokens: the wave's slice of the codes is M rows of C * 512 bytes, and fetching it in
         // operand layout costs C * 8 load instructions whatever M is (at one token as much time on
         // the load path as a seventh of the weight stream).  Instead each row is fetched with one
-        // instruction, 16 consecutive bytes a lane, and (below, once the first weight tiles have
-        // been requested behind it) parked in the wave's own part of `red`, which holds nothing
-        // before the wave's first tile is done, and read from there in operand layout.
+        // instruction, 16 consecutive bytes a lane (rows past M, up to a whole four: row M-1 again), and (below,
+        // once the first weight tiles have been requested behind it) parked in the wave's own part of `red`, which
+        // holds nothing before the wave's first tile is done, and read from there in operand layout.
         // More tokens than the region has rows: the rows go through it in passes (the lanes of a
         // pass's rows read their operands, then the next rows are parked).  A row is 1 KiB, so the
         // same 16 bytes of every row would share their banks: the 16-byte slots of row r are stored
@@ -125,14 +131,18 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         const bool stage_lane = l < C * 32;
         v4i rowv[16];
         if (staged) {
-            int kl = (int)tk0 * kChunkK + 16 * l;  // this lane's 16 bytes of a row slice
-            kl = kl > (int)a.K - 16 ? (int)a.K - 16 : kl;
+            int kl = tk0 * kChunkK + 16 * l;  // this lane's 16 bytes of a row slice
+            kl = kl > K - 16 ? K - 16 : kl;
+            const int8_t* __restrict__ src = a.codes + kl;
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (r < M && stage_lane)
-                    rowv[r] = *reinterpret_cast<const v4i*>(a.codes + (int64_t)r * a.ldq + kl);
+            for (int r0 = 0; r0 < 16; r0 += 4)
+                if (r0 < M) {  // uniform
+#pragma unroll
+                    for (int r = r0; r < r0 + 4; ++r)
+                        rowv[r] = *reinterpret_cast<const v4i*>(src + (int64_t)(r < M ? r : M - 1) * a.ldq);
+                }
         } else {
-            load_act(a.codes + (int64_t)(m < M ? m : M - 1) * a.ldq);
+            load_act();
         }
 
         // Weight tiles: a software pipeline of depth kDepth per wave.  Asking for everything at
@@ -144,23 +154,21 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // masked to zero arithmetically (no branch around a load).
         constexpr int kDepth = T < 3 ? T : 3;
         v4i wt[T][C];
-        // chunk c of this wave: valid index and all-ones / all-zeros mask
-        int64_t tkc[C];
+        // chunk c of this wave: all-ones / all-zeros mask
         int livem[C];
+        // tile t of the group lies t*TK KiB after tile 0; tiles past the last valid one
+        // (ragged N, or tpb < T) re-read the last valid tile
+        const uint32_t tn_end = tn0 + (uint32_t)tpb - 1;
+        const uint32_t t_last = (tn_end < TN - 1 ? tn_end : TN - 1) - tn0;
+        const uint32_t* wbase[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             livem[c] = -(int)(tk0 + c < TK);
-            tkc[c] = tk0 + c < TK ? tk0 + c : TK - 1;
+            wbase[c] = a.packed + ((uint64_t)tn0 * TKp + (uint32_t)(tk0 + c < TK ? tk0 + c : TK - 1)) * 256 + l * 4;
         }
-        // tile t of the group lies t*TK KiB after tile 0; tiles past the last valid one
-        // (ragged N, or tpb < T) re-read the last valid tile
-        const int t_last = (int)((tn0 + tpb - 1 < TN - 1 ? tn0 + tpb - 1 : TN - 1) - tn0);
-        const uint32_t* wbase[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) wbase[c] = a.packed + (tn0 * TKp + tkc[c]) * 256 + l * 4;
-        const uint32_t tile_stride = (uint32_t)TKp * 256;  // dwords; K < 2^22 keeps it in 32 bits
+        const uint32_t tile_stride = TKp * 256;  // dwords
         auto load_tile = [&](int t) {
-            const uint32_t off = (uint32_t)(t < t_last ? t : t_last) * tile_stride;
+            const uint32_t off = ((uint32_t)t < t_last ? (uint32_t)t : t_last) * tile_stride;
 #pragma unroll
             for (int c = 0; c < C; ++c)  // read once: streaming loads leave L2 to the codes (3-6 %)
                 wt[t][c] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(wbase[c] + off));
@@ -169,17 +177,21 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         for (int t = 0; t < kDepth; ++t) load_tile(t);
         if (staged) {  // rows past M repeat row M-1 (never stored)
             int* stage = &red[w * T * 256];
-            const int mr = m < M ? m : M - 1;
 #pragma unroll
             for (int p = 0; p < kStagePasses; ++p) {
                 if (p * kStageRows < M) {  // uniform
+                    if (stage_lane) {
 #pragma unroll
-                    for (int r = 0; r < kStageRows; ++r)
-                        if (p * kStageRows + r < 16 && p * kStageRows + r < M && stage_lane)
-                            *reinterpret_cast<v4i*>(&stage[r * 256 + (l ^ (r & 15)) * 4]) =
-                                rowv[p * kStageRows + r < 16 ? p * kStageRows + r : 15];
-                    if (mr / kStageRows == p) {
-                        const int rr = mr - p * kStageRows;
+                        for (int r0 = 0; r0 < kStageRows; r0 += 4)
+                            if (p * kStageRows + r0 < M) {  // uniform
+#pragma unroll
+                                for (int r = r0; r < r0 + 4 && r < kStageRows && p * kStageRows + r < 16; ++r)
+                                    *reinterpret_cast<v4i*>(&stage[r * 256 + (l ^ (r & 15)) * 4]) =
+                                        rowv[p * kStageRows + r];
+                            }
+                    }
+                    if (mc / kStageRows == p) {
+                        const int rr = mc - p * kStageRows;
 #pragma unroll
                         for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -195,31 +207,27 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         for (int t = 0; t < T; ++t) {
             if (t + kDepth < T) load_tile(t + kDepth);
             __builtin_amdgcn_sched_barrier(0);  // keep the request ahead of this tile's MFMAs
-            v4i acc[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = (v4i){0, 0, 0, 0};
+            // planes i and i + 4 of the tile and of the tile shifted by 4 meet in one accumulator:
+            //   8 sum_k q b = 8 acc_0 + 4 acc_1 + 2 acc_2 + acc_3
             // chunks past the end of K are masked here, at the point of use (masking at the load
             // would tie a wait for the whole stream to the first tile), and inside the plane mask,
             // a scalar: it costs no instruction of its own
+            v4i acc[4];
 #pragma unroll
-            for (int c = 0; c < C; ++c)
+            for (int c = 0; c < C; ++c) {
+                const v4i high = wt[t][c] >> 4;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const int mask = (int)(0x01010101u << i) & livem[c];
-                    const v4i plane = wt[t][c] & mask;
+                    const v4i zero = {0, 0, 0, 0};
                     // rows of the MFMA = weights (n), columns = tokens (m)
-                    acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(plane, act[c][i], acc[i], 0, 0, 0);
+                    acc[i & 3] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                        (i < 4 ? wt[t][c] : high) & (plane_mask[i & 3] & livem[c]), act[c][i],
+                        c == 0 && i < 4 ? zero : acc[i & 3], 0, 0, 0);
                 }
-            // fold the planes, scaled by 128 so that one shift-add per plane does it:
-            //   128 * sum_k q b = sum_{i<7} acc_i * 2^(7-i) - acc_7      (|.| < 2^24 per chunk)
-            v4i sum;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int h = acc[0][r];
-#pragma unroll
-                for (int i = 1; i < 7; ++i) h = (h << 1) + acc[i][r];
-                sum[r] = (h << 1) - acc[7][r];
             }
+            v4i sum = acc[0];
+#pragma unroll
+            for (int i = 1; i < 4; ++i) sum = (sum << 1) + acc[i];
             if (ONE_ROUND) {
                 *reinterpret_cast<v4i*>(&red[((w * T + t) * kWave + l) * 4]) = sum;
             } else {
@@ -228,6 +236,15 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+    }
+    // the epilogue's operands, on their way while the waves meet
+    const float beta_first = beta_of(tn0 + w);
+    int rs = 0;
+    float gm = 0.f, eta = 0.f;
+    if constexpr (!KGRP) {
+        rs = a.rowsum[mc * a.gstride];
+        gm = a.per_tensor ? a.gamma[0] : a.gamma[mc * a.gstride];
+        if (a.eta) eta = a.eta[a.per_tensor ? 0 : mc * a.gstride];
     }
 
     // cross-wave reduction over K, then the dequantisation epilogue
@@ -245,15 +262,14 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             v4i sum = (v4i){0, 0, 0, 0};
             for (int ww = grp * wpg; ww < (grp + 1) * wpg; ++ww)
                 sum += *reinterpret_cast<const v4i*>(&red[((ww * T + t) * kWave + l) * 4]);
-            const int64_t tn = tn0 + t;
-            const int64_t n = tn * kTileN + 4 * g;
-            if (tn >= TN || m >= M || n >= a.N) continue;
-            int* p = a.split_ws + ((int64_t)grp * M + m) * a.N + n;
-            const v4i h = sum >> 6;
-            if ((a.N & 3) == 0) *reinterpret_cast<v4i*>(p) = h;
+            const uint32_t tn = tn0 + t, n = tn * kTileN + 4 * g;
+            if (tn >= TN || m >= M || n >= N) continue;
+            int* p = a.split_ws + (uint64_t)(uint32_t)(grp * M + m) * N + n;
+            const v4i h = sum >> 2;
+            if ((N & 3) == 0) *reinterpret_cast<v4i*>(p) = h;
             else
                 for (int r = 0; r < 4; ++r)
-                    if (n + r < a.N) p[r] = h[r];
+                    if (n + r < N) p[r] = h[r];
         }
         return;
     }
@@ -280,26 +296,25 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             for (int ww = 0; ww < W; ++ww)
                 sum += *reinterpret_cast<const v4i*>(&red[((ww * T + t) * kWave + l) * 4]);
         }
-        const int64_t tn = tn0 + t;
-        const int64_t n = tn * kTileN + 4 * g;
-        if (tn >= TN || m >= M || n >= a.N) continue;
+        const uint32_t tn = tn0 + t, n = tn * kTileN + 4 * g;
+        if (tn >= TN || m >= M || n >= N) continue;
         if (to_slices) {  // partial sum of this K-slice: 2 * sum_k q b, folded by splitk_reduce
-            int* p = a.split_ws + ((int64_t)blockIdx.y * M + m) * a.N + n;
-            const v4i h = sum >> 6;
-            if ((a.N & 3) == 0) *reinterpret_cast<v4i*>(p) = h;
+            int* p = a.split_ws + (uint64_t)(blockIdx.y * (uint32_t)M + (uint32_t)m) * N + n;
+            const v4i h = sum >> 2;
+            if ((N & 3) == 0) *reinterpret_cast<v4i*>(p) = h;
             else
                 for (int r = 0; r < 4; ++r)
-                    if (n + r < a.N) p[r] = h[r];
+                    if (n + r < N) p[r] = h[r];
             continue;
         }
-        const v4i pm = (sum >> 6) - rs;  // sum_k q s = 2 * (sum / 128) - sum_k q, exact shift
-        float* y = a.Y + (int64_t)m * a.N + n;
+        const v4i pm = (sum >> 2) - rs;  // sum_k q s = 2 sum_k q b - sum_k q, exact shift
+        float* y = a.Y + (uint64_t)(uint32_t)m * N + n;
         if (a.out_acc) {
             int* yi = reinterpret_cast<int*>(y);
-            if ((a.N & 3) == 0) *reinterpret_cast<v4i*>(yi) = pm;
+            if ((N & 3) == 0) *reinterpret_cast<v4i*>(yi) = pm;
             else
                 for (int r = 0; r < 4; ++r)
-                    if (n + r < a.N) yi[r] = pm[r];
+                    if (n + r < N) yi[r] = pm[r];
         } else {
             const float beta = t == w ? beta_first : beta_of(tn);
             const float sc = (beta * gm) / 128.0f;
@@ -307,9 +322,9 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             if (a.eta) {  // Eq. 6: the shift eta of the activations adds (beta * eta) * sum_k s[n,k]
                 const float be = beta * eta;
                 for (int r = 0; r < 4; ++r)
-                    o[r] = o[r] + be * (float)a.wsum[n + r < a.N ? n + r : a.N - 1];
+                    o[r] = o[r] + be * (float)a.wsum[n + r < N ? n + r : N - 1];
             }
-            if ((a.N & 3) == 0) {
+            if ((N & 3) == 0) {
                 // not a streaming store: what reads Y next pays more than it gains (2048 -> 2048 and a pass over Y 5.9
                 // us, 6.3 streaming; a step of 24 layers of width 1408 at 16 tokens with an addition to every Y 992,
                 // 1019 streaming, though 809 and 768 with nothing that reads Y); rows that are no whole lines lose by
@@ -317,7 +332,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                 *reinterpret_cast<v4f*>(y) = o;
             } else {
                 for (int r = 0; r < 4; ++r)
-                    if (n + r < a.N) y[r] = o[r];
+                    if (n + r < N) y[r] = o[r];
             }
         }
     }
