@@ -74,6 +74,33 @@ __device__ inline void lds_issue(v4i (&a)[2], uint32_t ad) {
 __device__ inline void lds_wait(v4i (&a)[2]) {
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]));
 }
+
+
+// What the kernel wants to know, in 32 bits and with what a division needs worked out by the host: ahead of a launch's
+// first request stood 330 instructions, 64-bit products and divisions most of them, and five waits for arguments.
+// us a launch, before / now: 64 x 2048 -> 2048 7.7 / 7.3, 64 x 4096 -> 16384 11.5 / 10.9, 64 x 7168 -> 7168 15.5 / 15.1,
+// 333 x 2048 -> 2048 8.1 / 7.6, 333 x 8192 -> 2048 16.0 / 15.4.
+struct Args {
+    const int8_t* codes;
+    const uint32_t* packed;
+    uint32_t M, N, ldq, last_row, TKp, K, split_k, gmode;  // last_row: of tiles
+    uint32_t items, grid_m, div_m, splits, grid_n, div_n, kgroups;
+    int64_t group_packed;
+    const float *gamma, *beta, *eta;
+    const int32_t *rowsum, *wsum;
+    uint32_t gstride, beta_rows;
+    int64_t beta_stride, ldy;
+    bool per_tensor, out_acc, to_slices;
+    float* Y;
+    int32_t* split_ws;
+};
+// n / d by a multiplication where the host found it exact (m = 2^32 / d, rounded up; n d < 2^32)
+__device__ inline uint32_t divided(uint32_t n, uint32_t d, uint32_t m) {
+    return d == 1 ? n : m ? __umulhi(n, m) : n / d;
+}
+static uint32_t divisor(int64_t d, int64_t n_max) {
+    return d > 1 && n_max * d < (int64_t)1 << 32 ? (uint32_t)(((int64_t)1 << 32) / d + 1) : 0;
+}
 }  // namespace mid
 
 // Tile BM x 128 (64 x 64 per wave): BM = 64 has four K-groups of two waves, BM = 128 two K-groups of
@@ -89,8 +116,7 @@ __device__ inline void lds_wait(v4i (&a)[2]) {
 // NS = stages in each group's ring.
 // ROWS = false: one row tile (M <= BM).  STREAM: streaming stores (streaming_stores below).
 template <int BM, int NS, bool ROWS, bool STREAM>
-__global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int grid_m, int grid_n,
-                                                                int splits, int gmode) {
+__global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(mid::Args a) {
     using namespace mid;
     constexpr int WM = BM / 64, GW = WM * WN;   // waves of a K-group
     constexpr int KG = THREADS / kWave / GW;    // K-groups
@@ -103,67 +129,56 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     __shared__ __attribute__((aligned(1024))) uint8_t smB[KG * (BN / 16) * 1024];
     static_assert(NS >= 4, "the wait bookkeeping below: a stage's codes are requested NS-1 >= 3 stages ahead");
 
+    // all of the arguments that the first requests need at once, not as the branches come to them
+    asm volatile(""
+                 : "+s"(a.codes), "+s"(a.packed), "+s"(a.M), "+s"(a.N), "+s"(a.ldq), "+s"(a.last_row), "+s"(a.TKp),
+                   "+s"(a.K), "+s"(a.split_k), "+s"(a.gmode));
+    if constexpr (ROWS)
+        asm volatile("" : "+s"(a.items), "+s"(a.grid_m), "+s"(a.div_m), "+s"(a.splits), "+s"(a.grid_n), "+s"(a.div_n));
     // wave-uniform values in scalar registers: the loop below branches on them
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
     const int kg = w / GW, wi = w % GW, wm = wi / WN, wn = wi % WN;
     const int tg = threadIdx.x % GT;  // thread inside the K-group
     const int j = l & 31, g2 = l >> 5;
-    const int64_t M = a.M, N = a.N;
-    const int64_t TN = tiles_n(N);
-    const int64_t TKp = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
+    const int M = (int)a.M, N = (int)a.N;  // at most 2^30
     int tm = 0, tcol = (int)blockIdx.x, sp = (int)blockIdx.y;
     if constexpr (ROWS) {  // the host rounds the grid up to a multiple of 8
         const uint32_t item = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-        if (item >= (uint32_t)(grid_m * grid_n * splits)) return;  // uniform for the workgroup
-        const uint32_t rest = item / (uint32_t)grid_m;
-        tm = (int)(item - rest * grid_m);
-        sp = splits > 1 ? (int)(rest / (uint32_t)grid_n) : 0;
-        tcol = (int)rest - sp * grid_n;
+        if (item >= a.items) return;  // uniform for the workgroup
+        const uint32_t rest = divided(item, a.grid_m, a.div_m);
+        tm = (int)(item - rest * a.grid_m);
+        sp = a.splits > 1 ? (int)divided(rest, a.grid_n, a.div_n) : 0;
+        tcol = (int)(rest - (uint32_t)sp * a.grid_n);
     }
-    const int64_t m0 = ROWS ? (int64_t)tm * BM : 0;
-    const int64_t n0 = (int64_t)tcol * BN;
+    const int m0 = ROWS ? tm * BM : 0;
+    const int n0 = tcol * BN;
 
     // ---- this item's slice of K, then this group's chunks of it ----------------------------
-    int64_t ki0 = 0, Ki = a.K;
-    const bool to_slices = a.split_k || a.kgroups > 1;  // partial sums go to split_ws
+    int ki0 = 0, Ki = (int)a.K;
+    const bool to_slices = a.to_slices;  // partial sums go to split_ws
+    const int gmode = (int)a.gmode;
     const int lgrp = gmode == 2 ? sp * KG + kg : sp;  // gmode 1, 2: the layer's K-group walked here
     if (gmode) {  // a K-group of a grouped layer: its own codes columns and blob
-        const int gi = lgrp < a.kgroups ? lgrp : a.kgroups - 1;
+        const int gi = lgrp < (int)a.kgroups ? lgrp : (int)a.kgroups - 1;
         a.codes += (int64_t)gi * a.K;
         a.packed += (int64_t)gi * a.group_packed;
     } else if (a.split_k) {
-        ki0 = (int64_t)sp * a.split_k;
-        Ki = a.K - ki0 < a.split_k ? a.K - ki0 : a.split_k;
+        ki0 = sp * (int)a.split_k;
+        Ki = Ki - ki0 < (int)a.split_k ? Ki - ki0 : (int)a.split_k;
     }
-    const int TKi = (int)tiles_k(Ki);  // K < 2^22
+    const int TKi = (int)((uint32_t)(Ki + kChunkK - 1) / kChunkK);  // K < 2^22
     // gmode 2: the whole group (nothing for a group past the layer's last)
     const int c0 = gmode == 2 ? 0 : TKi * kg / KG;
-    const int c1 = gmode == 2 ? (lgrp < a.kgroups ? TKi : 0) : TKi * (kg + 1) / KG;
+    const int c1 = gmode == 2 ? (lgrp < (int)a.kgroups ? TKi : 0) : TKi * (kg + 1) / KG;
     const int TK = c1 - c0;
-    const int64_t k0 = ki0 + (int64_t)c0 * kChunkK;
-    int K = (int)Ki - c0 * kChunkK;  // this group's K
+    const int k0 = ki0 + c0 * kChunkK;
+    int K = Ki - c0 * kChunkK;  // this group's K
     if (K > TK * kChunkK) K = TK * kChunkK;
     // Every group walks the same number of stages, whole chunks of the longest group; what lies
     // past a group's own K meets zero bits (padding of its last chunk, or a zero mask past its
     // last chunk), so it adds nothing.
     const int TKmax = gmode == 2 ? TKi : (TKi + KG - 1) / KG;
     const int nrun = TKmax * SPC;
-
-    // ---- epilogue operands, requested now: thread -> one row, or one column, of the tile ------
-    // (waves 0 .. BM/64 - 1 the rows, waves 4 and 5 the columns; nothing for sums that go to slices)
-    int e0 = 0, e1 = 0, e2 = 0;
-    if (!to_slices) {
-        if (w < BM / kWave) {
-            const int64_t r = m0 + (int)threadIdx.x, m = r < M ? r : M - 1, mg = a.per_tensor ? 0 : m * a.gstride;
-            e0 = __float_as_int(a.gamma[mg]);
-            e1 = a.rowsum[m * a.gstride];
-            if (a.eta) e2 = __float_as_int(a.eta[mg]);
-        } else if (w == 4 || w == 5) {
-            const int64_t c = n0 + (int)threadIdx.x - 4 * kWave, n = c < N ? c : N - 1;
-            e0 = __float_as_int(a.beta[a.beta_rows >= N ? 0 : (uint32_t)n / (uint32_t)a.beta_rows * a.beta_stride]);
-            if (a.eta) e1 = a.wsum[n];
-        }
-    }
 
     // ---- DMA of this group.  A stage is BM rows of 128 bytes; thread -> four 16-byte pieces of
     // it, piece = (row, physical segment).  The eight lanes of a row sit in one instruction, so
@@ -172,29 +187,30 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     uint8_t* const ringA = smA + kg * (NS * STAGE_BYTES);
     uint8_t* const ringB = smB + kg * ((BN / 16) * 1024);
     // (row offsets fit 32 bits: at most 128 rows of less than 2^22 bytes)
-    const int8_t* const gbase = a.codes + m0 * a.ldq + k0;
-    uint32_t grow[P], gseg[P];
+    const int8_t* const gbase = a.codes + ((uint64_t)(uint32_t)m0 * a.ldq + (uint32_t)k0);
+    static_assert((GT / 8) % 16 == 0, "the pieces of a thread lie in the same segment of their rows");
+    const uint32_t gseg = (uint32_t)(((tg & 7) ^ ((tg >> 4) & 7)) * 16);
+    uint32_t grow[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-        const int slot = q * GT + tg;
-        int row = slot >> 3;
-        gseg[q] = (uint32_t)(((slot & 7) ^ ((row >> 1) & 7)) * 16);
-        if (m0 + row > M - 1) row = (int)(M - 1 - m0);
-        grow[q] = (uint32_t)row * (uint32_t)a.ldq;
+        const int row = q * (GT / 8) + (tg >> 3);
+        grow[q] = __umul24((uint32_t)(row < M - 1 - m0 ? row : M - 1 - m0), a.ldq);
     }
     const uint32_t klast = K >= 16 ? (uint32_t)K - 16 : 0;
-    const uint32_t* bsrc[NBW];
+    // uniform base, 32-bit offsets: eight rows of tiles of at most 128 KiB
+    const uint32_t* const bbase =
+        a.packed + ((uint64_t)(uint32_t)(n0 >> 4) * a.TKp + (uint32_t)k0 / kChunkK) * 256;
+    uint32_t brow[NBW];
 #pragma unroll
     for (int q = 0; q < NBW; ++q) {
-        int64_t tn = (n0 >> 4) + wi + q * GW;
-        if (tn > TN - 1) tn = TN - 1;
-        bsrc[q] = a.packed + tile_dword_offset(tn, k0 / kChunkK, TKp) + l * 4;
+        const uint32_t row = (uint32_t)(wi + q * GW), last = a.last_row - (uint32_t)(n0 >> 4);
+        brow[q] = (row < last ? row : last) * a.TKp * 256;
     }
     const uint32_t lds_wave = (uint32_t)(wi * kWave * 16);
     // Past the group's K the last 16 valid bytes of the row are read again (the packed bits there are
     // zero, or masked); a min per piece instead of a branch.
     auto issue_piece = [&](int st, int q) {
-        const uint32_t k = (uint32_t)(st * STAGE_K) + gseg[q];
+        const uint32_t k = (uint32_t)(st * STAGE_K) + gseg;
         __builtin_amdgcn_global_load_lds(
             (const void*)(gbase + (grow[q] + (k < klast ? k : klast))),
             (__attribute__((address_space(3))) void*)(ringA + (st % NS) * STAGE_BYTES + q * GT * 16 +
@@ -209,9 +225,35 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
 #pragma unroll
         for (int q = 0; q < NBW; ++q)
             __builtin_amdgcn_global_load_lds(
-                (const void*)(bsrc[q] + (int64_t)tk * 256),
+                (const void*)(bbase + (brow[q] + (uint32_t)tk * 256 + (uint32_t)l * 4)),
                 (__attribute__((address_space(3))) void*)(ringB + (wi + q * GW) * 1024), 16, 0, 0);
     };
+    const bool has_k = TK > 0;  // a group without chunks requests nothing and multiplies by zero
+    if (has_k) {
+        issue_bits(0);
+#pragma unroll
+        for (int s = 0; s < NS - 1; ++s) issue(s);
+    }
+
+    // ---- epilogue operands, behind the first stages' requests (the waits below count those and may so wait for
+    // these as well): thread -> one row, or one column, of the tile (waves 0 .. BM/64 - 1 the rows, waves 4 and
+    // 5 the columns; nothing for sums that go to slices)
+    int e0 = 0, e1 = 0, e2 = 0;
+    if (!to_slices) {
+        if (w < BM / kWave) {
+            const int r = m0 + (int)threadIdx.x;
+            const int64_t m = (int64_t)(r < M ? r : M - 1) * a.gstride, mg = a.per_tensor ? 0 : m;
+            e0 = __float_as_int(a.gamma[mg]);
+            e1 = a.rowsum[m];
+            if (a.eta) e2 = __float_as_int(a.eta[mg]);
+        } else if (w == 4 || w == 5) {
+            const int c = n0 + (int)threadIdx.x - 4 * kWave, n = c < N ? c : N - 1;
+            int64_t at = 0;
+            if ((int)a.beta_rows < N) at = (int64_t)((uint32_t)n / a.beta_rows) * a.beta_stride;
+            e0 = __float_as_int(a.beta[at]);
+            if (a.eta) e1 = a.wsum[n];
+        }
+    }
 
     const uint32_t b_lane = (uint32_t)(uintptr_t)ringB + ((wn * 64 + j) >> 4) * 1024 +
                             (g2 * 16 + (j & 15)) * 16;
@@ -235,12 +277,6 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
     // multiplies A[u % 2] by B[u % 4], starts the LDS reads of A[(u + 1) % 2] and builds B[(u + 2) % 4].
     v4i bw[2][2], bwn[2][2];
     v4i A[2][2], B[4][2];
-    const bool has_k = TK > 0;  // a group without chunks requests nothing and multiplies by zero
-    if (has_k) {
-        issue_bits(0);
-#pragma unroll
-        for (int s = 0; s < NS - 1; ++s) issue(s);
-    }
     wait_vmcnt<(NS - 2) * P>();  // younger than stage 0: stages 1 .. NS-2
     block_barrier();
     read_bits(bw, b_lane);
@@ -392,15 +428,15 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
         else *at = v;
     };
     auto store_sums = [&](const v4i& p, int q, int64_t grp) {
-        const int64_t m = m0 + prow + 32 * (q >> 3) + 8 * (q & 3), n = n0 + pcol + 32 * ((q >> 2) & 1);
+        const int m = m0 + prow + 32 * (q >> 3) + 8 * (q & 3), n = n0 + pcol + 32 * ((q >> 2) & 1);
         int32_t* o = a.split_ws + (grp * M + m) * N + n;
-        const int rows = n < N ? (int)(M - m < 4 ? M - m : 4) : 0;
+        const int rows = n < N ? (M - m < 4 ? M - m : 4) : 0;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr, o += N)
             if (inside || rr < rows) put(2 * p[rr], o);
     };
     if (!add_groups) {  // each group's sums to its layer group's slice
-        if (lgrp < a.kgroups)
+        if (lgrp < (int)a.kgroups)
             static_for<0, 16>([&](auto qc) {
                 store_sums(piece(decltype(qc)::value), decltype(qc)::value, lgrp);
             });
@@ -425,9 +461,9 @@ __global__ __launch_bounds__(mid::THREADS) void gemm_mid_kernel(GemmArgs a, int 
             if constexpr (ETA) eta = *reinterpret_cast<const v4f*>(scales + 2 * BM + row);
             const float beta = __int_as_float(scales[3 * BM + col]);
             const float ws = ETA ? (float)scales[3 * BM + BN + col] : 0.f;
-            float* o = a.Y + (m0 + row) * a.ldy + n0 + col;
-            const int64_t left = M - m0 - row;
-            const int rows = n0 + col < N ? (int)(left < 4 ? left : 4) : 0;
+            float* o = a.Y + (int64_t)(m0 + row) * a.ldy + (n0 + col);
+            const int left = M - m0 - row;
+            const int rows = n0 + col < N ? (left < 4 ? left : 4) : 0;
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr, o += a.ldy) {
                 const int pm = 2 * own[i][rr] - rs[rr];
@@ -513,6 +549,44 @@ static bool streaming_stores(const GemmArgs& a, int splits, bool grouped) {
     return splits > 1 || a.M * a.ldy >= (int64_t)1 << 20;
 }
 
+static mid::Args mid_args(const GemmArgs& a, int grid_m, int grid_n, int splits, int gmode) {
+    const int64_t items = (int64_t)grid_m * grid_n * splits;
+    mid::Args m{};
+    m.codes = a.codes;
+    m.packed = a.packed;
+    m.M = (uint32_t)a.M;
+    m.N = (uint32_t)a.N;
+    m.ldq = (uint32_t)a.ldq;
+    m.last_row = (uint32_t)tiles_n(a.N) - 1;
+    m.TKp = (uint32_t)(a.tk_pitch ? a.tk_pitch : tiles_k(a.K));
+    m.K = (uint32_t)a.K;
+    m.split_k = (uint32_t)a.split_k;
+    m.grid_m = (uint32_t)grid_m;
+    m.grid_n = (uint32_t)grid_n;
+    m.splits = (uint32_t)splits;
+    m.items = (uint32_t)items;
+    m.div_m = mid::divisor(grid_m, items);
+    m.div_n = mid::divisor(grid_n, (int64_t)grid_n * splits);
+    m.gmode = (uint32_t)gmode;
+    m.kgroups = (uint32_t)a.kgroups;
+    m.group_packed = a.group_packed;
+    m.gamma = a.gamma;
+    m.beta = a.beta;
+    m.eta = a.eta;
+    m.rowsum = a.rowsum;
+    m.wsum = a.wsum;
+    m.gstride = (uint32_t)a.gstride;
+    m.beta_rows = (uint32_t)a.beta_rows;
+    m.beta_stride = a.beta_stride;
+    m.ldy = a.ldy;
+    m.per_tensor = a.per_tensor;
+    m.out_acc = a.out_acc;
+    m.to_slices = a.split_k || a.kgroups > 1;
+    m.Y = a.Y;
+    m.split_ws = a.split_ws;
+    return m;
+}
+
 // 16 < M <= 64.  K is also split over workgroups (second kernel: splitk_reduce) when N gives
 // few tiles and the caller brought the workspace for it, as mid_slice_tiles decides.
 hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
@@ -539,10 +613,9 @@ hipError_t launch_gemm_mid(const GemmArgs& a_in, hipStream_t s) {
         a.split_k = per * kChunkK;
     }
     const dim3 grid((unsigned)grid_n, (unsigned)splits);
-    if (streaming_stores(a, splits, gmode != 0))
-        gemm_mid_kernel<64, 4, false, true><<<grid, mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
-    else
-        gemm_mid_kernel<64, 4, false, false><<<grid, mid::THREADS, 0, s>>>(a, 1, grid_n, splits, gmode);
+    const mid::Args args = mid_args(a, 1, grid_n, splits, gmode);
+    if (streaming_stores(a, splits, gmode != 0)) gemm_mid_kernel<64, 4, false, true><<<grid, mid::THREADS, 0, s>>>(args);
+    else gemm_mid_kernel<64, 4, false, false><<<grid, mid::THREADS, 0, s>>>(args);
     if (splits > 1 || gmode) launch_splitk_reduce(a, gmode ? a.kgroups : splits, s);
     return hipGetLastError();
 }
@@ -565,7 +638,7 @@ hipError_t launch_gemm_mid_tiles(const GemmArgs& a_in, int bm, int64_t per, hipS
     if (items > ((int64_t)1 << 30)) return hipErrorInvalidValue;
     items = (items + 7) / 8 * 8;
     auto launch = [&](auto kernel) {
-        kernel<<<(unsigned)items, mid::THREADS, 0, s>>>(a, grid_m, grid_n, splits, grouped);
+        kernel<<<(unsigned)items, mid::THREADS, 0, s>>>(mid_args(a, grid_m, grid_n, splits, grouped));
     };
     const bool streaming = streaming_stores(a, splits, grouped);
     if (bm == 64) launch(streaming ? gemm_mid_kernel<64, 4, true, true> : gemm_mid_kernel<64, 4, true, false>);
