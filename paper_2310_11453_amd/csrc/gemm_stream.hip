@@ -35,9 +35,29 @@ constexpr int kStageRow = 528; // bytes per token in a wave's staging area: 512 
 constexpr int kStageBytes = kTokens * kStageRow;
 }  // namespace stream
 
+// What the kernel wants to know, in 32 bits (M <= 32, N <= 2^30): 150 instructions stood ahead of a wave's first
+// request, most of them 64-bit arithmetic and the scales' addresses, and four waits for arguments.  us a launch,
+// before / now, 24 tokens: 2048 -> 8192 4.4 / 4.05, 4096 -> 12288 7.2 / 6.45, 16384 -> 4096 10.6 / 10.15, 7168 -> 28672
+// 15.2 / 14.8.
+namespace stream {
+struct Args {
+    const int8_t* codes;
+    const uint32_t* packed;
+    uint32_t M, N, ldq, TKp, K, split_k, pairs_wg, extra;  // pairs of tile rows: pairs_wg a workgroup, one more in the
+                                                           // first `extra`
+    uint32_t gstride, beta_rows;
+    const float *gamma, *beta, *eta;
+    const int32_t *rowsum, *wsum;
+    int64_t beta_stride;
+    bool per_tensor, out_acc;
+    float* Y;
+    int32_t* split_ws;
+};
+}  // namespace stream
+
 // grid.x workgroups share the pairs of tile rows, grid.y = K-slices (a.split_k elements each,
 // 0 = one slice).  M <= 32.
-__global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(GemmArgs a) {
+__global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(stream::Args a) {
     using namespace stream;
     __shared__ int red[kMaxPairs * 32 * kPitch];
     // per wave: one chunk of the codes of 32 tokens on its way from row-major memory (read as
@@ -46,43 +66,42 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     __shared__ int tok_sum[kWave];
     __shared__ float tok_gamma[kWave], tok_eta[kWave];
 
+    // all of the arguments that the first requests need at once, not as the branches come to them
+    asm volatile(""
+                 : "+s"(a.M), "+s"(a.N), "+s"(a.ldq), "+s"(a.TKp), "+s"(a.K),
+                   "+s"(a.split_k), "+s"(a.pairs_wg), "+s"(a.extra));
     const int W = (int)blockDim.x / kWave;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
     const int tok = l & 31, half = l >> 5;
-    const int M = (int)a.M;
-    const int64_t N = a.N;
-    const int64_t TN = tiles_n(N);
-    const int64_t TKp = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
+    const int M = (int)a.M, N = (int)a.N;
     const int sp = (int)blockIdx.y;
-    int64_t k0 = 0, K = a.K;  // K, ldq < 2^22, M <= 32: offsets into the codes fit 32 bits
+    int k0 = 0, K = (int)a.K;  // ldq < 2^22, M <= 32: offsets into the codes fit 32 bits
     if (a.split_k) {
-        k0 = (int64_t)sp * a.split_k;
-        K = a.K - k0 < a.split_k ? a.K - k0 : a.split_k;
+        k0 = sp * (int)a.split_k;
+        K = K - k0 < (int)a.split_k ? K - k0 : (int)a.split_k;
     }
-    const int TK = (int)tiles_k(K);
+    const int TK = (int)((uint32_t)(K + kChunkK - 1) / kChunkK);
 
     // this workgroup's pairs of tile rows
-    const uint32_t TP = (uint32_t)(TN + 1) / 2;  // <= kMaxPairs workgroups' worth
-    const int p0 = (int)(TP * blockIdx.x / gridDim.x), p1 = (int)(TP * (blockIdx.x + 1) / gridDim.x);
-    const int np = p1 - p0;  // <= kMaxPairs (the launcher sees to it)
+    const uint32_t wg = blockIdx.x;
+    const int p0 = (int)(wg * a.pairs_wg + (wg < a.extra ? wg : a.extra));
+    const int np = (int)(a.pairs_wg + (wg < a.extra ? 1 : 0));  // 1 .. kMaxPairs (the launcher sees to it)
 
-    // Factors of the epilogue, requested now and straight into LDS, so that nothing waits on a load of theirs:
-    // a token's by wave 0, beta as a scalar while the matrix has one.  Neither they nor the clearing of the
-    // sums stand ahead of the first chunk's requests, and the indices of those are 32 bits: 64-bit divisions,
-    // products and a barrier behind the factors' loads were 1.5 us of a launch.
-    if (w == 0 && !a.split_k) {
-        const int64_t m = l < M ? l : M - 1, mg = a.per_tensor ? 0 : m * a.gstride;
-        auto to_lds = [](const void* src, void* dst) {
-            __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
-        };
-        to_lds(a.rowsum + m * a.gstride, tok_sum);
-        to_lds(a.gamma + mg, tok_gamma);
-        if (a.eta) to_lds(a.eta + mg, tok_eta);
-    }
-    const bool one_beta = a.beta_rows >= N;
-    const float beta0 = a.beta[0];
+    const bool one_beta = a.beta_rows >= a.N;
     auto clear_sums = [&]() {  // every thread, once: it synchronises
         for (int i = threadIdx.x; i < np * 32 * kPitch; i += blockDim.x) red[i] = 0;
+        // Factors of the epilogue, straight into LDS, so that nothing waits on a load of theirs: a token's by wave 0.
+        // Neither they nor the clearing of the sums stand ahead of the first chunk's requests: 64-bit divisions,
+        // products and a barrier behind the factors' loads were 1.5 us of a launch.
+        if (w == 0 && !a.split_k) {
+            const uint32_t m = (uint32_t)(l < M ? l : M - 1) * a.gstride, mg = a.per_tensor ? 0 : m;
+            auto to_lds = [](const void* src, void* dst) {
+                __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+            };
+            to_lds(a.rowsum + m, tok_sum);
+            to_lds(a.gamma + mg, tok_gamma);
+            if (a.eta) to_lds(a.eta + mg, tok_eta);
+        }
         // a bare barrier behind the LDS writes: a fence would also wait for the chunk's loads
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         block_barrier();
@@ -93,18 +112,17 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     const int wrow = tok;
     const uint32_t slot_dw = (uint32_t)((half * 16 + (wrow & 15)) * 4);  // + 128 dwords for mf = 1
     // uniform bases, 32-bit offsets (a tile row is at most 128 KiB here, a row of codes less than 4 MiB)
-    const uint32_t* const wbase = a.packed + tile_dword_offset((int64_t)p0 * 2, k0 / kChunkK, TKp);
-    const int8_t* const cbase = a.codes + k0;
-    const int last_row = (int)(TN - 1) - 2 * p0;  // rows behind it are never stored
+    const uint32_t* const wbase = a.packed + ((uint64_t)(uint32_t)(2 * p0) * a.TKp + (uint32_t)k0 / kChunkK) * 256;
+    const int8_t* const cbase = a.codes + (uint32_t)k0;
+    const int last_row = (int)((a.N + kTileN - 1) / kTileN - 1) - 2 * p0;  // rows behind it are never stored
     auto pair_off = [&](int p) {
         const int row = 2 * p + (wrow >> 4);
-        return __umul24((uint32_t)(row < last_row ? row : last_row), (uint32_t)TKp * 256) + slot_dw;
+        return __umul24((uint32_t)(row < last_row ? row : last_row), a.TKp * 256) + slot_dw;
     };
 
     // NP = pairs of this workgroup, a compile-time count so that the tiles sit in registers
     auto wave_chunks = [&](auto np_c) {
         constexpr int NP = decltype(np_c)::value;
-        const int steps = (TK - w + W - 1) / W;  // chunks w, w + W, ...
         uint8_t* const mine = stage + w * kStageBytes;
         v4i q[NP][2], qn[NP][2], raw[16];
         auto load_q = [&](v4i (&dst)[NP][2], int c) {
@@ -120,23 +138,27 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
         auto load_raw = [&](int c) {
             uint32_t k = (uint32_t)c * kChunkK + 16 * tok;
             if (k > (uint32_t)K - 16) k = (uint32_t)K - 16;  // the packed bits there are zero
+            // tokens 0 .. 15 exist; a token's offset adds up from the one before, the last token's is the largest
+            const uint32_t last = __umul24((uint32_t)M - 1, a.ldq) + k;
+            uint32_t at = __umul24((uint32_t)half, a.ldq) + k;
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj) {
-                const int t = 2 * jj + half;
-                raw[jj] = *reinterpret_cast<const v4i*>(
-                    cbase + (__umul24((uint32_t)(t < M ? t : M - 1), (uint32_t)a.ldq) + k));
+                raw[jj] = *reinterpret_cast<const v4i*>(cbase + (jj < 8 || at < last ? at : last));
+                at += 2 * a.ldq;
             }
         };
         load_q(q, w);
         load_raw(w);
         __builtin_amdgcn_sched_barrier(0);
+        int ones = 0x01010101;  // in a scalar register: as a literal it doubles the size of the ANDs
+        asm volatile("" : "+s"(ones));
         clear_sums();
         // the first tiles are waited for here, once: inside the loop a wait for them would have to
         // count the conditional fetches behind them as absent, and so wait for those as well
 #pragma unroll
         for (int p = 0; p < NP; ++p) asm volatile("" : "+v"(q[p][0]), "+v"(q[p][1]));
 #pragma unroll 1
-        for (int st = 0; st < steps; ++st) {
+        for (int chunk = w; chunk < TK; chunk += W) {
             // ---- the fetched codes become the B operands of plane i, k-half mf -------------------
             v4i act[8][2];
 #pragma unroll
@@ -152,10 +174,10 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_sched_barrier(0);
             // ---- the next chunk's fetches (wave-uniform branch) ------------------------------------
-            const bool more = st + 1 < steps;
+            const bool more = chunk + W < TK;
             if (more) {
-                load_raw((st + 1) * W + w);
-                load_q(qn, (st + 1) * W + w);
+                load_raw(chunk + W);
+                load_q(qn, chunk + W);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -170,7 +192,7 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
                         const v4i wv = q[p][mf];
                         v4i b;
 #pragma unroll
-                        for (int d = 0; d < 4; ++d) b[d] = (int)(((uint32_t)wv[d] >> i) & 0x01010101u);
+                        for (int d = 0; d < 4; ++d) b[d] = (int)(((uint32_t)wv[d] >> i) & (uint32_t)ones);
                         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(b, act[i][mf], acc, 0, 0, 0);
                     }
                 // lane (tok, half) holds token tok, weight rows 8 (r/4) + 4 half + r%4
@@ -204,6 +226,7 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     }
     wait_vmcnt<0>();  // the tokens' factors
     __syncthreads();
+    const float beta0 = a.beta[0];
 
     // ---- epilogue (Eq. 11): sum_k q s = 2 sum_k q b - sum_k q ; y = that * (beta gamma / 128) ----
     // item -> four consecutive weight rows of a pair and a token, eight items to a line of the output.
@@ -216,11 +239,11 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     auto finish = [&](auto kind) {
         constexpr int KIND = decltype(kind)::value;
         uint32_t* const out = KIND == 1 && a.split_k
-                                  ? reinterpret_cast<uint32_t*>(a.split_ws) + (int64_t)sp * M * N
+                                  ? reinterpret_cast<uint32_t*>(a.split_ws) + (int64_t)(sp * M) * N
                                   : reinterpret_cast<uint32_t*>(a.Y);
         for (int i = threadIdx.x; i < np * 8 * kTokens; i += blockDim.x) {
             const int nl = (i >> 8) * 32 + (i & 7) * 4, m = (i >> 3) & (kTokens - 1);
-            const int64_t n = (int64_t)p0 * 32 + nl;
+            const int n = p0 * 32 + nl;
             if (m >= M || n >= N) continue;
             int sum[4];
 #pragma unroll
@@ -235,9 +258,9 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
                 const float sc = tok_gamma[m] * 0.0078125f;  // gamma / 128, exact
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int64_t nj = n + j < N ? n + j : N - 1;
+                    const int nj = n + j < N ? n + j : N - 1;
                     const float beta =
-                        KIND != 2 || one_beta ? beta0 : a.beta[((uint32_t)nj / (uint32_t)a.beta_rows) * a.beta_stride];
+                        KIND != 2 || one_beta ? beta0 : a.beta[(int64_t)((uint32_t)nj / a.beta_rows) * a.beta_stride];
                     // beta * (gamma / 128) has the bits of (beta * gamma) / 128
                     float y = (float)(sum[j] - tok_sum[m]) * (beta * sc);
                     if (KIND == 2 && a.eta) y = y + (beta * tok_eta[m]) * (float)a.wsum[nj];       // Eq. 6
@@ -258,7 +281,7 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(G
     };
     if (a.split_k || a.out_acc) finish(std::integral_constant<int, 1>{});
     else if (!one_beta || a.eta) finish(std::integral_constant<int, 2>{});
-    else if (M * N >= (int64_t)3 << 16 && (N & 31) == 0) finish(std::integral_constant<int, 3>{});
+    else if ((int64_t)M * N >= (int64_t)3 << 16 && (N & 31) == 0) finish(std::integral_constant<int, 3>{});
     else finish(std::integral_constant<int, 0>{});
 }
 
@@ -313,7 +336,30 @@ bool launch_gemm_stream(const GemmArgs& a_in, hipStream_t s) {
     const int64_t rounds = (TKs + kMaxWaves - 1) / kMaxWaves;
     const int W = (int)((TKs + rounds - 1) / rounds);
     const dim3 g((unsigned)grid, (unsigned)splits);
-    gemm_stream_kernel<<<g, W * kWave, 0, s>>>(a);
+    Args t{};
+    t.codes = a.codes;
+    t.packed = a.packed;
+    t.M = (uint32_t)a.M;
+    t.N = (uint32_t)a.N;
+    t.ldq = (uint32_t)a.ldq;
+    t.TKp = (uint32_t)(a.tk_pitch ? a.tk_pitch : tiles_k(a.K));
+    t.K = (uint32_t)a.K;
+    t.split_k = (uint32_t)a.split_k;
+    t.pairs_wg = (uint32_t)(TP / grid);
+    t.extra = (uint32_t)(TP % grid);
+    t.gstride = (uint32_t)a.gstride;
+    t.beta_rows = (uint32_t)a.beta_rows;
+    t.gamma = a.gamma;
+    t.beta = a.beta;
+    t.eta = a.eta;
+    t.rowsum = a.rowsum;
+    t.wsum = a.wsum;
+    t.beta_stride = a.beta_stride;
+    t.per_tensor = a.per_tensor;
+    t.out_acc = a.out_acc;
+    t.Y = a.Y;
+    t.split_ws = a.split_ws;
+    gemm_stream_kernel<<<g, W * kWave, 0, s>>>(t);
     if (splits > 1) launch_splitk_reduce(a, splits, s);
     return true;
 }
