@@ -340,48 +340,73 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
 
 // Second step of a K split: Y[m,n] = epilogue(sum_s partial[s][m][n] - rowsum[m]).  V consecutive columns a
 // thread (V = 4: N % 4 == 0, split_ws and Y 16-byte aligned), rows m = blockIdx.y, + gridDim.y, ...
-// With the slices of a small batch this launch is latency: four slices are read at a time, and nothing
-// that can be a scalar (the row, and beta while the matrix has one) costs a vector instruction; read one
+// With the slices of a small batch this launch is latency: four slices and the row's scales are requested at once, and
+// nothing that can be a scalar (the row, and beta while the matrix has one) costs a vector instruction; read one
 // after another behind a 64-bit division the launch took 4.0 us at 8 x 7168 and 4.8 at 333 x 2048.
+struct FoldArgs {
+    const int32_t* sums;
+    uint32_t M, N, splits, gstride;
+    const int32_t* rowsum;
+    const float *gamma, *beta, *eta;
+    const int32_t* wsum;
+    float* Y;
+    int64_t ldy, beta_stride;
+    uint32_t beta_rows;
+    bool per_tensor, out_acc;
+};
 template <int V>
-__global__ __launch_bounds__(256) void splitk_reduce(GemmArgs a, int splits) {
+__global__ __launch_bounds__(256) void splitk_reduce(FoldArgs a) {
     typedef int vi __attribute__((ext_vector_type(V)));
     typedef float vf __attribute__((ext_vector_type(V)));
-    const int64_t n = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
+    const uint32_t n = (blockIdx.x * blockDim.x + threadIdx.x) * V;
     if (n >= a.N) return;
+    const int splits = (int)a.splits;
+    const uint64_t stride = (uint64_t)a.M * a.N;
+    uint32_t m = blockIdx.y;
+    // the first row's slices are on their way before anything else is asked for
+    auto slices = [&](int sp, vi(&q)[4]) {
+        const int32_t* p = a.sums + ((uint64_t)m * a.N + n);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            q[i] = *reinterpret_cast<const vi*>(p + (uint32_t)(sp + i < splits ? sp + i : splits - 1) * stride);
+    };
+    vi q[4];
+    slices(0, q);
     float beta[V], wsum[V];
 #pragma unroll
     for (int c = 0; c < V; ++c) {
-        beta[c] = a.beta_rows >= a.N ? a.beta[0] : a.beta[((uint32_t)(n + c) / (uint32_t)a.beta_rows) * a.beta_stride];
+        beta[c] = a.beta_rows >= a.N ? a.beta[0] : a.beta[(int64_t)((n + c) / a.beta_rows) * a.beta_stride];
         wsum[c] = a.eta ? (float)a.wsum[n + c] : 0.f;
     }
-    const int64_t stride = a.M * a.N, ldy = a.ldy ? a.ldy : a.N;
-    for (int64_t m = blockIdx.y; m < a.M; m += gridDim.y) {
-        const int32_t* p = a.split_ws + m * a.N + n;
+    while (true) {
+        const uint64_t mg = (uint64_t)m * a.gstride;
+        const int rs = a.rowsum[mg];
+        const float gm = a.gamma[a.per_tensor ? 0 : mg];
+        const float eta = *(a.eta ? a.eta + (a.per_tensor ? 0 : mg) : a.gamma);  // (always a valid address)
+        __builtin_amdgcn_sched_barrier(0);
         vi sum = {};
-        for (int sp = 0; sp < splits; sp += 4) {
-            vi q[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                q[i] = *reinterpret_cast<const vi*>(p + (sp + i < splits ? sp + i : splits - 1) * stride);
+        for (int sp = 0;;) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) sum += q[i] & -(int)(sp + i < splits);
+            sp += 4;
+            if (sp >= splits) break;
+            slices(sp, q);
         }
-        const vi pm = sum - a.rowsum[m * a.gstride];
+        const vi pm = sum - rs;
         if (a.out_acc) {
-            *reinterpret_cast<vi*>(reinterpret_cast<int*>(a.Y) + m * ldy + n) = pm;
-            continue;
-        }
-        const float gm = a.gamma[a.per_tensor ? 0 : m * a.gstride];
-        const float eta = a.eta ? a.eta[a.per_tensor ? 0 : m * a.gstride] : 0.f;
-        vf* const o = reinterpret_cast<vf*>(a.Y + m * ldy + n);
-        vf y;
+            *reinterpret_cast<vi*>(reinterpret_cast<int*>(a.Y) + (uint64_t)m * a.ldy + n) = pm;
+        } else {
+            vf y;
 #pragma unroll
-        for (int c = 0; c < V; ++c) {
-            y[c] = (float)pm[c] * ((beta[c] * gm) / 128.0f);
-            if (a.eta) y[c] = y[c] + (beta[c] * eta) * wsum[c];
+            for (int c = 0; c < V; ++c) {
+                y[c] = (float)pm[c] * ((beta[c] * gm) / 128.0f);
+                if (a.eta) y[c] = y[c] + (beta[c] * eta) * wsum[c];
+            }
+            *reinterpret_cast<vf*>(a.Y + (uint64_t)m * a.ldy + n) = y;
         }
-        *o = y;
+        m += gridDim.y;
+        if (m >= a.M) return;
+        slices(0, q);
     }
 }
 
@@ -516,11 +541,13 @@ void launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s) {
         const unsigned blocks = (unsigned)((a.M * cols + 255) / 256);
         if (vec) groups_reduce<4><<<blocks, 256, 0, s>>>(a);
         else groups_reduce<1><<<blocks, 256, 0, s>>>(a);
-    } else if (vec) {
-        splitk_reduce<4><<<grid, threads, 0, s>>>(a, splits);
-    } else {
-        splitk_reduce<1><<<grid, threads, 0, s>>>(a, splits);
+        return;
     }
+    const FoldArgs f{a.split_ws, (uint32_t)a.M, (uint32_t)a.N, (uint32_t)splits, (uint32_t)a.gstride, a.rowsum, a.gamma,
+                     a.beta, a.eta, a.wsum, a.Y, a.ldy ? a.ldy : a.N, a.beta_stride, (uint32_t)a.beta_rows,
+                     a.per_tensor, a.out_acc};
+    if (vec) splitk_reduce<4><<<grid, threads, 0, s>>>(f);
+    else splitk_reduce<1><<<grid, threads, 0, s>>>(f);
 }
 
 hipError_t launch_gemm_decode(const GemmArgs& a_in, hipStream_t s) {
