@@ -37,7 +37,8 @@ namespace bl {
 template <int C, int T, int MAXT, bool ONE_ROUND, bool KGRP = false>
 __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) {
     static_assert(!KGRP || ONE_ROUND, "K-groups inside the workgroup: one round");
-    __shared__ __attribute__((aligned(16))) int red[(MAXT / kWave) * T * 256];  // [W][T][64][4]
+    constexpr int kStageRows = 8, kRegion = ONE_ROUND && T < kStageRows ? kStageRows : T;  // KiB of a wave's part
+    __shared__ __attribute__((aligned(16))) int red[(MAXT / kWave) * kRegion * 256];  // [W][T][64][4]
     constexpr int MAXW = MAXT / kWave;
     const int W = blockDim.x / kWave;
     // the wave's index as a scalar: which chunks and tiles it owns is then scalar arithmetic and
@@ -115,35 +116,34 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                     }
             }
         };
-        // Few tokens: the wave's slice of the codes is M rows of C * 512 bytes, and fetching it in
-        // operand layout costs C * 8 load instructions whatever M is (at one token as much time on
-        // the load path as a seventh of the weight stream).  Instead each row is fetched with one
-        // instruction, 16 consecutive bytes a lane (rows past M, up to a whole four: row M-1 again), and (below,
-        // once the first weight tiles have been requested behind it) parked in the wave's own part of `red`, which
-        // holds nothing before the wave's first tile is done, and read from there in operand layout.
-        // More tokens than the region has rows: the rows go through it in passes (the lanes of a
-        // pass's rows read their operands, then the next rows are parked).  A row is 1 KiB, so the
-        // same 16 bytes of every row would share their banks: the 16-byte slots of row r are stored
-        // at slot ^ (r % 16).
-        constexpr int kStageRows = T < 8 ? T : 8;
-        constexpr int kStagePasses = (16 + kStageRows - 1) / kStageRows;
-        const bool staged = ONE_ROUND && (M <= kStageRows || T >= 4);
+        // One round: the wave's slice of the codes is M rows of C * 512 bytes.  In operand layout a load touches
+        // half a line of each row, so L2 serves every line twice, and there are C * 8 of them whatever M is.
+        // Instead each row is fetched with one instruction, 16 consecutive bytes a lane (rows past M, up to a whole
+        // four: row M-1 again), and (below, once the first weight tiles have been requested behind it) parked in the
+        // wave's own part of `red`, which holds nothing before the wave's first tile is done, eight rows at a time, and
+        // read from there in operand layout.  A row is 1 KiB, so the same 16 bytes of every row would share their
+        // banks: the 16-byte slots of row r are stored at slot ^ r.  us a launch, from memory in operand layout
+        // (unless the part of `red` that the sums need held the rows) / now: 8 tokens 4096 -> 4096 3.95 / 3.2, 7168 -> 7168
+        // 5.4 / 4.5, 8192 -> 2048 5.0 / 3.8, 16 tokens 8192 -> 2048 6.3 / 4.55, 7168 -> 7168 6.4 / 5.3, 16384 -> 4096
+        // 10.2 / 6.85.  A single chunk of K is read in place: parking is a longer chain then (16 x 256 -> 512 2.8, 2.45).
         const bool stage_lane = l < C * 32;
-        v4i rowv[16];
-        if (staged) {
+        constexpr int kHeld = MAXT == 512 ? 16 : kStageRows;  // rows in registers; 16 waves have room for eight
+        v4i rowv[kHeld];
+        auto load_rows = [&](int first, int count) {  // rows first, first + 1, ... into rowv[0], ...
             int kl = tk0 * kChunkK + 16 * l;  // this lane's 16 bytes of a row slice
             kl = kl > K - 16 ? K - 16 : kl;
             const int8_t* __restrict__ src = a.codes + kl;
 #pragma unroll
-            for (int r0 = 0; r0 < 16; r0 += 4)
-                if (r0 < M) {  // uniform
+            for (int r0 = 0; r0 < kHeld; r0 += 4)
+                if (r0 < count && first + r0 < M) {  // uniform
 #pragma unroll
                     for (int r = r0; r < r0 + 4; ++r)
-                        rowv[r] = *reinterpret_cast<const v4i*>(src + (int64_t)(r < M ? r : M - 1) * a.ldq);
+                        rowv[r] = *reinterpret_cast<const v4i*>(src + (int64_t)(first + r < M ? first + r : M - 1) * a.ldq);
                 }
-        } else {
-            load_act();
-        }
+        };
+        const bool staged = ONE_ROUND && (C > 1 || TK > 1);  // uniform
+        if (staged) load_rows(0, kHeld);
+        else load_act();
 
         // Weight tiles: a software pipeline of depth kDepth per wave.  Asking for everything at
         // once looks attractive for a 4-microsecond stream, but the memory system then returns
@@ -175,29 +175,32 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         };
 #pragma unroll
         for (int t = 0; t < kDepth; ++t) load_tile(t);
-        if (staged) {  // rows past M repeat row M-1 (never stored)
-            int* stage = &red[w * T * 256];
+        if (staged) {
+            uint8_t* stage = reinterpret_cast<uint8_t*>(&red[w * kRegion * 256]);
 #pragma unroll
-            for (int p = 0; p < kStagePasses; ++p) {
+            for (int p = 0; p < 16 / kStageRows; ++p) {
                 if (p * kStageRows < M) {  // uniform
                     if (stage_lane) {
 #pragma unroll
                         for (int r0 = 0; r0 < kStageRows; r0 += 4)
                             if (p * kStageRows + r0 < M) {  // uniform
 #pragma unroll
-                                for (int r = r0; r < r0 + 4 && r < kStageRows && p * kStageRows + r < 16; ++r)
-                                    *reinterpret_cast<v4i*>(&stage[r * 256 + (l ^ (r & 15)) * 4]) =
-                                        rowv[p * kStageRows + r];
+                                for (int r = r0; r < r0 + 4; ++r)
+                                    *reinterpret_cast<v4i*>(stage + r * 1024 + (l ^ r) * 16) =
+                                        rowv[kHeld == 16 ? p * kStageRows + r : r];
                             }
                     }
+                    if (kHeld == kStageRows && p == 0 && M > kStageRows) load_rows(kStageRows, kStageRows);
                     if (mc / kStageRows == p) {
-                        const int rr = mc - p * kStageRows;
+                        const int rr = mc % kStageRows;
+                        // slot 32 c + 4 i + g of row rr: the row number flips bit 2 of it for odd i or for even
+                        const uint8_t* even = stage + rr * 1024 + (g ^ rr) * 16;
+                        const uint8_t* odd = stage + rr * 1024 + ((4 + g) ^ rr) * 16;
 #pragma unroll
                         for (int c = 0; c < C; ++c)
 #pragma unroll
                             for (int i = 0; i < 8; ++i)
-                                act[c][i] = *reinterpret_cast<const v4i*>(
-                                    &stage[rr * 256 + ((c * 32 + 4 * i + g) ^ (rr & 15)) * 4]);
+                                act[c][i] = *reinterpret_cast<const v4i*>((i & 1 ? odd : even) + c * 512 + (i >> 1) * 128);
                     }
                 }
             }
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
 #pragma unroll
             for (int i = 1; i < 4; ++i) sum = (sum << 1) + acc[i];
             if (ONE_ROUND) {
-                *reinterpret_cast<v4i*>(&red[((w * T + t) * kWave + l) * 4]) = sum;
+                *reinterpret_cast<v4i*>(&red[((w * kRegion + t) * kWave + l) * 4]) = sum;
             } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) part[t][r] += sum[r];
@@ -251,7 +254,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
     if (!ONE_ROUND) {
 #pragma unroll
         for (int t = 0; t < T; ++t)
-            *reinterpret_cast<v4i*>(&red[((w * T + t) * kWave + l) * 4]) =
+            *reinterpret_cast<v4i*>(&red[((w * kRegion + t) * kWave + l) * 4]) =
                 (v4i){part[t][0], part[t][1], part[t][2], part[t][3]};
     }
     __syncthreads();
@@ -261,7 +264,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             const int t = item % tpb, grp = item / tpb;
             v4i sum = (v4i){0, 0, 0, 0};
             for (int ww = grp * wpg; ww < (grp + 1) * wpg; ++ww)
-                sum += *reinterpret_cast<const v4i*>(&red[((ww * T + t) * kWave + l) * 4]);
+                sum += *reinterpret_cast<const v4i*>(&red[((ww * kRegion + t) * kWave + l) * 4]);
             const uint32_t tn = tn0 + t, n = tn * kTileN + 4 * g;
             if (tn >= TN || m >= M || n >= N) continue;
             int* p = a.split_ws + (uint64_t)(uint32_t)(grp * M + m) * N + n;
@@ -285,7 +288,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int ww = w0 + i < W ? w0 + i : W - 1;
-                    p[i] = *reinterpret_cast<const v4i*>(&red[((ww * T + t) * kWave + l) * 4]);
+                    p[i] = *reinterpret_cast<const v4i*>(&red[((ww * kRegion + t) * kWave + l) * 4]);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) sum += p[i] & -(int)(w0 + i < W);
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             // with one or two waves, or with 16, the plain loop is the faster one (from codes 1 x 256 -> 512 2.47 us
             // for 2.56, 1 x 16384 -> 4096 4.4 for 4.7)
             for (int ww = 0; ww < W; ++ww)
-                sum += *reinterpret_cast<const v4i*>(&red[((ww * T + t) * kWave + l) * 4]);
+                sum += *reinterpret_cast<const v4i*>(&red[((ww * kRegion + t) * kWave + l) * 4]);
         }
         const uint32_t tn = tn0 + t, n = tn * kTileN + 4 * g;
         if (tn >= TN || m >= M || n >= N) continue;
