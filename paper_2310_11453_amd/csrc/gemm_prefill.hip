@@ -113,6 +113,17 @@ __device__ inline void lds_read_rows(v4f& sc, v4i& rs, uint32_t ad_sc, uint32_t 
         : "=&v"(sc), "=&v"(rs)
         : "v"(ad_sc), "v"(ad_rs));
 }
+// four times four consecutive rows, 8 rows apart
+__device__ inline void lds_read_quads(v4i (&q)[4], uint32_t ad) {
+    asm volatile(
+        "ds_read_b128 %0, %4\n\t"
+        "ds_read_b128 %1, %4 offset:32\n\t"
+        "ds_read_b128 %2, %4 offset:64\n\t"
+        "ds_read_b128 %3, %4 offset:96\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3])
+        : "v"(ad));
+}
 __device__ inline float lds_read_f32(uint32_t ad) {
     float v;
     asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(ad));
@@ -515,24 +526,30 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
 // Bound by the matrix pipe and, at short groups, by whatever happens between items: K = 7168 in 8
 // groups is 14 stages an item.  So the stream of operands does not stop there.  Codes, packed bits
 // and the items' scales have cursors of their own that run ahead of the multiplication (7 stages, two
-// 512-chunks, one item) straight across the ends of groups and tiles; every mid-stage point issues
+// 512-chunks, two items) straight across the ends of groups and tiles; every mid-stage point issues
 // the same operations, so the waits are the same constants everywhere.  The bits have two LDS buffers
-// (a chunk's bits are requested when the chunk before the last starts), the scales two as well.
+// (a chunk's bits are requested when the chunk before the last starts), the scales four.
 // A group's K may end inside a stage or a chunk: what follows meets zero bits (tiles are padded with
 // them), and the at most 32 bytes behind the codes of the last row lie in the workspace.  A cursor
 // at the end of the workgroup's work re-reads its last piece into a buffer nobody reads.
 //
 // The waits.  Mid-point of stage s (between its half-steps), per wave and in this order: wait,
-// barrier, [last stage of a chunk: read the next chunk's bits], [first stage of an item: request
-// the next item's scales], [first stage of a chunk: request the bits of the chunk after the next],
+// barrier, [last stage of a chunk: read the next chunk's bits], [first stage of an item: request the scales of
+// the item after the next], [first stage of a chunk: request the bits of the chunk after the next],
 // request codes of stage s + 7.  Needed there: codes of stage s + 1, with the codes of stages s + 2
-// .. s + 6 (five operations) younger; the bits read there, and at the fold the scales: younger than
-// these are the codes of at least 2 nst - 1 stages and the bits of a chunk, five or more when an item
-// has two stages or more (nst).  One wait for all but the last five covers all three; items of one
-// stage wait for everything.
+// .. s + 6 (five operations) younger; the bits read there; and behind the last stage of an item the scales of
+// the next one, whose row sums its products start from.  Younger than these are the codes of at least 2 nst - 1
+// stages and the bits of two chunks, five or more when an item has two stages or more (nst).  One wait for
+// all but the last five covers all three; items of one stage wait for everything.
 //
-// 1000 x 7168 x 28672 in 8 x 8 groups: the layer takes 240 us; with the ring drained and filled for every item
-// and the scales loaded behind it, 445 us.
+// The fold is vector instructions that all waves issue at once while the matrix pipe stands still, two waves a SIMD and four
+// cycles each, beside 112 MFMAs of 32 cycles in an item of 14 stages.  So what can be is in the MFMAs: a set bit is a byte of 2
+// and an item's first half-step adds to the negated row sums instead of to zeros, and the accumulators are sum_k q s
+// as they are; left are conversion, product of the scales, product and addition, 320 instructions of 450 a wave.  us of the
+// layer, before / after: 1000 x 7168 x 28672 in 8 x 8 groups 238.6 / 224.5, 4096 x 7168 x 7168 in 2 x 8 265 / 249, 3000 x 2048 x
+// 8192 in 8 x 8 106.7 / 92.0, 4096 x 1024 x 4096 in 1 x 8 71.8 / 58.2.  (The scales' products from a 32 x 32 x 2 f32 MFMA, 64
+// vector instructions fewer, are 1 to 6 % slower; bytes of {0, -128} are no faster; with the ring drained and filled for
+// every item and the scales loaded behind it the first of these took 445 us.)
 template <bool ETA>
 __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid_m, int grid_n) {
     constexpr int BM = 128, BN = 256, WN = 4, NS = 8, THREADS = 512, NWAVES = 8;
@@ -542,9 +559,9 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
     constexpr int NBW = BN / 16 / NWAVES;
     __shared__ __attribute__((aligned(1024))) uint8_t smA[NS * STAGE_BYTES];
     __shared__ __attribute__((aligned(1024))) uint8_t smB[2 * BITS_BYTES];
-    // per item: gamma [128], row sums [128], beta [256]; Eq. 6: eta [128], unused [128], wsum [256]
-    __shared__ __attribute__((aligned(1024))) uint32_t smS[2][THREADS];
-    __shared__ __attribute__((aligned(1024))) uint32_t smE[2][ETA ? THREADS : 4];
+    // per item, in a ring: gamma [128], row sums [128], beta [256]; Eq. 6: eta [128], unused [128], wsum [256]
+    __shared__ __attribute__((aligned(1024))) uint32_t smS[4][THREADS];
+    __shared__ __attribute__((aligned(1024))) uint32_t smE[4][ETA ? THREADS : 4];
 
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), l = threadIdx.x % kWave;
     const int wm = w / WN, wn = w % WN;
@@ -647,7 +664,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
             __builtin_amdgcn_global_load_lds(
                 src, (__attribute__((address_space(3))) void*)(&smE[sbuf][w * kWave]), 4, 0, 0);
         }
-        sbuf ^= 1;
+        sbuf = (sbuf + 1) & 3;
         next_item(cs);
     };
 
@@ -673,10 +690,16 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
                 for (int r = 0; r < 16; ++r) side[mi][s][r] = -0.f;
     };
     clear_side();
+    // bit plane i as {0, 2} bytes
+    auto plane = [](int bits, int i) {
+        return (int)(__builtin_amdgcn_alignbit((uint32_t)bits, (uint32_t)bits, (uint32_t)(i + 31) & 31) & 0x02020202u);
+    };
     // acc += ac x b; meanwhile an = operands at `ad`, bn = plane i of half h (see gemm_prefill_kernel);
     // between() goes behind the first two MFMAs: the cursors' scalar work would idle the matrix pipe of
     // all waves at once if it stood right behind the barrier
-    auto half_step = [&](const v4i(&ac)[MI], const v4i(&b)[NI], v4i(&bn)[NI], int h, int i, v4i(&an)[MI],
+    // `first`: the item's first, on top of the rows' -sum_k q
+    v16i base[MI];
+    auto half_step = [&](auto first, const v4i(&ac)[MI], const v4i(&b)[NI], v4i(&bn)[NI], int h, int i, v4i(&an)[MI],
                          uint32_t ad, auto between) {
         lds_issue(an, ad);
         asm volatile("" : "+v"(bw[0][h]), "+v"(bw[1][h]));
@@ -685,12 +708,12 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int s = 0; s < NI; ++s) {
-                acc[mi][s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ac[mi], b[s], acc[mi][s], 0, 0, 0);
+                acc[mi][s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ac[mi], b[s], first ? base[mi] : acc[mi][s], 0, 0, 0);
                 const int q = mi * NI + s;
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const int idx = q * 2 + e;
-                    bn[idx >> 2][idx & 3] = (int)(((uint32_t)bw[idx >> 2][h][idx & 3] >> i) & 0x01010101u);
+                    bn[idx >> 2][idx & 3] = plane(bw[idx >> 2][h][idx & 3], i);
                 }
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
@@ -709,7 +732,9 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
     int slot = 0, rbuf = 0;  // the stage's ring slot; the buffer the current chunk's bits came from
     auto stage = [&](auto ic, bool last, bool first_chunk) {
         constexpr int i = decltype(ic)::value;
-        half_step(ax, bx, by, 1, i, ay, a_lane[1] + (uint32_t)(slot * STAGE_BYTES), []() {});
+        const uint32_t second = a_lane[1] + (uint32_t)(slot * STAGE_BYTES);
+        if (i == 0 && first_chunk) half_step(std::true_type{}, ax, bx, by, 1, i, ay, second, []() {});
+        else half_step(std::false_type{}, ax, bx, by, 1, i, ay, second, []() {});
         if (one_stage) wait_vmcnt<0>();
         else wait_vmcnt<5>();
         block_barrier();
@@ -718,7 +743,7 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
             lds_read_bits(bw, b_lane + (uint32_t)(rbuf * BITS_BYTES));
         }
         slot = (slot + 1) & (NS - 1);
-        half_step(ay, by, bx, 0, last ? 0 : i + 1, ax, a_lane[0] + (uint32_t)(slot * STAGE_BYTES), [&]() {
+        half_step(std::false_type{}, ay, by, bx, 0, last ? 0 : i + 1, ax, a_lane[0] + (uint32_t)(slot * STAGE_BYTES), [&]() {
             if constexpr (i == 0) {
                 if (first_chunk) issue_scales();
                 issue_bits();
@@ -726,16 +751,20 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
             issue_codes();
         });
     };
-    auto clear = [&]() {
+    // the row sums of an item, negated, from its scales' buffer
+    auto load_base = [&](int buf) {
+        const uint32_t ad = (uint32_t)(uintptr_t)&smS[buf][BM + wm * WTM + 4 * g2];
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < MI; ++mi) {
+            v4i q[4];
+            lds_read_quads(q, ad + 128 * mi);
 #pragma unroll
-            for (int s = 0; s < NI; ++s)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mi][s][r] = 0;
+            for (int r = 0; r < 16; ++r) base[mi][r] = -q[r >> 2][r & 3];
+        }
     };
 
     set_codes();
+    issue_scales();
     issue_scales();
     issue_bits();
     issue_bits();
@@ -748,8 +777,8 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
 #pragma unroll
     for (int s = 0; s < NI; ++s)
 #pragma unroll
-        for (int d = 0; d < 4; ++d) bx[s][d] = (int)((uint32_t)bw[s][0][d] & 0x01010101u);
-    clear();
+        for (int d = 0; d < 4; ++d) bx[s][d] = plane(bw[s][0][d], 0);
+    load_base(0);
 
     int fbuf = 0;  // the scales of the item being folded
     while (true) {
@@ -772,26 +801,21 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
         const uint32_t row_base = (uint32_t)(uintptr_t)&smS[fbuf][wm * WTM + 4 * g2];
         const uint32_t eta_base = (uint32_t)(uintptr_t)&smE[fbuf][wm * WTM + 4 * g2];
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < MI; ++mi) {
+            v4i q[4];
+            lds_read_quads(q, row_base + 128 * mi);
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                v4f sc4;
-                v4i rs4;
-                lds_read_rows(sc4, rs4, row_base + (32 * mi + 8 * rq) * 4, row_base + (BM + 32 * mi + 8 * rq) * 4);
+            for (int r = 0; r < 16; ++r) {
+                const float sc = __int_as_float(q[r >> 2][r & 3]) * 0.0078125f;  // gamma / 128, exact
+                const float e = ETA ? lds_read_f32(eta_base + (32 * mi + 8 * (r >> 2) + (r & 3)) * 4) : 0.f;
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = rq * 4 + rr;
-                    const float sc = sc4[rr] * 0.0078125f;  // gamma / 128, exact
-                    const int nrs = -rs4[rr];
-                    const float e = ETA ? lds_read_f32(eta_base + (32 * mi + 8 * rq + rr) * 4) : 0.f;
-#pragma unroll
-                    for (int s = 0; s < NI; ++s) {
-                        float y = (float)((int)((uint32_t)acc[mi][s][r] << 1) + nrs) * (bcol[s] * sc);
-                        if constexpr (ETA) y = y + (bcol[s] * e) * wcol[s];
-                        side[mi][s][r] = y + side[mi][s][r];
-                    }
+                for (int s = 0; s < NI; ++s) {
+                    float y = (float)acc[mi][s][r] * (bcol[s] * sc);
+                    if constexpr (ETA) y = y + (bcol[s] * e) * wcol[s];
+                    side[mi][s][r] = y + side[mi][s][r];
                 }
             }
+        }
         if (cur.grp + 1 == ngroups) {
             const int row = cur.m0 + wm * WTM, col = cur.n0 + wn * WTN;
             store_tile<MI, NI, true>(a.Y + (int64_t)row * N + col, N, M - row, N - col, j, g2, [](int, int) {},
@@ -799,8 +823,8 @@ __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid
             clear_side();
         }
         if (!next_item(cur)) break;
-        fbuf ^= 1;
-        clear();
+        fbuf = (fbuf + 1) & 3;
+        load_base(fbuf);
     }
     wait_vmcnt<0>();
 }
@@ -920,10 +944,11 @@ size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K, bool one_beta) {
 // The same choice for a grouped layer (K = a group's): 0 = the stream kernel, 3 or 4 = the tiles of
 // gemm_mid.hip with every K-group an item of its own, its int32 sums in a slice that the fold
 // dequantises (same fp32 operations in the same order, same bits).  The stream kernel's round of
-// tiles costs 6 + groups (1 + 0.42 n) us (1000 x 7168 x 28672, 8 groups: 238 us in 4 rounds).
-// Whole layers, stream / 128 x 128 slices / 64 x 128 slices: 100 x 4096 x 4096 in 2 groups 37 / 20 / 18, 300 x
-// 4096 x 7168 in 4 groups 63 / 44 / 44, 500 x 2048 x 2048 in 4 groups 29 / 27 / 33; 1000 x 4096 x 4096 in
-// 8 groups 54 / 102 / 150.
+// tiles is taken to cost 6 + groups (1 + 0.42 n) us (1000 x 7168 x 28672, 8 groups: 228 us in 4 rounds, measured 212;
+// with constants that fit this one, layers of 66 to 641 tokens at the line, 2 % of all, got up to 15 % slower).
+// Whole layers, stream / 128 x 128 slices / 64 x 128 slices: 172 x 1024 x 2560 in 4 groups 19.1 / 18.0 / 17.9, 306 x
+// 4352 x 4352 in 4 groups 40.8 / 39.4 / 38.5, 300 x 4096 x 7168 in 4 groups 37.6 / 42.8 / 51.1, 500 x 2048 x 2048 in 4
+// groups 25.8 / 24.1 / 28.7; 1000 x 4096 x 4096 in 8 groups 46 / 87 / 126.
 static int group_plan(int64_t M, int64_t N, int64_t K, int groups, size_t ws_bytes) {
     const int64_t cus = num_cus(), TK = tiles_k(K), nst = (K + kStageK - 1) / kStageK;
     const int force = tuning().prefill_tile;
