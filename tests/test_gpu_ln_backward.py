@@ -89,6 +89,24 @@ def test_ln_backward_in_place(bl):
     assert np.abs(host(dgain) - ref[1]).max() <= 1e-4 and np.abs(host(dbias) - ref[2]).max() <= 1e-4
 
 
+@pytest.mark.parametrize("M,K,groups", [(50, 1024, 1), (7, 20480, 1), (33, 768, 3)])
+def test_ln_backward_affine_wherever_dx_lies(bl, M, K, groups):
+    """dX by itself (its pass leaves the statistics that the column sums read), or over dXhat or X (they are summed
+    before it is written): the same bits."""
+    g = dev(wl.make_grad(M, K, seed=wl.seed_for(4, 902), std=1.0))
+    X = dev(wl.make_activation(M, K, seed=wl.seed_for(4, 903)))
+    want = bl.bitlinear_layernorm_backward(g, X, groups_k=groups, want_affine=True)
+    flat = torch.empty(2 * M * K, device="cuda")
+    g2, behind = flat[:M * K].view(M, K).copy_(g), flat[M * K:].view(M, K)  # dX right behind dXhat: apart
+    places = [(g2, X, behind), (g.clone(), X, None), (g, X.clone(), None)]
+    for i, (gi, xi, out) in enumerate(places):
+        out = (out, gi, xi)[i]
+        if i == 2 and K // groups > 16384:
+            continue  # rows walked from memory are read again behind their first stores
+        got = bl.bitlinear_layernorm_backward(gi, xi, groups_k=groups, want_affine=True, out=out)
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), i
+
+
 def test_ln_backward_full_training_shape_sampled(bl):
     """M = 8192, K = 4096 (the training configuration): sampled rows against the oracle."""
     M, K = 8192, 4096
