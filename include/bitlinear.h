@@ -330,6 +330,7 @@ int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int thre
  *   prefill_xbm=r       M > 64: rows of tiles in the block of tiles an XCD owns (1, 2, 4, 8; 0 = 1, the fastest measured; more rows fetch fewer bytes)
  *   quant_wpr=w         quantiser: waves per row (1, 2, 4, 8)
  *   bwd_ring=1|2        backward, dW: 256 x 256 or 128 x 128 output tiles
+ *   bwd_dx=1|2          backward, dX: 256 x 256 or 128 x 256 output tiles
  *   bwd_grid=g, bwd_rowmajor=1   backward ring kernel: workgroups, plain tile order
  *   bwd_splits=n        backward ring kernels: slices of the reduction (256 x 256 tiles)
  * Returns BL_OK, or BL_ERR_UNSUPPORTED (unknown name or bad syntax; nothing changes). */

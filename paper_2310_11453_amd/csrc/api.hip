@@ -28,7 +28,7 @@ const TuningField kTuningFields[] = {
     {"group_slices", &Tuning::group_slices},
     {"quant_wpr", &Tuning::quant_wpr},           {"bwd_ring", &Tuning::bwd_ring},
     {"bwd_grid", &Tuning::bwd_grid},             {"bwd_rowmajor", &Tuning::bwd_rowmajor},
-    {"bwd_splits", &Tuning::bwd_splits},
+    {"bwd_splits", &Tuning::bwd_splits},         {"bwd_dx", &Tuning::bwd_dx},
     {"mid_kernel", &Tuning::mid_kernel},
 };
 Tuning g_tuning{};

@@ -499,7 +499,8 @@ __global__ __launch_bounds__(256, T == 256 ? 1 : 2) void gemm_tn_bf16_wide(const
 // that the words of stage st+1 can be read while stage st is being multiplied.  A lane turns its
 // word into the four dwords of an MFMA operand (eight +-1 bf16 values) with a shift and an
 // and-or each, placed between the MFMAs of the half-step before (the same scheduling as in the
-// forward GEMM).  Group of DMA operations of stage s: the words of stage s+1, then A of stage s;
+// forward GEMM).  BM = 256: waves of 128 x 64, one workgroup per CU; BM = 128 (few tiles, dx_plan): waves of 64 x 64, two
+// workgroups per CU.  Group of DMA operations of stage s: the words of stage s+1, then A of stage s;
 // they complete in this order, so the hand-counted waits are those of the kernel above with one
 // more operation per stage.
 __device__ inline void a_issue(v4i (&a)[4], uint32_t ad) {
@@ -509,6 +510,13 @@ __device__ inline void a_issue(v4i (&a)[4], uint32_t ad) {
         "ds_read_b128 %2, %4 offset:4096\n\t"
         "ds_read_b128 %3, %4 offset:6144"
         : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
+        : "v"(ad));
+}
+__device__ inline void a_issue(v4i (&a)[2], uint32_t ad) {
+    asm volatile(
+        "ds_read_b128 %0, %2\n\t"
+        "ds_read_b128 %1, %2 offset:2048"
+        : "=&v"(a[0]), "=&v"(a[1])
         : "v"(ad));
 }
 __device__ inline void words_issue(uint32_t (&wd)[2], uint32_t ad) {
@@ -526,15 +534,20 @@ __device__ inline void a_words_wait(v4i (&a)[4], uint32_t (&wd)[2]) {
                  : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(wd[0]), "+v"(wd[1]));
 }
 
-template <int NS, bool SPLIT>
-__global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __restrict__ A,
+__device__ inline void a_wait(v4i (&a)[2]) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1])); }
+__device__ inline void a_words_wait(v4i (&a)[2], uint32_t (&wd)[2]) {
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(wd[0]), "+v"(wd[1]));
+}
+
+template <int BM, int NS, bool SPLIT>
+__global__ __launch_bounds__(512, BM == 256 ? 2 : 4) void gemm_tn_signs_ring(const uint16_t* __restrict__ A,
                                                              const uint32_t* __restrict__ Sw,
                                                              int64_t I, int64_t J, int64_t Rp,
                                                              const float* __restrict__ scale_ptr,
                                                              float scale_mul, float* __restrict__ C,
                                                              int grid_i, int grid_j, int blk_i,
                                                              int blk_j, RingSlices sl) {
-    constexpr int BM = 256, BN = 256, WN = 4, THREADS = 512, WTM = 128, WTN = 64, MI = 4, NI = 2;
+    constexpr int BN = 256, WN = 4, THREADS = 512, WTM = BM / 2, WTN = 64, MI = WTM / 32, NI = 2;
     constexpr int PA = BM * 4 / THREADS, P = PA + 1;  // DMA operations per thread and stage
     constexpr int STAGE_BYTES = BM * 64;
     static_assert((NS - 1) * P + 1 < 64, "vmcnt range");
@@ -645,11 +658,16 @@ __global__ __launch_bounds__(512, 2) void gemm_tn_signs_ring(const uint16_t* __r
             for (int s = 0; s < NI; ++s) {
                 acc[mi][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(v8bf, ac[mi]), __builtin_bit_cast(v8bf, b[s]), acc[mi][s], 0, 0, 0);
-                const int idx = mi * NI + s;  // 0 .. 7: dword idx % 4 of sub-tile idx / 4
-                bn[idx >> 2][idx & 3] = pm_one(ws[idx >> 2], h, idx & 3);
+                constexpr int DW = NI * 4 / (MI * NI);  // dwords of the new operand per MFMA: 1 or 2
+                const int q = mi * NI + s;
+#pragma unroll
+                for (int e = 0; e < DW; ++e) {
+                    const int idx = q * DW + e;  // 0 .. 7: dword idx % 4 of sub-tile idx / 4
+                    bn[idx >> 2][idx & 3] = pm_one(ws[idx >> 2], h, idx & 3);
+                }
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-                if (idx == 1) {  // the DMA of a stage: behind two MFMAs, not ahead of them
+                __builtin_amdgcn_sched_group_barrier(0x002, 2 * DW, 0);
+                if (q == 1) {  // the DMA of a stage: behind two MFMAs, not ahead of them
                     __builtin_amdgcn_sched_barrier(0);
                     between();
                     __builtin_amdgcn_sched_barrier(0);
@@ -776,26 +794,31 @@ static int bwd_num_cus() {
 // blk_i x blk_j = grid / 8 tiles out of its grid_i / 8 rows, as square as the divisors allow; 0 =
 // no such tiling; and the slices of the reduction.
 struct RingPlan {
-    int tile, grid, gi, gj, blk_i, blk_j;
+    int tile, grid, gi, gj, blk_i, blk_j;  // tile: rows of a tile
     RingSlices sl;
 };
 
-// Cost in us of a product of `tiles` 256 x 256 tiles in slices of `per` of its nst stages on `cus` CUs: a
-// stage takes 0.6 us on a CU, an item 7 us besides, and the fp32 sums of a slice (`bytes`) are written
-// and read at 5 TB/s by a second launch of 4 us.
-static double ring_cost(int64_t tiles, int64_t nst, int64_t per, double bytes, int64_t cus) {
+// Cost in us of a product in slices of `per` of its nst stages on `cus` CUs: a stage of a tile takes `stage` us on a
+// CU, an item `item` us besides (two workgroups of a CU take the time of both), and the fp32 sums of a slice
+// (`bytes`) are written and read at 5 TB/s by a second launch of 4 us.
+struct RingCost {
+    double stage, item;
+};
+constexpr RingCost kWideCost{0.6, 7.0};    // 256 x 256
+constexpr RingCost kRowsCost{0.345, 4.5};  // 128 x 256 (dX)
+static double ring_cost(RingCost c, int64_t tiles, int64_t nst, int64_t per, double bytes, int64_t cus) {
     const int64_t n = (nst + per - 1) / per, rounds = (tiles * n + cus - 1) / cus;
-    return (double)rounds * (0.6 * (double)per + 7.0) + (n > 1 ? 4.0 + (double)n * bytes * 2.0 / 5e6 : 0.0);
+    return (double)rounds * (c.stage * (double)per + c.item) + (n > 1 ? 4.0 + (double)n * bytes * 2.0 / 5e6 : 0.0);
 }
-// The slices that cost least.  dX^ of M = 1000, N = 8192, K = 2048 (32 tiles of 256 stages): 6 slices, 43 us
-// and 11 us for the fold; in 64 tiles of 256 x 128, each walking all of N, it took 185 us.
-static RingSlices ring_slices(int64_t tiles, int64_t nst, double bytes, int64_t cus) {
+// The slices that cost least.  dX^ of M = 1000, N = 8192, K = 2048 (64 tiles of 128 x 256 and 256 stages): whole call
+// 98.9 us in one slice, 66.9 in two, 53.0 in four, 66.6 in eight (62.8 in six slices of 32 tiles of 256 x 256).
+static RingSlices ring_slices(RingCost c, int64_t tiles, int64_t nst, double bytes, int64_t cus) {
     RingSlices best{1, (int)nst};
     double best_cost = 1e30;
     for (int64_t want = 1; want <= 16; ++want) {
         const int64_t per = (nst + want - 1) / want, n = (nst + per - 1) / per;
         if (want > 1 && per < 8) break;
-        const double cost = ring_cost(tiles, nst, per, bytes, cus);
+        const double cost = ring_cost(c, tiles, nst, per, bytes, cus);
         if (cost < best_cost * 0.97) {
             best_cost = cost;
             best = RingSlices{(int)n, (int)per};
@@ -806,22 +829,23 @@ static RingSlices ring_slices(int64_t tiles, int64_t nst, double bytes, int64_t 
 
 static int ring_cus() { return tuning().bwd_grid > 0 ? tuning().bwd_grid : bwd_num_cus(); }
 
-// tile: 256, or 128 (dW only; not sliced)
-static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp, int tile) {
+// Tiles of bm x bn: 256 x 256; 128 x 256 (dX); 128 x 128 (dW, not sliced).  Of the smaller ones a CU holds two.
+static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp, int bm, int bn) {
     RingPlan p{};
-    const int64_t gi = (I + tile - 1) / tile, gj = (J + tile - 1) / tile;
-    p.tile = tile;
+    const int64_t gi = (I + bm - 1) / bm, gj = (J + bn - 1) / bn;
+    p.tile = bm;
     p.gi = (int)gi;
     p.gj = (int)gj;
     const int64_t ntiles = gi * gj, nst = Rp / 32;
     p.sl = RingSlices{1, (int)nst};
     if (ntiles == 0 || nst == 0) return p;  // no tokens: nothing to launch (a size query asks)
-    if (tile == 256) p.sl = ring_slices(ntiles, nst, (double)I * (double)J * 4.0, ring_cus());
-    if (const int n = tuning().bwd_splits; n > 0 && tile == 256) {
+    if (bn == 256)
+        p.sl = ring_slices(bm == 256 ? kWideCost : kRowsCost, ntiles, nst, (double)I * (double)J * 4.0, ring_cus());
+    if (const int n = tuning().bwd_splits; n > 0 && bn == 256) {
         const int64_t per = (nst + n - 1) / n;
         p.sl = RingSlices{(int)((nst + per - 1) / per), (int)per};
     }
-    const int64_t items = ntiles * p.sl.splits, cap = (int64_t)ring_cus() * (tile == 256 ? 1 : 2);
+    const int64_t items = ntiles * p.sl.splits, cap = (int64_t)ring_cus() * (bm == 256 ? 1 : 2);
     const int grid = (int)(cap > items ? items : cap);
     p.grid = grid;
     if (p.sl.splits == 1 && ntiles % 8 == 0 && grid % 8 == 0 && gi % 8 == 0 &&
@@ -861,6 +885,24 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
             part, p.sl.splits, count, scale_ptr, scale_mul, C);
 }
 
+// dX's plan: 256 x 256 tiles, or 128 x 256 where they cost less.  A stage of the smaller tile takes more than half of the
+// larger one's time (its waves read and expand the same signs for half the rows), but with few tokens the
+// larger ones are too few for the CUs, or in so many slices that their sums cost what the product does.
+// The whole call, M x K x N, us, 256 / 128 rows: 1 x 4096 x 16384 47.0 / 36.5, 500 x 4096 x 4096 45.1 / 37.6, 1000 x 2048 x
+// 8192 63.8 / 54.7, 2048 x 4096 x 4096 91.3 / 76.7, 4000 x 2048 x 8192 166 / 153, 8192 x 1024 x 4096 118 / 97; but 1700 x
+// 2560 x 7680 98.5 / 110, 1000 x 4096 x 16384 151 / 155 (costs within 5 %) and 8192 x 4096 x 16384 901 / 923.
+static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
+    const RingPlan wide = ring_plan(I, J, Rp, 256, 256), rows = ring_plan(I, J, Rp, 128, 256);
+    if (const int force = tuning().bwd_dx) return force == 2 ? rows : wide;
+    const int64_t nst = Rp / 32, cus = ring_cus();
+    const double bytes = (double)I * (double)J * 4.0;
+    if (wide.grid == 0) return wide;
+    return ring_cost(kRowsCost, (int64_t)rows.gi * rows.gj, nst, rows.sl.per, bytes, cus) <
+                   0.95 * ring_cost(kWideCost, (int64_t)wide.gi * wide.gj, nst, wide.sl.per, bytes, cus)
+               ? rows
+               : wide;
+}
+
 // dW's plan: 256 x 256 tiles, or 128 x 128 where they cost less.  The fixed cost of a 256 x 256 tile (7 us: its
 // first DMA, its 64 K outputs stored by four waves) is what a product of a few stages consists of; the
 // 128 x 128 tile has a quarter of it and two workgroups per CU, but reads every operand twice as often:
@@ -873,16 +915,16 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
 // 7168 x 7168 115 / 107, 1000 x 7168 x 7168 159 / 171, 512 x 21504 x 7168 261 / 287, 256 x 7168 x 28672 248 / 265).
 static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int force = tuning().bwd_ring;
-    if (force == 2) return ring_plan(I, J, Rp, 128);
-    const RingPlan p = ring_plan(I, J, Rp, 256);
+    if (force == 2) return ring_plan(I, J, Rp, 128, 128);
+    const RingPlan p = ring_plan(I, J, Rp, 256, 256);
     if (force == 1 || tuning().bwd_splits > 0 || p.grid == 0) return p;
     const int64_t cus = ring_cus(), nst = Rp / 32, ntiles = (I + 127) / 128 * ((J + 127) / 128);
     const int64_t full = ntiles / (2 * cus), rest = ntiles % (2 * cus);
     if (ntiles > 2 * cus && (nst > (full < 2 ? 32 : full < 9 ? 16 : 12) || J * Rp * 2 > 12000000)) return p;
-    const double wide = ring_cost((int64_t)p.gi * p.gj, nst, p.sl.per, (double)I * (double)J * 4.0, cus);
+    const double wide = ring_cost(kWideCost, (int64_t)p.gi * p.gj, nst, p.sl.per, (double)I * (double)J * 4.0, cus);
     const double two = 2.5 + 0.38 * (double)nst, one = 1.0 + 0.25 * (double)nst;
     const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);
-    return small < wide ? ring_plan(I, J, Rp, 128) : p;
+    return small < wide ? ring_plan(I, J, Rp, 128, 128) : p;
 }
 
 // C[I][J] = scale * A[I][:] . B[J][:], in slices of r where the plan has them and `part` has room
@@ -925,7 +967,7 @@ static BackwardWs backward_ws(int64_t M, int64_t N, int64_t K) {
 size_t backward_workspace_min_bytes(int64_t M, int64_t N, int64_t K) { return backward_ws(M, N, K).total; }
 // The same and room for the slices of whichever product is cut (one after the other): optional.
 size_t backward_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    const size_t dx = slices_bytes(ring_plan(M, K, pad32(N), 256), M, K);
+    const size_t dx = slices_bytes(dx_plan(M, K, pad32(N)), M, K);
     const size_t dw = slices_bytes(dw_plan(N, K, pad32(M)), N, K);
     const size_t need = backward_ws(M, N, K).total + (dx > dw ? dx : dw);
     // never less than four bf16 copies of a small product's operands, which callers may have budgeted
@@ -948,15 +990,16 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
     // dY is read once: g for dX and gwT for dW come out of the same pass when both are wanted
     launch_prepare(a, a.dX ? g : nullptr, a.dX ? Sw : nullptr, a.dW ? gwT : nullptr, a.dW ? qT : nullptr, Np, Mp, s);
     if (a.dX) {  // +-1 from sign words inside the kernel: no bf16 copy of the weights
-        RingPlan p = ring_plan(M, K, Np, 256);
+        RingPlan p = dx_plan(M, K, Np);
         if (slices_bytes(p, M, K) > part_bytes) p = unsliced(p, Np);
         if (p.sl.splits > 1) {
-            gemm_tn_signs_ring<4, true><<<(unsigned)p.grid, 512, 0, s>>>(g, Sw, M, K, Np, nullptr, 1.0f, part,
-                                                                          p.gi, p.gj, 0, 0, p.sl);
+            const auto kernel = p.tile == 256 ? gemm_tn_signs_ring<256, 4, true> : gemm_tn_signs_ring<128, 4, true>;
+            kernel<<<(unsigned)p.grid, 512, 0, s>>>(g, Sw, M, K, Np, nullptr, 1.0f, part, p.gi, p.gj, 0, 0, p.sl);
             launch_fold(part, p, M * K, a.beta, 1.0f, a.dX, s);
         } else {
-            gemm_tn_signs_ring<4, false><<<(unsigned)p.grid, 512, 0, s>>>(
-                g, Sw, M, K, Np, a.beta, 1.0f, a.dX, p.gi, p.gj, p.blk_i, p.blk_j, p.sl);
+            const auto kernel = p.tile == 256 ? gemm_tn_signs_ring<256, 4, false> : gemm_tn_signs_ring<128, 4, false>;
+            kernel<<<(unsigned)p.grid, 512, 0, s>>>(g, Sw, M, K, Np, a.beta, 1.0f, a.dX, p.gi, p.gj, p.blk_i, p.blk_j,
+                                                    p.sl);
         }
     }
     if (a.dW) {

@@ -24,6 +24,7 @@ struct Tuning {
     int prefill_xbm;       // M > 64: tile rows in the block of tiles an XCD owns (0: one)
     int quant_wpr;         // quantiser: waves per row (1, 2, 4, 8)
     int bwd_ring;          // dW: 1 = 256 x 256 tiles, 2 = 128 x 128
+    int bwd_dx;            // dX: 1 = 256 x 256 tiles, 2 = 128 x 256
     int bwd_grid;          // backward ring kernel: workgroups
     int bwd_rowmajor;      // backward ring kernel: plain row-major tile order
     int bwd_splits;        // backward ring kernels: slices of the reduction

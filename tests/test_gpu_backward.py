@@ -38,7 +38,7 @@ SHAPES = [(8, 512, 256), (12, 20, 64), (300, 200, 96), (64, 136, 1056), (257, 51
 
 
 # The library picks dW's tile from the shape (256 x 256, or 128 x 128 where that costs less); the bwd_ring
-# switch forces either one so that both see the ragged shapes.  dX has one tile.
+# switch forces either one so that both see the ragged shapes.
 @pytest.mark.parametrize("M,N,K", SHAPES)
 @pytest.mark.parametrize("per_tensor", [True, False])
 @pytest.mark.parametrize("ring", ["2", "1"])
@@ -107,6 +107,26 @@ def test_backward_ring_kernel_walks_several_tiles(bl, tuning, spec, N):
                                          float(beta.cpu()[0]), False)
     close(dX.cpu().numpy(), dX_ref)
     close(dW.cpu().numpy(), dW_ref)
+
+
+# dX in tiles of 256 and of 128 rows: one row, the rows around a tile's last, fewer stages than the ring and one more,
+# columns of a second tile, slices, and several tiles a workgroup (with the tile order that groups tiles by L2).
+# On integers, so exact.
+@pytest.mark.parametrize("M,N,K", [(1, 32, 32), (127, 96, 256), (128, 130, 288), (129, 160, 544), (257, 520, 96),
+                                   (1024, 136, 1024)])
+@pytest.mark.parametrize("spec", ["", "bwd_splits=2", "bwd_grid=8"])
+@pytest.mark.parametrize("rows", [1, 2])
+def test_backward_dx_tiles_exact(bl, tuning, M, N, K, spec, rows):
+    print(f"backward dX M={M} N={N} K={K} {spec} bwd_dx={rows}", flush=True)
+    tuning(",".join(filter(None, [spec, f"bwd_dx={rows}"])))
+    rng = np.random.default_rng(M + N)
+    dY = rng.integers(-4, 5, (M, N)).astype(f32)
+    packed, _, _ = bl.bitlinear_pack_weights(dev(wl.make_weight(N, K, 0.02, 5)))
+    sign = oracle.unpack_canonical(
+        bl.bitlinear_packed_to_canonical(packed, N, K).cpu().numpy().view(np.uint32), K)
+    codes, one = torch.zeros(M, K, dtype=torch.int8, device="cuda"), torch.ones(1, device="cuda")
+    dX, _ = bl.bitlinear_backward_ste(dev(dY), codes, one, packed, one, True, want_dw=False)
+    assert np.array_equal(dX.cpu().numpy(), (dY.astype(np.int64) @ sign.astype(np.int64)).astype(f32))
 
 
 @pytest.mark.parametrize("ring", ["2", "1"])
