@@ -903,16 +903,19 @@ static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
                : wide;
 }
 
-// dW's plan: 256 x 256 tiles, or 128 x 128 where they cost less.  The fixed cost of a 256 x 256 tile (7 us: its
+// dW's plan: 256 x 256 tiles, or 128 x 128 where they cost less.  The fixed cost of a 256 x 256 tile (13 us: its
 // first DMA, its 64 K outputs stored by four waves) is what a product of a few stages consists of; the
 // 128 x 128 tile has a quarter of it and two workgroups per CU, but reads every operand twice as often:
-//   a round of up to one workgroup per CU    1.0 + 0.25 us per stage
-//   a round of two per CU                    2.5 + 0.38
-// The whole call (M x N x K, with the operand copies), 256 against 128: 8 x 512 x 256 18.2 / 10.5 us, 64 x 2048 x 2048
-// 21.3 / 13.2, 1000 x 2048 x 2048 44.6 / 25.7, 8 x 4096 x 16384 74.6 / 64.4; 4096 x 512 x 256 (16 slices of
-// 256 tiles) 33.9 / 44.5.  Past one full round the second read of the operands decides: beyond 32 stages (16 from two
-// full rounds on, 12 from nine), or with a B operand well beyond an XCD's 4 MB of L2, the large tile it is (512 x
-// 7168 x 7168 115 / 107, 1000 x 7168 x 7168 159 / 171, 512 x 21504 x 7168 261 / 287, 256 x 7168 x 28672 248 / 265).
+//   a round of 256 x 256, one workgroup per CU   12.8 + 0.68 us per stage
+//   of 128 x 128, up to one workgroup per CU      3.6 + 0.23
+//   of 128 x 128, two per CU                      4.9 + 0.39
+// (fitted to 82 shapes of 64 to 2000 tokens; a sliced product of 256 x 256 tiles is cheaper, kWideCost).  From two full
+// rounds on the second reading of the operands decides: beyond so many stages, or with a B operand well beyond an
+// XCD's 4 MB of L2, the large tile it is.  The whole call (M x N x K, with the operand copies), 256 against 128, us: 64 x
+// 2048 x 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048 37.6 / 32.8, 1300 x 8192 x
+// 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x 16384 x 4096 120.9 / 108.5, 1600 x 16384 x
+// 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 / 331, 2000 x 21504 x 7168 647 / 811; in slices 3300 x 4224 x
+// 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
 static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int force = tuning().bwd_ring;
     if (force == 2) return ring_plan(I, J, Rp, 128, 128);
@@ -920,11 +923,13 @@ static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     if (force == 1 || tuning().bwd_splits > 0 || p.grid == 0) return p;
     const int64_t cus = ring_cus(), nst = Rp / 32, ntiles = (I + 127) / 128 * ((J + 127) / 128);
     const int64_t full = ntiles / (2 * cus), rest = ntiles % (2 * cus);
-    if (ntiles > 2 * cus && (nst > (full < 2 ? 32 : full < 9 ? 16 : 12) || J * Rp * 2 > 12000000)) return p;
-    const double wide = ring_cost(kWideCost, (int64_t)p.gi * p.gj, nst, p.sl.per, (double)I * (double)J * 4.0, cus);
-    const double two = 2.5 + 0.38 * (double)nst, one = 1.0 + 0.25 * (double)nst;
+    const int64_t most = full < 4 ? 44 : full < 9 ? 32 : 16;  // stages
+    if (full >= 2 && (nst > most || J * Rp * 2 > 12000000)) return p;
+    const double wide = ring_cost(p.sl.splits > 1 ? kWideCost : RingCost{0.68, 12.8}, (int64_t)p.gi * p.gj, nst, p.sl.per,
+                                  (double)I * (double)J * 4.0, cus);
+    const double two = 4.9 + 0.39 * (double)nst, one = 3.6 + 0.226 * (double)nst;
     const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);
-    return small < wide ? ring_plan(I, J, Rp, 128, 128) : p;
+    return small < 1.02 * wide ? ring_plan(I, J, Rp, 128, 128) : p;
 }
 
 // C[I][J] = scale * A[I][:] . B[J][:], in slices of r where the plan has them and `part` has room
