@@ -855,21 +855,23 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 
 // Kernel and K-slices for M > 64: the cheapest of all by these costs in us, fitted to medians of graph
 // replays (n stages of 64 k, c 512-chunks per K-group of the workgroup):
-//   a round of 128 x 256 tiles   8 + 0.37 n     (n = 32: 19.5, 64: 30, 128: 50, 256: 89 to 112)
-//   a round of 256 x 256 tiles  14 + 0.62 n     (n = 32: 33, 64: 51 to 58, 112: 82, 256: 158)
-//   a round of the 128 x 128 and 64 x 128 tiles  3.5 + 4.2 c   (c = 1: 7.5, 2: 12, 4: 20)
-//   slices of K                  6.5 + the int32 sums written and read at 5 TB/s
+//   a round of 128 x 256 tiles    8 + 0.35 n     (n = 32: 19, 64: 30, 112: 45)
+//   a round of 256 x 256 tiles   14 + 0.62 n     (n = 32: 33, 64: 51 to 58, 112: 82, 256: 158)
+//   a round of 128 x 128 tiles    5 + 3.0 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 16: 53)
+//   a round of 64 x 128 tiles   4.5 + 3.1 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 14: 46)
+//   the last two in three rounds and more 5 % more (the large tiles read the operands less often)
+//   slices of K                   4 + the int32 sums written and read at 5 TB/s
 // The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
-// ones win; the layer, us, M x K x N: 333 x 2048 x 2048 12.8 (64 x 128) against 19.4 (128 x 256), 200 x 4096 x
-// 16384 22.3 (128 x 128) against 30.2, 333 x 8192 x 2048 25.4 (64 x 128; in 2 slices 25.0) against 51.9, 200 x
-// 16384 x 4096 31.3 (64 x 128 in 2 slices; without 36.1).  Over 126 shapes of 65 to 512 tokens the plan is 0.6 %
-// slower than the best of all these on average, 6.4 % at most (333 x 7168 x 28672 82.9, 77.9 as 128 x 128).
+// ones win; the layer, us, M x K x N: 333 x 2048 x 2048 12.8 (64 x 128) against 19.4 (128 x 256), 700 x 4096 x 16384
+// 60.5 (128 x 128) against 64.0 (128 x 256 and 256 x 256), 700 x 28672 x 7168 161.5 (64 x 128) against 186.1.  Over 171
+// shapes of 80 to 2200 tokens, K and N of 1024 to 28672, the plan is 0.3 % slower than the best of all these on average,
+// 4 % at most (2200 x 3200 x 9600 89.8, 86.4 as 128 x 256); with 8 + 0.37 n, 3.5 + 4.2 c and 6.5 it was 1.0 and 17 %.
 struct TilePlan {
     int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
     int64_t per;  // 512-chunks of K per slice (3 and 4)
     double us;
 };
-static double large_round_us(int tile, int64_t nst) { return tile == 1 ? 8.0 + 0.37 * nst : 14.0 + 0.62 * nst; }
+static double large_round_us(int tile, int64_t nst) { return tile == 1 ? 8.0 + 0.35 * nst : 14.0 + 0.62 * nst; }
 static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
     const int64_t cus = num_cus(), TK = tiles_k(K), nst = (K + kStageK - 1) / kStageK;
     const int force = tuning().prefill_tile;
@@ -895,8 +897,9 @@ static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
             const double bytes = (double)n * (double)M * (double)N * 4.0;
             if (n > 1 && ((n != want && !force_n) || bytes > (double)ws_bytes)) continue;
             const int64_t rounds = (tiles * n + cus - 1) / cus;
-            offer(tile, per, (double)rounds * (3.5 + 4.2 * (double)((per + kg - 1) / kg)) +
-                                 (n > 1 ? 6.5 + bytes * 2.0 / 5e6 : 0.0));
+            const double c = (double)((per + kg - 1) / kg);
+            offer(tile, per, (double)rounds * (tile == 3 ? 5.0 + 3.0 * c : 4.5 + 3.1 * c) * (rounds > 2 ? 1.05 : 1.0) +
+                                 (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0));
         }
     }
     return best;
