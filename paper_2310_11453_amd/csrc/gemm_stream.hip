@@ -16,7 +16,7 @@
 //    dequantise and store 16 bytes each.
 // Every workgroup reads all M x K codes (from L2), which is why the token count is bounded: at
 // more tokens that traffic, not the weight stream, sets the time, and the LDS-tiled mid-batch
-// kernel is as fast.  Long K is split over workgroups (second kernel: splitk_reduce) when the
+// kernel is as fast.  Long K is split over workgroups (second kernel: splitk_reduce) where these are few and the
 // caller brought the workspace.
 
 #include "common.h"
@@ -297,8 +297,8 @@ static int stream_cus() {
     return n;
 }
 
-// K-slices for 16 < M <= 32: longer K than 16 chunks (two per wave) is cut into slices of at most
-// 16 chunks.  0 = no split.
+// K-slices for 16 < M <= 32 that a call brings room for: longer K than 16 chunks (two per wave) in slices of at most
+// 16 chunks; the launch takes as many of them as pay.  0 = no split.
 int64_t stream_split_tiles(int64_t M, int64_t K) {
     if (M <= 16 || M > stream::kTokens) return 0;
     const int64_t TK = tiles_k(K);
@@ -318,21 +318,36 @@ bool launch_gemm_stream(const GemmArgs& a_in, hipStream_t s) {
     if (grid > TP) grid = (int)TP;
     if ((TP + grid - 1) / grid > kMaxPairs) return false;
     // every workgroup reads the codes of 32 tokens over all of K from L2 (K-slices share the
-    // workgroups' pairs, so the split does not change the sum): past about 128 MB of that the
-    // LDS-tiled kernel, whose workgroups share codes across more weight rows, measured faster
-    // (M = 32, K = 28672, N = 7168: 34 us here, 27 us there)
-    if ((int64_t)grid * kTokens * a.K > ((int64_t)1 << 27)) return false;
+    // workgroups' pairs, so the split does not change the sum): past about 256 MB of that the
+    // LDS-tiled kernel, whose workgroups share codes across more weight rows, takes over (24 x 28672 -> 7168, 205 MB, 25.5
+    // us here, 27.9 there; 24 x 24576 -> 10240, 201 MB in rounds of two pairs, 28.6 and 28.4)
+    if ((int64_t)grid * kTokens * a.K > ((int64_t)1 << 28)) return false;
+    // K-slices, of those the workspace has room for: the number that costs least, in us: a round of workgroups (one a
+    // CU) 4.4 + 1.75 for every chunk and pair that a wave walks, the fold of the slices 3 and its sums at 5 TB/s.  The
+    // layer at 24 tokens, in one slice / as many as give a wave two chunks: 16384 -> 4096 16.7 / 15.8, 12800 -> 3200 14.6 / 14.3;
+    // but 22528 -> 5632 21.1 / 27.3, whose 528 workgroups are three rounds.
     int splits = 1;
-    const int64_t per = stream_split_tiles(a.M, a.K);
-    const int64_t nsl = per ? (tiles_k(a.K) + per - 1) / per : 1;
-    const size_t need = (size_t)nsl * (size_t)a.M * (size_t)a.N * 4;
-    if (per && a.split_ws && a.split_ws_bytes >= need && !tuning().mid_nosplit) {
-        splits = (int)nsl;
-        a.tk_pitch = a.tk_pitch ? a.tk_pitch : tiles_k(a.K);
-        a.split_k = per * kChunkK;
+    const int64_t TK = tiles_k(a.K), most = stream_split_tiles(a.M, a.K);
+    if (most && a.split_ws && !tuning().mid_nosplit) {
+        const int64_t n_max = (TK + most - 1) / most, pairs = (TP + grid - 1) / grid;
+        double best_us = 1e30;
+        for (int64_t want = 1; want <= n_max; ++want) {
+            const int64_t per = (TK + want - 1) / want, n = (TK + per - 1) / per, cus = stream_cus();
+            const double bytes = (double)n * (double)a.M * (double)a.N * 4.0;
+            if (n > 1 && bytes > (double)a.split_ws_bytes) break;
+            const double us = (double)((grid * n + cus - 1) / cus) *
+                                  (4.4 + 1.75 * (double)((per + kMaxWaves - 1) / kMaxWaves * pairs)) +
+                              (n > 1 ? 3.0 + bytes * 2.0 / 5e6 : 0.0);
+            if (us < best_us) {
+                best_us = us;
+                splits = (int)n;
+                a.split_k = n > 1 ? per * kChunkK : 0;
+            }
+        }
+        if (splits > 1) a.tk_pitch = a.tk_pitch ? a.tk_pitch : TK;
     }
     // as many waves as give every wave the same number of chunks (14 chunks: 7 waves, not 8)
-    const int64_t TKs = splits > 1 ? per : tiles_k(a.K);
+    const int64_t TKs = splits > 1 ? a.split_k / kChunkK : TK;
     const int64_t rounds = (TKs + kMaxWaves - 1) / kMaxWaves;
     const int W = (int)((TKs + rounds - 1) / rounds);
     const dim3 g((unsigned)grid, (unsigned)splits);

@@ -524,6 +524,21 @@ def test_forward_tokens_in_one_launch(bl, M, K, N, variant, tuning):
         assert np.array_equal(one, two)
 
 
+# 17 to 32 tokens of long rows: one slice of K walked in many steps, two or more where the workgroups are few, a last
+# slice that is shorter, and the most codes the register-streaming kernel takes: the bits of the LDS-tiled kernel.
+@pytest.mark.parametrize("M,K,N", [(17, 8704, 4352), (32, 28672, 7168), (24, 16416, 4100), (31, 40992, 520),
+                                   (20, 32768, 8192), (25, 10240, 10243)])
+def test_17_to_32_tokens_of_long_rows(bl, M, K, N, tuning):
+    print(f"17 to 32 tokens of long rows M={M} K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + K + N)
+    packed, _, beta = bl.bitlinear_pack_weights(torch.randn(N, K, device="cuda", generator=g) * 0.02)
+    X = torch.randn(M, K, device="cuda", generator=g)
+    y = bl.bitlinear_forward(X, packed, N, beta)
+    for spec in ("mid_only=1", "mid_nosplit=1"):
+        tuning(spec)
+        assert torch.equal(bl.bitlinear_forward(X, packed, N, beta), y), spec
+
+
 def test_empty_batch_and_errors(bl):
     W = dev(wl.make_weight(32, 64, 0.02, 1))
     packed, alpha, beta = bl.bitlinear_pack_weights(W)
