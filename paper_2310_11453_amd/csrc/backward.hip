@@ -800,15 +800,18 @@ struct RingPlan {
 
 // Cost in us of a product in slices of `per` of its nst stages on `cus` CUs: a stage of a tile takes `stage` us on a
 // CU, an item `item` us besides (two workgroups of a CU take the time of both), and the fp32 sums of a slice
-// (`bytes`) are written and read at 5 TB/s by a second launch of 4 us.
+// (`bytes`) are written and read at `rate` MB/us by a second launch of `fold` us.  Fitted: over 78 shapes of 256 to 5000
+// tokens (K and N of 1024 to 16384) dX's plan is 1.2 % slower than the best tile and slices on average (with 0.345, 4.5, 4 and
+// 5 for the smaller tile 2.2 %).
 struct RingCost {
-    double stage, item;
+    double stage, item, fold, rate;
 };
-constexpr RingCost kWideCost{0.6, 7.0};    // 256 x 256
-constexpr RingCost kRowsCost{0.345, 4.5};  // 128 x 256 (dX)
+constexpr RingCost kWideCost{0.6, 7.0, 4.0, 5.0};   // 256 x 256
+constexpr RingCost kRowsCost{0.33, 4.5, 3.0, 8.0};  // 128 x 256 (dX)
 static double ring_cost(RingCost c, int64_t tiles, int64_t nst, int64_t per, double bytes, int64_t cus) {
     const int64_t n = (nst + per - 1) / per, rounds = (tiles * n + cus - 1) / cus;
-    return (double)rounds * (c.stage * (double)per + c.item) + (n > 1 ? 4.0 + (double)n * bytes * 2.0 / 5e6 : 0.0);
+    return (double)rounds * (c.stage * (double)per + c.item) +
+           (n > 1 ? c.fold + (double)n * bytes * 2e-6 / c.rate : 0.0);
 }
 // The slices that cost least.  dX^ of M = 1000, N = 8192, K = 2048 (64 tiles of 128 x 256 and 256 stages): whole call
 // 98.9 us in one slice, 66.9 in two, 53.0 in four, 66.6 in eight (62.8 in six slices of 32 tiles of 256 x 256).
@@ -890,7 +893,7 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
 // larger ones are too few for the CUs, or in so many slices that their sums cost what the product does.
 // The whole call, M x K x N, us, 256 / 128 rows: 1 x 4096 x 16384 47.0 / 36.5, 500 x 4096 x 4096 45.1 / 37.6, 1000 x 2048 x
 // 8192 63.8 / 54.7, 2048 x 4096 x 4096 91.3 / 76.7, 4000 x 2048 x 8192 166 / 153, 8192 x 1024 x 4096 118 / 97; but 1700 x
-// 2560 x 7680 98.5 / 110, 1000 x 4096 x 16384 151 / 155 (costs within 5 %) and 8192 x 4096 x 16384 901 / 923.
+// 2560 x 7680 98.5 / 110 and 8192 x 4096 x 16384 901 / 923; 1000 x 4096 x 16384, 145 / 147, goes the wrong way.
 static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
     const RingPlan wide = ring_plan(I, J, Rp, 256, 256), rows = ring_plan(I, J, Rp, 128, 256);
     if (const int force = tuning().bwd_dx) return force == 2 ? rows : wide;
@@ -898,7 +901,7 @@ static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
     const double bytes = (double)I * (double)J * 4.0;
     if (wide.grid == 0) return wide;
     return ring_cost(kRowsCost, (int64_t)rows.gi * rows.gj, nst, rows.sl.per, bytes, cus) <
-                   0.95 * ring_cost(kWideCost, (int64_t)wide.gi * wide.gj, nst, wide.sl.per, bytes, cus)
+                   ring_cost(kWideCost, (int64_t)wide.gi * wide.gj, nst, wide.sl.per, bytes, cus)
                ? rows
                : wide;
 }
@@ -925,7 +928,7 @@ static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int64_t full = ntiles / (2 * cus), rest = ntiles % (2 * cus);
     const int64_t most = full < 4 ? 44 : full < 9 ? 32 : 16;  // stages
     if (full >= 2 && (nst > most || J * Rp * 2 > 12000000)) return p;
-    const double wide = ring_cost(p.sl.splits > 1 ? kWideCost : RingCost{0.68, 12.8}, (int64_t)p.gi * p.gj, nst, p.sl.per,
+    const double wide = ring_cost(p.sl.splits > 1 ? kWideCost : RingCost{0.68, 12.8, 4.0, 5.0}, (int64_t)p.gi * p.gj, nst, p.sl.per,
                                   (double)I * (double)J * 4.0, cus);
     const double two = 4.9 + 0.39 * (double)nst, one = 3.6 + 0.226 * (double)nst;
     const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);
