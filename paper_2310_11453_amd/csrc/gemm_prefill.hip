@@ -859,7 +859,8 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 //   a round of 256 x 256 tiles   14 + 0.62 n     (n = 32: 33, 64: 51 to 58, 112: 82, 256: 158)
 //   a round of 128 x 128 tiles    5 + 3.0 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 16: 53)
 //   a round of 64 x 128 tiles   4.5 + 3.1 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 14: 46)
-//   the last two in three rounds and more 5 % more (the large tiles read the operands less often)
+//   the last two in three rounds and more 5 % more (the large tiles read the operands less often), and 1.2 c more where
+//   the codes are more than 40 MB (out of the caches: three rounds of 4096 x 28672 -> 6144 in 128 x 128 tiles 378 us)
 //   slices of K                   4 + the int32 sums written and read at 5 TB/s
 // The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
 // ones win; the layer, us, M x K x N: 333 x 2048 x 2048 12.8 (64 x 128) against 19.4 (128 x 256), 700 x 4096 x 16384
@@ -898,7 +899,8 @@ static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
             if (n > 1 && ((n != want && !force_n) || bytes > (double)ws_bytes)) continue;
             const int64_t rounds = (tiles * n + cus - 1) / cus;
             const double c = (double)((per + kg - 1) / kg);
-            offer(tile, per, (double)rounds * (tile == 3 ? 5.0 + 3.0 * c : 4.5 + 3.1 * c) * (rounds > 2 ? 1.05 : 1.0) +
+            const double chunk = (tile == 3 ? 3.0 : 3.1) + (M * K > (int64_t)40 << 20 ? 1.2 : 0.0);
+            offer(tile, per, (double)rounds * ((tile == 3 ? 5.0 : 4.5) + chunk * c) * (rounds > 2 ? 1.05 : 1.0) +
                                  (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0));
         }
     }
