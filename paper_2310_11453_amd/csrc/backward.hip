@@ -138,9 +138,9 @@ __device__ inline void bits_transpose_tile(const uint32_t* __restrict__ packed, 
 
 // All of it in one launch: 64 x 64 tiles of dY, of the codes, and 32 x 512 pieces of the sign matrix are the items of
 // one grid.  Each part alone is HBM-bound when large, but at a thousand tokens the two small ones are launches of
-// latency (whole call, us, three launches / one, M x N x K: 256 x 1024 x 1024 32.0 / 26.5, 333 x 2048 x 2048 40.5 / 36.0,
-// 1000 x 8192 x 2048 108.9 / 104.2; 8192 x 16384 x 4096 1752 / 1752).  The small parts come first: behind dY they
-// would be the tail.
+// latency (whole call, us, three launches / one, M x N x K: 256 x 1024 x 1024 32.0 / 26.5, 333 x 2048 x 2048 40.5 /
+// 36.0, 1000 x 8192 x 2048 108.9 / 104.2; 8192 x 16384 x 4096 1752 / 1752).  The small parts come first: behind dY
+// they would be the tail.
 struct PrepareArgs {
     const float* dY;
     const int8_t* codes;
@@ -499,10 +499,9 @@ __global__ __launch_bounds__(256, T == 256 ? 1 : 2) void gemm_tn_bf16_wide(const
 // that the words of stage st+1 can be read while stage st is being multiplied.  A lane turns its
 // word into the four dwords of an MFMA operand (eight +-1 bf16 values) with a shift and an
 // and-or each, placed between the MFMAs of the half-step before (the same scheduling as in the
-// forward GEMM).  BM = 256: waves of 128 x 64, one workgroup per CU; BM = 128 (few tiles, dx_plan): waves of 64 x 64, two
-// workgroups per CU.  Group of DMA operations of stage s: the words of stage s+1, then A of stage s;
-// they complete in this order, so the hand-counted waits are those of the kernel above with one
-// more operation per stage.
+// forward GEMM).  BM = 256: waves of 128 x 64, one workgroup per CU; BM = 128 (few tiles, dx_plan): waves of 64 x 64,
+// two workgroups per CU.  Group of DMA operations of stage s: the words of stage s+1, then A of stage s; they complete
+// in this order, so the hand-counted waits are those of the kernel above with one more operation per stage.
 __device__ inline void a_issue(v4i (&a)[4], uint32_t ad) {
     asm volatile(
         "ds_read_b128 %0, %4\n\t"
@@ -800,9 +799,9 @@ struct RingPlan {
 
 // Cost in us of a product in slices of `per` of its nst stages on `cus` CUs: a stage of a tile takes `stage` us on a
 // CU, an item `item` us besides (two workgroups of a CU take the time of both), and the fp32 sums of a slice
-// (`bytes`) are written and read at `rate` MB/us by a second launch of `fold` us.  Fitted: over 78 shapes of 256 to 5000
-// tokens (K and N of 1024 to 16384) dX's plan is 1.2 % slower than the best tile and slices on average (with 0.345, 4.5, 4 and
-// 5 for the smaller tile 2.2 %).
+// (`bytes`) are written and read at `rate` MB/us by a second launch of `fold` us.  Fitted: over 78 shapes of 256 to
+// 5000 tokens (K and N of 1024 to 16384) dX's plan is 1.2 % slower than the best tile and slices on average (with
+// 0.345, 4.5, 4 and 5 for the smaller tile 2.2 %).
 struct RingCost {
     double stage, item, fold, rate;
 };
@@ -888,12 +887,12 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
             part, p.sl.splits, count, scale_ptr, scale_mul, C);
 }
 
-// dX's plan: 256 x 256 tiles, or 128 x 256 where they cost less.  A stage of the smaller tile takes more than half of the
-// larger one's time (its waves read and expand the same signs for half the rows), but with few tokens the
-// larger ones are too few for the CUs, or in so many slices that their sums cost what the product does.
-// The whole call, M x K x N, us, 256 / 128 rows: 1 x 4096 x 16384 47.0 / 36.5, 500 x 4096 x 4096 45.1 / 37.6, 1000 x 2048 x
-// 8192 63.8 / 54.7, 2048 x 4096 x 4096 91.3 / 76.7, 4000 x 2048 x 8192 166 / 153, 8192 x 1024 x 4096 118 / 97; but 1700 x
-// 2560 x 7680 98.5 / 110 and 8192 x 4096 x 16384 901 / 923; 1000 x 4096 x 16384, 145 / 147, goes the wrong way.
+// dX's plan: 256 x 256 tiles, or 128 x 256 where they cost less.  A stage of the smaller tile takes more than half of
+// the larger one's time (its waves read and expand the same signs for half the rows), but with few tokens the larger
+// ones are too few for the CUs, or in so many slices that their sums cost what the product does. The whole call, M x K
+// x N, us, 256 / 128 rows: 1 x 4096 x 16384 47.0 / 36.5, 500 x 4096 x 4096 45.1 / 37.6, 1000 x 2048 x 8192 63.8 /
+// 54.7, 2048 x 4096 x 4096 91.3 / 76.7, 4000 x 2048 x 8192 166 / 153, 8192 x 1024 x 4096 118 / 97; but 1700 x 2560 x
+// 7680 98.5 / 110 and 8192 x 4096 x 16384 901 / 923; 1000 x 4096 x 16384, 145 / 147, goes the wrong way.
 static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
     const RingPlan wide = ring_plan(I, J, Rp, 256, 256), rows = ring_plan(I, J, Rp, 128, 256);
     if (const int force = tuning().bwd_dx) return force == 2 ? rows : wide;
@@ -914,11 +913,11 @@ static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
 //   of 128 x 128, two per CU                      4.9 + 0.39
 // (fitted to 82 shapes of 64 to 2000 tokens; a sliced product of 256 x 256 tiles is cheaper, kWideCost).  From two full
 // rounds on the second reading of the operands decides: beyond so many stages, or with a B operand well beyond an
-// XCD's 4 MB of L2, the large tile it is.  The whole call (M x N x K, with the operand copies), 256 against 128, us: 64 x
-// 2048 x 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048 37.6 / 32.8, 1300 x 8192 x
-// 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x 16384 x 4096 120.9 / 108.5, 1600 x 16384 x
-// 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 / 331, 2000 x 21504 x 7168 647 / 811; in slices 3300 x 4224 x
-// 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
+// XCD's 4 MB of L2, the large tile it is.  The whole call (M x N x K, with the operand copies), 256 against 128, us:
+// 64 x 2048 x 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048 37.6 /
+// 32.8, 1300 x 8192 x 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x 16384 x
+// 4096 120.9 / 108.5, 1600 x 16384 x 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 / 331,
+// 2000 x 21504 x 7168 647 / 811; in slices 3300 x 4224 x 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
 static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int force = tuning().bwd_ring;
     if (force == 2) return ring_plan(I, J, Rp, 128, 128);
@@ -928,7 +927,8 @@ static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int64_t full = ntiles / (2 * cus), rest = ntiles % (2 * cus);
     const int64_t most = full < 4 ? 44 : full < 9 ? 32 : 16;  // stages
     if (full >= 2 && (nst > most || J * Rp * 2 > 12000000)) return p;
-    const double wide = ring_cost(p.sl.splits > 1 ? kWideCost : RingCost{0.68, 12.8, 4.0, 5.0}, (int64_t)p.gi * p.gj, nst, p.sl.per,
+    const RingCost uncut{0.68, 12.8, 4.0, 5.0};
+    const double wide = ring_cost(p.sl.splits > 1 ? kWideCost : uncut, (int64_t)p.gi * p.gj, nst, p.sl.per,
                                   (double)I * (double)J * 4.0, cus);
     const double two = 4.9 + 0.39 * (double)nst, one = 3.6 + 0.226 * (double)nst;
     const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);

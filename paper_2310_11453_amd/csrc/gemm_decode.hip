@@ -11,8 +11,8 @@
 //   sum_k q s = 2 * sum_k q b - sum_k q,        s = 2 b - 1
 // with sum_k q taken from the quantiser's row sums.
 //
-// Four accumulators rather than eight, 32-bit scalars ahead of the first load and the epilogue's operands behind the last
-// one (a wave issues one instruction in four cycles, and these launches are short): us a launch, before / now, 8
+// Four accumulators rather than eight, 32-bit scalars ahead of the first load and the epilogue's operands behind the
+// last one (a wave issues one instruction in four cycles, and these launches are short): us a launch, before / now, 8
 // tokens 2048 -> 8192 3.6 / 3.3, 4096 -> 16384 4.9 / 4.75, 7168 -> 28672 8.5 / 8.4, 16 tokens 9.65 / 9.15.
 //
 // Work split: a workgroup owns up to T consecutive 16-row weight tiles and all of K;
@@ -123,9 +123,10 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // wave's own part of `red`, which holds nothing before the wave's first tile is done, eight rows at a time, and
         // read from there in operand layout.  A row is 1 KiB, so the same 16 bytes of every row would share their
         // banks: the 16-byte slots of row r are stored at slot ^ r.  us a launch, from memory in operand layout
-        // (unless the part of `red` that the sums need held the rows) / now: 8 tokens 4096 -> 4096 3.95 / 3.2, 7168 -> 7168
-        // 5.4 / 4.5, 8192 -> 2048 5.0 / 3.8, 16 tokens 8192 -> 2048 6.3 / 4.55, 7168 -> 7168 6.4 / 5.3, 16384 -> 4096
-        // 10.2 / 6.85.  A single chunk of K is read in place: parking is a longer chain then (16 x 256 -> 512 2.8, 2.45).
+        // (unless the part of `red` that the sums need held the rows) / now: 8 tokens 4096 -> 4096 3.95 / 3.2, 7168 ->
+        // 7168 5.4 / 4.5, 8192 -> 2048 5.0 / 3.8, 16 tokens 8192 -> 2048 6.3 / 4.55, 7168 -> 7168 6.4 / 5.3, 16384 ->
+        // 4096 10.2 / 6.85.  A single chunk of K is read in place: parking is a longer chain then (16 x 256 -> 512
+        // 2.8, 2.45).
         const bool stage_lane = l < C * 32;
         constexpr int kHeld = MAXT == 512 ? 16 : kStageRows;  // rows in registers; 16 waves have room for eight
         v4i rowv[kHeld];

@@ -78,8 +78,8 @@ __device__ inline void lds_wait(v4i (&a)[2]) {
 
 // What the kernel wants to know, in 32 bits and with what a division needs worked out by the host: ahead of a launch's
 // first request stood 330 instructions, 64-bit products and divisions most of them, and five waits for arguments.
-// us a launch, before / now: 64 x 2048 -> 2048 7.7 / 7.3, 64 x 4096 -> 16384 11.5 / 10.9, 64 x 7168 -> 7168 15.5 / 15.1,
-// 333 x 2048 -> 2048 8.1 / 7.6, 333 x 8192 -> 2048 16.0 / 15.4.
+// us a launch, before / now: 64 x 2048 -> 2048 7.7 / 7.3, 64 x 4096 -> 16384 11.5 / 10.9, 64 x 7168 -> 7168 15.5 /
+// 15.1, 333 x 2048 -> 2048 8.1 / 7.6, 333 x 8192 -> 2048 16.0 / 15.4.
 struct Args {
     const int8_t* codes;
     const uint32_t* packed;

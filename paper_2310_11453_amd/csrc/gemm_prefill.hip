@@ -542,14 +542,15 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prefill_kernel(GemmArgs 
 // stages and the bits of two chunks, five or more when an item has two stages or more (nst).  One wait for
 // all but the last five covers all three; items of one stage wait for everything.
 //
-// The fold is vector instructions that all waves issue at once while the matrix pipe stands still, two waves a SIMD and four
-// cycles each, beside 112 MFMAs of 32 cycles in an item of 14 stages.  So what can be is in the MFMAs: a set bit is a byte of 2
-// and an item's first half-step adds to the negated row sums instead of to zeros, and the accumulators are sum_k q s
-// as they are; left are conversion, product of the scales, product and addition, 320 instructions of 450 a wave.  us of the
-// layer, before / after: 1000 x 7168 x 28672 in 8 x 8 groups 238.6 / 224.5, 4096 x 7168 x 7168 in 2 x 8 265 / 249, 3000 x 2048 x
-// 8192 in 8 x 8 106.7 / 92.0, 4096 x 1024 x 4096 in 1 x 8 71.8 / 58.2.  (The scales' products from a 32 x 32 x 2 f32 MFMA, 64
-// vector instructions fewer, are 1 to 6 % slower; bytes of {0, -128} are no faster; with the ring drained and filled for
-// every item and the scales loaded behind it the first of these took 445 us.)
+// The fold is vector instructions that all waves issue at once while the matrix pipe stands still, two waves a SIMD
+// and four cycles each, beside 112 MFMAs of 32 cycles in an item of 14 stages.  So what can be is in the MFMAs: a set
+// bit is a byte of 2 and an item's first half-step adds to the negated row sums instead of to zeros, and the
+// accumulators are sum_k q s as they are; left are conversion, product of the scales, product and addition, 320
+// instructions of 450 a wave.  us of the layer, before / after: 1000 x 7168 x 28672 in 8 x 8 groups 238.6 / 224.5,
+// 4096 x 7168 x 7168 in 2 x 8 265 / 249, 3000 x 2048 x 8192 in 8 x 8 106.7 / 92.0, 4096 x 1024 x 4096 in 1 x 8 71.8 /
+// 58.2.  (The scales' products from a 32 x 32 x 2 f32 MFMA, 64 vector instructions fewer, are 1 to 6 % slower; bytes
+// of {0, -128} are no faster; with the ring drained and filled for every item and the scales loaded behind it the
+// first of these took 445 us.)
 template <bool ETA>
 __global__ __launch_bounds__(512, 2) void gemm_group_kernel(GemmArgs a, int grid_m, int grid_n) {
     constexpr int BM = 128, BN = 256, WN = 4, NS = 8, THREADS = 512, NWAVES = 8;
@@ -865,8 +866,9 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 // The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
 // ones win; the layer, us, M x K x N: 333 x 2048 x 2048 12.8 (64 x 128) against 19.4 (128 x 256), 700 x 4096 x 16384
 // 60.5 (128 x 128) against 64.0 (128 x 256 and 256 x 256), 700 x 28672 x 7168 161.5 (64 x 128) against 186.1.  Over 171
-// shapes of 80 to 2200 tokens, K and N of 1024 to 28672, the plan is 0.3 % slower than the best of all these on average,
-// 4 % at most (2200 x 3200 x 9600 89.8, 86.4 as 128 x 256); with 8 + 0.37 n, 3.5 + 4.2 c and 6.5 it was 1.0 and 17 %.
+// shapes of 80 to 2200 tokens, K and N of 1024 to 28672, the plan is 0.3 % slower than the best of all these on
+// average, 4 % at most (2200 x 3200 x 9600 89.8, 86.4 as 128 x 256); with 8 + 0.37 n, 3.5 + 4.2 c and 6.5 it was 1.0
+// and 17 %.
 struct TilePlan {
     int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
     int64_t per;  // 512-chunks of K per slice (3 and 4)

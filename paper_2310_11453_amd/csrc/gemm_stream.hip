@@ -319,13 +319,13 @@ bool launch_gemm_stream(const GemmArgs& a_in, hipStream_t s) {
     if ((TP + grid - 1) / grid > kMaxPairs) return false;
     // every workgroup reads the codes of 32 tokens over all of K from L2 (K-slices share the
     // workgroups' pairs, so the split does not change the sum): past about 256 MB of that the
-    // LDS-tiled kernel, whose workgroups share codes across more weight rows, takes over (24 x 28672 -> 7168, 205 MB, 25.5
-    // us here, 27.9 there; 24 x 24576 -> 10240, 201 MB in rounds of two pairs, 28.6 and 28.4)
+    // LDS-tiled kernel, whose workgroups share codes across more weight rows, takes over (24 x 28672 -> 7168, 205 MB,
+    // 25.5 us here, 27.9 there; 24 x 24576 -> 10240, 201 MB in rounds of two pairs, 28.6 and 28.4)
     if ((int64_t)grid * kTokens * a.K > ((int64_t)1 << 28)) return false;
     // K-slices, of those the workspace has room for: the number that costs least, in us: a round of workgroups (one a
     // CU) 4.4 + 1.75 for every chunk and pair that a wave walks, the fold of the slices 3 and its sums at 5 TB/s.  The
-    // layer at 24 tokens, in one slice / as many as give a wave two chunks: 16384 -> 4096 16.7 / 15.8, 12800 -> 3200 14.6 / 14.3;
-    // but 22528 -> 5632 21.1 / 27.3, whose 528 workgroups are three rounds.
+    // layer at 24 tokens, in one slice / as many as give a wave two chunks: 16384 -> 4096 16.7 / 15.8, 12800 -> 3200
+    // 14.6 / 14.3; but 22528 -> 5632 21.1 / 27.3, whose 528 workgroups are three rounds.
     int splits = 1;
     const int64_t TK = tiles_k(a.K), most = stream_split_tiles(a.M, a.K);
     if (most && a.split_ws && !tuning().mid_nosplit) {

@@ -1,19 +1,19 @@
 // One to eight tokens of a short row in one launch: LayerNorm (Eq. 12), the 8-bit absmax quantiser (Eq. 4-5) and the
 // 1-bit x 8-bit product with its dequantisation (Eq. 7, Eq. 11) of arXiv 2310.11453, gamma per token.
 //
-// What bounds the layer at these sizes is launches and their dependent chains, not bytes: a graph node costs 1.6 us when it
-// is empty, the stand-alone quantiser of such a batch 3 us more, and its work (a few thousand elements) can be repeated
-// by every workgroup while the workgroup's weight tiles are on their way.  So each workgroup loads all rows (M * K * 4
-// bytes, out of L2), requests its tiles behind them (loads return in order), quantises the rows into LDS and multiplies.
-// With one or two waves a SIMD the chain's length is the number of instructions of a wave, each four cycles whatever
-// its kind: scalars come from the host in 32 bits, the row is requested before anything else is worked out, and
-// the bit planes of a tile meet in four accumulators instead of eight.
-// Two and more rows are split over waves exactly as the stand-alone quantiser splits them (quant_shape) and every sum runs
-// in its order, so codes, gamma and row sums are the same bits as in two launches.
-// us a launch in a graph of such layers, K -> N, one token (the 1300 to 2600 instructions of the small-batch
-// kernel with a quantiser in it / here) and two tokens (two launches / here): 2048 -> 2048 3.8 / 3.1 and 6.1 / 3.3, 2048 ->
-// 8192 4.1 / 3.3 and 6.4 / 3.6, 8192 -> 2048 5.7 / 4.3 and 8.9 / 6.4, 4096 -> 16384 5.6 / 4.8 and 8.7 / 6.1, 7168 -> 28672
-// 12.0 / 10.8, 28672 -> 7168 16.8 / 15.1; eight tokens of 256 -> 512 5.1 / 2.8.
+// What bounds the layer at these sizes is launches and their dependent chains, not bytes: a graph node costs 1.6 us
+// when it is empty, the stand-alone quantiser of such a batch 3 us more, and its work (a few thousand elements) can be
+// repeated by every workgroup while the workgroup's weight tiles are on their way.  So each workgroup loads all rows
+// (M * K * 4 bytes, out of L2), requests its tiles behind them (loads return in order), quantises the rows into LDS
+// and multiplies. With one or two waves a SIMD the chain's length is the number of instructions of a wave, each four
+// cycles whatever its kind: scalars come from the host in 32 bits, the row is requested before anything else is worked
+// out, and the bit planes of a tile meet in four accumulators instead of eight. Two and more rows are split over waves
+// exactly as the stand-alone quantiser splits them (quant_shape) and every sum runs in its order, so codes, gamma and
+// row sums are the same bits as in two launches. us a launch in a graph of such layers, K -> N, one token (the 1300 to
+// 2600 instructions of the small-batch kernel with a quantiser in it / here) and two tokens (two launches / here):
+// 2048 -> 2048 3.8 / 3.1 and 6.1 / 3.3, 2048 -> 8192 4.1 / 3.3 and 6.4 / 3.6, 8192 -> 2048 5.7 / 4.3 and 8.9 / 6.4,
+// 4096 -> 16384 5.6 / 4.8 and 8.7 / 6.1, 7168 -> 28672 12.0 / 10.8, 28672 -> 7168 16.8 / 15.1; eight tokens of 256 ->
+// 512 5.1 / 2.8.
 #include "common.h"
 #include "kernels.h"
 #include "rowops.h"
@@ -80,8 +80,8 @@ __global__ __launch_bounds__(kTokWaves* kWave) void gemm_tokens_kernel(TokArgs a
         }
         first[p] = *reinterpret_cast<const float*>(x);
     }
-    // the tiles behind them, without a branch (behind one, the row's arithmetic would wait for them too): a chunk past the
-    // end of K is the last one again, masked below, a tile past the workgroup's last one that one, never stored
+    // the tiles behind them, without a branch (behind one, the row's arithmetic would wait for them too): a chunk past
+    // the end of K is the last one again, masked below, a tile past the workgroup's last one that one, never stored
     const int slots = 1 << a.slot_shift, slot = w & (slots - 1), set = w >> a.slot_shift, sets = kTokWaves >> a.slot_shift;
     const int tk0 = slot * C, TK = (int)a.TK;
     const int tn0 = (int)(blockIdx.x * a.tpb), tn_end = tn0 + (int)a.tpb - 1;
@@ -237,8 +237,8 @@ __global__ __launch_bounds__(kTokWaves* kWave) void gemm_tokens_kernel(TokArgs a
     const int m = l & 15, g = l >> 4;
     const int mr = m < (int)a.M ? m : (int)a.M - 1;
 
-    // ---- the product.  A bit plane of a tile is one AND, {0, 2^i} bytes; planes i and i + 4 of the tile and of the tile
-    // shifted by 4 meet in one accumulator: 8 sum_k q b = 8 acc_0 + 4 acc_1 + 2 acc_2 + acc_3
+    // ---- the product.  A bit plane of a tile is one AND, {0, 2^i} bytes; planes i and i + 4 of the tile and of the
+    // tile shifted by 4 meet in one accumulator: 8 sum_k q b = 8 acc_0 + 4 acc_1 + 2 acc_2 + acc_3
     if (multiplies) {
         v4i act[kActRegs ? C : 1][8];
         auto load_act = [&](int c, v4i(&x)[8], int offset) {
@@ -347,8 +347,8 @@ bool tokens_plan(int64_t M, int64_t K, int64_t N, TokensPlan& p) {
     p.tpb = (int)tpb;
     p.T = (int)((tpb + sets - 1) / sets);
     // Every workgroup repeats the quantiser, so it pays only while one round of workgroups covers N, and while a
-    // wave has one or two pairs: each costs 0.7 to 1 us (8 x 1024 -> 1024 with two 4.3 us, 6.0 in two launches; 8 x 2048
-    // -> 2048 with four 7.0 and 6.4, 4 x 4096 -> 4096 with four 6.95 and 6.9).
+    // wave has one or two pairs: each costs 0.7 to 1 us (8 x 1024 -> 1024 with two 4.3 us, 6.0 in two launches; 8 x
+    // 2048 -> 2048 with four 7.0 and 6.4, 4 x 4096 -> 4096 with four 6.95 and 6.9).
     const int most = p.C == 4 ? 2 : p.C == 8 ? 3 : p.P > 1 || p.NV != 2 * p.C ? 4 : 8;
     return p.wpr <= kTokWaves && p.P <= 2 && p.P * p.NV <= (M == 1 ? 16 : 8) && p.T <= most &&
            M * TK * kChunkK <= (p.C < 8 ? kTokCodes : 32768);

@@ -400,9 +400,9 @@ hipError_t launch_ln_backward(const LnBackwardArgs& a, float* dgain, float* dbia
 #undef BL_LNB_CASE
         return true;
     };
-    // The column sums read the rows' statistics, x and g.  The pass that writes dX leaves the statistics too, so it goes
-    // first and they need no launch of their own, unless dX lies on x or g: then statistics, sums, dX.
-    // us of the call with dgain and dbias, statistics in a launch of their own / with dX: 256 x 1024 12.5 / 9.9, 1000 x 2048
+    // The column sums read the rows' statistics, x and g.  The pass that writes dX leaves the statistics too, so it
+    // goes first and they need no launch of their own, unless dX lies on x or g: then statistics, sums, dX. us of the
+    // call with dgain and dbias, statistics in a launch of their own / with dX: 256 x 1024 12.5 / 9.9, 1000 x 2048
     // 18.4 / 15.1, 3000 x 4096 60.3 / 44.4, 8192 x 4096 157 / 117.
     auto apart = [&](const float* v) {
         const uintptr_t p = (uintptr_t)v, d = (uintptr_t)a.dX, bytes = (uintptr_t)(a.M * a.K) * sizeof(float);

@@ -36,8 +36,8 @@ __device__ inline void offer_extremes(const QuantArgs& a, int g, float lo, float
         atomicMax(a.gmax_bits + g, kh);
 }
 
-// A batch of a few rows is the length of one row's instruction stream (a wave issues one in four cycles, 2.5 ns in a graph
-// of short launches): the row's address is scalar, whole pieces of it go without masks, gain, bias and the shift
+// A batch of a few rows is the length of one row's instruction stream (a wave issues one in four cycles, 2.5 ns in a
+// graph of short launches): the row's address is scalar, whole pieces of it go without masks, gain, bias and the shift
 // of Eq. 6 stand behind one branch each.  us in a layer's two launches, with these in every element's path and the
 // address in 64-bit vector arithmetic / now: 8 x 7168 4.2 / 3.4, 8 x 28672 7.7 / 6.7, 16 x 2048 3.4 / 3.2.
 // WPR waves share one token (row); a lane holds NV float4 of it.  Workgroups have at least
