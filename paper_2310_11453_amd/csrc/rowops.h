@@ -111,7 +111,8 @@ __device__ inline void stats_add(RowStats& st, const float4& v, double c, double
         : "+v"(st.nmn) : "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
 }
 // The wave's totals with the even lanes carrying the sum and the maximum, the odd ones the sum of squares and the
-// negated minimum: two reductions instead of four.
+// negated minimum: two reductions instead of four.  All even lanes hold the same bits, and all odd ones: each step adds
+// two values that the two lanes meet in either order.
 struct PairStats {
     double k;
     float f;
@@ -129,8 +130,8 @@ __device__ inline PairStats stats_wave(const RowStats& st) {
     p.k = (odd ? st.q : st.s) + dpp_mov<kXor1>(odd ? st.s : st.q);
     p.f = max_raw(odd ? st.nmn : st.mx, dpp_mov<kXor1>(odd ? st.mx : st.nmn));
     pair_step<kXor2>(p);
+    pair_step<kRor8>(p);  // (quads j and j + 2 hold the same bits now, so that the next sum is commuted, not reordered)
     pair_step<kRor4>(p);
-    pair_step<kRor8>(p);
     double lo, hi;
     float flo, fhi;
     lane_swap<false>(p.k, lo, hi);
@@ -156,8 +157,8 @@ __device__ inline PairStats stats_fold(const double* k, const float* f, int part
     const int i = threadIdx.x & (2 * parts - 1);
     PairStats p{k[i], f[i]};
     pair_step<kXor2>(p);
-    if (parts > 2) pair_step<kRor4>(p);
     if (parts > 4) pair_step<kRor8>(p);
+    if (parts > 2) pair_step<kRor4>(p);
     if (parts > 8) {
         double lo, hi;
         float flo, fhi;

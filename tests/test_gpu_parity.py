@@ -524,6 +524,32 @@ def test_forward_tokens_in_one_launch(bl, M, K, N, variant, tuning):
         assert np.array_equal(one, two)
 
 
+# Equal elements of a row have equal x^, whichever lane holds them: the row's mean and 1 / sigma are the same bits in all
+# lanes.  Half of each row is zero and the rest sums to zero, so that x^ of a zero, c / sigma - c / sigma, is nothing but
+# the rounding of that product: the last bit of 1 / sigma decides all of it.  One wave a row to 16, the one-launch kernel too.
+@pytest.mark.parametrize("M,K", [(16, 256), (16, 512), (16, 1024), (16, 2048), (16, 4096), (9, 6144), (16, 32768),
+                                 (1, 512), (1, 1024), (1, 2048), (1, 8192), (1, 28672)])
+def test_row_statistics_are_the_same_in_every_lane(bl, M, K):
+    for seed in range(16 // M):
+        rng = np.random.default_rng(K + seed)
+        X = np.zeros((M, K), f32)
+        for row in X:
+            v = rng.standard_normal(K // 4).astype(f32)
+            row[:K // 2] = np.concatenate([v, -v])
+            row[1:] = rng.permutation(row[1:])  # the first element, not a zero, is what the sums are taken about
+        if M == 1:
+            packed, _, beta = bl.bitlinear_pack_weights(dev(wl.make_weight(16, K, 0.02, 1)))
+            ws = torch.zeros(bl.workspace_bytes(bl.OP_FORWARD, 1, 16, K), dtype=torch.uint8, device="cuda")
+            bl.bitlinear_forward(dev(X), packed, 16, beta, ln_eps=0.0, workspace=ws)
+            at = bl.forward_workspace_layout(1, 16, K)["xhat"]
+            xhat = host(ws[at:at + 4 * K]).view(f32).reshape(1, K)
+        else:
+            xhat = host(bl.bitlinear_quant_act(dev(X), ln_eps=0.0, want_xhat=True)[3])
+        for m in range(M):
+            zeros = xhat[m][X[m] == 0]
+            assert len(zeros) >= K // 2 and len(np.unique(zeros.view(np.uint32))) == 1, (seed, m, np.unique(zeros))
+
+
 # 17 to 32 tokens of long rows: one slice of K walked in many steps, two or more where the workgroups are few, a last
 # slice that is shorter, and the most codes the register-streaming kernel takes: the bits of the LDS-tiled kernel.
 @pytest.mark.parametrize("M,K,N", [(17, 8704, 4352), (32, 28672, 7168), (24, 16416, 4100), (31, 40992, 520),
