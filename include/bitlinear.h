@@ -237,8 +237,8 @@ int bitlinear_backward_ste(const float* dY, int64_t M, int64_t N, int64_t K, con
  *   Y[m,n] = acc[m,n] * (beta * gamma_m / 128) + (beta * eta_m) * wsum[n],
  *   wsum[n] = sum_k W~[n,k]   (bitlinear_weight_rowsums, once per weight).
  * Per token or per tensor (one eta and one gamma for the whole tensor: the training-time
- * granularity of the paragraph after Eq. 6; the running minimum and maximum are integer
- * atomics on an order-preserving key, exact and order-free).
+ * granularity of the paragraph after Eq. 6; the minimum and maximum are taken over
+ * order-preserving integer keys, exact and order-free).
  *   eta   out/in  fp32 [M] (per token) or [1] (per tensor), like gamma
  *   wsum  out/in  int32 [N];   the rest as in the functions above.
  * bitlinear_quant_act_nonneg needs a workspace only per tensor

@@ -90,7 +90,7 @@ QuantWs quant_ws(int64_t M, int granularity) {
     size_t off = 0;
     w.rowstats = off;
     off += granularity == BL_GAMMA_PER_TENSOR ? align256((size_t)M * 16) : 0;
-    w.gmax = off;  // running maxima [kMaxGroups], then (Eq. 6 per tensor) running minima [kMaxGroups]
+    w.gmax = off;  // maxima [kMaxGroups], then (Eq. 6 per tensor) minima [kMaxGroups]
     off += 512;
     w.total = off;
     return w;
@@ -416,8 +416,7 @@ int bitlinear_forward_static(const float* X, int64_t M, int64_t K, const void* p
     if (!X || !packed || !beta || !Y) return BL_ERR_NULL;
     void* ws = scratch_address();
     if (!ws) return BL_ERR_HIP;
-    // nothing in the workspace has to start at zero: the kernels write every byte they later
-    // read (the running maximum of a per-tensor gamma is cleared by a fill kernel of its own)
+    // nothing in the workspace has to start at zero: the kernels write every byte they later read
     return bitlinear_forward(X, M, K, packed, N, beta, ln_gain, ln_bias, ln_eps, granularity, flags,
                              Y, ws, kScratchBytes, stream);
 }

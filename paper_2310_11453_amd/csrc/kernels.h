@@ -62,9 +62,9 @@ struct QuantArgs {
     int32_t* rowsum;
     float* xhat_dump;
     double* rowstats;   // per-tensor only: [M][2] = (mean, rstd)
-    uint32_t* gmax_bits; // per-tensor only: [groups], bit pattern of the running max
-    uint32_t* gmin_bits; // per-tensor Eq. 6 only: [groups], ordered key of the running minimum
-                         // (gmax_bits then holds the ordered key of the running maximum)
+    uint32_t* gmax_bits; // per-tensor only: [groups], bit pattern of the largest magnitude
+    uint32_t* gmin_bits; // per-tensor Eq. 6 only: [groups], ordered key of the minimum
+                         // (gmax_bits then holds the ordered key of the maximum)
     // Group normalisation / quantisation (Eq. 14-15): a token of `groups` * K elements is
     // handled as `groups` consecutive rows of K; row r belongs to group r % groups.  M counts
     // those rows.  gain/bias hold groups * K entries.  groups = 1: the plain layer.

@@ -181,6 +181,35 @@ def test_quant_codes_bit_exact_given_xhat(bl, M, K, per_tensor):
     assert mism <= max(1, M * K // 100000), f"{mism} codes differ end to end"
 
 
+# Per tensor: the rows' extremes meet in a launch between the two passes, 1024 entries at a time: fewer than that, one more,
+# several rounds with a rest; an entry for four rows, two or one, and of a K-group; the extremes in the first and last row.
+@pytest.mark.parametrize("M,K,groups", [(1, 32, 1), (3, 32, 1), (1023, 256, 1), (4101, 32, 1), (40001, 64, 1),
+                                        (1027, 1024, 1), (9001, 4096, 1), (2500, 33024, 1), (683, 96, 3), (70, 2048, 64)])
+@pytest.mark.parametrize("nonneg", [False, True])
+@pytest.mark.parametrize("at", [0, -1])
+def test_quant_extremes_of_a_tensor(bl, M, K, groups, nonneg, at):
+    print(f"extremes of a tensor M={M} K={K} groups={groups} nonneg={nonneg} at={at}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    X = torch.randn(M, K, device="cuda", generator=g)
+    X[at, ::K // groups] += 40.0 if at else -40.0  # per K-group one element far out
+    kw = dict(per_tensor=True, want_xhat=True, flags=bl.FLAG_SKIP_LN)
+    eta = torch.zeros(groups, device="cuda")
+    if nonneg:
+        codes, gamma, eta, _, xhat = bl.bitlinear_quant_act_nonneg(X, groups_k=groups, **kw)
+    elif groups > 1:
+        codes, gamma, _, xhat = bl.bitlinear_quant_act_grouped(X, groups, **kw)
+    else:
+        codes, gamma, _, xhat = bl.bitlinear_quant_act(X, **kw)
+    x = xhat.view(M, groups, -1)
+    assert torch.equal(xhat, X)
+    if nonneg:
+        assert torch.equal(eta, x.amin((0, 2)))
+    want = x.amax((0, 2)) - eta if nonneg else x.abs().amax((0, 2))
+    assert torch.equal(gamma, want)
+    t = (x - eta.view(1, -1, 1)) * (128.0 / gamma.view(1, -1, 1))  # fp32, one operation each, as in the kernel
+    assert torch.equal(codes.view(x.shape).float(), t.round().clamp(0.0 if nonneg else -128.0, 127.0))
+
+
 def test_quant_skip_ln_ties_clip_zero_row_affine(bl):
     row = np.zeros((3, 32), f32)
     row[0, :8] = [1, 1 / 256, 3 / 256, 5 / 256, -1 / 256, -3 / 256, -1, 127.5 / 128]
