@@ -799,9 +799,8 @@ struct RingPlan {
 
 // Cost in us of a product in slices of `per` of its nst stages on `cus` CUs: a stage of a tile takes `stage` us on a
 // CU, an item `item` us besides (two workgroups of a CU take the time of both), and the fp32 sums of a slice
-// (`bytes`) are written and read at `rate` MB/us by a second launch of `fold` us.  Fitted: over 78 shapes of 256 to
-// 5000 tokens (K and N of 1024 to 16384) dX's plan is 1.2 % slower than the best tile and slices on average (with
-// 0.345, 4.5, 4 and 5 for the smaller tile 2.2 %).
+// (`bytes`) are written and read at `rate` MB/us by a second launch of `fold` us.  These choose the slices (with 0.345,
+// 4.5, 4 and 5 for the smaller tile dX over 78 shapes of 256 to 5000 tokens was 1 % slower).
 struct RingCost {
     double stage, item, fold, rate;
 };
@@ -888,19 +887,25 @@ static void launch_fold(const float* part, const RingPlan& p, int64_t count, con
 }
 
 // dX's plan: 256 x 256 tiles, or 128 x 256 where they cost less.  A stage of the smaller tile takes more than half of
-// the larger one's time (its waves read and expand the same signs for half the rows), but with few tokens the larger
-// ones are too few for the CUs, or in so many slices that their sums cost what the product does. The whole call, M x K
-// x N, us, 256 / 128 rows: 1 x 4096 x 16384 47.0 / 36.5, 500 x 4096 x 4096 45.1 / 37.6, 1000 x 2048 x 8192 63.8 /
-// 54.7, 2048 x 4096 x 4096 91.3 / 76.7, 4000 x 2048 x 8192 166 / 153, 8192 x 1024 x 4096 118 / 97; but 1700 x 2560 x
-// 7680 98.5 / 110 and 8192 x 4096 x 16384 901 / 923; 1000 x 4096 x 16384, 145 / 147, goes the wrong way.
+// the larger one's time (its waves read and expand the same signs for half the rows), and more still in a single
+// round, where a CU has one workgroup, but with few tokens the larger ones are too few for the CUs, or in so many
+// slices that their sums cost what the product does.  The constants compare the two, each in the slices chosen above,
+// and are fitted to whole calls under either tile, 487 shapes of 100 to 8192 tokens, K and N of 1024 to 28672, half of
+// them near the line: 0.25 % slower than the better tile on average, 2.6 % at most where the smaller one is taken, 4.9
+// % where the larger one is (with the constants that choose the slices 0.54 %, and 8.4 % at most).  M x K x N, us, 256
+// / 128 rows: 1 x 4096 x 16384 47.0 / 36.5, 500 x 4096 x 4096 45.1 / 37.6, 1000 x 2048 x 8192 63.8 / 54.7, 2048 x 4096
+// x 4096 91.3 / 76.7, 4000 x 2048 x 8192 166 / 153, 8192 x 1024 x 4096 118 / 97; but 1700 x 2560 x 7680 92.4 / 94.7,
+// 677 x 6048 x 6048 72.3 / 78.4, 1000 x 4096 x 16384 136 / 143, 8192 x 4096 x 16384 873 / 908; 4232 x 3456 x 1760,
+// 63.3 / 60.3, goes the wrong way.
 static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
+    constexpr RingCost kWide{0.615, 12.0, 5.0, 6.0}, kRows{0.33, 5.0, 5.0, 6.0}, kRowsAlone{0.39, 2.0, 5.0, 6.0};
     const RingPlan wide = ring_plan(I, J, Rp, 256, 256), rows = ring_plan(I, J, Rp, 128, 256);
     if (const int force = tuning().bwd_dx) return force == 2 ? rows : wide;
-    const int64_t nst = Rp / 32, cus = ring_cus();
+    const int64_t nst = Rp / 32, cus = ring_cus(), tiles = (int64_t)rows.gi * rows.gj;
     const double bytes = (double)I * (double)J * 4.0;
     if (wide.grid == 0) return wide;
-    return ring_cost(kRowsCost, (int64_t)rows.gi * rows.gj, nst, rows.sl.per, bytes, cus) <
-                   ring_cost(kWideCost, (int64_t)wide.gi * wide.gj, nst, wide.sl.per, bytes, cus)
+    return ring_cost(tiles * rows.sl.splits > cus ? kRows : kRowsAlone, tiles, nst, rows.sl.per, bytes, cus) <
+                   ring_cost(kWide, (int64_t)wide.gi * wide.gj, nst, wide.sl.per, bytes, cus)
                ? rows
                : wide;
 }

@@ -27,10 +27,10 @@ __device__ inline float key_float(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 // Per tensor: the first pass leaves every row's largest magnitude (Eq. 6: its maximum and minimum), as integers of the
-// same order, where the codes will be, which nobody writes before the second pass (a row has 32 bytes there or more); a
-// launch between the passes folds them.  As atomic maxima on one address, behind a launch that cleared it, rows that end
-// together queue, the longer the faster the pass is.  us of a call, atomic / now: 16 x 4096 6.9 / 6.7, 512 x 4096 11.5 /
-// 7.8, 8192 x 1024 30.5 / 13.8, 2000 x 4096 25.7 / 13.8, 2000 x 5120 41.0 / 20.1, 8192 x 4096 57.0 / 49.0.
+// same order, where the codes will be, which nobody writes before the second pass (a row has 32 bytes there or more);
+// a launch between the passes folds them.  As atomic maxima on one address, behind a launch that cleared it, rows that
+// end together queue, the longer the faster the pass is.  us of a call, atomic / now: 16 x 4096 6.9 / 6.7, 512 x 4096
+// 11.5 / 7.8, 8192 x 1024 30.5 / 13.8, 2000 x 4096 25.7 / 13.8, 2000 x 5120 41.0 / 20.1, 8192 x 4096 57.0 / 49.0.
 struct Extremes {
     uint32_t *most, *least;
 };
