@@ -916,13 +916,19 @@ static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
 //   a round of 256 x 256, one workgroup per CU   12.8 + 0.68 us per stage
 //   of 128 x 128, up to one workgroup per CU      3.6 + 0.23
 //   of 128 x 128, two per CU                      4.9 + 0.39
-// (fitted to 82 shapes of 64 to 2000 tokens; a sliced product of 256 x 256 tiles is cheaper, kWideCost).  From two full
-// rounds on the second reading of the operands decides: beyond so many stages, or with a B operand well beyond an
-// XCD's 4 MB of L2, the large tile it is.  The whole call (M x N x K, with the operand copies), 256 against 128, us:
-// 64 x 2048 x 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048 37.6 /
-// 32.8, 1300 x 8192 x 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x 16384 x
-// 4096 120.9 / 108.5, 1600 x 16384 x 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 / 331,
-// 2000 x 21504 x 7168 647 / 811; in slices 3300 x 4224 x 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
+// (a sliced product of 256 x 256 tiles is cheaper, kWideCost).  From two full rounds on the second reading of the
+// operands decides: beyond so many stages, or with a B operand well beyond an XCD's 4 MB of L2, the large tile it is.
+// Where the small tiles' number is no multiple of 8 they go round the XCDs one by one (ring_tile_origin), and with an
+// odd number of columns every XCD then reads all columns of B: 22 % more a stage in products of a round and more, from
+// 16 stages on (27 columns, 5115 x 3360 x 3360 161 / 187; 26 columns, 6631 x 3328 x 3328 198 / 189).  From two full
+// rounds on the small tile is taken where it costs up to 2 % more: without that 1000 x 16384 x 4096, 184 / 166, goes
+// the wrong way; with it for fewer 1090 x 11456 x 1280, 56 / 62, does.  Over 549 shapes of 100 to 8192 tokens, most of
+// them near the line, this is 0.6 % slower than the better tile on average, and 13 of them 10 to 33 % (1700 x 7680 x
+// 2560, 117 / 88, beyond `most`).  The whole call (M x N x K, with the operand copies), 256 against 128,
+// us: 64 x 2048 x 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048
+// 37.6 / 32.8, 1300 x 8192 x 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x
+// 16384 x 4096 120.9 / 108.5, 1600 x 16384 x 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 /
+// 331, 2000 x 21504 x 7168 647 / 811; in slices 3300 x 4224 x 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
 static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int force = tuning().bwd_ring;
     if (force == 2) return ring_plan(I, J, Rp, 128, 128);
@@ -935,9 +941,11 @@ static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const RingCost uncut{0.68, 12.8, 4.0, 5.0};
     const double wide = ring_cost(p.sl.splits > 1 ? kWideCost : uncut, (int64_t)p.gi * p.gj, nst, p.sl.per,
                                   (double)I * (double)J * 4.0, cus);
-    const double two = 4.9 + 0.39 * (double)nst, one = 3.6 + 0.226 * (double)nst;
+    const bool scattered = full > 0 && nst >= 16 && ntiles % 8 != 0 && (J + 127) / 128 % 2 != 0;
+    const double st = (double)nst * (scattered ? 1.22 : 1.0);
+    const double two = 4.9 + 0.39 * st, one = 3.6 + 0.226 * st;
     const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);
-    return small < 1.02 * wide ? ring_plan(I, J, Rp, 128, 128) : p;
+    return small < (full < 2 ? 1.0 : 1.02) * wide ? ring_plan(I, J, Rp, 128, 128) : p;
 }
 
 // C[I][J] = scale * A[I][:] . B[J][:], in slices of r where the plan has them and `part` has room
