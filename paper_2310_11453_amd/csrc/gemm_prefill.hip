@@ -860,15 +860,16 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 //   a round of 256 x 256 tiles   14 + 0.62 n     (n = 32: 33, 64: 51 to 58, 112: 82, 256: 158)
 //   a round of 128 x 128 tiles    5 + 3.0 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 16: 53)
 //   a round of 64 x 128 tiles   4.5 + 3.1 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 14: 46)
-//   the last two in three rounds and more 5 % more (the large tiles read the operands less often), and 1.2 c more where
-//   the codes are more than 40 MB (out of the caches: three rounds of 4096 x 28672 -> 6144 in 128 x 128 tiles 378 us)
+//   the last two in three rounds and more 5 % more (the large tiles read the operands less often), and 0.8 c more with
+//   more than 24 rows of tiles: items run down a column of tiles, so that an XCD's 32 workgroups then hold hardly more
+//   than one column and share no codes (in all, c costs 3.0 up to 20 rows, 3.3 at 24, 3.8 to 4.0 from 28 on)
 //   slices of K                   4 + the int32 sums written and read at 5 TB/s
 // The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
 // ones win; the layer, us, M x K x N: 333 x 2048 x 2048 12.8 (64 x 128) against 19.4 (128 x 256), 700 x 4096 x 16384
-// 60.5 (128 x 128) against 64.0 (128 x 256 and 256 x 256), 700 x 28672 x 7168 161.5 (64 x 128) against 186.1.  Over 171
-// shapes of 80 to 2200 tokens, K and N of 1024 to 28672, the plan is 0.3 % slower than the best of all these on
-// average, 4 % at most (2200 x 3200 x 9600 89.8, 86.4 as 128 x 256); with 8 + 0.37 n, 3.5 + 4.2 c and 6.5 it was 1.0
-// and 17 %.
+// 60.5 (128 x 128) against 64.0 (128 x 256 and 256 x 256), 700 x 28672 x 7168 161.5 (64 x 128) against 186.1; the
+// product, 2176 x 16384 x 2586 96 (128 x 256) against 113 (64 x 128).  Over 185 shapes of 440 to 5000 tokens, K and N of
+// 1024 to 28672, the tile is 0.3 % slower than the best of the four on average, 11 % at most (1320 x 20288 x 882 39.9,
+// 36.0 as 128 x 128); with 1.2 c more from 40 MB of codes on in place of the line of 24 rows it was 1.1 and 32 %.
 struct TilePlan {
     int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
     int64_t per;  // 512-chunks of K per slice (3 and 4)
@@ -901,7 +902,7 @@ static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
             if (n > 1 && ((n != want && !force_n) || bytes > (double)ws_bytes)) continue;
             const int64_t rounds = (tiles * n + cus - 1) / cus;
             const double c = (double)((per + kg - 1) / kg);
-            const double chunk = (tile == 3 ? 3.0 : 3.1) + (M * K > (int64_t)40 << 20 ? 1.2 : 0.0);
+            const double chunk = (tile == 3 ? 3.0 : 3.1) + (M > 24 * bm ? 0.8 : 0.0);
             offer(tile, per, (double)rounds * ((tile == 3 ? 5.0 : 4.5) + chunk * c) * (rounds > 2 ? 1.05 : 1.0) +
                                  (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0));
         }
