@@ -119,15 +119,21 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // One round: the wave's slice of the codes is M rows of C * 512 bytes.  In operand layout a load touches
         // half a line of each row, so L2 serves every line twice, and there are C * 8 of them whatever M is.
         // Instead each row is fetched with one instruction, 16 consecutive bytes a lane (rows past M, up to a whole
-        // four: row M-1 again), and (below, once the first weight tiles have been requested behind it) parked in the
-        // wave's own part of `red`, which holds nothing before the wave's first tile is done, eight rows at a time, and
-        // read from there in operand layout.  A row is 1 KiB, so the same 16 bytes of every row would share their
-        // banks: the 16-byte slots of row r are stored at slot ^ r.  us a launch, from memory in operand layout
+        // set of four: row M-1 again), and (below, once the first weight tiles have been requested behind it) parked
+        // in the wave's own part of `red`, which holds nothing before the wave's first tile is done, eight rows at a
+        // time, and read from there in operand layout.  A row is 1 KiB, so the same 16 bytes of every row would share
+        // their banks: the 16-byte slots of row r are stored at slot ^ r.  us a launch, from memory in operand layout
         // (unless the part of `red` that the sums need held the rows) / now: 8 tokens 4096 -> 4096 3.95 / 3.2, 7168 ->
         // 7168 5.4 / 4.5, 8192 -> 2048 5.0 / 3.8, 16 tokens 8192 -> 2048 6.3 / 4.55, 7168 -> 7168 6.4 / 5.3, 16384 ->
-        // 4096 10.2 / 6.85.  A single chunk of K is read in place: parking is a longer chain then (16 x 256 -> 512
-        // 2.8, 2.45).
+        // 4096 10.2 / 6.85.  With 16 waves rows 0 and 1 are sets of their own: one token's launch of several rounds
+        // was 14.95 us with four rows loaded for it (9312 -> 28672), 14.2 now.
+        // In place where parking is the longer chain: a single chunk of K (16 x 256 -> 512 2.8, 2.45 in place), and
+        // with a chunk a wave, few tiles and a second pass of eight rows (parked / in place: 9 x 544 -> 2048 2.99 /
+        // 2.61, 16 x 2496 -> 2048 3.69 / 3.34, 9 x 3584 -> 2048 3.77 / 3.55; four tiles, 16 x 2048 -> 16384, 4.03 /
+        // 4.17), but for 12 rows and more of four whole chunks or more (12 x 3584 -> 2048 3.78 / 3.94).
         const bool stage_lane = l < C * 32;
+        // one past the last row of the set that starts with row r
+        auto rows_end = [](int r) { return MAXT == 1024 && r < 2 ? r + 1 : (r + 4) & ~3; };
         constexpr int kHeld = MAXT == 512 ? 16 : kStageRows;  // rows in registers; 16 waves have room for eight
         v4i rowv[kHeld];
         auto load_rows = [&](int first, int count) {  // rows first, first + 1, ... into rowv[0], ...
@@ -135,14 +141,16 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
             kl = kl > K - 16 ? K - 16 : kl;
             const int8_t* __restrict__ src = a.codes + kl;
 #pragma unroll
-            for (int r0 = 0; r0 < kHeld; r0 += 4)
+            for (int r0 = 0; r0 < kHeld; r0 = rows_end(r0))
                 if (r0 < count && first + r0 < M) {  // uniform
 #pragma unroll
-                    for (int r = r0; r < r0 + 4; ++r)
-                        rowv[r] = *reinterpret_cast<const v4i*>(src + (int64_t)(first + r < M ? first + r : M - 1) * a.ldq);
+                    for (int r = r0; r < rows_end(r0); ++r)
+                        rowv[r] =
+                            *reinterpret_cast<const v4i*>(src + (int64_t)(first + r < M ? first + r : M - 1) * a.ldq);
                 }
         };
-        const bool staged = ONE_ROUND && (C > 1 || TK > 1);  // uniform
+        const bool long_whole = M >= 12 && K >= 4 * kChunkK && K % kChunkK == 0;
+        const bool staged = ONE_ROUND && (C > 1 || (TK > 1 && (T >= 4 || M <= 8 || long_whole)));  // uniform
         if (staged) load_rows(0, kHeld);
         else load_act();
 
@@ -183,10 +191,10 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                 if (p * kStageRows < M) {  // uniform
                     if (stage_lane) {
 #pragma unroll
-                        for (int r0 = 0; r0 < kStageRows; r0 += 4)
+                        for (int r0 = 0; r0 < kStageRows; r0 = rows_end(r0))
                             if (p * kStageRows + r0 < M) {  // uniform
 #pragma unroll
-                                for (int r = r0; r < r0 + 4; ++r)
+                                for (int r = r0; r < rows_end(r0); ++r)
                                     *reinterpret_cast<v4i*>(stage + r * 1024 + (l ^ r) * 16) =
                                         rowv[kHeld == 16 ? p * kStageRows + r : r];
                             }

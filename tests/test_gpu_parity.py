@@ -579,6 +579,23 @@ def test_row_statistics_are_the_same_in_every_lane(bl, M, K):
             assert len(zeros) >= K // 2 and len(np.unique(zeros.view(np.uint32))) == 1, (seed, m, np.unique(zeros))
 
 
+# Up to 16 tokens, codes parked in LDS or read in place: the rows around each set of them, whole and ragged last chunks, few
+# tiles of a workgroup and four, eight waves and 16.  On integers, so exact.
+@pytest.mark.parametrize("K,tiles", [(480, 1), (544, 1), (544, 4), (1536, 2), (2048, 3), (2080, 1), (3584, 2), (4640, 1),
+                                     (9312, 1), (9312, 2), (16384, 2)])
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 9, 11, 12, 13, 16])
+def test_codes_of_up_to_16_tokens(bl, M, K, tiles, tuning):
+    N = 70
+    tuning(f"decode_tiles={tiles}")
+    packed, _, beta = bl.bitlinear_pack_weights(dev(wl.make_weight(N, K, 0.02, K)))
+    sign = oracle.unpack_canonical(host(bl.bitlinear_packed_to_canonical(packed, N, K)).view(np.uint32), K)
+    codes = np.random.default_rng(M + K).integers(-128, 128, (M, K)).astype(np.int8)
+    rowsum = codes.astype(np.int64).sum(1).astype(np.int32)
+    acc = bl.bitlinear_matmul(dev(codes), torch.ones(M, device="cuda"), dev(rowsum), packed, N, beta,
+                              flags=bl.FLAG_OUT_ACC_I32)
+    assert np.array_equal(host(acc), oracle.matmul_i32(codes, sign))
+
+
 # 17 to 32 tokens of long rows: one slice of K walked in many steps, two or more where the workgroups are few, a last
 # slice that is shorter, and the most codes the register-streaming kernel takes: the bits of the LDS-tiled kernel.
 @pytest.mark.parametrize("M,K,N", [(17, 8704, 4352), (32, 28672, 7168), (24, 16416, 4100), (31, 40992, 520),
