@@ -166,6 +166,34 @@ __global__ __launch_bounds__(kTokWaves* kWave) void gemm_tokens_kernel(TokArgs a
             }
         }
     }
+    // Gain and bias.  Two pairs: all pieces' at once, past the row the last one's, and one butterfly over the parts (one
+    // after another, each behind a branch of its own, they are up to 16 trips to L2 in a row: 3 x 2496 -> 16384 9.0 us,
+    // 8.2 now, 6.6 without gain and bias).  One pair: piece by piece, so that those past the row cost nothing (1 x
+    // 16416 -> 1024 11.8 us, 12.5 at once).
+    if constexpr (P == 2) {
+        if (affine && !skip_ln) {  // uniform
+            float4 gn[P][NV], bs[P][NV];
+#pragma unroll
+            for (int i = 0; i < P * NV; ++i) {
+                const int p = i / NV, j = i % NV, idx = t[p] + j * RT, at = idx < K4 ? idx : K4 - 1;
+                if (a.gain) gn[p][j] = reinterpret_cast<const float4*>(a.gain)[at];
+                if (a.bias) bs[p][j] = reinterpret_cast<const float4*>(a.bias)[at];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < P * NV; ++i) {
+                const int p = i / NV, j = i % NV;
+                float4& o = v[p][j];
+                const float4 g = gn[p][j], b = bs[p][j];
+                if (a.gain) {
+                    o.x = o.x * g.x; o.y = o.y * g.y; o.z = o.z * g.z; o.w = o.w * g.w;
+                }
+                if (a.bias) {
+                    o.x = o.x + b.x; o.y = o.y + b.y; o.z = o.z + b.z; o.w = o.w + b.w;
+                }
+            }
+        }
+    }
     if (affine || skip_ln) {  // uniform
 #pragma unroll
         for (int p = 0; p < P; ++p) {
@@ -175,11 +203,11 @@ __global__ __launch_bounds__(kTokWaves* kWave) void gemm_tokens_kernel(TokArgs a
                 const int idx = t[p] + j * RT;
                 if (idx < K4) {
                     float4 o = v[p][j];
-                    if (a.gain && !skip_ln) {
+                    if (P == 1 && a.gain && !skip_ln) {
                         const float4 gn = reinterpret_cast<const float4*>(a.gain)[idx];
                         o.x = o.x * gn.x; o.y = o.y * gn.y; o.z = o.z * gn.z; o.w = o.w * gn.w;
                     }
-                    if (a.bias && !skip_ln) {
+                    if (P == 1 && a.bias && !skip_ln) {
                         const float4 b = reinterpret_cast<const float4*>(a.bias)[idx];
                         o.x = o.x + b.x; o.y = o.y + b.y; o.z = o.z + b.z; o.w = o.w + b.w;
                     }
@@ -195,7 +223,14 @@ __global__ __launch_bounds__(kTokWaves* kWave) void gemm_tokens_kernel(TokArgs a
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 const int base = (w * P + p) >> a.part_shift << a.part_shift;
-                for (int i = 0; i < parts; ++i) amax[p] = fmaxf(amax[p], sm_amax[base + i]);
+                if constexpr (P == 1) {
+                    for (int i = 0; i < parts; ++i) amax[p] = fmaxf(amax[p], sm_amax[base + i]);
+                } else {  // parts is 2, 4 or 8
+                    amax[p] = sm_amax[base + (l & (parts - 1))];
+                    amax[p] = OpMax{}(amax[p], dpp_mov<kXor1>(amax[p]));
+                    if (parts > 2) amax[p] = OpMax{}(amax[p], dpp_mov<kXor2>(amax[p]));
+                    if (parts > 4) amax[p] = OpMax{}(amax[p], dpp_mov<kRor4>(amax[p]));
+                }
             }
         }
     }
@@ -348,7 +383,8 @@ bool tokens_plan(int64_t M, int64_t K, int64_t N, TokensPlan& p) {
     p.T = (int)((tpb + sets - 1) / sets);
     // Every workgroup repeats the quantiser, so it pays only while one round of workgroups covers N, and while a
     // wave has one or two pairs: each costs 0.7 to 1 us (8 x 1024 -> 1024 with two 4.3 us, 6.0 in two launches; 8 x
-    // 2048 -> 2048 with four 7.0 and 6.4, 4 x 4096 -> 4096 with four 6.95 and 6.9).
+    // 2048 -> 2048 with four 7.0 and 6.4, 4 x 4096 -> 4096 with four 6.95 and 6.9).  Two pairs of four pieces are the
+    // line: 0.93 to 0.98 of the time of two launches, 1.01 to 1.06 with gain and bias.
     const int most = p.C == 4 ? 2 : p.C == 8 ? 3 : p.P > 1 || p.NV != 2 * p.C ? 4 : 8;
     return p.wpr <= kTokWaves && p.P <= 2 && p.P * p.NV <= (M == 1 ? 16 : 8) && p.T <= most &&
            M * TK * kChunkK <= (p.C < 8 ? kTokCodes : 32768);

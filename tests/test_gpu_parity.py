@@ -579,6 +579,32 @@ def test_row_statistics_are_the_same_in_every_lane(bl, M, K):
             assert len(zeros) >= K // 2 and len(np.unique(zeros.view(np.uint32))) == 1, (seed, m, np.unique(zeros))
 
 
+# Gain or bias alone, and both on rows with infinities and a NaN: one to eight pieces of a lane, ragged rows, one wave to a
+# row and eight.
+@pytest.mark.parametrize("M,K,N", [(2, 96, 20), (3, 992, 16), (6, 1376, 70), (7, 1568, 300), (4, 2048, 33), (2, 4640, 48)])
+@pytest.mark.parametrize("variant", ["gain", "bias", "inf"])
+def test_forward_tokens_affine(bl, M, K, N, variant, tuning):
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    packed, _, beta = bl.bitlinear_pack_weights(torch.randn(N, K, device="cuda", generator=g) * 0.02)
+    X = torch.randn(M, K, device="cuda", generator=g) * 3 + 1
+    if variant == "inf":
+        X[0, 0], X[0, K // 2], X[1, K - 1] = float("inf"), float("-inf"), float("nan")
+    kw = {}
+    if variant != "bias":
+        kw["ln_gain"] = 1 + 0.1 * torch.randn(K, device="cuda", generator=g)
+    if variant != "gain":
+        kw["ln_bias"] = 0.1 * torch.randn(K, device="cuda", generator=g)
+    got = []
+    for spec in (None, "decode_nofuse=1"):
+        tuning(spec)
+        ws = torch.zeros(bl.workspace_bytes(bl.OP_FORWARD, M, N, K), dtype=torch.uint8, device="cuda")
+        y = bl.bitlinear_forward(X, packed, N, beta, workspace=ws, **kw)
+        at = bl.forward_workspace_layout(M, N, K)["gamma"]
+        got.append((host(y.view(torch.int32)), host(ws[:M * K]), host(ws[at:at + 4 * M])))
+    for one, two in zip(*got):
+        assert np.array_equal(one, two)
+
+
 # Up to 16 tokens, codes parked in LDS or read in place: the rows around each set of them, whole and ragged last chunks, few
 # tiles of a workgroup and four, eight waves and 16.  On integers, so exact.
 @pytest.mark.parametrize("K,tiles", [(480, 1), (544, 1), (544, 4), (1536, 2), (2048, 3), (2080, 1), (3584, 2), (4640, 1),
