@@ -34,10 +34,11 @@ namespace bl {
 // waves each, C chunks of the group's K per wave), every group reads its own columns of the codes
 // and its own blob of tiles, and a tile's sums are added per group and written to the group's slice
 // of split_ws (2 * sum_k q b, as a K split does), for groups_reduce to dequantise group by group.
-template <int C, int T, int MAXT, bool ONE_ROUND, bool KGRP = false>
+// PARKS: the codes may go through LDS (below), eight rows of a KiB a wave where T is less.
+template <int C, int T, int MAXT, bool ONE_ROUND, bool KGRP = false, bool PARKS = ONE_ROUND>
 __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) {
     static_assert(!KGRP || ONE_ROUND, "K-groups inside the workgroup: one round");
-    constexpr int kStageRows = 8, kRegion = ONE_ROUND && T < kStageRows ? kStageRows : T;  // KiB of a wave's part
+    constexpr int kStageRows = 8, kRegion = PARKS && T < kStageRows ? kStageRows : T;  // KiB of a wave's part
     __shared__ __attribute__((aligned(16))) int red[(MAXT / kWave) * kRegion * 256];  // [W][T][64][4]
     constexpr int MAXW = MAXT / kWave;
     const int W = blockDim.x / kWave;
@@ -126,14 +127,16 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
         // (unless the part of `red` that the sums need held the rows) / now: 8 tokens 4096 -> 4096 3.95 / 3.2, 7168 ->
         // 7168 5.4 / 4.5, 8192 -> 2048 5.0 / 3.8, 16 tokens 8192 -> 2048 6.3 / 4.55, 7168 -> 7168 6.4 / 5.3, 16384 ->
         // 4096 10.2 / 6.85.  With 16 waves rows 0 and 1 are sets of their own: one token's launch of several rounds
-        // was 14.95 us with four rows loaded for it (9312 -> 28672), 14.2 now.
+        // was 14.95 us with four rows loaded for it (9312 -> 28672), 14.2 now; launches of K-groups, shorter, lose by
+        // it (4 x 7168 -> 736 in 2 x 2 groups 9.15 us the layer, 9.45).
         // In place where parking is the longer chain: a single chunk of K (16 x 256 -> 512 2.8, 2.45 in place), and
         // with a chunk a wave, few tiles and a second pass of eight rows (parked / in place: 9 x 544 -> 2048 2.99 /
         // 2.61, 16 x 2496 -> 2048 3.69 / 3.34, 9 x 3584 -> 2048 3.77 / 3.55; four tiles, 16 x 2048 -> 16384, 4.03 /
-        // 4.17), but for 12 rows and more of four whole chunks or more (12 x 3584 -> 2048 3.78 / 3.94).
+        // 4.17), but for 12 rows and more of four whole chunks or more (12 x 3584 -> 2048 3.78 / 3.94)
+        // and for K-groups over 9 to 16 waves (12 x 4736 -> 224 in 2 x 4 groups, the layer, 10.4 / 10.9).
         const bool stage_lane = l < C * 32;
         // one past the last row of the set that starts with row r
-        auto rows_end = [](int r) { return MAXT == 1024 && r < 2 ? r + 1 : (r + 4) & ~3; };
+        auto rows_end = [](int r) { return MAXT == 1024 && !KGRP && r < 2 ? r + 1 : (r + 4) & ~3; };
         constexpr int kHeld = MAXT == 512 ? 16 : kStageRows;  // rows in registers; 16 waves have room for eight
         v4i rowv[kHeld];
         auto load_rows = [&](int first, int count) {  // rows first, first + 1, ... into rowv[0], ...
@@ -150,7 +153,8 @@ __global__ __launch_bounds__(MAXT) void gemm_decode_kernel(GemmArgs a, int tpb) 
                 }
         };
         const bool long_whole = M >= 12 && K >= 4 * kChunkK && K % kChunkK == 0;
-        const bool staged = ONE_ROUND && (C > 1 || (TK > 1 && (T >= 4 || M <= 8 || long_whole)));  // uniform
+        const bool staged =
+            PARKS && (C > 1 || (TK > 1 && (T >= 4 || M <= 8 || long_whole || (KGRP && MAXT == 1024))));  // uniform
         if (staged) load_rows(0, kHeld);
         else load_act();
 
@@ -469,13 +473,13 @@ int num_cus() {
     return n;
 }
 
-template <int C, int T, int MAXT, bool ONE_ROUND, bool KGRP = false>
+template <int C, int T, int MAXT, bool ONE_ROUND, bool KGRP = false, bool PARKS = ONE_ROUND>
 static void launch_one(const GemmArgs& a, int W, int tpb, hipStream_t s) {
     const int64_t TN = tiles_n(a.N);
     const unsigned splits = KGRP ? 1u : a.kgroups > 1 ? (unsigned)a.kgroups
                             : a.split_k ? (unsigned)((a.K + a.split_k - 1) / a.split_k) : 1u;
     const dim3 grid((unsigned)((TN + tpb - 1) / tpb), splits);
-    gemm_decode_kernel<C, T, MAXT, ONE_ROUND, KGRP><<<grid, W * kWave, 0, s>>>(a, tpb);
+    gemm_decode_kernel<C, T, MAXT, ONE_ROUND, KGRP, PARKS><<<grid, W * kWave, 0, s>>>(a, tpb);
 }
 
 // one round, up to 8 waves, exactly tpb = 1..8 tiles per group
@@ -590,8 +594,13 @@ hipError_t launch_gemm_decode(const GemmArgs& a_in, hipStream_t s) {
             if (tiles_for(2) <= 1) launch_one<2, 1, 1024, true, true>(a, (int)(V / 2), 1, s);
             else launch_one<2, 2, 1024, true, true>(a, (int)(V / 2), 2, s);
         } else if (V <= 16) {
+            // In more than one round of workgroups the codes are read in place: without LDS for eight rows a wave a
+            // CU holds two workgroups (the layer, us, parked / in place: 5 x 5504 -> 23296 in 8 x 4 groups 17.1 /
+            // 15.2, 14 x 4736 -> 22784 24.0 / 21.0, 16 x 4608 -> 8208 in 1 x 3 13.8 / 13.0; in one round 16 x 4608 ->
+            // 8192 11.7 / 11.9, 4 x 7168 -> 736 in 2 x 2 9.2 / 9.7).
             if (tiles_for(2) <= 1) launch_one<1, 1, 1024, true, true>(a, (int)V, 1, s);
-            else launch_one<1, 2, 1024, true, true>(a, (int)V, 2, s);
+            else if (TN <= 2 * num_cus()) launch_one<1, 2, 1024, true, true>(a, (int)V, 2, s);
+            else launch_one<1, 2, 1024, true, true, false>(a, (int)V, 2, s);
         } else {
             done = false;
         }

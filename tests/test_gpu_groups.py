@@ -133,6 +133,9 @@ def test_grouped_forward_ragged(bl):
 
 @pytest.mark.parametrize("M,K,N,gn,gk", [(5, 16384, 256, 1, 8),   # 16 waves of two chunks
                                          (9, 6144, 256, 2, 4),    # 12 waves of one chunk
+                                         (4, 4512, 8192, 1, 3),   # 9 waves, two tiles each, one round: codes parked
+                                         (7, 4512, 8224, 2, 3),   # 9 waves, more than one round: codes read in place
+                                         (16, 7104, 16416, 3, 2), # 14 waves, three rounds, K past a chunk's end
                                          (3, 32768, 128, 1, 8),   # too many chunks for one workgroup
                                          (40, 8192, 384, 1, 2),   # 33-64 tokens, long K-groups
                                          (64, 3072, 256, 2, 6)])  # 33-64 tokens, six groups in two items
