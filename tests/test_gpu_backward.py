@@ -34,7 +34,7 @@ def close(a, ref):
 
 # several tiles with ragged tails in every dimension, and both granularities of gamma
 SHAPES = [(8, 512, 256), (12, 20, 64), (300, 200, 96), (64, 136, 1056), (257, 513, 544),
-          (1024, 640, 512)]
+          (1024, 640, 512), (65, 3, 32), (1, 1, 96)]
 
 
 # The library picks dW's tile from the shape (256 x 256, or 128 x 128 where that costs less); the bwd_ring
@@ -69,7 +69,7 @@ def test_backward_ste_matches_oracle(bl, tuning, M, N, K, per_tensor, ring):
 
 # The copies of the operands come out of one launch, with four elements a load where rows and pointer allow it: the
 # four combinations of that for dY and the codes give the same bits.
-@pytest.mark.parametrize("M,N,K", [(70, 68, 96), (33, 1000, 544), (130, 66, 32)])
+@pytest.mark.parametrize("M,N,K", [(70, 68, 96), (33, 1000, 544), (130, 66, 32), (129, 131, 64)])
 @pytest.mark.parametrize("per_tensor", [True, False])
 def test_backward_operands_at_any_alignment(bl, M, N, K, per_tensor):
     def moved(t):  # the same values one element behind an aligned address
