@@ -936,15 +936,20 @@ static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
 // operands decides: beyond so many stages, or with a B operand well beyond an XCD's 4 MB of L2, the large tile it is.
 // Where the small tiles' number is no multiple of 8 they go round the XCDs one by one (ring_tile_origin), and with an
 // odd number of columns every XCD then reads all columns of B: 22 % more a stage in products of a round and more, from
-// 16 stages on (27 columns, 5115 x 3360 x 3360 161 / 187; 26 columns, 6631 x 3328 x 3328 198 / 189).  From two full
-// rounds on the small tile is taken where it costs up to 2 % more: without that 1000 x 16384 x 4096, 184 / 166, goes
-// the wrong way; with it for fewer 1090 x 11456 x 1280, 56 / 62, does.  Over 549 shapes of 100 to 8192 tokens, most of
-// them near the line, this is 0.6 % slower than the better tile on average, and 13 of them 10 to 33 % (1700 x 7680 x
-// 2560, 117 / 88, beyond `most`).  The whole call (M x N x K, with the operand copies), 256 against 128,
-// us: 64 x 2048 x 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048
-// 37.6 / 32.8, 1300 x 8192 x 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x
-// 16384 x 4096 120.9 / 108.5, 1600 x 16384 x 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 /
-// 331, 2000 x 21504 x 7168 647 / 811; in slices 3300 x 4224 x 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
+// 16 stages on (27 columns, 5115 x 3360 x 3360 161 / 187; 26 columns, 6631 x 3328 x 3328 198 / 189).  Between one and
+// two full rounds a stage of the small tile costs more the longer the reduction (with constants as below from 140 to
+// 210 stages on): 4779 x 2560 x 4096 149 / 157, 6661 x 2048 x 5120 199 / 212, 6987 x 2560 x 4096 207 / 224, but 5016 x
+// 4262 x 2816 172 / 161.  With operands of more than some 140 MB, which with dY before them do not stay in the 256 MB
+// cache, a stage of it takes half as long again (7819 x 10120 x 256 167 / 193, 4124 x 18061 x 224 176 / 185; with 120
+// MB, 3931 x 16384 x 512, 155 / 135).  From two full rounds on the small tile is taken where it costs up to 2 % more:
+// without that 1000 x 16384 x 4096, 184 / 166, goes the wrong way; with it for fewer 1090 x 11456 x 1280, 56 / 62,
+// does.  Over 549 shapes of 100 to 8192 tokens, most of them near the line, this was 0.6 % slower than the better tile
+// on average without the rules for long reductions and large operands, and 13 of them 10 to 33 % (1700 x 7680 x 2560,
+// 117 / 88, beyond `most`).  The whole call (M x N x K, with the operand copies), 256 against 128, us: 64 x 2048 x
+// 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048 37.6 / 32.8, 1300
+// x 8192 x 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x 16384 x 4096 120.9
+// / 108.5, 1600 x 16384 x 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 / 331, 2000 x 21504
+// x 7168 647 / 811; in slices 3300 x 4224 x 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
 static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int force = tuning().bwd_ring;
     if (force == 2) return ring_plan(I, J, Rp, 128, 128);
@@ -953,12 +958,14 @@ static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int64_t cus = ring_cus(), nst = Rp / 32, ntiles = (I + 127) / 128 * ((J + 127) / 128);
     const int64_t full = ntiles / (2 * cus), rest = ntiles % (2 * cus);
     const int64_t most = full < 4 ? 44 : full < 9 ? 32 : 16;  // stages
+    if (full == 1 && rest && nst > 136) return p;
     if (full >= 2 && (nst > most || J * Rp * 2 > 12000000)) return p;
     const RingCost uncut{0.68, 12.8, 4.0, 5.0};
     const double wide = ring_cost(p.sl.splits > 1 ? kWideCost : uncut, (int64_t)p.gi * p.gj, nst, p.sl.per,
                                   (double)I * (double)J * 4.0, cus);
     const bool scattered = full > 0 && nst >= 16 && ntiles % 8 != 0 && (J + 127) / 128 % 2 != 0;
-    const double st = (double)nst * (scattered ? 1.22 : 1.0);
+    const bool cold = (I + J) * Rp * 2 > 140000000;
+    const double st = (double)nst * (scattered ? 1.22 : 1.0) * (cold ? 1.5 : 1.0);
     const double two = 4.9 + 0.39 * st, one = 3.6 + 0.226 * st;
     const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);
     return small < (full < 2 ? 1.0 : 1.02) * wide ? ring_plan(I, J, Rp, 128, 128) : p;
