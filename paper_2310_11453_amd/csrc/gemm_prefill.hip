@@ -860,16 +860,16 @@ static void launch_tile(const GemmArgs& a, hipStream_t s) {
 //   a round of 256 x 256 tiles   14 + 0.62 n     (n = 32: 33, 64: 51 to 58, 112: 82, 256: 158)
 //   a round of 128 x 128 tiles    5 + 3.0 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 16: 53)
 //   a round of 64 x 128 tiles   4.5 + 3.1 c      (c = 1: 8, 2: 11, 4: 17, 7: 26, 14: 46)
-//   the last two in three rounds and more 5 % more (the large tiles read the operands less often), and 0.8 c more with
-//   more than 24 rows of tiles: items run down a column of tiles, so that an XCD's 32 workgroups then hold hardly more
-//   than one column and share no codes (in all, c costs 3.0 up to 20 rows, 3.3 at 24, 3.8 to 4.0 from 28 on)
+//   the last two in three rounds and more 5 % more (the large tiles read the operands less often), and from 20 to 28
+//   rows of tiles up to 0.8 c more: items run down a column of tiles, so that an XCD's 32 workgroups then hold hardly
+//   more than one column and share no codes (in all, c costs 3.0 up to 20 rows, 3.3 at 24, 3.8 to 4.0 from 28 on)
 //   slices of K                   4 + the int32 sums written and read at 5 TB/s
 // The large tiles do the most work per byte and expanded bit; where they leave CUs idle the small
 // ones win; the layer, us, M x K x N: 333 x 2048 x 2048 12.8 (64 x 128) against 19.4 (128 x 256), 700 x 4096 x 16384
 // 60.5 (128 x 128) against 64.0 (128 x 256 and 256 x 256), 700 x 28672 x 7168 161.5 (64 x 128) against 186.1; the
 // product, 2176 x 16384 x 2586 96 (128 x 256) against 113 (64 x 128).  Over 185 shapes of 440 to 5000 tokens, K and N of
 // 1024 to 28672, the tile is 0.3 % slower than the best of the four on average, 11 % at most (1320 x 20288 x 882 39.9,
-// 36.0 as 128 x 128); with 1.2 c more from 40 MB of codes on in place of the line of 24 rows it was 1.1 and 32 %.
+// 36.0 as 128 x 128); with 1.2 c more from 40 MB of codes on in place of what the rows cost it was 1.1 and 32 %.
 struct TilePlan {
     int tile;     // 1: 128 x 256, 2: 256 x 256 (this file); 3: 128 x 128, 4: 64 x 128 (gemm_mid.hip)
     int64_t per;  // 512-chunks of K per slice (3 and 4)
@@ -902,7 +902,8 @@ static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
             if (n > 1 && ((n != want && !force_n) || bytes > (double)ws_bytes)) continue;
             const int64_t rounds = (tiles * n + cus - 1) / cus;
             const double c = (double)((per + kg - 1) / kg);
-            const double chunk = (tile == 3 ? 3.0 : 3.1) + (M > 24 * bm ? 0.8 : 0.0);
+            const double more = 0.1 * (double)((M + bm - 1) / bm - 20);
+            const double chunk = (tile == 3 ? 3.0 : 3.1) + (more < 0.0 ? 0.0 : more < 0.8 ? more : 0.8);
             offer(tile, per, (double)rounds * ((tile == 3 ? 5.0 : 4.5) + chunk * c) * (rounds > 2 ? 1.05 : 1.0) +
                                  (n > 1 ? 4.0 + bytes * 2.0 / 5e6 : 0.0));
         }
@@ -914,7 +915,10 @@ static TilePlan tile_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
 // CUs, run as 6).  Then the columns that fill the rounds before it keep the large tiles, and the rest
 // is a launch of its own with whatever costs least there, 3 us between the two.  us of the layer, one launch /
 // two: 4096 x 7168 x 21504 553 / 528 (a quarter-filled round runs at a higher clock, or it would be more),
-// 300 x 4096 x 24000 57.9 / 52.3, 2048 x 3072 x 12288 88.6 / 85.7, 4096 x 2048 x 6144 70.7 / 69.6.
+// 300 x 4096 x 24000 57.9 / 52.3, 2048 x 3072 x 12288 88.6 / 85.7, 4096 x 2048 x 6144 70.7 / 69.6.  Where one
+// launch is of large tiles too, two have to cost 4 % less: of 23 shapes nearer the line, of 1500 drawn, 17 are faster in
+// one (the product, 4008 x 7168 x 3072 78 to 85 / 87 to 89, 1218 x 960 x 17006 45.5 / 57.4, 4086 x 19328 x 2959 189 /
+// 212; but 4806 x 512 x 28672 136 / 126).
 struct PrefillPlan {
     TilePlan first, rest;
     int64_t cut;  // columns of the first launch, a multiple of 256; 0: one launch
@@ -924,7 +928,7 @@ static PrefillPlan prefill_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes
     PrefillPlan best{tile_plan(M, N, K, ws_bytes), {}, 0};
     if (!one_beta || tuning().prefill_tile || tuning().prefill_split || tuning().prefill_grid) return best;
     const int64_t cus = num_cus(), nst = (K + kStageK - 1) / kStageK;
-    double best_us = best.first.us;
+    double best_us = (best.first.tile <= 2 ? 0.96 : 1.0) * best.first.us;
     for (int tile = 1; tile <= 2; ++tile) {
         const int64_t bm = tile == 1 ? 128 : 256;
         const int64_t grid_m = (M + bm - 1) / bm, grid_n = (N + 255) / 256;
