@@ -793,18 +793,6 @@ __global__ __launch_bounds__(256) void fold_slices(const float* __restrict__ par
     }
 }
 
-static int bwd_num_cus() {
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            n = prop.multiProcessorCount;
-        if (n <= 0) n = 256;
-    }
-    return n;
-}
-
 // The plan of a product: the grid, the block of tiles an XCD runs together (ring_tile_origin):
 // blk_i x blk_j = grid / 8 tiles out of its grid_i / 8 rows, as square as the divisors allow; 0 =
 // no such tiling; and the slices of the reduction.
@@ -844,7 +832,7 @@ static RingSlices ring_slices(RingCost c, int64_t tiles, int64_t nst, double byt
     return best;
 }
 
-static int ring_cus() { return tuning().bwd_grid > 0 ? tuning().bwd_grid : bwd_num_cus(); }
+static int ring_cus() { return tuning().bwd_grid > 0 ? tuning().bwd_grid : num_cus(); }
 
 // Tiles of bm x bn: 256 x 256; 128 x 256 (dX); 128 x 128 (dW, not sliced).  Of the smaller ones a CU holds two.
 static RingPlan ring_plan(int64_t I, int64_t J, int64_t Rp, int bm, int bn) {

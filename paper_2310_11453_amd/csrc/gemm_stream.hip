@@ -285,18 +285,6 @@ __global__ __launch_bounds__(stream::kMaxWaves* kWave) void gemm_stream_kernel(s
     else finish(std::integral_constant<int, 0>{});
 }
 
-static int stream_cus() {
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            n = prop.multiProcessorCount;
-        if (n <= 0) n = 256;
-    }
-    return n;
-}
-
 // K-slices for 16 < M <= 32 that a call brings room for: longer K than 16 chunks (two per wave) in slices of at most
 // 16 chunks; the launch takes as many of them as pay.  0 = no split.
 int64_t stream_split_tiles(int64_t M, int64_t K) {
@@ -314,7 +302,7 @@ bool launch_gemm_stream(const GemmArgs& a_in, hipStream_t s) {
     a.split_k = 0;
     if (a.M <= 16 || a.M > kTokens || a.K >= ((int64_t)1 << 22)) return false;
     const int64_t TP = (tiles_n(a.N) + 1) / 2;
-    int grid = stream_cus();
+    int grid = num_cus();
     if (grid > TP) grid = (int)TP;
     if ((TP + grid - 1) / grid > kMaxPairs) return false;
     // every workgroup reads the codes of 32 tokens over all of K from L2 (K-slices share the
@@ -332,7 +320,7 @@ bool launch_gemm_stream(const GemmArgs& a_in, hipStream_t s) {
         const int64_t n_max = (TK + most - 1) / most, pairs = (TP + grid - 1) / grid;
         double best_us = 1e30;
         for (int64_t want = 1; want <= n_max; ++want) {
-            const int64_t per = (TK + want - 1) / want, n = (TK + per - 1) / per, cus = stream_cus();
+            const int64_t per = (TK + want - 1) / want, n = (TK + per - 1) / per, cus = num_cus();
             const double bytes = (double)n * (double)a.M * (double)a.N * 4.0;
             if (n > 1 && bytes > (double)a.split_ws_bytes) break;
             const double us = (double)((grid * n + cus - 1) / cus) *

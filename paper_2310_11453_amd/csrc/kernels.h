@@ -147,7 +147,7 @@ hipError_t launch_read_probe(const void* src, size_t bytes, int workgroups, int 
 hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t s);
 bool gemm_tokens_fuses_quant(int64_t M, int64_t K, int64_t N);  // gamma per token
 hipError_t launch_gemm_tokens(const GemmArgs& a, hipStream_t s);
-int num_cus();
+int num_cus();  // of the device current at the first call
 hipError_t launch_gemm_prefill(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_mid(const GemmArgs& a, hipStream_t s);  // 16 < M <= 64
 hipError_t launch_gemm_mid_tiles(const GemmArgs& a, int bm, int64_t per, hipStream_t s);  // M > 64
