@@ -128,9 +128,13 @@ int bitlinear_matmul(const int8_t* codes, const float* gamma, const int32_t* row
                      void* stream);
 
 /* Eq. 11, the whole layer: bitlinear_quant_act into the workspace, then
- * bitlinear_matmul.  Arguments as above.  For one token (K <= 32768 and an N that one
- * round of workgroups covers) and for up to eight tokens of short rows with gamma per token
- * both steps run in one launch: the GEMM kernel normalises and quantises the rows itself.  With
+ * bitlinear_matmul.  Arguments as above.  A few tokens run in one launch, whose GEMM kernel
+ * normalises and quantises the rows itself: one token where every workgroup of one round (a
+ * CU each) has at most 8 times 16 rows of weights for K <= 8192 (N <= 32768 on 256 CUs), 2
+ * for K <= 16384 (N <= 8192) and 3 for K <= 32768 (N <= 12288); two to eight tokens with gamma
+ * per token where besides M * K, K padded to 512, is at most 20480 and a wave of eight has one or two
+ * rows or parts of rows to quantise (8 x 1024, 4 x 2048 or 2 x 8192, at most 4 times 16 rows
+ * of weights a workgroup from two a wave on).  With
  * two to eight tokens the codes are the same bits as bitlinear_quant_act's; with one the summation
  * order is its own, so a code can differ where x^ * 128 / gamma sits on a rounding tie.  The
  * workspace is required in every case
@@ -317,7 +321,7 @@ int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int thre
  * BITLINEAR_TUNING (same syntax) is read once, at the first call that launches or asks for a size.
  *   decode_nofuse=1     bitlinear_forward of a few tokens: quantiser and GEMM always as two launches
  *   decode_nosplit=1    M <= 16: never split K over workgroups
- *   decode_tiles=t      M <= 16: weight tiles per workgroup
+ *   decode_tiles=t      M <= 16: weight tiles per workgroup (no effect where a few tokens run in one launch)
  *   mid_nosplit=1       16 < M <= 64: never split K over workgroups
  *   mid_split_tiles=c   16 < M <= 64: 512-element chunks of K per slice
  *   mid_only=1          16 < M <= 32: skip the register-streaming kernel
@@ -332,7 +336,7 @@ int bitlinear_probe_read(const void* src, size_t bytes, int workgroups, int thre
  *   bwd_ring=1|2        backward, dW: 256 x 256 or 128 x 128 output tiles
  *   bwd_dx=1|2          backward, dX: 256 x 256 or 128 x 256 output tiles
  *   bwd_grid=g, bwd_rowmajor=1   backward ring kernel: workgroups, plain tile order
- *   bwd_splits=n        backward ring kernels: slices of the reduction (256 x 256 tiles)
+ *   bwd_splits=n        backward ring kernels: slices of the reduction (tiles of 256 columns)
  * Returns BL_OK, or BL_ERR_UNSUPPORTED (unknown name or bad syntax; nothing changes). */
 int bitlinear_set_tuning(const char* spec);
 

@@ -956,7 +956,7 @@ size_t prefill_split_bytes(int64_t M, int64_t N, int64_t K, bool one_beta) {
 // The same choice for a grouped layer (K = a group's): 0 = the stream kernel, 3 or 4 = the tiles of
 // gemm_mid.hip with every K-group an item of its own, its int32 sums in a slice that the fold
 // dequantises (same fp32 operations in the same order, same bits).  The stream kernel's round of
-// tiles is taken to cost 6 + groups (1 + 0.42 n) us (1000 x 7168 x 28672, 8 groups: 228 us in 4 rounds, measured 212;
+// tiles is taken to cost 6 + groups (1 + 0.42 n) us (1000 x 7168 x 28672, 8 groups: 244 us in 4 rounds, measured 212;
 // with constants that fit this one, layers of 66 to 641 tokens at the line, 2 % of all, got up to 15 % slower).
 // Whole layers, stream / 128 x 128 slices / 64 x 128 slices: 172 x 1024 x 2560 in 4 groups 19.1 / 18.0 / 17.9, 306 x
 // 4352 x 4352 in 4 groups 40.8 / 39.4 / 38.5, 300 x 4096 x 7168 in 4 groups 37.6 / 42.8 / 51.1, 500 x 2048 x 2048 in 4

@@ -61,7 +61,10 @@ struct QuantArgs {
     float* gamma;
     int32_t* rowsum;
     float* xhat_dump;
-    double* rowstats;   // per-tensor only: [M][2] = (mean, rstd)
+    // Per-tensor only: [M][2], left by the first pass for the second and private to the pair: (mean, rstd) from
+    // ln_quant_long; from ln_quant_rows (shift, rstd) of x^ = (x - c) rstd + shift, c being the row's first element as
+    // both passes see it (stats_centre).
+    double* rowstats;
     uint32_t* gmax_bits; // per-tensor only: [groups], bit pattern of the largest magnitude
     uint32_t* gmin_bits; // per-tensor Eq. 6 only: [groups], ordered key of the minimum
                          // (gmax_bits then holds the ordered key of the maximum)

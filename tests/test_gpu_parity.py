@@ -473,19 +473,24 @@ def test_forward_single_token(bl, K, N, variant, tuning):
         acc = host(bl.bitlinear_forward(dev(X), packed, N, beta, **kw_acc))
         assert np.array_equal(acc, acc_ref), mode
         assert np.array_equal(y, oracle.dequant(acc_ref, g_ref, r["beta"], pt)), mode
+        if mode == "one launch":
+            Xd = dev(X)
+            assert kernel_launches(bl, lambda: bl.bitlinear_forward(Xd, packed, N, beta, workspace=ws, **kw)) == 1
         # the normalised row itself, and the layer end to end from raw X
         assert np.abs(xh - r["xhat"]).max() <= 4e-6 * max(1.0, np.abs(r["xhat"]).max()), mode
         assert np.abs(y - r["y"]).max() <= 1e-3 * rms, mode
 
 
-# Two to four tokens: the batch sizes next to the one-launch single-token path (they take the
-# quantiser and the small-batch GEMM as two launches), in every variant of the quantiser.
+# Two to four tokens, in every variant of the quantiser: as the library runs them (short rows with gamma per token in
+# one launch, the others as quantiser and small-batch GEMM) and always in two launches.
 @pytest.mark.parametrize("M,K,N", [(4, 2048, 6144), (2, 2048, 2048), (3, 8192, 2048), (4, 8192, 520),
                                    (2, 7168, 1000), (3, 7168, 21504), (4, 7168, 300), (2, 12320, 264),
                                    (2, 16384, 1000), (4, 512, 40), (3, 3616, 257)])
 @pytest.mark.parametrize("variant", ["plain", "affine", "skip_ln", "per_tensor"])
-def test_forward_few_tokens(bl, M, K, N, variant):
-    print(f"forward few tokens M={M} K={K} N={N} {variant}", flush=True)
+@pytest.mark.parametrize("spec", [None, "decode_nofuse=1"])
+def test_forward_few_tokens(bl, M, K, N, variant, spec, tuning):
+    print(f"forward few tokens M={M} K={K} N={N} {variant} {spec}", flush=True)
+    tuning(spec)
     sd = wl.seed_for(0, 9 * K + N + M)
     W = wl.make_weight(N, K, 0.02, sd)
     X = wl.make_activation(M, K, sd)
@@ -516,8 +521,10 @@ def test_forward_few_tokens(bl, M, K, N, variant):
     assert np.array_equal(y, y_ref)
 
 
-# five to eight tiles a workgroup, with one chunk of K a wave and with two
-@pytest.mark.parametrize("K,N", [(2080, 16390), (3104, 28688), (4096, 32761), (4640, 24560), (8192, 32768)])
+# five to eight tiles a workgroup, with one chunk of K a wave and with two; rows of up to four chunks, whose waves
+# share the tiles
+@pytest.mark.parametrize("K,N", [(2080, 16390), (3104, 28688), (4096, 32761), (4640, 24560), (8192, 32768),
+                                 (96, 32768), (1024, 20500), (1504, 24570), (2048, 28700)])
 def test_forward_single_token_many_tiles(bl, K, N, tuning):
     test_forward_single_token(bl, K, N, "plain", tuning)
 
@@ -919,6 +926,22 @@ def test_streaming_stores_of_small_tiles(bl, tuning, M, K, N, spec):
     assert torch.equal(y, torch.cat([bl.bitlinear_matmul(codes[r], gamma[r], rowsum[r], packed, N, beta) for r in rows]))
     assert torch.equal(shifted, torch.cat([bl.bitlinear_matmul_nonneg(codes[r], gamma[r], eta[r], rowsum[r], packed, N, beta,
                                                                       wsum) for r in rows]))
+
+
+# So many rows of tiles that the kernel divides by their number itself: n / d by a multiplication is exact only while
+# n d < 2^32, and the host says where it is not.
+def test_small_tiles_beyond_the_exact_reciprocal(bl, tuning):
+    M, K, N = 65537 * 64 - 5, 32, 16
+    print(f"small tiles M={M} K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    packed, _, beta = bl.bitlinear_pack_weights(torch.randn(N, K, device="cuda", generator=g))
+    codes = torch.randint(-128, 128, (M, K), dtype=torch.int8, device="cuda", generator=g)
+    rowsum = codes.sum(dim=1, dtype=torch.int32)
+    gamma = torch.rand(M, device="cuda", generator=g)
+    tuning("prefill_tile=4")
+    y = bl.bitlinear_matmul(codes, gamma, rowsum, packed, N, beta)
+    tuning("prefill_tile=1")
+    assert torch.equal(y, bl.bitlinear_matmul(codes, gamma, rowsum, packed, N, beta))
 
 
 def kernel_launches(bl, call):
