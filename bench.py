@@ -20,6 +20,7 @@ sample of the same workload on this machine's host cores.
 from __future__ import annotations
 
 import argparse
+import ctypes
 import json
 import sys
 import time
@@ -165,7 +166,7 @@ def decode_stacks(bl, torch, dev, decode):
         stacks = [sets[i * 24:(i + 1) * 24] for i in range(4)]
         ref = run_stack(stacks[0]).clone()
         torch.cuda.synchronize()
-        mode = "eager launches"
+        mode, n_launch = "eager launches", None
         runners = [lambda st=st: run_stack(st) for st in stacks]
         try:
             graphs = []
@@ -175,10 +176,14 @@ def decode_stacks(bl, torch, dev, decode):
                 with torch.cuda.stream(side):
                     run_stack(st)
                 torch.cuda.current_stream().wait_stream(side)
-                g2 = torch.cuda.CUDAGraph()
+                g2 = torch.cuda.CUDAGraph(keep_graph=True)
                 with torch.cuda.graph(g2):
                     run_stack(st)
                 graphs.append(g2)
+            nodes = ctypes.c_size_t()  # all of them kernels
+            if bl.load_library().hipGraphGetNodes(ctypes.c_void_p(graphs[0].raw_cuda_graph()), None,
+                                                  ctypes.byref(nodes)) == 0:
+                n_launch = nodes.value
             graphs[0].replay()
             torch.cuda.synchronize()
             if torch.equal(ref, bufs["down"]):
@@ -193,11 +198,8 @@ def decode_stacks(bl, torch, dev, decode):
         run_all()
         t = event_ms(run_all, 5, torch) / len(runners)
         nbytes = sum(gemm_bytes(Md, L2.K, L2.N) + 5 * Md * L2.K for (L2, _, _) in protos) * 24
-        # one token with K <= 32768: the GEMM launch quantises the row itself (one launch a
-        # layer); otherwise quantiser + GEMM
-        n_launch = 24 * sum(1 if Md == 1 and L2.K <= 32768 else 2 for (L2, _, _) in protos)
         block.append(dict(M=Md, layers=24, launches=n_launch, us_per_step=t * 1e3,
-                          us_per_launch=t * 1e3 / n_launch,
+                          us_per_launch=t * 1e3 / n_launch if n_launch else None,
                           gbs=nbytes / (t * 1e-3) / 1e9, launch=mode))
     decode["block_decode_1p3b"] = block
     del sets, protos
