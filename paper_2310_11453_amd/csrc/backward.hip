@@ -56,55 +56,52 @@ template <typename IN, bool VEC>
 __device__ inline void cast_transpose_tile(const IN* __restrict__ in, int64_t R, int64_t C, int64_t Cp, int64_t Rp,
                                            const float* __restrict__ row_gamma, uint16_t* __restrict__ rows,
                                            uint16_t* __restrict__ tr, int64_t r0, int64_t c0, CastTile& tile) {
-    // Everything is requested first, without a branch: past the input's end the last row or column again, zeroed
-    // below.  Behind branches, load and use by turns, inputs whose rows are no whole float4 pay four trips to memory a
-    // tile (M x K x N, us of the call, behind branches / now: dX of 4154 x 192 x 20971 190.6 / 170.5, dW of 8192 x 256 x
-    // 16382 281 / 249; rows of whole float4, dX and dW of 8192 x 4096 x 16384, 1825 / 1820).
+    // Rows that are no whole float4: everything is requested first, without a branch, past the input's end the last row
+    // or column again, zeroed below.  Behind branches, load and use by turns, they pay four trips to memory a tile (M x K
+    // x N, us of the call, behind branches / now: dX of 4154 x 192 x 20971 190 / 169, dW of 8192 x 256 x 16382 281 /
+    // 252).  A float4 a row at once takes registers that more waves use better: the launch for 1000 x 2048 x 8192 16.9 us,
+    // 15.9 one by one.
     const int cl = ((int)threadIdx.x & 15) * 4;
     const int64_t c = c0 + cl;
-    float v[4][4], sc[4];
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int64_t r = r0 + it * 16 + (threadIdx.x >> 4);
-        const IN* src = in + (r < R ? r : R - 1) * C;
-        if constexpr (VEC) {
-            src += c < C ? c : C - 4;
-            if constexpr (sizeof(IN) == 4) {
-                const float4 t = *reinterpret_cast<const float4*>(src);
-                v[it][0] = t.x, v[it][1] = t.y, v[it][2] = t.z, v[it][3] = t.w;
-            } else {
-                const char4 t = *reinterpret_cast<const char4*>(src);
-                v[it][0] = (float)t.x, v[it][1] = (float)t.y, v[it][2] = (float)t.z, v[it][3] = (float)t.w;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[it][e] = (float)src[c + e < C ? c + e : C - 1];
-        }
-    }
-    if (row_gamma) {
+    float all[VEC ? 1 : 4][4], gamma[VEC ? 1 : 4];
+    if constexpr (!VEC) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            const int64_t r = r0 + it * 16 + (threadIdx.x >> 4);
-            sc[it] = row_gamma[r < R ? r : R - 1] / 128.0f;
+            const int64_t r = r0 + it * 16 + (threadIdx.x >> 4), at = r < R ? r : R - 1;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) all[it][e] = (float)in[at * C + (c + e < C ? c + e : C - 1)];
+            if (row_gamma) gamma[it] = row_gamma[at];  // uniform
         }
     }
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int rl = it * 16 + (threadIdx.x >> 4);
         const int64_t r = r0 + rl;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (!VEC) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[it][e] = r < R && c + e < C ? v[it][e] : 0.f;
+            for (int e = 0; e < 4; ++e) v[e] = r < R && c + e < C ? all[it][e] : 0.f;
+        } else if (r < R && c < C) {
+            if constexpr (sizeof(IN) == 4) {
+                const float4 t = *reinterpret_cast<const float4*>(in + r * C + c);
+                v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
+            } else {
+                const char4 t = *reinterpret_cast<const char4*>(in + r * C + c);
+                v[0] = (float)t.x, v[1] = (float)t.y, v[2] = (float)t.z, v[3] = (float)t.w;
+            }
+        }
         if (rows && r < R && c < Cp)
             *reinterpret_cast<uint2*>(rows + block_offset(r, c, R)) =
-                make_uint2(bf16_bits(v[it][0]) | (bf16_bits(v[it][1]) << 16),
-                           bf16_bits(v[it][2]) | (bf16_bits(v[it][3]) << 16));
-        if (row_gamma) {
+                make_uint2(bf16_bits(v[0]) | (bf16_bits(v[1]) << 16),
+                           bf16_bits(v[2]) | (bf16_bits(v[3]) << 16));
+        if (row_gamma && r < R) {
+            const float sc = (VEC ? row_gamma[r] : gamma[VEC ? 0 : it]) / 128.0f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[it][e] = v[it][e] * sc[it];
+            for (int e = 0; e < 4; ++e) v[e] = v[e] * sc;
         }
         uint32_t* t32 = reinterpret_cast<uint32_t*>(&tile[rl][cl]);
-        t32[0] = bf16_bits(v[it][0]) | (bf16_bits(v[it][1]) << 16);
-        t32[1] = bf16_bits(v[it][2]) | (bf16_bits(v[it][3]) << 16);
+        t32[0] = bf16_bits(v[0]) | (bf16_bits(v[1]) << 16);
+        t32[1] = bf16_bits(v[2]) | (bf16_bits(v[3]) << 16);
     }
     if (!tr) return;
     __syncthreads();
