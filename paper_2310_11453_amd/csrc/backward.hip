@@ -67,6 +67,7 @@ __device__ inline void cast_transpose_tile(const IN* __restrict__ in, int64_t R,
     if constexpr (!VEC) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
+            if (r0 + it * 16 >= R) break;  // uniform (2 x 256 x 774, dW, 7.1 us, 7.7 with all four)
             const int64_t r = r0 + it * 16 + (threadIdx.x >> 4), at = r < R ? r : R - 1;
 #pragma unroll
             for (int e = 0; e < 4; ++e) all[it][e] = (float)in[at * C + (c + e < C ? c + e : C - 1)];
