@@ -931,11 +931,13 @@ static RingPlan dx_plan(int64_t I, int64_t J, int64_t Rp) {
 // without that 1000 x 16384 x 4096, 184 / 166, goes the wrong way; with it for fewer 1090 x 11456 x 1280, 56 / 62,
 // does.  Over 549 shapes of 100 to 8192 tokens, most of them near the line, this was 0.6 % slower than the better tile
 // on average without the rules for long reductions and large operands, and 13 of them 10 to 33 % (1700 x 7680 x 2560,
-// 117 / 88, beyond `most`).  The whole call (M x N x K, with the operand copies), 256 against 128, us: 64 x 2048 x
-// 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x 2048 268 / 257, 512 x 8192 x 2048 37.6 / 32.8, 1300
-// x 8192 x 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000 x 9216 x 3072 89.7 / 78.5, 512 x 16384 x 4096 120.9
-// / 108.5, 1600 x 16384 x 4096 242.7 / 249.2, 700 x 7168 x 7168 133 / 123, 700 x 21504 x 7168 321 / 331, 2000 x 21504
-// x 7168 647 / 811; in slices 3300 x 4224 x 1056 73.9 / 72.1, 6000 x 4224 x 1056 106 / 126.
+// 117 / 88, beyond `most`).  Up to 32 small tiles count 1.5 us less: the slices' fold is dearer than its bytes there
+// (2059 x 512 x 256 28.1 / 24.2; 38 of 5400 drawn shapes, 3 % faster on average).  The whole call (M x N x K, with the
+// operand copies), 256 against 128, us: 64 x 2048 x 2048 18.6 / 10.0, 1000 x 2048 x 2048 42.0 / 22.6, 8192 x 6144 x
+// 2048 268 / 257, 512 x 8192 x 2048 37.6 / 32.8, 1300 x 8192 x 2048 62.8 / 61.0, 2000 x 8192 x 2048 86.0 / 87.5, 1000
+// x 9216 x 3072 89.7 / 78.5, 512 x 16384 x 4096 120.9 / 108.5, 1600 x 16384 x 4096 242.7 / 249.2, 700 x 7168 x 7168
+// 133 / 123, 700 x 21504 x 7168 321 / 331, 2000 x 21504 x 7168 647 / 811; in slices 3300 x 4224 x 1056 73.9 / 72.1,
+// 6000 x 4224 x 1056 106 / 126.
 static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const int force = tuning().bwd_ring;
     if (force == 2) return ring_plan(I, J, Rp, 128, 128);
@@ -953,7 +955,7 @@ static RingPlan dw_plan(int64_t I, int64_t J, int64_t Rp) {
     const bool cold = (I + J) * Rp * 2 > 140000000;
     const double st = (double)nst * (scattered ? 1.22 : 1.0) * (cold ? 1.5 : 1.0);
     const double two = 4.9 + 0.39 * st, one = 3.6 + 0.226 * st;
-    const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0);
+    const double small = (double)full * two + (rest > cus ? two : rest ? one : 0.0) - (ntiles <= 32 ? 1.5 : 0.0);
     return small < (full < 2 ? 1.0 : 1.02) * wide ? ring_plan(I, J, Rp, 128, 128) : p;
 }
 
